@@ -1,5 +1,5 @@
-// bf16 MFMA softmax attention (Eq. 1 of the paper) for head size 64 and up to 256 tokens, the shape
-// of every ViT-B/16 and DeiT-S block after token dropping.  The CLS row of the softmax map, which
+// bf16 MFMA softmax attention (Eq. 1 of the paper) for head size 64 and up to 1024 tokens: up to 256 tokens (every
+// ViT-B/16 and DeiT-S block at 224 pixels) a head's keys are staged whole, beyond that in chunks (second half of the file).  The CLS row of the softmax map, which
 // Eq. 6 ranks tokens by, leaves the forward kernel in fp32 as a by-product.
 //
 // Forward.  One workgroup = one (image, head): K and V of the head are staged once, and each of
@@ -392,9 +392,312 @@ void launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float*
   attn_bwd_dkv_kernel<NJ><<<grid, 256, lds_kv, s>>>(qkv, dout, lse, delta, T, H, dqkv);
 }
 
+// ------------------------------------------------------------------------------------------ more than 256 tokens
+// The same products with the other side of the softmax walked in chunks of LC rows that pass through LDS (fetched
+// into registers while the previous chunk is worked on): a workgroup owns 128 queries (4 wavefronts of 32) and the
+// softmax is kept running, output and sum rescaled when a chunk raises the maximum.  What bounds it is the softmax
+// arithmetic (VALU) beside 16 MFMAs per 32 x 64 block; 128-row chunks leave 32 KB of LDS per workgroup, so four or
+// five of them share a CU and cover each other's waits.  At 577 tokens, 16 images of 6 heads, the one-wavefront-per-
+// query kernels this replaces took 469 us forward and 717 us backward, these 26 and 49 us.
+// Workgroups are numbered head first: the query blocks of a head then run on one XCD and share its L2.
+constexpr int LC = 128, LCB = LC / 32, LONG_T = 1024;
+
+struct ChunkRegs { u32x4 v[4]; };      // a thread's share of one operand's chunk: LC rows of 8 16-byte pieces, 256 threads
+__device__ inline void chunk_fetch(ChunkRegs& c, const bf16* base, int64_t rs, int r0, int T, int tid) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int row = (tid >> 3) + 32 * u;
+    c.v[u] = *(const u32x4*)(base + (int64_t)min(r0 + row, T - 1) * rs + (tid & 7) * 8);
+    if (r0 + row >= T) c.v[u] = u32x4{0u, 0u, 0u, 0u};
+  }
+}
+__device__ inline void chunk_stash(const ChunkRegs& c, u32x4* s, int tid) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int row = (tid >> 3) + 32 * u;
+    s[row * 8 + ((tid & 7) ^ swz(row))] = c.v[u];
+  }
+}
+
+__global__ __launch_bounds__(256) void attn_fwd_long_kernel(const bf16* __restrict__ qkv, int T, int H, int heads_total,
+                                                            bf16* __restrict__ out, float* __restrict__ lse,
+                                                            float* __restrict__ cls_prob) {
+  __shared__ u32x4 Ks[LC * 8], Vs[LC * 8];
+  __shared__ float cls_s[LONG_T];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
+  const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD;
+  const int q0 = (blockIdx.x / heads_total) * 128 + wave * 32, qi = q0 + lr;
+  const int64_t rs = 3 * (int64_t)D;
+  const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
+  bf16x8 qf[4];
+  const bf16* qrow = base + (int64_t)min(qi, T - 1) * rs;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) qf[ks] = *(const bf16x8*)(qrow + (2 * ks + lh) * 8);
+  const float c = 0.125f * 1.44269504088896341f;    // 1/sqrt(64) * log2(e)
+  float m = -INFINITY, l = 0.f;                     // running maximum of the raw scores, running sum
+  f32x16 o[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
+  const bool cls_lane = cls_prob && qi == 0;
+  const int sw = swz(lr);
+  ChunkRegs kr, vr;
+  chunk_fetch(kr, base + D, rs, 0, T, tid);
+  chunk_fetch(vr, base + 2 * D, rs, 0, T, tid);
+  for (int c0 = 0; c0 < T; c0 += LC) {
+    if (c0) __syncthreads();
+    chunk_stash(kr, Ks, tid);
+    chunk_stash(vr, Vs, tid);
+    __syncthreads();
+    if (c0 + LC < T) {
+      chunk_fetch(kr, base + D, rs, c0 + LC, T, tid);
+      chunk_fetch(vr, base + 2 * D, rs, c0 + LC, T, tid);
+    }
+    f32x16 s[LCB];
+    float mx = m;
+#pragma unroll
+    for (int jb = 0; jb < LCB; ++jb) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[jb][r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const bf16x8 kf = *(const bf16x8*)(Ks + (jb * 32 + lr) * 8 + ((2 * ks + lh) ^ sw));
+        s[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[jb], 0, 0, 0);
+      }
+      if (c0 + jb * 32 + 32 > T) {                  // uniform: this block reaches past the last key
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (c0 + key_of(jb, r, lh) >= T) s[jb][r] = -INFINITY;
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[jb][r]);
+    }
+    if (cls_lane) {
+#pragma unroll
+      for (int jb = 0; jb < LCB; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int j = c0 + key_of(jb, r, lh);
+          if (j < T) cls_s[j] = s[jb][r];
+        }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));         // finite: a chunk holds at least one key
+    const float alpha = __builtin_amdgcn_exp2f((m - mx) * c), mc = mx * c;
+    m = mx;
+    float sum = 0.f;
+    bf16x8 pf[2 * LCB];
+#pragma unroll
+    for (int jb = 0; jb < LCB; ++jb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[jb][r], c, -mc));
+        sum += p;
+        pf[2 * jb + (r >> 3)][r & 7] = (bf16)p;
+      }
+    l = l * alpha + sum + __shfl_xor(sum, 32, 64);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[nb][r] *= alpha;
+#pragma unroll
+      for (int st = 0; st < 2 * LCB; ++st)
+        o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(Vs, nb, lane, st), pf[st], o[nb], 0, 0, 0);
+    }
+  }
+  const float inv = 1.0f / l;
+  if (qi < T) {
+    if (lse && lh == 0) lse[((int64_t)b * H + h) * T + qi] = m * 0.125f + __logf(l);
+    bf16* orow = out + ((int64_t)b * T + qi) * D + h * HD + 4 * lh;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) {
+        bf16x4 v4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v4[e] = (bf16)(o[nb][4 * rq + e] * inv);
+        *(bf16x4*)(orow + nb * 32 + 8 * rq) = v4;
+      }
+  }
+  if (cls_prob && q0 - wave * 32 == 0) {            // the workgroup of the CLS query: its softmax row in fp32 (Eq. 6)
+    __syncthreads();
+    float* red = (float*)Ks;
+    if (tid == 0) { red[0] = m; red[1] = inv; }
+    __syncthreads();
+    const float m0 = red[0] * c, i0 = red[1];
+    for (int j = tid; j < T; j += 256) cls_prob[((int64_t)b * H + h) * T + j] = __builtin_amdgcn_exp2f(fmaf(cls_s[j], c, -m0)) * i0;
+  }
+}
+
+// Backward beyond 256 tokens, one launch: workgroups of the first half own 128 queries (dQ, chunks of keys), those
+// of the second half 128 keys (dK and dV, chunks of queries; delta is taken from the rows of dO and O as they are
+// staged, so nothing waits for the first half).
+__global__ __launch_bounds__(256) void attn_bwd_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
+                                                            const bf16* __restrict__ dout, const float* __restrict__ lse, int T,
+                                                            int H, int heads_total, bf16* __restrict__ dqkv) {
+  __shared__ u32x4 As[LC * 8], Bs[LC * 8];
+  __shared__ __attribute__((aligned(16))) float lse_s[LC], del_s[LC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
+  const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD, nblk = (T + 127) / 128;
+  const int blk = blockIdx.x / heads_total;
+  const int64_t rs = 3 * (int64_t)D;
+  const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
+  const bf16* dobase = dout + (int64_t)b * T * D + h * HD;
+  const bf16* obase = out + (int64_t)b * T * D + h * HD;
+  const float* lrow = lse + ((int64_t)b * H + h) * T;
+  const float c = 0.125f * 1.44269504088896341f;
+  ChunkRegs ra, rb;
+  if (blk < nblk) {
+    const int q0 = blk * 128 + wave * 32, qc = min(q0 + lr, T - 1);
+    bf16x8 qf[4], dof[4];
+    float dl = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      qf[ks] = *(const bf16x8*)(base + (int64_t)qc * rs + (2 * ks + lh) * 8);
+      dof[ks] = *(const bf16x8*)(dobase + (int64_t)qc * D + (2 * ks + lh) * 8);
+      const bf16x8 of = *(const bf16x8*)(obase + (int64_t)qc * D + (2 * ks + lh) * 8);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dl += (float)dof[ks][e] * (float)of[e];
+    }
+    dl += __shfl_xor(dl, 32, 64);
+    const float l2 = lrow[qc] * 1.44269504088896341f;
+    f32x16 o[2];
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
+    chunk_fetch(ra, base + D, rs, 0, T, tid);
+    chunk_fetch(rb, base + 2 * D, rs, 0, T, tid);
+    for (int c0 = 0; c0 < T; c0 += LC) {
+      if (c0) __syncthreads();
+      chunk_stash(ra, As, tid);
+      chunk_stash(rb, Bs, tid);
+      __syncthreads();
+      if (c0 + LC < T) {
+        chunk_fetch(ra, base + D, rs, c0 + LC, T, tid);
+        chunk_fetch(rb, base + 2 * D, rs, c0 + LC, T, tid);
+      }
+#pragma unroll
+      for (int jb = 0; jb < LCB; ++jb) {
+        f32x16 sa, dp;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(As, jb * 32 + lr, 2 * ks + lh), qf[ks], sa, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Bs, jb * 32 + lr, 2 * ks + lh), dof[ks], dp, 0, 0, 0);
+        }
+        bf16x8 dsf[2];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float pr = __builtin_amdgcn_exp2f(sa[r] * c - l2);
+          if (c0 + key_of(jb, r, lh) >= T) pr = 0.f;
+          dsf[r >> 3][r & 7] = (bf16)(pr * (dp[r] - dl) * 0.125f);
+        }
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf)
+            o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf[hf], lds_frag_t(As, nb, lane, 2 * jb + hf), o[nb], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int i = q0 + 8 * (r >> 2) + 4 * lh + (r & 3);
+        if (i < T) dqkv[((int64_t)b * T + i) * rs + h * HD + nb * 32 + lr] = (bf16)o[nb][r];
+      }
+    return;
+  }
+  const int j0 = (blk - nblk) * 128 + wave * 32, jc = min(j0 + lr, T - 1);
+  bf16x8 kf[4], vf[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    kf[ks] = *(const bf16x8*)(base + D + (int64_t)jc * rs + (2 * ks + lh) * 8);
+    vf[ks] = *(const bf16x8*)(base + 2 * D + (int64_t)jc * rs + (2 * ks + lh) * 8);
+  }
+  f32x16 ok[2], ov[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { ok[nb][r] = 0.f; ov[nb][r] = 0.f; }
+  ChunkRegs ro;
+  chunk_fetch(ra, base, rs, 0, T, tid);
+  chunk_fetch(rb, dobase, D, 0, T, tid);
+  chunk_fetch(ro, obase, D, 0, T, tid);
+  for (int c0 = 0; c0 < T; c0 += LC) {
+    if (c0) __syncthreads();
+    chunk_stash(ra, As, tid);
+    chunk_stash(rb, Bs, tid);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {                   // delta of the staged rows: 8 lanes hold a row
+      const bf16x8 x = __builtin_bit_cast(bf16x8, rb.v[u]), y = __builtin_bit_cast(bf16x8, ro.v[u]);
+      float d = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d += (float)x[e] * (float)y[e];
+      d += __shfl_xor(d, 1, 64);
+      d += __shfl_xor(d, 2, 64);
+      d += __shfl_xor(d, 4, 64);
+      if ((tid & 7) == 0) del_s[(tid >> 3) + 32 * u] = d;
+    }
+    if (tid < LC) lse_s[tid] = c0 + tid < T ? lrow[c0 + tid] * 1.44269504088896341f : INFINITY;
+    __syncthreads();
+    if (c0 + LC < T) {
+      chunk_fetch(ra, base, rs, c0 + LC, T, tid);
+      chunk_fetch(rb, dobase, D, c0 + LC, T, tid);
+      chunk_fetch(ro, obase, D, c0 + LC, T, tid);
+    }
+#pragma unroll
+    for (int ib = 0; ib < LCB; ++ib) {
+      f32x16 sa, dp;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(As, ib * 32 + lr, 2 * ks + lh), kf[ks], sa, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Bs, ib * 32 + lr, 2 * ks + lh), vf[ks], dp, 0, 0, 0);
+      }
+      bf16x8 pf[2], dsf[2];
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {              // queries c0 + 32 ib + 8 g4 + 4 lh + {0..3}
+        const float4 l4 = *(const float4*)(lse_s + ib * 32 + 8 * g4 + 4 * lh);
+        const float4 d4 = *(const float4*)(del_s + ib * 32 + 8 * g4 + 4 * lh);
+        const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+        const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = g4 * 4 + e;
+          const float pr = __builtin_amdgcn_exp2f(sa[r] * c - lv[e]);
+          pf[r >> 3][r & 7] = (bf16)pr;
+          dsf[r >> 3][r & 7] = (bf16)(pr * (dp[r] - dv[e]) * 0.125f);
+        }
+      }
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          ov[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[hf], lds_frag_t(Bs, nb, lane, 2 * ib + hf), ov[nb], 0, 0, 0);
+          ok[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf[hf], lds_frag_t(As, nb, lane, 2 * ib + hf), ok[nb], 0, 0, 0);
+        }
+    }
+  }
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = j0 + 8 * (r >> 2) + 4 * lh + (r & 3);
+      if (j < T) {
+        bf16* dst = dqkv + ((int64_t)b * T + j) * rs + h * HD + nb * 32 + lr;
+        dst[D] = (bf16)ok[nb][r];
+        dst[2 * D] = (bf16)ov[nb][r];
+      }
+    }
+}
+
 }  // namespace
 
-bool attn_mfma_supported(int T, int d) { return d == HD && T >= 1 && T <= 256; }
+bool attn_mfma_supported(int T, int d) { return d == HD && T >= 1 && T <= LONG_T; }
 
 void attn_fwd_mfma(const void* qkv, int B, int T, int H, void* out, float* lse, float* cls_prob, hipStream_t s) {
   const bf16* q = (const bf16*)qkv;
@@ -407,13 +710,10 @@ void attn_fwd_mfma(const void* qkv, int B, int T, int H, void* out, float* lse, 
     case 5: launch_fwd<5>(q, B, T, H, o, lse, cls_prob, s); break;
     case 6: launch_fwd<6>(q, B, T, H, o, lse, cls_prob, s); break;
     case 7: launch_fwd<7>(q, B, T, H, o, lse, cls_prob, s); break;
-    default: launch_fwd<8>(q, B, T, H, o, lse, cls_prob, s); break;
+    case 8: launch_fwd<8>(q, B, T, H, o, lse, cls_prob, s); break;
+    default: attn_fwd_long_kernel<<<B * H * ((T + 127) / 128), 256, 0, s>>>(q, T, H, B * H, o, lse, cls_prob); break;
   }
 }
-
-}  // namespace bsr
-
-namespace bsr {
 
 void attn_bwd_mfma(const void* qkv, const void* out, const void* dout, const float* lse, int B, int T, int H,
                    float* delta, void* dqkv, hipStream_t s) {
@@ -429,7 +729,8 @@ void attn_bwd_mfma(const void* qkv, const void* out, const void* dout, const flo
     case 5: launch_bwd<5>(q, o, d, lse, B, T, H, delta, g, s); break;
     case 6: launch_bwd<6>(q, o, d, lse, B, T, H, delta, g, s); break;
     case 7: launch_bwd<7>(q, o, d, lse, B, T, H, delta, g, s); break;
-    default: launch_bwd<8>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 8: launch_bwd<8>(q, o, d, lse, B, T, H, delta, g, s); break;
+    default: attn_bwd_long_kernel<<<2 * B * H * ((T + 127) / 128), 256, 0, s>>>(q, o, d, lse, T, H, B * H, g); break;
   }
 }
 
