@@ -511,14 +511,15 @@ void gemm(bsr_ctx* c, const GemmDesc& g, hipStream_t s) {
     tile_done(c, ch, s);
   }
   else if (g.grp_off) defer_fail(c, BSR_ERR_BAD_CONFIG, "grouped GEMM %d x %d x %d is not an MFMA shape", g.M, g.N, g.K);
+  else if (gemm_f32_supported(g)) gemm_f32(g, s);
   else gemm_generic(g, s);
 }
 
-// Eq. 4 for one linear layer: dW = x^T dy and db = column sums of dy.  The MFMA kernel produces db
-// alongside dW; other shapes (and fp32 mode) take the separate column-sum kernels.
+// Eq. 4 for one linear layer: dW = x^T dy and db = column sums of dy.  The MFMA kernels produce db
+// alongside dW; other shapes take the separate column-sum kernels.
 void wgrad(bsr_ctx* c, const void* x, const void* dy, int M, int in, int out, void* dw, void* db, hipStream_t s) {
   GemmDesc g = wgrad_desc(c, x, dy, M, in, out, dw);
-  if (gemm_mfma_supported(g)) {
+  if (gemm_mfma_supported(g) || gemm_f32_supported(g)) {
     g.bsum = (float*)db;
     gemm(c, g, s);
   } else {
@@ -621,6 +622,7 @@ void attention_fwd(bsr_ctx* c, const void* qkv, int B, int T, void* out, float* 
   const int H = c->cfg.heads, d = c->cfg.dim / H;
   ProfScope ps(c, BSR_PROF_ATTN_FWD, 4.0 * B * H * (double)T * T * d, s);
   if (!c->f32 && attn_mfma_supported(T, d)) attn_fwd_mfma(qkv, B, T, H, out, lse, clsp, s);
+  else if (c->f32 && attn_f32_supported(T, d)) attn_fwd_f32((const float*)qkv, B, T, H, (float*)out, lse, clsp, s);
   else attn_fwd_generic(qkv, B, T, H, d, c->f32, out, lse, clsp, s);
 }
 
@@ -629,6 +631,8 @@ void attention_bwd(bsr_ctx* c, const void* qkv, const void* out, const void* dou
   const int H = c->cfg.heads, d = c->cfg.dim / H;
   ProfScope ps(c, BSR_PROF_ATTN_BWD, 10.0 * B * H * (double)T * T * d, s);
   if (!c->f32 && attn_mfma_supported(T, d)) attn_bwd_mfma(qkv, out, dout, lse, B, T, H, c->b.delta, dqkv, s);
+  else if (c->f32 && attn_f32_supported(T, d))
+    attn_bwd_f32((const float*)qkv, (const float*)out, (const float*)dout, lse, B, T, H, (float*)dqkv, s);
   else attn_bwd_generic(qkv, out, dout, lse, B, T, H, d, c->f32, c->b.delta, dqkv, s);
 }
 

@@ -50,6 +50,14 @@ void attn_fwd_generic(const void* qkv, int B, int T, int H, int d, bool f32, voi
 void attn_bwd_generic(const void* qkv, const void* out, const void* dout, const float* lse, int B,
                       int T, int H, int d, bool f32, float* delta, void* dqkv, hipStream_t s);
 
+// ---- fp32 MFMA paths (any row count; contiguous extents in multiples of four, head size 64) -------
+bool gemm_f32_supported(const GemmDesc& g);
+void gemm_f32(const GemmDesc& g, hipStream_t s);
+bool attn_f32_supported(int T, int d);
+void attn_fwd_f32(const float* qkv, int B, int T, int H, float* out, float* lse, float* cls_prob, hipStream_t s);
+void attn_bwd_f32(const float* qkv, const float* out, const float* dout, const float* lse, int B, int T, int H,
+                  float* dqkv, hipStream_t s);
+
 // W'(n,k) = bf16(w[k,n] gamma[k]) as [out][in], colsum[n] = sum_k W'(n,k), bias_out[n] = bias[n] + sum_k beta[k] w[k,n]
 // (w is the fp32 master matrix [in][out]; in a multiple of 8)
 void ln_fold_weights(const float* w, const float* bias, const float* gamma, const float* beta, int in, int out,
