@@ -726,6 +726,199 @@ void launch_ntd(const GemmDesc& g, hipStream_t s) {
 // what the direct-to-LDS kernels take: whole k-tiles, one weight matrix, no folded LayerNorm
 bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.grp_off && !g.ln_colsum; }
 
+// ------------------------------------------------------------------------------------------ NT, few rows
+// The same product where block tiles shared by eight wavefronts would leave most CUs idle.  A workgroup owns
+// 32 MI x 32 NI outputs and its four wavefronts share k: wavefront w takes the k-groups (of 64) w, w + 4, ..., with a ring
+// of NST stages of its own in LDS, filled by global_load_lds as in the kernel above.  Nobody shares a stage, so there
+// is no barrier in the loop: a wavefront waits for its own loads by count and keeps NST groups in flight.  The four
+// partial tiles are added through LDS in wavefront order (the sum over k has another order than in the tiled
+// kernels, so which products come here depends on their size alone).
+// What bounds it: the CU's path from L2 (about 100 GB/s of operands per CU; a 32 x 32 tile has no reuse to speak of),
+// then launch and epilogue.  Chain of equal launches, tiled kernels -> here: 197 rows, 768 x 768 8.1 -> 4.0 us, 768 from
+// 3072 21.0 -> 6.4, 2304 from 768 8.2 -> 5.2; 788 rows, 384 from 1536 12.6 -> 6.3; 1182 rows, 768 from 3072 21 -> 16.
+// (Fragments straight from global memory, without LDS: 13.5 us for 197 x 768 x 3072; a load then touches 32 lines.)
+// LNF: the folded LayerNorm; a wavefront adds up the rows of its k-groups from its fragments of A.
+template <int MI, int NI, int NST, bool LNF>
+__global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
+  constexpr int NW = 4, BM = 32 * MI, BN = 32 * NI, LDP = BN + 4, LPT = 4 * (MI + NI), STAGE = LPT * 1024;
+  static_assert(NST >= 2 && NST <= 4 && NST * LPT <= 60, "vmcnt has 6 bits");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ntm = (g.M + BM - 1) / BM;
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);        // an XCD's range runs over the rows first: weights are read once
+  const int m0 = (tile % ntm) * BM, n0 = (tile / ntm) * BN;
+  const bf16* __restrict__ A = (const bf16*)g.A;
+  const bf16* __restrict__ Bt = (const bf16*)g.B;
+  unsigned char* ring = smem + wave * NST * STAGE;
+  // load i fills tile rows 8 i .. 8 i + 7 (A rows first): lane (row lane / 8, slot lane % 8) fetches chunk slot ^ swz(row)
+  unsigned off[LPT];
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) {
+    const int row = 8 * i + (lane >> 3), chunk = ((lane & 7) ^ swz(row)) * 8;
+    off[i] = i < 4 * MI ? (unsigned)min(m0 + row, g.M - 1) * (unsigned)g.a_rs + chunk
+                        : (unsigned)min(n0 + row - BM, g.N - 1) * (unsigned)g.b_cs + chunk;
+  }
+  auto issue = [&](int grp, int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i)
+      __builtin_amdgcn_global_load_lds(BSR_GLOBAL_PTR((i < 4 * MI ? A : Bt) + (size_t)grp * 64 + off[i]),
+                                       BSR_LDS_VOID(ring + st * STAGE + i * 1024), 16, 0, 0);
+  };
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+  float rsum[MI], rsq[MI];
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) rsum[mi] = rsq[mi] = 0.f;
+  const int sw = swz(lr), ng = g.K / 64;
+  const int mine = ng > wave ? (ng - wave + NW - 1) / NW : 0;      // k-groups of this wavefront
+#pragma unroll
+  for (int j = 0; j < NST; ++j)
+    if (j < mine) issue(wave + j * NW, j);
+  int st = 0;
+  for (int i = 0; i < mine; ++i) {
+    const int ahead = min(mine - 1 - i, NST - 1);                  // groups that may stay in flight
+    if (ahead >= 3) wait_vmcnt<(NST > 3 ? 3 : 0) * LPT>();
+    else if (ahead == 2) wait_vmcnt<(NST > 2 ? 2 : 0) * LPT>();
+    else if (ahead == 1) wait_vmcnt<LPT>();
+    else wait_vmcnt<0>();
+    BSR_SCHED_FENCE();
+    const unsigned char* s = ring + st * STAGE;
+    bf16x8 fa[4][MI], fb[4][NI];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) fa[ks][mi] = *(const bf16x8*)(s + (mi * 32 + lr) * 128 + (((ks * 2 + lh) ^ sw) << 4));
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) fb[ks][ni] = *(const bf16x8*)(s + (BM + ni * 32 + lr) * 128 + (((ks * 2 + lh) ^ sw) << 4));
+    }
+    if (i + NST < mine) {
+      wait_lgkmcnt0();                                             // the stage has been read: it can be filled again
+      BSR_SCHED_FENCE();
+      issue(wave + (i + NST) * NW, st);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][mi], fb[ks][ni], acc[mi][ni], 0, 0, 0);
+    if constexpr (LNF) {
+      const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            unsigned word = __builtin_bit_cast(u32x4, fa[ks][mi])[w];
+            asm("" : "+v"(word));                                  // (keeps the four words of a chunk apart, as above)
+            const bf16x2 pr = __builtin_bit_cast(bf16x2, word);
+            rsum[mi] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, rsum[mi], false);
+            rsq[mi] = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, rsq[mi], false);
+          }
+    }
+    st = st + 1 == NST ? 0 : st + 1;
+  }
+  __syncthreads();
+  float* part = (float*)smem;
+  float2* stat = (float2*)(part + NW * BM * LDP);                  // per wavefront and row: sum, sum of squares
+  if constexpr (LNF) {
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+      rsum[mi] += __shfl_xor(rsum[mi], 32);
+      rsq[mi] += __shfl_xor(rsq[mi], 32);
+      if (lh == 0) stat[wave * BM + mi * 32 + lr] = make_float2(rsum[mi], rsq[mi]);
+    }
+  }
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        part[(wave * BM + mi * 32 + 8 * (r >> 2) + 4 * lh + (r & 3)) * LDP + ni * 32 + lr] = acc[mi][ni][r];
+  __syncthreads();
+#pragma unroll 1
+  for (int it = tid; it < BM * BN / 8; it += 256) {
+    const int row = it / (BN / 8), col8 = it % (BN / 8) * 8, m = m0 + row, col = n0 + col8;
+    if (m >= g.M || col >= g.N) continue;
+    float v[8], bias[8], cs[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      v[j] = part[row * LDP + col8 + j];
+      bias[j] = g.bias ? g.bias[col + j] : 0.f;
+      cs[j] = LNF ? g.ln_colsum[col + j] : 0.f;
+    }
+#pragma unroll
+    for (int w = 1; w < NW; ++w)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] += part[(w * BM + row) * LDP + col8 + j];
+    float2 ms = make_float2(0.f, 0.f);
+    if constexpr (LNF) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) { ms.x += stat[w * BM + row].x; ms.y += stat[w * BM + row].y; }
+      const float mean = ms.x / (float)g.K;
+      ms = make_float2(mean, rsqrtf(fmaxf(ms.y / (float)g.K - mean * mean, 0.f) + g.ln_eps));
+    }
+    finish8(g, v, m, col, bias, cs, LNF ? &ms : nullptr);
+  }
+}
+
+template <int MI, int NI, int NST, bool LNF>
+void launch_few_as(const GemmDesc& g, hipStream_t s) {
+  constexpr size_t ring = (size_t)4 * NST * 4 * (MI + NI) * 1024;
+  constexpr size_t part = (size_t)4 * 32 * MI * ((32 * NI + 4) * sizeof(float) + sizeof(float2));
+  constexpr size_t lds = ring > part ? ring : part;
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void*)gemm_nt_few_kernel<MI, NI, NST, LNF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    attr_set = true;
+  }
+  const int tiles = ((g.M + 32 * MI - 1) / (32 * MI)) * ((g.N + 32 * NI - 1) / (32 * NI));
+  gemm_nt_few_kernel<MI, NI, NST, LNF><<<tiles, 256, lds, s>>>(g);
+}
+template <int MI, int NI>
+void launch_few(const GemmDesc& g, hipStream_t s) {
+  if (g.ln_colsum) launch_few_as<MI, NI, 2, true>(g, s);
+  else launch_few_as<MI, NI, 2, false>(g, s);
+}
+// Two stages each: three or four brought nothing (197 x 768 x 3072: 6.4 and 6.6 us with two and four) and keep a second
+// workgroup off the CU.  32 x 64 tiles are never ahead of both 64 x 32 and 64 x 64.
+// Modelled time of a product here, in microseconds: launch and epilogue, then ceil(tiles / 256) rounds of a start-up
+// and the tile's operand bytes.  Constants fitted to chains of equal launches at 1 .. 2144 rows, N and K of 384 .. 3072
+// (within 15 % where the kernel is the faster one).
+struct FewShape { int mi, ni; float launch_us, round_us, bytes_per_us; };
+const FewShape kFewShapes[] = {{1, 1, 2.6f, 0.5f, 105e3f}, {2, 1, 2.8f, 0.5f, 103e3f}, {2, 2, 3.3f, 1.0f, 65e3f}};
+constexpr float TILED_LAUNCH_US = 2.6f;               // the same fixed part of a tiled launch
+// A product comes here when the model gives it a clear lead over the tiled kernels: inside a step, where every launch
+// follows another kernel, near-ties of the two models (384 columns from 1536 at 2144 rows) went to the tiled ones.
+constexpr float FEW_LEAD = 0.8f;
+
+// The shape of this kernel for a product and what the model gives it; -1: not one it takes
+int few_pick(const GemmDesc& g, float* us) {
+  int pick = -1;
+  if (g.K % 64 == 0 && !g.grp_off)
+    for (int i = 0; i < 3; ++i) {
+      const FewShape& f = kFewShapes[i];
+      const int64_t tiles = (int64_t)((g.M + 32 * f.mi - 1) / (32 * f.mi)) * ((g.N + 32 * f.ni - 1) / (32 * f.ni));
+      const float t = f.launch_us + (float)((tiles + 255) / 256) * (f.round_us + 64.f * (f.mi + f.ni) * g.K / f.bytes_per_us);
+      if (pick < 0 || t < *us) { pick = i; *us = t; }
+    }
+  return pick;
+}
+void launch_few(int pick, const GemmDesc& g, hipStream_t s) {
+  if (pick == 0) launch_few<1, 1>(g, s);
+  else if (pick == 1) launch_few<2, 1>(g, s);
+  else launch_few<2, 2>(g, s);
+}
+
 // ------------------------------------------------------------------------------------------ TN
 // Weight gradient dW[Mo,No] = sum_t X[t,Mo]^T dY[t,No] (Eq. 4): both operands have the contraction
 // index t (tokens) as their row index, so an MFMA fragment (8 consecutive t for one column) is
@@ -1144,7 +1337,8 @@ static int ntd_stages(int id) {
   }
 }
 
-int gemm_nt_model_tile(int M, int N, int K) {
+// the model's pick and its time (without the launch itself)
+static int gemm_nt_model(int M, int N, int K, float* us_out) {
   int pick = 0;
   float best = 0.f;
   for (const NtShape& t : kNtShapes) {
@@ -1153,7 +1347,12 @@ int gemm_nt_model_tile(int M, int N, int K) {
     const float us = (float)((tiles + 255) / 256) * (t.fixed_us + t.per_ktile_us * (float)((K + BK - 1) / BK));
     if (!pick || us < best) { pick = t.id; best = us; }
   }
+  *us_out = best;
   return pick;
+}
+int gemm_nt_model_tile(int M, int N, int K) {
+  float us = 0.f;
+  return gemm_nt_model(M, N, K, &us);
 }
 size_t gemm_nt_tile_lds_bytes(int id) {
   const int bm = id % 1000000 / 1000, bn = id % 1000, nst = ntd_stages(id);
@@ -1172,6 +1371,13 @@ void gemm_tn_flush(TnChain* chain, hipStream_t s) {
 void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile, TnChain* chain) {
   if (is_tn(g)) {
     launch_tn(g, splitk_ws, splitk_ws_floats, s, chain);
+    return;
+  }
+  float few_us = 0.f, tiled_us = 0.f;
+  const int few = few_pick(g, &few_us);
+  gemm_nt_model(g.M, g.N, g.K, &tiled_us);
+  if (few >= 0 && few_us < FEW_LEAD * (tiled_us + TILED_LAUNCH_US)) {      // by size alone, whatever tile is asked for
+    launch_few(few, g, s);
     return;
   }
   // groups are a few hundred rows and each ends in a partial row tile: 128-row tiles, 64-row ones where a group
@@ -1214,7 +1420,13 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
                     int tile, TnChain* chain) {
   int pick = tile;
   if (!pick) pick = gemm_nt_model_tile(nt.M, nt.N, nt.K);
-  const bool can = is_nt(nt) && is_tn(tn) && !nt.grp_off && !tn.grp_off && nt.K % BK == 0;
+  // (an input gradient of few rows goes to the kernel for those, in a launch of its own, where that saves more than
+  // the launch costs)
+  float few_us = 0.f, tiled_us = 0.f;
+  const int few = few_pick(nt, &few_us);
+  gemm_nt_model(nt.M, nt.N, nt.K, &tiled_us);
+  const bool few_pays = few >= 0 && few_us < FEW_LEAD * tiled_us;
+  const bool can = is_nt(nt) && is_tn(tn) && !nt.grp_off && !tn.grp_off && nt.K % BK == 0 && !few_pays;
   if (can) {
     switch (pick) {
       case 128064: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<128, 64, 4, 2, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
