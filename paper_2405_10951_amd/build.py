@@ -22,8 +22,8 @@ def sources() -> list[str]:
 
 def _compile(src: str, force: bool, obj_dir: str = OBJ, extra: tuple = ()) -> str:
     obj = os.path.join(obj_dir, src[:-4] + ".o")
-    deps = [os.path.join(CSRC, src), os.path.join(CSRC, "bsr_internal.h"),
-            os.path.join(HERE, "..", "include", "bsr.h")]
+    deps = [os.path.join(CSRC, src), os.path.join(HERE, "..", "include", "bsr.h"),
+            *(os.path.join(CSRC, h) for h in os.listdir(CSRC) if h.endswith(".h"))]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(d) for d in deps):
         return obj
     cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]

@@ -64,10 +64,10 @@ struct Buffers {
   bf16* t_patch = nullptr;
   Shadow sh[BSR_MAX_BLOCKS] = {};
   char *patches = nullptr, *x0 = nullptr, *x1 = nullptr, *h = nullptr, *qkv = nullptr, *o = nullptr, *g = nullptr;
-  float *clsp = nullptr, *scores = nullptr, *fw = nullptr;   // fw: fusion weights of a frozen drop location
+  float *clsp = nullptr, *fw = nullptr;   // fw: fusion weights of a frozen drop location
   // Scratch of the trainable part that is not kept for backward.  It has buffers of its own because the
   // frozen prefix of the next batch may run beside it on another stream.
-  float *clsp_t = nullptr, *scores_t = nullptr;
+  float *clsp_t = nullptr;
   char *h_t = nullptr, *o_t = nullptr, *g_t = nullptr;
   int32_t* idx_tmp = nullptr;
   SavedBlock sv[BSR_MAX_BLOCKS] = {};
@@ -316,9 +316,7 @@ size_t carve(const bsr_config& c, const Schedule& s, char* base, Buffers* out, b
   b.o = w.take<char>(B * T0 * D * E);
   b.g = w.take<char>(B * T0 * F * E);
   b.clsp = w.take<float>(B * H * T0);
-  b.scores = w.take<float>(B * T0);
   b.clsp_t = w.take<float>(B * H * T0);
-  b.scores_t = w.take<float>(B * T0);
   b.fw = w.take<float>(B * T0);
   b.idx_tmp = w.take<int32_t>(B * T0);
   const size_t KE = c.n_moe > 0 ? (size_t)c.moe_top_k : 1, NE = c.n_moe > 0 ? (size_t)c.n_experts : 0;
@@ -395,7 +393,7 @@ size_t carve(const bsr_config& c, const Schedule& s, char* base, Buffers* out, b
   b.partial = w.take<float>(std::max(colsum_partial_floats(0, (int)std::max(3 * D, F)), mean_sq_partial_floats()));
   int n_ln = 0;
   for (int l = ft; l < L; ++l) n_ln += s.trainable[l] ? 2 : 0;
-  if (!f32 && n_ln > 0 && n_ln <= LN_DEFER_MAX) b.ln_partial = w.take<float>((size_t)n_ln * ln_deferred_partial_floats((int)D));
+  if (n_ln > 0 && n_ln <= LN_DEFER_MAX) b.ln_partial = w.take<float>((size_t)n_ln * ln_deferred_partial_floats((int)D));
   b.splitk_floats = f32 ? 0 : gemm_splitk_ws_floats((int)D, (int)F);
   if (ft < L && b.splitk_floats) b.splitk = w.take<float>(b.splitk_floats);
   const size_t C = std::max(c.num_classes, 1);
@@ -636,12 +634,11 @@ void attention_bwd(bsr_ctx* c, const void* qkv, const void* out, const void* dou
   else attn_bwd_generic(qkv, out, dout, lse, B, T, H, d, c->f32, c->b.delta, dqkv, s);
 }
 
-// Rank the patch tokens of a drop location and hand CLS + the K best to the FFN (Sec. 4.1).
-// Returns the device pointer holding the kept indices.
+// Rank the patch tokens of a drop location, hand CLS + the K best to the FFN (Sec. 4.1) and normalise them, in one
+// launch.  Returns the device pointer holding the kept indices.
 // fw != null: the dropped tokens are fused into one more token (row k+1 of x_kept, pitch k+2) and
 // fw receives the fusion weights.
-// LayerNorm that follows the token drop (LN2 of the drop location): when given, and when the one-pass kernel
-// takes the shape, gather and LayerNorm are one launch and done is set.
+// ln: the LayerNorm that follows the token drop (LN2 of the drop location); done is set when it was part of the launch.
 struct LnAfterDrop {
   const float *gamma, *beta;
   void* y;
@@ -651,27 +648,20 @@ struct LnAfterDrop {
 
 const int32_t* drop_tokens(bsr_ctx* c, int B, int T, int k, const void* x_full, void* x_kept,
                            int32_t* idx_own, const int32_t* forced, int32_t* idx_out, float* scores_out,
-                           float* fw, hipStream_t s, LnAfterDrop* ln = nullptr, bool trainable_part = false) {
-  const int H = c->cfg.heads, D = c->cfg.dim;
-  const float* clsp = trainable_part ? c->b.clsp_t : c->b.clsp;
-  float* scores = scores_out ? scores_out : (trainable_part ? c->b.scores_t : c->b.scores);
-  const int32_t* idx = forced;
-  if (!forced) {
-    topk_select_from_cls(clsp, B, H, T, k, scores, idx_own, s);
-    idx = idx_own;
-  } else if (scores_out || fw) {
-    cls_head_mean(clsp, B, H, T, scores, s);
+                           float* fw, hipStream_t s, LnAfterDrop* ln, bool trainable_part = false) {
+  SelectArgs a;
+  a.H = c->cfg.heads; a.T = T; a.k = k; a.D = c->cfg.dim;
+  if (!forced || scores_out || fw) {
+    a.cls_prob = trainable_part ? c->b.clsp_t : c->b.clsp;
+    a.scores = scores_out;
   }
-  if (idx_out && k > 0)
-    (void)hipMemcpyAsync(idx_out, idx, sizeof(int32_t) * (size_t)B * k, hipMemcpyDeviceToDevice, s);
-  if (ln && !fw) {
-    ln->done = gather_layernorm_fwd(x_full, idx, B, T, k, D, ln->gamma, ln->beta, c->eps, c->f32, x_kept, ln->y, ln->mean,
-                                    ln->rstd, s);
-    if (ln->done) return idx;
-  }
-  gather_tokens(x_full, idx, B, T, k, D, c->f32, x_kept, s, fw ? k + 2 : k + 1);
-  if (fw) fuse_dropped(x_full, scores, idx, B, T, k, D, c->f32, fw, x_kept, s);
-  return idx;
+  a.forced = forced;
+  a.idx = forced ? nullptr : idx_own;
+  a.idx2 = idx_out;
+  a.x = x_full; a.x_kept = x_kept; a.fw = fw;
+  a.gamma = ln->gamma; a.beta = ln->beta; a.eps = c->eps; a.y = ln->y; a.mean = ln->mean; a.rstd = ln->rstd;
+  ln->done = select_tokens(a, B, c->f32, s);
+  return forced ? forced : idx_own;
 }
 
 void build_shadows(bsr_ctx* c, int first_block, hipStream_t s) {
@@ -951,8 +941,14 @@ int32_t bsr_select_tokens(bsr_ctx* c, const float* cls_attn, const void* x_in, i
   if (x_in && (!aligned16(x_in) || !aligned16(x_out))) return fail(c, BSR_ERR_INVALID_ARG, "x_in / x_out not 16-byte aligned");
   if (B < 1 || n < 0 || n > 1024 || k < 0 || k > n) return fail(c, BSR_ERR_INVALID_ARG, "need B >= 1 and 0 <= k <= n <= 1024 (B=%d n=%d k=%d)", B, n, k);
   hipStream_t s = (hipStream_t)stream;
-  topk_select(cls_attn, B, n, k, idx_out, s);
-  if (x_in) gather_tokens(x_in, idx_out, B, n + 1, k, c->cfg.dim, c->f32, x_out, s);
+  if (x_in || k > 0) {
+    SelectArgs a;
+    a.scores = const_cast<float*>(cls_attn);
+    a.idx = idx_out;
+    a.T = n + 1; a.k = k; a.D = c->cfg.dim;
+    a.x = x_in; a.x_kept = x_out;
+    select_tokens(a, B, c->f32, s);
+  }
   return check_hip(c, "bsr_select_tokens");
 }
 
@@ -1090,10 +1086,8 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     }
     if (tr) {
       float* slot = b.ln_partial ? b.ln_partial + (size_t)(ln_slot++) * ln_deferred_partial_floats(D) : nullptr;
-      if (!layernorm_bwd_deferred(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, slot,
-                                  (float*)gw.ln2_g, (float*)gw.ln2_b, ln_tab, s))
-        layernorm_bwd(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, b.partial,
-                      (float*)gw.ln2_g, (float*)gw.ln2_b, s);
+      layernorm_bwd(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, b.partial, slot,
+                    (float*)gw.ln2_g, (float*)gw.ln2_b, ln_tab, s);
     }
     else
       layernorm_bwd_dx(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, s);
@@ -1116,10 +1110,8 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     // the gradient is not carried below the earliest trainable block (Fig. 2): no dx there
     if (tr) {
       float* slot = b.ln_partial ? b.ln_partial + (size_t)(ln_slot++) * ln_deferred_partial_floats(D) : nullptr;
-      if (!layernorm_bwd_deferred(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32,
-                                  l > ft ? dx_other : nullptr, slot, (float*)gw.ln1_g, (float*)gw.ln1_b, ln_tab, s))
-        layernorm_bwd(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32, l > ft ? dx_other : nullptr,
-                      b.partial, (float*)gw.ln1_g, (float*)gw.ln1_b, s);
+      layernorm_bwd(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32, l > ft ? dx_other : nullptr, b.partial,
+                    slot, (float*)gw.ln1_g, (float*)gw.ln1_b, ln_tab, s);
     }
     else
       layernorm_bwd_dx(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32, dx_other, s);

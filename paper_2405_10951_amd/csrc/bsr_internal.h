@@ -104,41 +104,34 @@ void attn_bwd_mfma(const void* qkv, const void* out, const void* dout, const flo
                    float* delta, void* dqkv, hipStream_t s);
 
 // ---- row-wise / element-wise kernels ------------------------------------------------------------
+// rows of x are pitch_x elements apart (0: D), rows of y follow each other
 void layernorm_fwd(const void* x, int64_t M, int D, const float* gamma, const float* beta, float eps,
-                   bool f32, void* y, float* mean, float* rstd, hipStream_t s);
-// dx = res + LN'(dy) (res may be null; dx may be null to skip it)
-// Token gather (x_kept[b,0] = x[b,0], x_kept[b,1+i] = x[b,1+idx[b,i]]; x is [B,T,D]) and the LayerNorm of the
-// gathered rows in one pass.  Returns false (nothing done) for shapes the one-pass kernel does not take.
-bool gather_layernorm_fwd(const void* x, const int32_t* idx, int B, int T, int k, int D, const float* gamma,
-                          const float* beta, float eps, bool f32, void* x_kept, void* y, float* mean, float* rstd,
-                          hipStream_t s);
+                   bool f32, void* y, float* mean, float* rstd, hipStream_t s, int64_t pitch_x = 0);
+// rows of x, res and dx are pitch elements apart; res may be null, dx null to skip it, dx may be res
+template <typename T> struct LnRows { const T* x; const T* res; T* dx; int64_t pitch; };
+// dx = res + LN'(dy); rows of dy follow each other, those of x, res and dx are pitch elements apart (0: D)
 void layernorm_bwd_dx(const void* dy, const void* x, const float* mean, const float* rstd,
                       const float* gamma, const void* res, int64_t M, int D, bool f32, void* dx,
-                      hipStream_t s);
+                      hipStream_t s, int64_t pitch = 0);
 // dgamma[j] = sum_m dy*xhat, dbeta[j] = sum_m dy ; partial is scratch of colsum_partial_floats()
 void layernorm_bwd_params(const void* dy, const void* x, const float* mean, const float* rstd,
                           int64_t M, int D, bool f32, float* partial, float* dgamma, float* dbeta,
                           hipStream_t s);
-// both of the above; one pass over dy and x on the bf16 path
-void layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma,
-                   const void* res, int64_t M, int D, bool f32, void* dx, float* partial, float* dgamma,
-                   float* dbeta, hipStream_t s);
 // out[j] = sum_m a[m*ld + j]
 void colsum(const void* a, int64_t M, int N, int64_t ld, bool f32, float* partial, float* out,
             hipStream_t s);
 size_t colsum_partial_floats(int64_t M, int N);
-// The LayerNorm backward of several layers with one final reduction for all of them: each call of
-// layernorm_bwd_deferred writes dx and its workgroup partials of dgamma / dbeta into `partial` (its own
-// buffer of ln_deferred_partial_floats(D) floats, kept until the reduction) and adds an entry to the
-// table; ln_deferred_finish adds the partials of every entry in one launch.  Returns false (nothing
-// done) when the shape is not one the one-pass kernel takes: then use layernorm_bwd.
-constexpr int LN_DEFER_MAX = 32;
+// dx and the parameter gradients in one pass, with one final reduction for several layers: a call writes dx and its
+// workgroup partials of dgamma / dbeta into `slot` (a buffer of its own of ln_deferred_partial_floats(D) floats, kept
+// until the reduction) and adds an entry to the table; ln_deferred_finish adds the partials of every entry in one
+// launch.  Shapes the one-pass kernel does not take, a null slot or a full table go through separate kernels.
+constexpr int LN_DEFER_MAX = 32, LN_BWD_BLOCKS = 256;
 struct LnDeferEntry { const float* partial; float* dgamma; float* dbeta; int blocks; };
 struct LnDeferTable { LnDeferEntry e[LN_DEFER_MAX]; int count = 0; int D = 0; };
 size_t ln_deferred_partial_floats(int D);
-bool layernorm_bwd_deferred(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma,
-                            const void* res, int64_t M, int D, bool f32, void* dx, float* partial, float* dgamma,
-                            float* dbeta, LnDeferTable& t, hipStream_t s);
+void layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma,
+                   const void* res, int64_t M, int D, bool f32, void* dx, float* partial, float* slot, float* dgamma,
+                   float* dbeta, LnDeferTable& t, hipStream_t s, int64_t pitch = 0);
 void ln_deferred_finish(LnDeferTable& t, hipStream_t s);
 
 // cls given: also writes the class-token rows x[b, 0, :] = cls + pos[0] of the token tensor x [B, T, D] (same launch
@@ -147,18 +140,23 @@ void patchify(const void* img, int B, int C, int S, int P, bool f32, void* out, 
               const float* cls = nullptr, const float* pos = nullptr, int T = 0, int D = 0, void* x = nullptr);
 void write_cls_rows(const float* cls, const float* pos, int B, int T, int D, bool f32, void* x,
                     hipStream_t s);
-void cls_head_mean(const float* cls_prob, int B, int H, int T, float* scores, hipStream_t s);
-void topk_select(const float* scores, int B, int n, int k, int32_t* idx, hipStream_t s);
-// head mean of the CLS softmax rows [B,H,T] -> scores [B,T-1], then the selection, in one launch
-void topk_select_from_cls(const float* cls_prob, int B, int H, int T, int k, float* scores, int32_t* idx,
-                          hipStream_t s);
-// y rows [CLS; kept] per image; T_out: rows per image of y (0: k + 1)
-void gather_tokens(const void* x, const int32_t* idx, int B, int T, int k, int D, bool f32, void* y,
-                   hipStream_t s, int T_out = 0);
-// Sec. 4.1: row k+1 of y (pitch k+2) = importance-weighted average of the dropped tokens; fw [B,T-1]
-// receives the weights (0 for kept tokens)
-void fuse_dropped(const void* x, const float* scores, const int32_t* idx, int B, int T, int k, int D, bool f32,
-                  float* fw, void* y, hipStream_t s);
+// Token selection and what follows it, in one launch (k_select.hip).  Per image: scores = head mean of the class token's
+// softmax rows (cls_prob [B,H,T], written to scores [B,T-1]) or, with cls_prob null, scores as given; the k best
+// (forced [B,k]: these instead) go to idx and idx2, ascending; with x [B,T,D], rows [class; kept] go to x_kept
+// (k + 1 rows per image; with fw one row more, the dropped tokens fused, and fw [B,T-1] receives the weights); with y also
+// the LayerNorm of x_kept's rows.  Null pointers are skipped.
+struct SelectArgs {
+  const float* cls_prob = nullptr; int H = 0;
+  float* scores = nullptr;
+  const int32_t* forced = nullptr;
+  int32_t *idx = nullptr, *idx2 = nullptr;
+  int T = 0, k = 0, D = 0;
+  const void* x = nullptr; void* x_kept = nullptr;
+  float* fw = nullptr;
+  const float *gamma = nullptr, *beta = nullptr; float eps = 0.f;
+  void* y = nullptr; float *mean = nullptr, *rstd = nullptr;
+};
+bool select_tokens(const SelectArgs& a, int B, bool f32, hipStream_t s);    // true: the LayerNorm was done
 // fw != null: dy has rows [CLS; kept; fused] and dropped tokens get fw times the fused token's gradient
 void scatter_tokens(const void* dy, const int32_t* idx, int B, int T, int k, int D, bool f32,
                     void* dx, hipStream_t s, const float* fw = nullptr);

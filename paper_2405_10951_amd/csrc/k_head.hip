@@ -3,35 +3,30 @@
 //   head_rows_kernel   one workgroup per image: final LayerNorm of the class token, logits, loss of the
 //                      image, dlogits = (softmax - onehot) / B, dz = dlogits . W_h^T, the LayerNorm
 //                      backward of that row, and the gradient at the last block's output (the class
-//                      row gets it, every other token row is zero);
+//                      row gets it; further workgroups set the other token rows to zero);
 //   head_batch_kernel  the sums over the batch: loss, dW_h = z^T dlogits, db_h, dgamma_f, dbeta_f,
-//                      each added over the images in ascending order (bit-reproducible).
+//                      each in a fixed order (bit-reproducible).
 // All arithmetic is fp32 whatever the activation type.
-#include "bsr_internal.h"
+// Bound by latency: an image's workgroup reads W_h twice (307 KB at 768 x 100, from L2).  Both passes walk W_h as it lies
+// in memory, VEC classes per load, as many rows at once as the 1024 threads cover, every load independent; what is to
+// be added across threads goes through LDS.  (Lanes along the classes with a wave sum per row of W_h: 32 us at 32 images, 768 x 100; now 20.
+// The batch kernel with a thread per element walking all images: 13 us at 32 images, 48 at 128; now 6 and 17.)
+#include "rowops.h"
 
 #include <stdint.h>
 
 namespace bsr {
 namespace {
 
-constexpr int WAVE = 64, HT = 1024, HW = HT / WAVE;    // threads and wavefronts per workgroup of the row kernel
-constexpr int NPART = 8;                               // d-ranges the logits are split over
+constexpr int HT = 1024, HW = HT / WAVE;               // threads and wavefronts per workgroup of the row kernel
+constexpr int SCRATCH = 8192;                          // floats of LDS for partial sums
+constexpr int ZERO_PARTS = 4;                          // workgroups per image that clear the other token rows
 constexpr int BT = 256;                                // threads per workgroup of the batch kernel
-constexpr int RPP = 16;                                // rows of W_h a wavefront has in flight in the dz pass
+constexpr int TD = 16, TC = 64, BCH = 32;              // batch kernel: rows x classes of W_h per workgroup, images per chunk
 
-__device__ inline float wave_sum_h(float v) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
-}
-__device__ inline float wave_max_h(float v) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
-  return v;
-}
 // sum (or max) over the workgroup; every thread gets the result; red: HW floats of LDS
 __device__ inline float block_sum(float v, float* red) {
-  v = wave_sum_h(v);
+  v = wave_sum(v);
   __syncthreads();
   if (threadIdx.x % WAVE == 0) red[threadIdx.x / WAVE] = v;
   __syncthreads();
@@ -41,7 +36,7 @@ __device__ inline float block_sum(float v, float* red) {
   return s;
 }
 __device__ inline float block_max(float v, float* red) {
-  v = wave_max_h(v);
+  v = wave_max(v);
   __syncthreads();
   if (threadIdx.x % WAVE == 0) red[threadIdx.x / WAVE] = v;
   __syncthreads();
@@ -52,6 +47,17 @@ __device__ inline float block_max(float v, float* red) {
 }
 
 template <typename T>
+__device__ __forceinline__ void zero_rows(T* dst, int64_t n, int part) {
+  if ((((uintptr_t)dst) & 15) == 0 && (n * sizeof(T)) % 16 == 0) {
+    uint4* z = (uint4*)dst;
+    const int64_t nv = n * sizeof(T) / 16;
+    for (int64_t i = (int64_t)part * HT + threadIdx.x; i < nv; i += ZERO_PARTS * HT) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  } else {
+    for (int64_t i = (int64_t)part * HT + threadIdx.x; i < n; i += ZERO_PARTS * HT) dst[i] = (T)0.f;
+  }
+}
+
+template <typename T, int VEC>
 __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, int Tl, int D, int C, int B,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
                                                        float eps, const float* __restrict__ w_head,
@@ -61,12 +67,17 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
                                                        float* __restrict__ dz_out, float* __restrict__ loss_rows,
                                                        T* __restrict__ dx) {
   extern __shared__ float sm[];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  if (blockIdx.y > 0) {           // the other token rows of this image receive no gradient from the head
+    zero_rows(dx + ((int64_t)b * Tl + 1) * D, (int64_t)(Tl - 1) * D, blockIdx.y - 1);
+    return;
+  }
+  typedef float vecf __attribute__((ext_vector_type(VEC)));
   float* xh = sm;                 // [D] normalised class token
-  float* zs = xh + D;             // [D] LayerNorm output
+  float* zs = xh + D;             // [D] LayerNorm output, later dz
   float* lg = zs + D;             // [C] logits, then dlogits
-  float* part = lg + C;           // [NPART][C] partial logits
-  float* red = part + NPART * C;  // [HW]
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid % WAVE, w = tid / WAVE;
+  float* red = lg + C;            // [HW]
+  float* scr = red + HW;          // [SCRATCH] partial sums
   const T* xr = x + (int64_t)b * Tl * D;
   // final LayerNorm of the class token (two passes over the row held in LDS)
   float s = 0.f;
@@ -82,41 +93,27 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     z_out[(int64_t)b * D + d] = z;
   }
   __syncthreads();
-  // logits: wavefront w covers the d-range of part w % NPART, its lanes walk the classes of the chunks
-  // w / NPART, w / NPART + HW / NPART, ...; four independent accumulators keep loads in flight
-  {
-    const int pt = w % NPART;
-    const int d0 = (int)((int64_t)pt * D / NPART), d1 = (int)((int64_t)(pt + 1) * D / NPART);
-    for (int c0 = (w / NPART) * WAVE; c0 < C; c0 += (HW / NPART) * WAVE) {
-      const int c = c0 + lane;
-      if (c < C) {
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-        const float* wc = w_head + c;
-        int d = d0;
-        for (; d + 31 < d1; d += 32) {          // 32 loads in flight
-          float wv[32];
+  // logits: G groups of VEC classes, R rows of W_h at a time; thread (r, group) adds rows r, r + R, ...
+  const int G = C / VEC, R = max(1, HT / G);
+  for (int i = tid; i < R * G; i += HT) {
+    const int r = i / G, g = i % G;
+    const float* wp = w_head + g * VEC;
+    vecf a = (vecf)0.f;
+#pragma unroll 8
+    for (int d = r; d < D; d += R) a += zs[d] * *(const vecf*)(wp + (int64_t)d * C);
 #pragma unroll
-          for (int u = 0; u < 32; ++u) wv[u] = wc[(int64_t)(d + u) * C];
-#pragma unroll
-          for (int u = 0; u < 32; u += 4) {
-            a0 = fmaf(zs[d + u], wv[u], a0);
-            a1 = fmaf(zs[d + u + 1], wv[u + 1], a1);
-            a2 = fmaf(zs[d + u + 2], wv[u + 2], a2);
-            a3 = fmaf(zs[d + u + 3], wv[u + 3], a3);
-          }
-        }
-        for (; d < d1; ++d) a0 = fmaf(zs[d], wc[(int64_t)d * C], a0);
-        part[pt * C + c] = (a0 + a1) + (a2 + a3);
-      }
-    }
+    for (int v = 0; v < VEC; ++v) scr[r * C + g * VEC + v] = a[v];
   }
   __syncthreads();
-  for (int c = tid; c < C; c += HT) {
-    float a = b_head ? b_head[c] : 0.f;
-#pragma unroll
-    for (int i = 0; i < NPART; ++i) a += part[i * C + c];
-    lg[c] = a;
-    logits_out[(int64_t)b * C + c] = a;
+  for (int i = tid / 8; i < C; i += HT / 8) {          // eight threads per class
+    float a = 0.f;
+    for (int r = tid & 7; r < R; r += 8) a += scr[r * C + i];
+    a += __shfl_xor(a, 1); a += __shfl_xor(a, 2); a += __shfl_xor(a, 4);
+    if ((tid & 7) == 0) {
+      if (b_head) a += b_head[i];
+      lg[i] = a;
+      logits_out[(int64_t)b * C + i] = a;
+    }
   }
   __syncthreads();
   // cross-entropy of this image and dlogits
@@ -135,31 +132,37 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     dlogits_out[(int64_t)b * C + c] = g;
   }
   __syncthreads();
-  // dz = dlogits . W_h^T, then the LayerNorm backward of the row:
-  //   dxhat = dz * gamma;  dx = rstd * (dxhat - mean(dxhat) - xhat * mean(dxhat * xhat))
-  // a wavefront per row d of W_h: lanes walk the classes (coalesced), then a wave sum
-  for (int d = w; d < D; d += RPP * HW) {               // RPP rows per pass: their loads overlap
-    float a[RPP];
+  // dz = dlogits . W_h^T: the same walk, a chunk of rows at a time; each thread leaves the product of its VEC classes, then
+  // eight threads add up a row
+  const int GP = G | 1, DC = max(1, SCRATCH / GP);
+  for (int d0 = 0; d0 < D; d0 += DC) {
+    const int rows = min(DC, D - d0);
+    for (int i = tid; i < R * G; i += HT) {
+      const int g = i % G;
+      float dl[VEC];
 #pragma unroll
-    for (int u = 0; u < RPP; ++u) a[u] = 0.f;
-    for (int c0 = 0; c0 < C; c0 += WAVE) {               // uniform trip count, lanes past C idle
-      const int c = c0 + lane;
-      const bool in = c < C;
-      const float g = in ? lg[c] : 0.f;
+      for (int v = 0; v < VEC; ++v) dl[v] = lg[g * VEC + v];
+      const float* wp = w_head + (int64_t)d0 * C + g * VEC;
+#pragma unroll 8
+      for (int r = i / G; r < rows; r += R) {
+        const vecf w = *(const vecf*)(wp + (int64_t)r * C);
+        float a = 0.f;
 #pragma unroll
-      for (int u = 0; u < RPP; ++u) {
-        const int dd = min(d + u * HW, D - 1);           // rows past D repeat the last one and are dropped below
-        a[u] = fmaf(g, in ? w_head[(int64_t)dd * C + c] : 0.f, a[u]);
+        for (int v = 0; v < VEC; ++v) a = fmaf(dl[v], w[v], a);
+        scr[r * GP + g] = a;
       }
     }
-#pragma unroll
-    for (int u = 0; u < RPP; ++u) {
-      const int dd = d + u * HW;
-      const float t = wave_sum_h(a[u]);
-      if (lane == 0 && dd < D) zs[dd] = t;               // raw dz (z is not needed any more)
+    __syncthreads();
+    for (int r = tid / 8; r < rows; r += HT / 8) {
+      float a = 0.f;
+      for (int g = tid & 7; g < G; g += 8) a += scr[r * GP + g];
+      a += __shfl_xor(a, 1); a += __shfl_xor(a, 2); a += __shfl_xor(a, 4);
+      if ((tid & 7) == 0) zs[d0 + r] = a;              // raw dz (z is not needed any more)
     }
+    __syncthreads();
   }
-  __syncthreads();
+  // the LayerNorm backward of the row:
+  //   dxhat = dz * gamma;  dx = rstd * (dxhat - mean(dxhat) - xhat * mean(dxhat * xhat))
   float s1 = 0.f, s2 = 0.f;
   for (int d = tid; d < D; d += HT) {
     const float t = zs[d];
@@ -173,71 +176,102 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
   s2 = block_sum(s2, red) / (float)D;
   T* dr = dx + (int64_t)b * Tl * D;
   for (int d = tid; d < D; d += HT) dr[d] = (T)(rstd * (zs[d] - s1 - xh[d] * s2));
-  // the other token rows of this image receive no gradient from the head
-  const int64_t rest = (int64_t)(Tl - 1) * D;
-  if ((((uintptr_t)(dr + D)) & 15) == 0 && (rest * sizeof(T)) % 16 == 0) {
-    uint4* zr = (uint4*)(dr + D);
-    const int64_t nv = rest * sizeof(T) / 16;
-    for (int64_t i = tid; i < nv; i += HT) zr[i] = make_uint4(0u, 0u, 0u, 0u);
-  } else {
-    for (int64_t i = tid; i < rest; i += HT) dr[D + i] = (T)0.f;
-  }
 }
 
-// item i < D*C: dW_h[d,c]; next C: db_h[c]; next D: dgamma_f[d], dbeta_f[d]; last: the loss
+// Workgroups [0, nw): a TD x TC piece of dW_h, the images through LDS BCH at a time, added in ascending order;
+// [nw, nw + D / 64): dgamma_f, dbeta_f of 64 features (four threads each take every fourth image); the last: db_h, loss.
 __global__ __launch_bounds__(BT) void head_batch_kernel(const float* __restrict__ z, const float* __restrict__ xhat,
                                                         const float* __restrict__ dlogits, const float* __restrict__ dz,
-                                                        const float* __restrict__ loss_rows, int B, int D, int C,
+                                                        const float* __restrict__ loss_rows, int B, int D, int C, int nw,
                                                         float* __restrict__ dw, float* __restrict__ db,
                                                         float* __restrict__ dgamma, float* __restrict__ dbeta,
                                                         float* __restrict__ loss) {
-  const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x, DC = (int64_t)D * C;
-  if (i < DC) {
-    const int d = (int)(i / C), c = (int)(i % C);
-    float a = 0.f;
-#pragma unroll 8
-    for (int b = 0; b < B; ++b) a = fmaf(z[(int64_t)b * D + d], dlogits[(int64_t)b * C + c], a);
-    dw[i] = a;
-  } else if (i < DC + C) {
-    const int c = (int)(i - DC);
-    float a = 0.f;
-    for (int b = 0; b < B; ++b) a += dlogits[(int64_t)b * C + c];
-    if (db) db[c] = a;
-  } else if (i < DC + C + D) {
-    const int d = (int)(i - DC - C);
-    float g = 0.f, bt = 0.f;
-    for (int b = 0; b < B; ++b) {
-      const float v = dz[(int64_t)b * D + d];
-      g = fmaf(v, xhat[(int64_t)b * D + d], g);
-      bt += v;
+  __shared__ __attribute__((aligned(16))) float zs[BCH][TD];
+  __shared__ float ls[BCH][TC];
+  const int tid = threadIdx.x, lane = tid % WAVE, w = tid / WAVE;
+  if ((int)blockIdx.x < nw) {
+    const int ntc = (C + TC - 1) / TC, d0 = (blockIdx.x / ntc) * TD, c0 = (blockIdx.x % ntc) * TC;
+    float a[4] = {0.f, 0.f, 0.f, 0.f};                 // rows d0 + 4 w .. + 3, class c0 + lane
+    for (int b0 = 0; b0 < B; b0 += BCH) {
+      if (b0) __syncthreads();
+      const int nb = min(BCH, B - b0);
+      for (int i = tid; i < nb * TD; i += BT) { const int d = d0 + i % TD; zs[i / TD][i % TD] = d < D ? z[(int64_t)(b0 + i / TD) * D + d] : 0.f; }
+      for (int i = tid; i < nb * TC; i += BT) { const int c = c0 + i % TC; ls[i / TC][i % TC] = c < C ? dlogits[(int64_t)(b0 + i / TC) * C + c] : 0.f; }
+      __syncthreads();
+#pragma unroll 4
+      for (int b = 0; b < nb; ++b) {
+        const float g = ls[b][lane];
+        const float4 v = *(const float4*)&zs[b][4 * w];
+        a[0] = fmaf(v.x, g, a[0]); a[1] = fmaf(v.y, g, a[1]); a[2] = fmaf(v.z, g, a[2]); a[3] = fmaf(v.w, g, a[3]);
+      }
     }
-    dgamma[d] = g;
-    dbeta[d] = bt;
-  } else if (i == DC + C + D) {
+    if (c0 + lane < C)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (d0 + 4 * w + i < D) dw[(int64_t)(d0 + 4 * w + i) * C + c0 + lane] = a[i];
+    return;
+  }
+  const int d0 = (blockIdx.x - nw) * WAVE;
+  float* r0 = &ls[0][0];
+  if (d0 < D) {
+    const int d = d0 + lane;
+    float g = 0.f, bt = 0.f;
+    if (d < D)
+#pragma unroll 8
+      for (int b = w; b < B; b += BT / WAVE) {
+        const float v = dz[(int64_t)b * D + d];
+        g = fmaf(v, xhat[(int64_t)b * D + d], g);
+        bt += v;
+      }
+    r0[tid] = g;
+    r0[BT + tid] = bt;
+    __syncthreads();
+    if (w == 0 && d < D) {
+#pragma unroll
+      for (int i = 1; i < BT / WAVE; ++i) { g += r0[i * WAVE + lane]; bt += r0[BT + i * WAVE + lane]; }
+      dgamma[d] = g;
+      dbeta[d] = bt;
+    }
+    return;
+  }
+  if (db)
+    for (int c = tid; c < C; c += BT) {
+      float a = 0.f;
+#pragma unroll 16
+      for (int b = 0; b < B; ++b) a += dlogits[(int64_t)b * C + c];
+      db[c] = a;
+    }
+  if (w == 0) {
     float a = 0.f;
-    for (int b = 0; b < B; ++b) a += loss_rows[b];
-    *loss = a / (float)B;
+    for (int b = lane; b < B; b += WAVE) a += loss_rows[b];
+    a = wave_sum(a);
+    if (lane == 0) *loss = a / (float)B;
   }
 }
 
 }  // namespace
 
-size_t head_lds_bytes(int D, int C) { return sizeof(float) * ((size_t)2 * D + (size_t)C + (size_t)NPART * C + HW); }
+size_t head_lds_bytes(int D, int C) { return sizeof(float) * ((size_t)2 * D + (size_t)C + HW + (C > SCRATCH ? C : SCRATCH)); }
 
 void head_fwd_bwd(const void* x, int B, int Tl, int D, int C, bool f32, const float* gamma, const float* beta, float eps,
                   const float* w_head, const float* b_head, const int32_t* labels, float* xhat, float* z, float* logits,
                   float* dlogits, float* dz, float* loss_rows, void* dx, float* dw, float* db, float* dgamma, float* dbeta,
                   float* loss, hipStream_t s) {
   const size_t lds = head_lds_bytes(D, C);
-  if (f32)
-    head_rows_kernel<float><<<B, HT, lds, s>>>((const float*)x, Tl, D, C, B, gamma, beta, eps, w_head, b_head, labels, xhat, z,
-                                               logits, dlogits, dz, loss_rows, (float*)dx);
-  else
-    head_rows_kernel<bf16><<<B, HT, lds, s>>>((const bf16*)x, Tl, D, C, B, gamma, beta, eps, w_head, b_head, labels, xhat, z,
-                                              logits, dlogits, dz, loss_rows, (bf16*)dx);
-  const int64_t items = (int64_t)D * C + C + D + 1;
-  head_batch_kernel<<<(unsigned)((items + BT - 1) / BT), BT, 0, s>>>(z, xhat, dlogits, dz, loss_rows, B, D, C, dw, db, dgamma,
-                                                                    dbeta, loss);
+  const dim3 grid(B, Tl > 1 ? 1 + ZERO_PARTS : 1);
+  auto rows = [&](auto zero, auto vec) {
+    typedef decltype(zero) T;
+    head_rows_kernel<T, decltype(vec)::value><<<grid, HT, lds, s>>>((const T*)x, Tl, D, C, B, gamma, beta, eps, w_head, b_head, labels,
+                                                                  xhat, z, logits, dlogits, dz, loss_rows, (T*)dx);
+  };
+  const bool four = C % 4 == 0 && ((uintptr_t)w_head & 15) == 0;     // (rows of W_h start at a multiple of 16 bytes)
+  if (f32 && four) rows(0.f, RowC<4>{});
+  else if (f32) rows(0.f, RowC<1>{});
+  else if (four) rows((bf16)0.f, RowC<4>{});
+  else rows((bf16)0.f, RowC<1>{});
+  const int nw = ((D + TD - 1) / TD) * ((C + TC - 1) / TC);
+  head_batch_kernel<<<nw + (D + WAVE - 1) / WAVE + 1, BT, 0, s>>>(z, xhat, dlogits, dz, loss_rows, B, D, C, nw, dw, db, dgamma, dbeta,
+                                                                loss);
 }
 
 }  // namespace bsr
