@@ -547,9 +547,10 @@ void dgrad_wgrad(bsr_ctx* c, const GemmDesc& dg, const void* x, const void* dy, 
 // Mixture-of-experts FFN of block l on M2 tokens (Sec. 5.3):  x_out = x_res + sum_s gate_s FFN_{e_s}(h),
 // h = LN2(x_res).  Routing, stable sort of the (token, slot) pairs by expert, gather, two grouped
 // GEMMs over the expert ranges (fc1 + GELU, fc2), weighted un-permute.  u (pre-GELU, may be null)
-// and g are [M2*K, F] in expert order.
+// and g are [M2*K, F] in expert order.  row_pitch > 0: the M2 tokens are rows 0, row_pitch, ... of the block's tokens (their
+// routing is then not reported).
 void moe_ffn_forward(bsr_ctx* c, int l, int B, const void* h, const void* x_res, int M2, MoeBuf& m, void* u,
-                     void* gbuf, void* x_out, hipStream_t s) {
+                     void* gbuf, void* x_out, hipStream_t s, int row_pitch = 0) {
   const bsr_config& cf = c->cfg;
   const int D = cf.dim, F = cf.mlp_hidden, E = cf.n_experts, K = cf.moe_top_k;
   const bsr_block_params& w = c->p.blocks[l];
@@ -558,10 +559,10 @@ void moe_ffn_forward(bsr_ctx* c, int l, int B, const void* h, const void* x_res,
   GemmDesc gl = fwd_desc(c, h, M2, D, E, nullptr, sh.t_router, m.logits);       // router logits, fp32
   gl.out_f32 = true;
   gemm(c, gl, s);
-  moe_topk(m.logits, M2, E, K, c->forced_experts ? c->forced_experts + row0 * K : nullptr, m.experts, m.gates, s);
-  if (c->experts_out)
+  moe_topk(m.logits, M2, E, K, c->forced_experts ? c->forced_experts + row0 * K : nullptr, row_pitch ? row_pitch : 1, m.experts, m.gates, s);
+  if (c->experts_out && !row_pitch)
     (void)hipMemcpyAsync(c->experts_out + row0 * K, m.experts, sizeof(int32_t) * (size_t)M2 * K, hipMemcpyDeviceToDevice, s);
-  if (c->router_logits_out)
+  if (c->router_logits_out && !row_pitch)
     (void)hipMemcpyAsync(c->router_logits_out + row0 * E, m.logits, sizeof(float) * (size_t)M2 * E, hipMemcpyDeviceToDevice, s);
   moe_sort(m.experts, M2, E, K, m.off, m.pos, m.perm_tok, s);
   moe_gather_rows(h, m.perm_tok, (int64_t)M2 * K, D, m.xg, s);
@@ -632,6 +633,18 @@ void attention_bwd(bsr_ctx* c, const void* qkv, const void* out, const void* dou
   else if (c->f32 && attn_f32_supported(T, d))
     attn_bwd_f32((const float*)qkv, (const float*)out, (const float*)dout, lse, B, T, H, (float*)dqkv, s);
   else attn_bwd_generic(qkv, out, dout, lse, B, T, H, d, c->f32, c->b.delta, dqkv, s);
+}
+
+void attention_cls_fwd(bsr_ctx* c, const void* qkv, int B, int T, void* out, float* lse, hipStream_t s) {
+  const int H = c->cfg.heads, d = c->cfg.dim / H;
+  ProfScope ps(c, BSR_PROF_ATTN_FWD, 4.0 * B * H * T * d, s);
+  attn_cls_fwd(qkv, B, T, H, d, c->f32, out, lse, s);
+}
+void attention_cls_bwd(bsr_ctx* c, const void* qkv, const void* out, const void* dout, const float* lse, int B, int T, void* dqkv,
+                       hipStream_t s) {
+  const int H = c->cfg.heads, d = c->cfg.dim / H;
+  ProfScope ps(c, BSR_PROF_ATTN_BWD, 10.0 * B * H * T * d, s);
+  attn_cls_bwd(qkv, out, dout, lse, B, T, H, d, c->f32, dqkv, s);
 }
 
 // Rank the patch tokens of a drop location, hand CLS + the K best to the FFN (Sec. 4.1) and normalise them, in one
@@ -973,23 +986,30 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
   const size_t E = c->esz;
   const int32_t* idx_used[BSR_MAX_BLOCKS] = {};
 
+  // The head reads the class token of the last block and nothing else, so only keys and values of the other tokens are
+  // needed there: the query, the projection, the FFN and everything backward of them down to the attention run on one
+  // row per image (tensors of B rows).  The gradient of the other rows is exactly zero, so nothing is left out.  When
+  // the caller asks for the block's output or for the routing of all its tokens, the block also runs in full, forward,
+  // for those; loss and gradients come from the class rows either way.  (A block that drops tokens runs in full.)
+  const bool cls_last = cf.loss == BSR_LOSS_CE && L > ft && sc.drop_of[L - 1] < 0 && sc.Ta[L - 1] > 1 &&
+                        attn_cls_supported(sc.Ta[L - 1], D / cf.heads, f32);
+
   // ---------------------------------------------------------------- forward, keeping activations
   const char* x = (const char*)x_in;
   size_t idx_off = 0, sc_off = 0;
-  for (int l = ft; l < L; ++l) {
+  // block l behind its qkv product: attention, projection, drop, FFN.  cls: for the class rows only
+  auto block_tail = [&](int l, bool cls) {
     const bsr_block_params& w = c->p.blocks[l];
     const Shadow& sh = b.sh[l];
     SavedBlock& v = b.sv[l];
-    const int Ta = sc.Ta[l], Tm = sc.Tm[l], M = B * Ta, M2 = B * Tm;
+    const int Ta = sc.Ta[l], Tm = sc.Tm[l], M = cls ? B : B * Ta, M2 = cls ? B : B * Tm;
     const int di = sc.drop_of[l];
-    layernorm_fwd(x, M, D, (const float*)w.ln1_g, (const float*)w.ln1_b, c->eps, f32, v.h1, v.mean1, v.rstd1, s);
-    GemmDesc g1 = fwd_desc(c, v.h1, M, D, 3 * D, w.w_qkv, sh.t_qkv, v.qkv);
-    g1.bias = (const float*)w.b_qkv;
-    gemm(c, g1, s);
-    attention_fwd(c, v.qkv, B, Ta, v.o, v.lse, di >= 0 ? b.clsp_t : nullptr, s);
+    if (cls) attention_cls_fwd(c, v.qkv, B, Ta, v.o, v.lse, s);
+    else attention_fwd(c, v.qkv, B, Ta, v.o, v.lse, di >= 0 ? b.clsp_t : nullptr, s);
     GemmDesc g2 = fwd_desc(c, v.o, M, D, D, w.w_proj, sh.t_proj, v.xmid_full);
     g2.bias = (const float*)w.b_proj;
     g2.res = x;
+    if (cls) g2.ldr = (int64_t)Ta * D;
     gemm(c, g2, s);
     LnAfterDrop ln2{(const float*)w.ln2_g, (const float*)w.ln2_b, v.h2, v.mean2, v.rstd2, false};
     if (di >= 0) {
@@ -1003,7 +1023,7 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     if (!ln2.done)
       layernorm_fwd(v.xmid, M2, D, (const float*)w.ln2_g, (const float*)w.ln2_b, c->eps, f32, v.h2, v.mean2, v.rstd2, s);
     if (sc.moe[l]) {
-      moe_ffn_forward(c, l, B, v.h2, v.xmid, M2, v.moe, v.u, v.g, v.xout, s);
+      moe_ffn_forward(c, l, B, v.h2, v.xmid, M2, v.moe, v.u, v.g, v.xout, s, cls ? Tm : 0);
     } else {
       GemmDesc g3 = fwd_desc(c, v.h2, M2, D, F, w.w_fc1, sh.t_fc1, v.g);
       g3.bias = (const float*)w.b_fc1;
@@ -1015,10 +1035,25 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
       g4.res = v.xmid;
       gemm(c, g4, s);
     }
+  };
+  for (int l = ft; l < L; ++l) {
+    const bsr_block_params& w = c->p.blocks[l];
+    SavedBlock& v = b.sv[l];
+    const int M = B * sc.Ta[l];
+    layernorm_fwd(x, M, D, (const float*)w.ln1_g, (const float*)w.ln1_b, c->eps, f32, v.h1, v.mean1, v.rstd1, s);
+    GemmDesc g1 = fwd_desc(c, v.h1, M, D, 3 * D, w.w_qkv, b.sh[l].t_qkv, v.qkv);
+    g1.bias = (const float*)w.b_qkv;
+    gemm(c, g1, s);
+    const bool cls = cls_last && l == L - 1;
+    const bool whole = x_final_out || (sc.moe[l] && (c->experts_out || c->router_logits_out));
+    if (!cls || whole) block_tail(l, false);
+    if (x_final_out && l == L - 1)
+      (void)hipMemcpyAsync(x_final_out, v.xout, (size_t)B * sc.T_last * D * E, hipMemcpyDeviceToDevice, s);
+    if (cls) block_tail(l, true);
     x = v.xout;
   }
-  const int Tl = sc.T_last;
-  if (x_final_out) (void)hipMemcpyAsync(x_final_out, x, (size_t)B * Tl * D * E, hipMemcpyDeviceToDevice, s);
+  if (x_final_out && L == ft) (void)hipMemcpyAsync(x_final_out, x, (size_t)B * sc.T_last * D * E, hipMemcpyDeviceToDevice, s);
+  const int Tl = cls_last ? 1 : sc.T_last;      // rows per image of the last block's output and of its gradient
 
   // ---------------------------------------------------------------- head, loss, dLoss/dx_last
   char* dx = b.dxa;
@@ -1065,7 +1100,8 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     const bsr_block_params& gw = grads->blocks[l];
     const Shadow& sh = b.sh[l];
     SavedBlock& v = b.sv[l];
-    const int Ta = sc.Ta[l], Tm = sc.Tm[l], M = B * Ta, M2 = B * Tm;
+    const bool cls = cls_last && l == L - 1;
+    const int Ta = sc.Ta[l], Tm = sc.Tm[l], M = B * Ta, Mo = cls ? B : M, M2 = cls ? B : B * Tm;
     const int di = sc.drop_of[l];
     const char* xin = (l == ft) ? (const char*)x_in : b.sv[l - 1].xout;
 
@@ -1100,21 +1136,23 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     }
 
     // MHSA branch.  dO = dx . Wproj^T; dWproj = o^T dx; attention backward; dWqkv = h1^T dqkv
-    const GemmDesc d3 = dgrad_desc(c, dx, M, D, D, w.w_proj, sh.s_proj, b.dh);
-    if (tr) dgrad_wgrad(c, d3, v.o, dx, M, D, D, gw.w_proj, gw.b_proj, s);
+    const GemmDesc d3 = dgrad_desc(c, dx, Mo, D, D, w.w_proj, sh.s_proj, b.dh);
+    if (tr) dgrad_wgrad(c, d3, v.o, dx, Mo, D, D, gw.w_proj, gw.b_proj, s);
     else gemm(c, d3, s);
-    attention_bwd(c, v.qkv, v.o, b.dh, v.lse, B, Ta, b.dqkv, s);
+    if (cls) attention_cls_bwd(c, v.qkv, v.o, b.dh, v.lse, B, Ta, b.dqkv, s);
+    else attention_bwd(c, v.qkv, v.o, b.dh, v.lse, B, Ta, b.dqkv, s);
     const GemmDesc d4 = dgrad_desc(c, b.dqkv, M, D, 3 * D, w.w_qkv, sh.s_qkv, b.dh);
     if (tr) dgrad_wgrad(c, d4, v.h1, b.dqkv, M, D, 3 * D, gw.w_qkv, gw.b_qkv, s);
     else gemm(c, d4, s);
     // the gradient is not carried below the earliest trainable block (Fig. 2): no dx there
+    const int period = cls ? Ta : 0;           // only the class rows have a residual gradient
     if (tr) {
       float* slot = b.ln_partial ? b.ln_partial + (size_t)(ln_slot++) * ln_deferred_partial_floats(D) : nullptr;
       layernorm_bwd(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32, l > ft ? dx_other : nullptr, b.partial,
-                    slot, (float*)gw.ln1_g, (float*)gw.ln1_b, ln_tab, s);
+                    slot, (float*)gw.ln1_g, (float*)gw.ln1_b, ln_tab, s, period);
     }
     else
-      layernorm_bwd_dx(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32, dx_other, s);
+      layernorm_bwd_dx(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32, dx_other, s, period);
     if (l > ft) std::swap(dx, dx_other);
   }
   ln_deferred_finish(ln_tab, s);

@@ -23,7 +23,8 @@ struct GemmDesc {
   int act = ACT_NONE;
   void* aux = nullptr;       // ACT_GELU: if set, receives the pre-activation u (dtype of C, ld = ldc)
                              // ACT_GELU_BWD: the stored u; C = acc * GELU'(u)
-  const void* res = nullptr; // residual added last (dtype of C, ld = ldc, same row mapping)
+  const void* res = nullptr; // residual added last (dtype of C, same row mapping)
+  int64_t ldr = 0;           // its row stride; 0: ldc
   int remap_np = 0;          // > 0 (patch embedding): row(m) = m + m / np + 1, and pos[(m % np + 1), n]
   const float* pos = nullptr;//   is added; rows of CLS tokens are left untouched
   float* bsum = nullptr;     // weight-gradient form only (A^T and B share the token index k): if set,
@@ -98,21 +99,28 @@ size_t gemm_nt_tile_lds_bytes(int id);          // dynamic LDS a workgroup of th
 bool gemm_nt_tile_is_free(const GemmDesc& g);
 size_t gemm_splitk_ws_floats(int dim, int mlp_hidden);
 
+// Attention of query 0 (the class token) alone: out [B, H d], lse [B, H]; backward from a gradient at those rows, dqkv
+// [B, T, 3 H d] written whole.  d: whole 16-byte pieces
+bool attn_cls_supported(int T, int d, bool f32);
+void attn_cls_fwd(const void* qkv, int B, int T, int H, int d, bool f32, void* out, float* lse, hipStream_t s);
+void attn_cls_bwd(const void* qkv, const void* out, const void* dout, const float* lse, int B, int T, int H, int d, bool f32,
+                  void* dqkv, hipStream_t s);
+
 bool attn_mfma_supported(int T, int d);
 void attn_fwd_mfma(const void* qkv, int B, int T, int H, void* out, float* lse, float* cls_prob, hipStream_t s);
 void attn_bwd_mfma(const void* qkv, const void* out, const void* dout, const float* lse, int B, int T, int H,
                    float* delta, void* dqkv, hipStream_t s);
 
 // ---- row-wise / element-wise kernels ------------------------------------------------------------
-// rows of x are pitch_x elements apart (0: D), rows of y follow each other
 void layernorm_fwd(const void* x, int64_t M, int D, const float* gamma, const float* beta, float eps,
-                   bool f32, void* y, float* mean, float* rstd, hipStream_t s, int64_t pitch_x = 0);
-// rows of x, res and dx are pitch elements apart; res may be null, dx null to skip it, dx may be res
-template <typename T> struct LnRows { const T* x; const T* res; T* dx; int64_t pitch; };
-// dx = res + LN'(dy); rows of dy follow each other, those of x, res and dx are pitch elements apart (0: D)
+                   bool f32, void* y, float* mean, float* rstd, hipStream_t s);
+// res may be null, dx null to skip it.  res_period 0: a residual row per row; P > 0: rows 0, P, 2P, ... have one each
+// (the residual then has M / P rows)
+template <typename T> struct LnRows { const T* x; const T* res; T* dx; int res_period; };
+// dx = res + LN'(dy)
 void layernorm_bwd_dx(const void* dy, const void* x, const float* mean, const float* rstd,
                       const float* gamma, const void* res, int64_t M, int D, bool f32, void* dx,
-                      hipStream_t s, int64_t pitch = 0);
+                      hipStream_t s, int res_period = 0);
 // dgamma[j] = sum_m dy*xhat, dbeta[j] = sum_m dy ; partial is scratch of colsum_partial_floats()
 void layernorm_bwd_params(const void* dy, const void* x, const float* mean, const float* rstd,
                           int64_t M, int D, bool f32, float* partial, float* dgamma, float* dbeta,
@@ -131,7 +139,7 @@ struct LnDeferTable { LnDeferEntry e[LN_DEFER_MAX]; int count = 0; int D = 0; };
 size_t ln_deferred_partial_floats(int D);
 void layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma,
                    const void* res, int64_t M, int D, bool f32, void* dx, float* partial, float* slot, float* dgamma,
-                   float* dbeta, LnDeferTable& t, hipStream_t s, int64_t pitch = 0);
+                   float* dbeta, LnDeferTable& t, hipStream_t s, int res_period = 0);
 void ln_deferred_finish(LnDeferTable& t, hipStream_t s);
 
 // cls given: also writes the class-token rows x[b, 0, :] = cls + pos[0] of the token tensor x [B, T, D] (same launch
@@ -181,8 +189,9 @@ size_t mean_sq_partial_floats();
 constexpr int MOE_MAX_EXPERTS = 32, MOE_MAX_TOPK = 4;
 // from the router logits [M,E]: the K largest (ties: lower index) in descending order, or the forced
 // choice; gates = softmax over the K selected logits
-void moe_topk(const float* logits, int64_t M, int E, int K, const int32_t* forced, int32_t* experts, float* gates,
-              hipStream_t s);
+// (of token t: row t * forced_pitch)
+void moe_topk(const float* logits, int64_t M, int E, int K, const int32_t* forced, int64_t forced_pitch, int32_t* experts,
+              float* gates, hipStream_t s);
 // bf16 copy of w_router [D,E] stored [E,D]
 void moe_router_copy(const float* w_router, int D, int E, void* t_router, hipStream_t s);
 // stable counting sort of the (token, slot) pairs by expert: off[E+1], pos[t*K+s] = row of the pair

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_f(u[e]);
     }
-    if (g.res) v += *(const f32x4*)((const float*)g.res + off);
+    if (g.res) v += *(const f32x4*)((const float*)g.res + (g.ldr ? row * g.ldr + n : off));
     *(f32x4*)(C + off) = v;
   }
 }
@@ -265,7 +265,7 @@ bool gemm_f32_supported(const GemmDesc& g) {
   if (am && (g.M % 4 || g.a_cs % 4)) return false;
   if (bk && (g.K % 4 || g.b_cs % 4)) return false;
   if (bn && (g.N % 4 || g.b_rs % 4)) return false;
-  if (g.N % 4 || g.ldc % 4) return false;
+  if (g.N % 4 || g.ldc % 4 || g.ldr % 4) return false;
   const uintptr_t all = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.res |
                         (uintptr_t)g.pos;
   return (all & 15) == 0 && (!g.bsum || bn);

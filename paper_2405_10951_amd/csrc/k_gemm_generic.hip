@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(GemmDesc g) {
         v *= gelu_grad_f((float)((const TOut*)g.aux)[off]);
       }
       if (posr) v += posr[n];
-      if (g.res) v += (float)((const TOut*)g.res)[off];
+      if (g.res) v += (float)((const TOut*)g.res)[g.ldr ? row * g.ldr + n : off];
       C[off] = (TOut)v;
     }
   }

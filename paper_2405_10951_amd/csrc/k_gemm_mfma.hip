@@ -111,7 +111,7 @@ __device__ __forceinline__ void finish8(const GemmDesc& g, float (&v)[8], int m,
     *(float4*)(c + 4) = make_float4(v[4], v[5], v[6], v[7]);
   } else {
     if (g.res) {
-      const bf16x8 rr = *(const bf16x8*)((const bf16*)g.res + off);
+      const bf16x8 rr = *(const bf16x8*)((const bf16*)g.res + (g.ldr ? row * g.ldr + col : off));
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] += (float)rr[j];
     }
@@ -1282,7 +1282,7 @@ void launch_nt_fused(const GemmDesc& g, const TnPlan& p, hipStream_t s) {
 
 bool is_nt(const GemmDesc& g) {
   return !g.in_f32 && g.a_cs == 1 && g.b_rs == 1 && g.K % 8 == 0 && g.a_rs % 8 == 0 && g.b_cs % 8 == 0 &&
-         g.N % 8 == 0 && g.ldc % 8 == 0 && (((uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C) & 15) == 0 &&
+         g.N % 8 == 0 && g.ldc % 8 == 0 && g.ldr % 8 == 0 && (((uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C) & 15) == 0 &&
          (((uintptr_t)g.aux | (uintptr_t)g.res) & 15) == 0 && g.M > 0 && g.N > 0 && g.K > 0;
 }
 

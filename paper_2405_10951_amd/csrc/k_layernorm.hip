@@ -12,17 +12,15 @@ namespace {
 constexpr int COLSUM_R = 64;      // row chunks of the generic column reduction
 constexpr int FINAL_WAVES = 16;
 
-// x and y rows are pitch_x / pitch_y elements apart
 template <typename T, int MAXC>
-__global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, int64_t pitch_x, int64_t M, int D,
-                                                     const float* __restrict__ gamma, const float* __restrict__ beta, float eps,
-                                                     T* __restrict__ y, int64_t pitch_y, float* __restrict__ mean,
-                                                     float* __restrict__ rstd) {
+__global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, int64_t M, int D, const float* __restrict__ gamma,
+                                                     const float* __restrict__ beta, float eps, T* __restrict__ y,
+                                                     float* __restrict__ mean, float* __restrict__ rstd) {
   constexpr int V = Chunk<T>::V;
   const int lane = threadIdx.x % WAVE;
   const int64_t m = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
   if (m >= M) return;
-  const T* xr = x + m * pitch_x;
+  const T* xr = x + m * D;
   float v[MAXC][V];
 #pragma unroll
   for (int i = 0; i < MAXC; ++i) {
@@ -33,19 +31,18 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, in
       for (int e = 0; e < V; ++e) v[i][e] = (float)t[e];
     }
   }
-  layernorm_row<T, MAXC>(v, D, lane, gamma, beta, eps, y + m * pitch_y, mean ? mean + m : nullptr, rstd ? rstd + m : nullptr);
+  layernorm_row<T, MAXC>(v, D, lane, gamma, beta, eps, y + m * D, mean ? mean + m : nullptr, rstd ? rstd + m : nullptr);
 }
 
 // any row length
 template <typename T>
-__global__ __launch_bounds__(256) void ln_fwd_any_kernel(const T* __restrict__ x, int64_t pitch_x, int64_t M, int D,
-                                                         const float* __restrict__ gamma, const float* __restrict__ beta, float eps,
-                                                         T* __restrict__ y, int64_t pitch_y, float* __restrict__ mean,
-                                                         float* __restrict__ rstd) {
+__global__ __launch_bounds__(256) void ln_fwd_any_kernel(const T* __restrict__ x, int64_t M, int D, const float* __restrict__ gamma,
+                                                         const float* __restrict__ beta, float eps, T* __restrict__ y,
+                                                         float* __restrict__ mean, float* __restrict__ rstd) {
   const int lane = threadIdx.x % WAVE;
   const int64_t m = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
   if (m >= M) return;
-  const T* xr = x + m * pitch_x;
+  const T* xr = x + m * D;
   float s = 0.f;
   for (int j = lane; j < D; j += WAVE) s += (float)xr[j];
   const float mu = wave_sum(s) / (float)D;
@@ -59,10 +56,17 @@ __global__ __launch_bounds__(256) void ln_fwd_any_kernel(const T* __restrict__ x
     if (mean) mean[m] = mu;
     if (rstd) rstd[m] = rs;
   }
-  for (int j = lane; j < D; j += WAVE) y[m * pitch_y + j] = (T)(((float)xr[j] - mu) * rs * gamma[j] + beta[j]);
+  for (int j = lane; j < D; j += WAVE) y[m * D + j] = (T)(((float)xr[j] - mu) * rs * gamma[j] + beta[j]);
 }
 
-// dx = res + rstd * (g - mean(g) - xhat * mean(g * xhat)),  g = dy * gamma; any row length, rows D apart
+// the residual row of row m, null where it has none
+template <typename T> __device__ inline const T* res_row(const LnRows<T>& r, int64_t m, int D) {
+  if (!r.res) return nullptr;
+  if (r.res_period == 0) return r.res + m * D;
+  return m % r.res_period == 0 ? r.res + m / r.res_period * D : nullptr;
+}
+
+// dx = res + rstd * (g - mean(g) - xhat * mean(g * xhat)),  g = dy * gamma; any row length
 template <typename T>
 __global__ __launch_bounds__(256) void ln_bwd_dx_any_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D,
                                                             const float* __restrict__ mean, const float* __restrict__ rstd,
@@ -72,7 +76,8 @@ __global__ __launch_bounds__(256) void ln_bwd_dx_any_kernel(const T* __restrict_
   if (m >= M) return;
   const float mu = mean[m], rs = rstd[m];
   const T* dyr = dy + m * D;
-  const T* xr = r.x + m * r.pitch;
+  const T* xr = r.x + m * D;
+  const T* rr = res_row(r, m, D);
   float s1 = 0.f, s2 = 0.f;
   for (int j = lane; j < D; j += WAVE) {
     const float g = (float)dyr[j] * gamma[j];
@@ -83,8 +88,8 @@ __global__ __launch_bounds__(256) void ln_bwd_dx_any_kernel(const T* __restrict_
   for (int j = lane; j < D; j += WAVE) {
     const float g = (float)dyr[j] * gamma[j], xh = ((float)xr[j] - mu) * rs;
     float v = rs * (g - m1 - xh * m2);
-    if (r.res) v += (float)r.res[m * r.pitch + j];
-    r.dx[m * r.pitch + j] = (T)v;
+    if (rr) v += (float)rr[j];
+    r.dx[m * D + j] = (T)v;
   }
 }
 
@@ -120,7 +125,7 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
       const int c = lane + i * WAVE;
-      if (c < nch) { na[i] = *(const vec*)(dy + m * D + c * V); nt[i] = *(const vec*)(r.x + m * r.pitch + c * V); }
+      if (c < nch) { na[i] = *(const vec*)(dy + m * D + c * V); nt[i] = *(const vec*)(r.x + m * D + c * V); }
     }
     nmu = mean[m]; nrs = rstd[m];
   };
@@ -131,10 +136,11 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) { a[i] = na[i]; t[i] = nt[i]; }
     const float mu = nmu, rs = nrs;
-    if (r.dx && r.res)
+    const T* res = r.dx ? res_row(r, m, D) : nullptr;
+    if (res)
 #pragma unroll
       for (int i = 0; i < MAXC; ++i)
-        if (lane + i * WAVE < nch) rr[i] = *(const vec*)(r.res + m * r.pitch + (lane + i * WAVE) * V);
+        if (lane + i * WAVE < nch) rr[i] = *(const vec*)(res + (lane + i * WAVE) * V);
     prefetch(m + stride);
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
@@ -158,10 +164,10 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
           for (int e = 0; e < V; ++e) {
             const float xh = ((float)t[i][e] - mu) * rs;
             float v = rs * ((float)a[i][e] * gg[i][e] - m1 - xh * m2);
-            if (r.res) v += (float)rr[i][e];
+            if (res) v += (float)rr[i][e];
             o[e] = (T)v;
           }
-          *(vec*)(r.dx + m * r.pitch + c * V) = o;
+          *(vec*)(r.dx + m * D + c * V) = o;
         }
       }
     }
@@ -207,7 +213,7 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
 // WITH_XHAT: two sums, dy*xhat (slot 0) and dy (slot 1); otherwise the plain column sum (slot 0).
 template <typename T, bool WITH_XHAT>
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict__ a, int64_t ld, const T* __restrict__ x,
-                                                             int64_t pitch_x, const float* __restrict__ mean,
+                                                             const float* __restrict__ mean,
                                                              const float* __restrict__ rstd, int64_t M, int N, int rows_per_chunk,
                                                              float* __restrict__ partial) {
   __shared__ float red[2][4][WAVE];
@@ -220,7 +226,7 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
     for (int64_t m = r0 + w; m < r1; m += 4) {
       const float v = (float)a[m * ld + col];
       if (WITH_XHAT) {
-        s0 += v * ((float)x[m * pitch_x + col] - mean[m]) * rstd[m];
+        s0 += v * ((float)x[m * N + col] - mean[m]) * rstd[m];
         s1 += v;
       } else {
         s0 += v;
@@ -283,13 +289,13 @@ inline int chunks_of(int64_t M) {
 }
 
 template <typename T>
-void ln_fwd(const void* x, int64_t pitch_x, int64_t M, int D, const float* gamma, const float* beta, float eps, void* y,
-            int64_t pitch_y, float* mean, float* rstd, hipStream_t s) {
+void ln_fwd(const void* x, int64_t M, int D, const float* gamma, const float* beta, float eps, void* y, float* mean, float* rstd,
+            hipStream_t s) {
   const unsigned grid = (unsigned)((M + 3) / 4);
-  const bool vec = pitch_x % Chunk<T>::V == 0 && pitch_y % Chunk<T>::V == 0 && with_row_chunks<T>(D, [&](auto C) {
-    ln_fwd_kernel<T, decltype(C)::value><<<grid, 256, 0, s>>>((const T*)x, pitch_x, M, D, gamma, beta, eps, (T*)y, pitch_y, mean, rstd);
+  const bool vec = with_row_chunks<T>(D, [&](auto C) {
+    ln_fwd_kernel<T, decltype(C)::value><<<grid, 256, 0, s>>>((const T*)x, M, D, gamma, beta, eps, (T*)y, mean, rstd);
   });
-  if (!vec) ln_fwd_any_kernel<T><<<grid, 256, 0, s>>>((const T*)x, pitch_x, M, D, gamma, beta, eps, (T*)y, pitch_y, mean, rstd);
+  if (!vec) ln_fwd_any_kernel<T><<<grid, 256, 0, s>>>((const T*)x, M, D, gamma, beta, eps, (T*)y, mean, rstd);
 }
 
 // wavefronts per workgroup and workgroups of the pass with parameter sums
@@ -301,7 +307,6 @@ template <typename T, int MAXC> int bwd_waves(int64_t M) {
 template <typename T>
 bool ln_bwd(const void* dy, const LnRows<T>& r, const float* mean, const float* rstd, const float* gamma, int64_t M, int D,
             float* partial, int* blocks_out, hipStream_t s) {
-  if (r.pitch % Chunk<T>::V) return false;
   return with_row_chunks<T>(D, [&](auto C) {
     constexpr int MAXC = decltype(C)::value;
     if (partial) {
@@ -322,69 +327,71 @@ bool ln_bwd(const void* dy, const LnRows<T>& r, const float* mean, const float* 
 }
 
 template <typename T>
-void bwd_dx_t(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma, const void* res, int64_t pitch,
-              int64_t M, int D, void* dx, hipStream_t s) {
-  const LnRows<T> r{(const T*)x, (const T*)res, (T*)dx, pitch};
+void bwd_dx_t(const void* dy, const LnRows<T>& r, const float* mean, const float* rstd, const float* gamma, int64_t M, int D,
+              hipStream_t s) {
+  if (!r.dx) return;
   if (!ln_bwd<T>(dy, r, mean, rstd, gamma, M, D, nullptr, nullptr, s))
     ln_bwd_dx_any_kernel<T><<<(unsigned)((M + 3) / 4), 256, 0, s>>>((const T*)dy, r, M, D, mean, rstd, gamma);
 }
 
 template <typename T>
-void bwd_params_t(const void* dy, const void* x, int64_t pitch, const float* mean, const float* rstd, int64_t M, int D, float* partial,
-                  float* dgamma, float* dbeta, hipStream_t s) {
+void bwd_params_t(const void* dy, const void* x, const float* mean, const float* rstd, int64_t M, int D, float* partial, float* dgamma,
+                  float* dbeta, hipStream_t s) {
   const int rpc = rows_per_chunk(M), ch = chunks_of(M);
-  colsum_partial_kernel<T, true><<<dim3((D + WAVE - 1) / WAVE, ch), 256, 0, s>>>((const T*)dy, D, (const T*)x, pitch, mean, rstd, M, D,
-                                                                               rpc, partial);
+  colsum_partial_kernel<T, true><<<dim3((D + WAVE - 1) / WAVE, ch), 256, 0, s>>>((const T*)dy, D, (const T*)x, mean, rstd, M, D, rpc,
+                                                                               partial);
   colsum_final_kernel<<<(D + WAVE - 1) / WAVE, FINAL_WAVES * WAVE, 0, s>>>(partial, D, ch, COLSUM_R, dgamma, dbeta);
+}
+
+template <typename T>
+void bwd_t(const void* dy, const LnRows<T>& r, const float* mean, const float* rstd, const float* gamma, int64_t M, int D,
+           float* partial, float* slot, float* dgamma, float* dbeta, LnDeferTable& t, hipStream_t s) {
+  int blocks = 0;
+  if (slot && t.count < LN_DEFER_MAX && (t.count == 0 || t.D == D) &&
+      ln_bwd<T>(dy, r, mean, rstd, gamma, M, D, slot, &blocks, s)) {
+    t.D = D;
+    t.e[t.count++] = LnDeferEntry{slot, dgamma, dbeta, blocks};
+    return;
+  }
+  bwd_params_t<T>(dy, r.x, mean, rstd, M, D, partial, dgamma, dbeta, s);
+  bwd_dx_t<T>(dy, r, mean, rstd, gamma, M, D, s);
+}
+
+template <typename T> LnRows<T> rows_of(const void* x, const void* res, void* dx, int res_period) {
+  return LnRows<T>{(const T*)x, (const T*)res, (T*)dx, res_period};
 }
 
 }  // namespace
 
 void layernorm_fwd(const void* x, int64_t M, int D, const float* gamma, const float* beta, float eps, bool f32, void* y, float* mean,
-                   float* rstd, hipStream_t s, int64_t pitch_x) {
+                   float* rstd, hipStream_t s) {
   if (M <= 0) return;
-  if (pitch_x == 0) pitch_x = D;
-  if (f32) ln_fwd<float>(x, pitch_x, M, D, gamma, beta, eps, y, D, mean, rstd, s);
-  else ln_fwd<bf16>(x, pitch_x, M, D, gamma, beta, eps, y, D, mean, rstd, s);
+  if (f32) ln_fwd<float>(x, M, D, gamma, beta, eps, y, mean, rstd, s);
+  else ln_fwd<bf16>(x, M, D, gamma, beta, eps, y, mean, rstd, s);
 }
 
 void layernorm_bwd_dx(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma, const void* res,
-                      int64_t M, int D, bool f32, void* dx, hipStream_t s, int64_t pitch) {
-  if (M <= 0 || !dx) return;
-  if (pitch == 0) pitch = D;
-  if (f32) bwd_dx_t<float>(dy, x, mean, rstd, gamma, res, pitch, M, D, dx, s);
-  else bwd_dx_t<bf16>(dy, x, mean, rstd, gamma, res, pitch, M, D, dx, s);
+                      int64_t M, int D, bool f32, void* dx, hipStream_t s, int res_period) {
+  if (M <= 0) return;
+  if (f32) bwd_dx_t<float>(dy, rows_of<float>(x, res, dx, res_period), mean, rstd, gamma, M, D, s);
+  else bwd_dx_t<bf16>(dy, rows_of<bf16>(x, res, dx, res_period), mean, rstd, gamma, M, D, s);
 }
 
 void layernorm_bwd_params(const void* dy, const void* x, const float* mean, const float* rstd, int64_t M, int D, bool f32,
                           float* partial, float* dgamma, float* dbeta, hipStream_t s) {
   if (M <= 0) return;
-  if (f32) bwd_params_t<float>(dy, x, D, mean, rstd, M, D, partial, dgamma, dbeta, s);
-  else bwd_params_t<bf16>(dy, x, D, mean, rstd, M, D, partial, dgamma, dbeta, s);
+  if (f32) bwd_params_t<float>(dy, x, mean, rstd, M, D, partial, dgamma, dbeta, s);
+  else bwd_params_t<bf16>(dy, x, mean, rstd, M, D, partial, dgamma, dbeta, s);
 }
 
 size_t ln_deferred_partial_floats(int D) { return (size_t)2 * LN_BWD_BLOCKS * (size_t)D; }
 
 void layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma, const void* res, int64_t M,
                    int D, bool f32, void* dx, float* partial, float* slot, float* dgamma, float* dbeta, LnDeferTable& t, hipStream_t s,
-                   int64_t pitch) {
+                   int res_period) {
   if (M <= 0) return;
-  if (pitch == 0) pitch = D;
-  int blocks = 0;
-  if (slot && t.count < LN_DEFER_MAX && (t.count == 0 || t.D == D)) {
-    const bool took = f32 ? ln_bwd<float>(dy, LnRows<float>{(const float*)x, (const float*)res, (float*)dx, pitch}, mean, rstd, gamma, M,
-                                          D, slot, &blocks, s)
-                          : ln_bwd<bf16>(dy, LnRows<bf16>{(const bf16*)x, (const bf16*)res, (bf16*)dx, pitch}, mean, rstd, gamma, M, D,
-                                         slot, &blocks, s);
-    if (took) {
-      t.D = D;
-      t.e[t.count++] = LnDeferEntry{slot, dgamma, dbeta, blocks};
-      return;
-    }
-  }
-  if (f32) bwd_params_t<float>(dy, x, pitch, mean, rstd, M, D, partial, dgamma, dbeta, s);
-  else bwd_params_t<bf16>(dy, x, pitch, mean, rstd, M, D, partial, dgamma, dbeta, s);
-  layernorm_bwd_dx(dy, x, mean, rstd, gamma, res, M, D, f32, dx, s, pitch);
+  if (f32) bwd_t<float>(dy, rows_of<float>(x, res, dx, res_period), mean, rstd, gamma, M, D, partial, slot, dgamma, dbeta, t, s);
+  else bwd_t<bf16>(dy, rows_of<bf16>(x, res, dx, res_period), mean, rstd, gamma, M, D, partial, slot, dgamma, dbeta, t, s);
 }
 
 void ln_deferred_finish(LnDeferTable& t, hipStream_t s) {
@@ -400,9 +407,9 @@ void colsum(const void* a, int64_t M, int N, int64_t ld, bool f32, float* partia
   const int rpc = rows_per_chunk(M), ch = chunks_of(M);
   const dim3 grid((N + WAVE - 1) / WAVE, ch);
   if (f32)
-    colsum_partial_kernel<float, false><<<grid, 256, 0, s>>>((const float*)a, ld, nullptr, 0, nullptr, nullptr, M, N, rpc, partial);
+    colsum_partial_kernel<float, false><<<grid, 256, 0, s>>>((const float*)a, ld, nullptr, nullptr, nullptr, M, N, rpc, partial);
   else
-    colsum_partial_kernel<bf16, false><<<grid, 256, 0, s>>>((const bf16*)a, ld, nullptr, 0, nullptr, nullptr, M, N, rpc, partial);
+    colsum_partial_kernel<bf16, false><<<grid, 256, 0, s>>>((const bf16*)a, ld, nullptr, nullptr, nullptr, M, N, rpc, partial);
   colsum_final_kernel<<<(N + WAVE - 1) / WAVE, FINAL_WAVES * WAVE, 0, s>>>(partial, N, ch, 0, out, nullptr);
 }
 

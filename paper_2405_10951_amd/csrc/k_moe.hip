@@ -23,7 +23,7 @@ __device__ inline float wave_sum(float v) {
 // comparison, never by a computed register index.
 template <int EMAX>
 __global__ __launch_bounds__(256) void moe_topk_kernel(const float* __restrict__ logits, int64_t M, int E, int K,
-                                                       const int32_t* __restrict__ forced,
+                                                       const int32_t* __restrict__ forced, int64_t forced_pitch,
                                                        int32_t* __restrict__ experts, float* __restrict__ gates) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= M) return;
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void moe_topk_kernel(const float* __restrict__
     int best = 0;
     float bv = -INFINITY;
     if (forced) {
-      best = min(max(forced[t * K + s], 0), E - 1);
+      best = min(max(forced[t * forced_pitch * K + s], 0), E - 1);
 #pragma unroll
       for (int e = 0; e < EMAX; ++e)
         if (e == best) bv = v[e];
@@ -270,13 +270,13 @@ __global__ __launch_bounds__(256) void moe_unpermute_bwd_kernel(const bf16* __re
 
 }  // namespace
 
-void moe_topk(const float* logits, int64_t M, int E, int K, const int32_t* forced, int32_t* experts, float* gates,
+void moe_topk(const float* logits, int64_t M, int E, int K, const int32_t* forced, int64_t forced_pitch, int32_t* experts, float* gates,
               hipStream_t s) {
   if (M <= 0) return;
   const unsigned grid = (unsigned)((M + 255) / 256);
-  if (E <= 8) moe_topk_kernel<8><<<grid, 256, 0, s>>>(logits, M, E, K, forced, experts, gates);
-  else if (E <= 16) moe_topk_kernel<16><<<grid, 256, 0, s>>>(logits, M, E, K, forced, experts, gates);
-  else moe_topk_kernel<32><<<grid, 256, 0, s>>>(logits, M, E, K, forced, experts, gates);
+  if (E <= 8) moe_topk_kernel<8><<<grid, 256, 0, s>>>(logits, M, E, K, forced, forced_pitch, experts, gates);
+  else if (E <= 16) moe_topk_kernel<16><<<grid, 256, 0, s>>>(logits, M, E, K, forced, forced_pitch, experts, gates);
+  else moe_topk_kernel<32><<<grid, 256, 0, s>>>(logits, M, E, K, forced, forced_pitch, experts, gates);
 }
 
 void moe_router_copy(const float* w_router, int D, int E, void* t_router, hipStream_t s) {

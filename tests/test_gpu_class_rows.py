@@ -1,0 +1,46 @@
+"""The last block on its class rows alone (what the head reads): loss, logits and every gradient against the oracle, and
+the same bits whether or not the block's whole output (or the routing of all its tokens) is asked for."""
+import numpy as np
+import pytest
+
+import bsr_synth as S
+from test_gpu_parity import TOL_BF16, TOL_FP32, hip  # noqa: F401  (hip is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+# several blocks trained; only the last one; the last one frozen in the gradient path; one image; a head size of 16
+# (fewer pieces per row than lanes on it); experts in the last block
+CASES = [("mini_4blk", dict()), ("mini_4blk", dict(first_trainable=3)), ("mini_interleaved", dict(trainable_blocks=[1, 3])),
+         ("mini_4blk", dict(batch=1, drop_blocks=[1], keep_k=[63])), ("mini_4blk", dict(heads=8)), ("mini_moe", dict(batch=16))]
+
+
+@pytest.mark.parametrize("dtype,tol", [("fp32", TOL_FP32), ("bf16", TOL_BF16)])
+@pytest.mark.parametrize("name,over", CASES, ids=lambda v: v if isinstance(v, str) else "-".join(map(str, v)) or "plain")
+def test_last_block_on_class_rows(hip, orc64, name, over, dtype, tol):
+    import torch
+    if name == "mini_moe" and dtype == "fp32":
+        pytest.skip("mixtures of experts exist in bf16 only")
+    cfg = S.get_config(name, dtype=dtype, **over)
+    p = S.make_params(cfg, std=0.05)
+    x, y = S.make_inputs(cfg)
+    ref = orc64.step(cfg, p, x, y)
+    forced = ref.get("experts") if name == "mini_moe" else None
+    full = hip.run_hip_step(cfg, p, x, y, forced_idx=ref["kept_idx"], forced_experts=forced)
+    ctx, dev, B = full["ctx"], torch.device("cuda:0"), x.shape[0]
+    if forced:
+        fex = torch.as_tensor(np.concatenate([np.asarray(forced[l], np.int32).reshape(-1) for l in sorted(forced)]), dtype=torch.int32)
+        ctx.bsr_moe_routing_io(fex.to(dev))
+    cat = lambda which: (torch.as_tensor(np.concatenate([np.asarray(ref["kept_idx"][i], np.int32).reshape(-1) for i in which]),  # noqa: E731
+                                         dtype=torch.int32).to(dev) if which else None)
+    xf = ctx.bsr_forward_frozen(torch.as_tensor(x).to(dev).to(ctx.act_dtype).contiguous(), forced_idx=cat(ctx.frozen_drops))
+    grads = ctx.new_grads()
+    logits = torch.zeros((B, cfg["num_classes"]), dtype=torch.float32, device=dev)
+    loss = ctx.bsr_train_blocks_fwd_bwd(xf, torch.as_tensor(y, dtype=torch.int32).to(dev), grads, logits_out=logits,
+                                        forced_idx=cat(ctx.train_drops))
+    torch.cuda.synchronize()
+    assert hip.rel(logits.cpu().numpy(), ref["logits"]) < tol
+    for n, g in ref["grads"].items():
+        bar = 2 * tol if n.endswith("w_router") else tol          # (the router matrix is measured, not held to the bar: see smoke())
+        assert hip.rel(grads[n].cpu().numpy(), g) < bar, n
+        assert np.array_equal(grads[n].cpu().numpy(), full["grads"][n]), n
+    assert float(loss[0]) == full["loss"] and np.array_equal(logits.cpu().numpy(), full["logits"])
