@@ -1302,31 +1302,16 @@ bool gemm_mfma_supported(const GemmDesc& g) { return is_nt(g) || is_tn(g); }
 // takes writes at about 64 bytes per clock, so a k-tile of a BM x BN block tile costs 2 (BM + BN)
 // clocks of LDS writes (plus the fragment reads) against BM * BN / 32 clocks of MFMA work.  Only
 // 256 x 256 tiles keep that ratio well below one, but at M = 2144 .. 6304 rows they leave most CUs
-// without a tile, so each launch takes the shape that a two-parameter model predicts to be fastest:
-//   time = ceil(tiles / 256 CUs) * (fixed + per_ktile * K / 64)
-// with (fixed, per_ktile) in microseconds fitted per tile shape to the durations of the step's own
-// GEMMs (N and K in {768, 2304, 3072}, epilogues included) with every shape forced in turn.  The
-// model's picks cost 2.5 % more than the per-launch best of those runs (its residual is 3 - 5 us per
-// launch), which is why a context can instead time every shape on its own launches and keep the
-// fastest (bsr_autotune).  The large tiles pay a long fixed part because their single workgroup per
-// CU cannot hide its prologue and epilogue.  Every shape accumulates an output element over k in the
-// same order, so the choice never changes a result.
-struct NtShape { int id, bm, bn; float fixed_us, per_ktile_us; };
-static const NtShape kNtShapes[] = {
-    {256128, 256, 128, 9.77f, 0.714f},  {128128, 128, 128, 2.78f, 0.577f}, {192128, 192, 128, 4.17f, 0.734f},
-    {160256, 160, 256, 11.85f, 0.975f}, {256256, 256, 256, 17.70f, 1.300f},
-    {128064, 128, 64, 1.39f, 0.351f},   {96128, 96, 128, 2.38f, 0.507f},
-    // offered to the measured choice only (no fitted constants: fixed_us < 0 keeps them out of the model)
-    {64128, 64, 128, -1.f, 0.f},        {128256, 128, 256, -1.f, 0.f},     {192256, 192, 256, -1.f, 0.f},
-    {256064, 256, 64, -1.f, 0.f},       {96256, 96, 256, -1.f, 0.f},
+// without a tile, so each launch takes the shape that a model predicts to be fastest (below), or the one a context
+// has measured to be (bsr_autotune).  Every shape accumulates an output element over k in the same order, so the choice
+// never changes a result.
+static const int kNtShapes[] = {
+    256128, 128128, 192128, 160256, 256256, 128064, 96128, 64128, 128256, 192256, 256064, 96256,
     // with deeper register prefetch (id = PF * 1000000 + shape)
-    {3128064, 128, 64, -1.f, 0.f},      {3064128, 64, 128, -1.f, 0.f},     {2192128, 192, 128, -1.f, 0.f},
-    {2256128, 256, 128, -1.f, 0.f},     {2128128, 128, 128, -1.f, 0.f},
+    3128064, 3064128, 2192128, 2256128, 2128128,
     // operands straight into LDS (id = 7000000 + shape; K a multiple of 64, one weight matrix, no folded LayerNorm:
     // a launch outside that takes the model's shape instead)
-    {7256256, 256, 256, -1.f, 0.f},     {7320256, 320, 256, -1.f, 0.f},    {7192256, 192, 256, -1.f, 0.f},
-    {7256192, 256, 192, -1.f, 0.f},     {7256128, 256, 128, -1.f, 0.f},    {7128256, 128, 256, -1.f, 0.f},
-    {7192128, 192, 128, -1.f, 0.f},     {7128128, 128, 128, -1.f, 0.f},
+    7256256, 7320256, 7192256, 7256192, 7256128, 7128256, 7192128, 7128128,
 };
 // stages of the direct-to-LDS shapes (0: not one of them)
 static int ntd_stages(int id) {
@@ -1337,29 +1322,56 @@ static int ntd_stages(int id) {
   }
 }
 
-// the model's pick and its time (without the launch itself)
-static int gemm_nt_model(int M, int N, int K, float* us_out) {
+// The model: with t tiles, time = c0 + ceil(t / 256) (c1 + c2 K / 64) + t / 256 (c3 + c4 K / 64) + ceil(t / 512) (c5 + c6 K / 64)
+// microseconds: a fixed part, rounds of one workgroup per CU, what scales with the work, rounds of two per CU.  Constants
+// fitted to every shape forced in turn on the launches of ViT-B and DeiT-S steps at 1 .. 128 images, keep ratios of 1 and
+// 0.5, 224 and 384 pixels (436 launches of 256 .. 25216 rows, event-bracketed, in their place in the step).  Over these
+// the six shapes' picks take 1.5 % longer than the fastest of all 25 (fitted on half of them, the other half: 1.2 %); the model
+// before, seven register-staged shapes with two constants each, took 7.4 %.  More shapes bring nothing.
+struct NtModel { int id, bm, bn; float c[7]; };
+const NtModel kNtModel[] = {
+    {64128, 64, 128, {6.508f, 0.000f, 0.142f, 1.061f, 0.000f, 0.000f, 0.353f}},
+    {192128, 192, 128, {7.783f, 1.559f, 0.501f, 1.705f, 0.104f, 0.000f, 0.182f}},
+    {256128, 256, 128, {3.608f, 3.854f, 0.664f, 2.056f, 0.342f, 2.154f, 0.001f}},
+    {3128064, 128, 64, {6.542f, 0.794f, 0.173f, 0.773f, 0.052f, 0.000f, 0.222f}},
+    {7256256, 256, 256, {0.000f, 8.827f, 1.173f, 1.403f, 0.332f, 5.356f, 0.142f}},
+    {7320256, 320, 256, {10.479f, 4.369f, 1.469f, 3.163f, 0.515f, 0.945f, 0.009f}},
+};
+// A launch that carries the layer's weight gradient as well: three shapes, 2.6 % above the fastest (shapes chosen by the
+// model of the input gradient alone: 9.6 %).
+const NtModel kPairModel[] = {
+    {128064, 128, 64, {10.593f, 0.000f, 0.213f, 3.588f, 0.481f, 0.000f, 0.079f}},
+    {192128, 192, 128, {9.635f, 0.000f, 0.405f, 12.419f, 1.218f, 0.000f, 0.112f}},
+    {3128064, 128, 64, {10.966f, 0.000f, 0.188f, 3.563f, 0.555f, 0.000f, 0.006f}},
+};
+constexpr float EVENTS_US = 4.5f;      // the part of c0 that a launch inside a chain does not take (the event pair)
+
+// the model's pick and its time, event pair included; direct_ok: direct-to-LDS shapes are allowed, folded: the LayerNorm is
+// folded in (64 columns per tile would double its dot instructions per MFMA)
+template <int N>
+static int model_pick(const NtModel (&table)[N], int M, int Nc, int K, bool direct_ok, bool folded, float* us_out) {
   int pick = 0;
-  float best = 0.f;
-  for (const NtShape& t : kNtShapes) {
-    if (t.fixed_us < 0.f) continue;
-    const int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-    const float us = (float)((tiles + 255) / 256) * (t.fixed_us + t.per_ktile_us * (float)((K + BK - 1) / BK));
-    if (!pick || us < best) { pick = t.id; best = us; }
+  const float k = (float)((K + BK - 1) / BK);
+  for (const NtModel& e : table) {
+    if ((ntd_stages(e.id) && !direct_ok) || (folded && e.bn < 128)) continue;
+    const int64_t t = (int64_t)((M + e.bm - 1) / e.bm) * ((Nc + e.bn - 1) / e.bn);
+    const float r1 = (float)((t + 255) / 256), w = (float)t / 256.f, r2 = (float)((t + 511) / 512);
+    const float us = e.c[0] + r1 * (e.c[1] + e.c[2] * k) + w * (e.c[3] + e.c[4] * k) + r2 * (e.c[5] + e.c[6] * k);
+    if (!pick || us < *us_out) { pick = e.id; *us_out = us; }
   }
-  *us_out = best;
   return pick;
 }
+static int nt_pick(const GemmDesc& g, float* us) { return model_pick(kNtModel, g.M, g.N, g.K, is_ntd(g), g.ln_colsum != nullptr, us); }
 int gemm_nt_model_tile(int M, int N, int K) {
   float us = 0.f;
-  return gemm_nt_model(M, N, K, &us);
+  return model_pick(kNtModel, M, N, K, K % BK == 0, false, &us);
 }
 size_t gemm_nt_tile_lds_bytes(int id) {
   const int bm = id % 1000000 / 1000, bn = id % 1000, nst = ntd_stages(id);
   return (size_t)(nst ? nst : 2) * (bm + bn) * BK * sizeof(bf16);
 }
 int gemm_nt_tile_count() { return (int)(sizeof(kNtShapes) / sizeof(kNtShapes[0])); }
-int gemm_nt_tile_id(int i) { return kNtShapes[i].id; }
+int gemm_nt_tile_id(int i) { return kNtShapes[i]; }
 bool gemm_nt_tile_is_free(const GemmDesc& g) { return is_nt(g) && !g.grp_off; }
 
 void gemm_tn_flush(TnChain* chain, hipStream_t s) {
@@ -1374,16 +1386,15 @@ void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hip
     return;
   }
   float few_us = 0.f, tiled_us = 0.f;
-  const int few = few_pick(g, &few_us);
-  gemm_nt_model(g.M, g.N, g.K, &tiled_us);
-  if (few >= 0 && few_us < FEW_LEAD * (tiled_us + TILED_LAUNCH_US)) {      // by size alone, whatever tile is asked for
+  const int few = few_pick(g, &few_us), model = nt_pick(g, &tiled_us);
+  if (few >= 0 && few_us < FEW_LEAD * (tiled_us - EVENTS_US)) {      // by size alone, whatever tile is asked for
     launch_few(few, g, s);
     return;
   }
   // groups are a few hundred rows and each ends in a partial row tile: 128-row tiles, 64-row ones where a group
   // averages under four of those (the last tile of a 268-row group is 9 % full at 128 rows, 19 % at 64)
   int pick = g.grp_off ? (g.M < 512 * g.groups ? 64128 : 128128) : tile;
-  if (!pick || (ntd_stages(pick) && !is_ntd(g))) pick = gemm_nt_model_tile(g.M, g.N, g.K);
+  if (!pick || (ntd_stages(pick) && !is_ntd(g))) pick = model;
   switch (pick) {
     case 7256256: launch_ntd<256, 256, 2, 4, 2>(g, s); break;
     case 7320256: launch_ntd<320, 256, 2, 4, 2>(g, s); break;
@@ -1418,14 +1429,13 @@ void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hip
 // behind the input-gradient tiles), otherwise as two.
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile, TnChain* chain) {
-  int pick = tile;
-  if (!pick) pick = gemm_nt_model_tile(nt.M, nt.N, nt.K);
+  float few_us = 0.f, tiled_us = 0.f, pair_us = 0.f;
+  const int pick = tile ? tile : model_pick(kPairModel, nt.M, nt.N, nt.K, false, false, &pair_us);
   // (an input gradient of few rows goes to the kernel for those, in a launch of its own, where that saves more than
   // the launch costs)
-  float few_us = 0.f, tiled_us = 0.f;
   const int few = few_pick(nt, &few_us);
-  gemm_nt_model(nt.M, nt.N, nt.K, &tiled_us);
-  const bool few_pays = few >= 0 && few_us < FEW_LEAD * tiled_us;
+  nt_pick(nt, &tiled_us);
+  const bool few_pays = few >= 0 && few_us < FEW_LEAD * (tiled_us - EVENTS_US - TILED_LAUNCH_US);
   const bool can = is_nt(nt) && is_tn(tn) && !nt.grp_off && !tn.grp_off && nt.K % BK == 0 && !few_pays;
   if (can) {
     switch (pick) {
@@ -1440,7 +1450,7 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
       default: break;
     }
   }
-  gemm_mfma(nt, splitk_ws, splitk_ws_floats, s, pick, chain);
+  gemm_mfma(nt, splitk_ws, splitk_ws_floats, s, tile, chain);
   gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
 }
 
