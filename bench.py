@@ -257,7 +257,8 @@ def main():
         return step_flops(c["dim"], c["mlp_hidden"], c["num_classes"], pd, ctx.tokens_attn[0] - 1,
                           ctx.tokens_attn, ctx.tokens_mlp, c["first_trainable"], nb or batch,
                           moe_blocks=tuple(c.get("moe_blocks", ())), n_experts=c.get("n_experts", 0),
-                          moe_top_k=c.get("moe_top_k", 0), trainable_blocks=c.get("trainable_blocks"))
+                          moe_top_k=c.get("moe_top_k", 0), trainable_blocks=c.get("trainable_blocks"),
+                          class_rows_last=c["num_classes"] > 0)
 
     ctx = build_context(cfg, batch)
     r = time_steps(ctx, cfg, batch, args.steps, args.warmup, profile_steps=min(args.steps, 10),

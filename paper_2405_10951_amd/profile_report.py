@@ -31,7 +31,7 @@ def _short(name: str) -> str:
 
 
 def _is_gemm(name: str) -> bool:
-    return "gemm_nt_kernel" in name or "gemm_ntd_kernel" in name or "gemm_tn_kernel" in name
+    return any(k in name for k in ("gemm_nt_kernel", "gemm_ntd_kernel", "gemm_nt_few_kernel", "gemm_tn_kernel"))
 
 
 def trace(path: str, nsteps: int = 20) -> None:
@@ -50,7 +50,7 @@ def trace(path: str, nsteps: int = 20) -> None:
     span = (int(sel[-1]["End_Timestamp"]) - int(sel[0]["Start_Timestamp"])) / 1e3
     print(f"# last {nsteps} steps: {len(sel)} dispatches ({len(sel) / nsteps:.1f} per step), kernel time "
           f"{tot / nsteps:.1f} us per step, span {span / nsteps:.1f} us per step")
-    print(f"# GEMM launches (gemm_nt / gemm_ntd / gemm_tn kernels): {gemm / nsteps:.1f} us per step, summed durations")
+    print(f"# GEMM launches (gemm_nt / gemm_ntd / gemm_nt_few / gemm_tn kernels): {gemm / nsteps:.1f} us per step, summed durations")
     print(f"{'kernel':72s} {'per_step':>8s} {'us/step':>9s} {'avg_us':>8s} {'pct':>6s}")
     for n, (c, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
         print(f"{n[:72]:72s} {c / nsteps:8.1f} {t / nsteps:9.1f} {t / c:8.1f} {100 * t / tot:6.2f}")
@@ -74,6 +74,8 @@ def counters(path: str, nsteps: int = 5) -> None:
     sel = rows[starts[-nsteps]:] + [r for r in rows[:starts[-nsteps]] if "copybuffer" in r[1].lower()][-1:]
 
     def cls(n: str) -> str:
+        if "gemm_nt_few_kernel" in n:
+            return "gemm_nt_few (few rows)"
         if "gemm_ntd_kernel" in n:
             return "gemm_ntd (operands straight into LDS)"
         if _is_gemm(n):
