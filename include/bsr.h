@@ -370,6 +370,9 @@ int32_t bsr_adamw_step(bsr_ctx* ctx, const bsr_params* grads, const bsr_params* 
  *   workspace  device fp32 scratch of workspace_floats elements, may be NULL.  With at least
  *              2*(in+1)*out floats the sum over M is split over several workgroups per output tile
  *              (partial sums are added in a fixed order: results are bit-reproducible).
+ * bsr_linear_backward: bsr_linear_dgrad and bsr_linear_wgrad of one layer as the step issues them, in one launch where
+ *   the block-tile shape allows it.  Arguments as for the two; `in` and `out` multiples of 8 (others: INVALID_ARG).  dx, dw
+ *   and db have the same bits whatever the tile.
  */
 int32_t bsr_linear_forward(const void* x, int32_t M, int32_t in, int32_t out, const void* w_t,
                            const float* bias, int32_t act, void* u_out, const void* res, void* y,
@@ -378,6 +381,9 @@ int32_t bsr_linear_dgrad(const void* dy, int32_t M, int32_t in, int32_t out, con
                          const void* u, void* dx, int32_t tile, int32_t* used_mfma, void* stream);
 int32_t bsr_linear_wgrad(const void* x, const void* dy, int32_t M, int32_t in, int32_t out, float* dw,
                          float* db, float* workspace, size_t workspace_floats, int32_t* used_mfma, void* stream);
+int32_t bsr_linear_backward(const void* x, const void* dy, int32_t M, int32_t in, int32_t out, const void* w_s,
+                            const void* u, void* dx, float* dw, float* db, float* workspace,
+                            size_t workspace_floats, int32_t tile, void* stream);
 
 /*
  * bsr_linear_wgrad for callers that cannot allocate device memory and have no workspace to hand over (code under

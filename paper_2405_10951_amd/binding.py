@@ -118,6 +118,9 @@ def load_library():
     lib.bsr_linear_wgrad.restype = C.c_int32
     lib.bsr_linear_wgrad.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p,
                                      C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]
+    lib.bsr_linear_backward.restype = C.c_int32
+    lib.bsr_linear_backward.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p,
+                                        C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_int32, C.c_void_p]
     lib.bsr_linear_wgrad_static.restype = C.c_int32
     lib.bsr_linear_wgrad_static.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p,
                                             C.c_void_p, C.c_void_p, C.c_void_p]
@@ -284,6 +287,20 @@ def bsr_linear_wgrad(x, dy, dw=None, workspace=None, db=None):
                                            C.c_size_t(0 if workspace is None else workspace.numel()),
                                            C.byref(used), _cur_stream(x)))
     return dw, used.value
+
+
+def bsr_linear_backward(x, dy, w_s, u=None, workspace=None, tile=0):
+    """x [M,in], dy [M,out], w_s [in,out] bf16 -> (dx [M,in] bf16, dw [in,out] fp32, db [out] fp32), issued as the step issues
+    them.  u [M,in]: dx is multiplied by GELU'(u)."""
+    import torch
+    M, kin = x.shape
+    out = dy.shape[1]
+    dx = torch.empty((M, kin), dtype=torch.bfloat16, device=x.device)
+    dw = torch.empty((kin, out), dtype=torch.float32, device=x.device)
+    db = torch.empty(out, dtype=torch.float32, device=x.device)
+    _check(load_library().bsr_linear_backward(_dp(x), _dp(dy), M, kin, out, _dp(w_s), _dp(u), _dp(dx), _dp(dw), _dp(db), _dp(workspace),
+                                              C.c_size_t(0 if workspace is None else workspace.numel()), tile, _cur_stream(x)))
+    return dx, dw, db
 
 
 def bsr_linear_wgrad_static(x, dy, dw=None, db=None):

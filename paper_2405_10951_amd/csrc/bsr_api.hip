@@ -1641,6 +1641,24 @@ int32_t bsr_linear_wgrad(const void* x, const void* dy, int32_t M, int32_t in, i
   return run_layer(g, used_mfma, stream, "bsr_linear_wgrad", workspace, workspace_floats);
 }
 
+int32_t bsr_linear_backward(const void* x, const void* dy, int32_t M, int32_t in, int32_t out, const void* w_s, const void* u,
+                            void* dx, float* dw, float* db, float* workspace, size_t workspace_floats, int32_t tile, void* stream) {
+  if (!aligned16(x) || !aligned16(dy) || !aligned16(w_s) || !aligned16(dx) || !aligned16(dw) || !aligned16(db) || (u && !aligned16(u)) ||
+      (workspace && !aligned16(workspace)) || M < 1 || in < 1 || out < 1)
+    return fail(nullptr, BSR_ERR_INVALID_ARG, "bsr_linear_backward: bad argument");
+  if (!known_tile(tile)) return fail(nullptr, BSR_ERR_INVALID_ARG, "bsr_linear_backward: %d is not a tile shape id", tile);
+  GemmDesc d, w;
+  d.A = dy; d.a_rs = out; d.a_cs = 1; d.B = w_s; d.b_rs = 1; d.b_cs = out;
+  d.C = dx; d.ldc = in; d.M = M; d.N = in; d.K = out;
+  if (u) { d.act = ACT_GELU_BWD; d.aux = const_cast<void*>(u); }
+  w.A = x; w.a_rs = 1; w.a_cs = in; w.B = dy; w.b_rs = out; w.b_cs = 1;
+  w.C = dw; w.ldc = out; w.M = in; w.N = out; w.K = M; w.out_f32 = true; w.bsum = db;
+  if (!gemm_nt_tile_is_free(d) || !gemm_mfma_supported(w))
+    return fail(nullptr, BSR_ERR_INVALID_ARG, "bsr_linear_backward: %d x %d x %d is not an MFMA shape", M, in, out);
+  gemm_mfma_pair(d, w, workspace, workspace_floats, (hipStream_t)stream, tile, nullptr);
+  return check_hip(nullptr, "bsr_linear_backward");
+}
+
 int32_t bsr_linear_wgrad_static(const void* x, const void* dy, int32_t M, int32_t in, int32_t out, float* dw, float* db,
                                 int32_t* used_mfma, void* stream) {
   if (!aligned16(x) || !aligned16(dy) || !aligned16(dw) || M < 1 || in < 1 || out < 1)

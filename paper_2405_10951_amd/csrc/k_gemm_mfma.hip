@@ -1374,27 +1374,30 @@ int gemm_nt_tile_count() { return (int)(sizeof(kNtShapes) / sizeof(kNtShapes[0])
 int gemm_nt_tile_id(int i) { return kNtShapes[i]; }
 bool gemm_nt_tile_is_free(const GemmDesc& g) { return is_nt(g) && !g.grp_off; }
 
+// The one rule that sends a product to the kernel for few rows: the shape of that kernel, or -1 for the tiled ones.  It
+// looks at the product's sizes, and at whether the launch could carry the layer's weight gradient as well (tiled kernels
+// do that in one launch; here it costs another one), and at nothing else: the kernel for few rows adds over k in another
+// order, so with the tile choice in the rule, tuning would change bits.
+static int few_rows_shape(const GemmDesc& g, bool carries_wgrad) {
+  float few_us = 0.f, tiled_us = 0.f;
+  const int few = few_pick(g, &few_us);
+  if (few < 0) return -1;
+  nt_pick(g, &tiled_us);
+  return few_us < FEW_LEAD * (tiled_us - EVENTS_US - (carries_wgrad ? TILED_LAUNCH_US : 0.f)) ? few : -1;
+}
+
 void gemm_tn_flush(TnChain* chain, hipStream_t s) {
   if (!chain || chain->pending.splits <= 0) return;
   launch_reduce(chain->pending, s);
   chain->pending = TnReduce();
 }
 
-void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile, TnChain* chain) {
-  if (is_tn(g)) {
-    launch_tn(g, splitk_ws, splitk_ws_floats, s, chain);
-    return;
-  }
-  float few_us = 0.f, tiled_us = 0.f;
-  const int few = few_pick(g, &few_us), model = nt_pick(g, &tiled_us);
-  if (few >= 0 && few_us < FEW_LEAD * (tiled_us - EVENTS_US)) {      // by size alone, whatever tile is asked for
-    launch_few(few, g, s);
-    return;
-  }
+// The tiled kernels, in the shape asked for or, for 0 and for a shape that cannot take the product, the model's.
+static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
   // groups are a few hundred rows and each ends in a partial row tile: 128-row tiles, 64-row ones where a group
   // averages under four of those (the last tile of a 268-row group is 9 % full at 128 rows, 19 % at 64)
   int pick = g.grp_off ? (g.M < 512 * g.groups ? 64128 : 128128) : tile;
-  if (!pick || (ntd_stages(pick) && !is_ntd(g))) pick = model;
+  if (!pick || (ntd_stages(pick) && !is_ntd(g))) { float us = 0.f; pick = nt_pick(g, &us); }
   switch (pick) {
     case 7256256: launch_ntd<256, 256, 2, 4, 2>(g, s); break;
     case 7320256: launch_ntd<320, 256, 2, 4, 2>(g, s); break;
@@ -1424,21 +1427,26 @@ void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hip
   }
 }
 
+void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile, TnChain* chain) {
+  if (is_tn(g)) {
+    launch_tn(g, splitk_ws, splitk_ws_floats, s, chain);
+    return;
+  }
+  const int few = few_rows_shape(g, false);
+  if (few >= 0) launch_few(few, g, s);
+  else nt_tiled(g, s, tile);
+}
+
 // The input gradient (NT) and the weight gradient (TN) of one layer.  When the tile shape chosen for the
 // NT part runs with 8 waves they go out as one launch (the weight-gradient workgroups fill the machine
-// behind the input-gradient tiles), otherwise as two.
+// behind the input-gradient tiles), otherwise as two.  Which kernel multiplies does not depend on the tile either way.
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile, TnChain* chain) {
-  float few_us = 0.f, tiled_us = 0.f, pair_us = 0.f;
-  const int pick = tile ? tile : model_pick(kPairModel, nt.M, nt.N, nt.K, false, false, &pair_us);
-  // (an input gradient of few rows goes to the kernel for those, in a launch of its own, where that saves more than
-  // the launch costs)
-  const int few = few_pick(nt, &few_us);
-  nt_pick(nt, &tiled_us);
-  const bool few_pays = few >= 0 && few_us < FEW_LEAD * (tiled_us - EVENTS_US - TILED_LAUNCH_US);
-  const bool can = is_nt(nt) && is_tn(tn) && !nt.grp_off && !tn.grp_off && nt.K % BK == 0 && !few_pays;
+  const int few = few_rows_shape(nt, true);
+  const bool can = few < 0 && is_nt(nt) && is_tn(tn) && !nt.grp_off && !tn.grp_off && nt.K % BK == 0;
   if (can) {
-    switch (pick) {
+    float us = 0.f;
+    switch (tile ? tile : model_pick(kPairModel, nt.M, nt.N, nt.K, false, false, &us)) {
       case 128064: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<128, 64, 4, 2, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
       case 64128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<64, 128, 2, 4, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
       case 192128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<192, 128, 2, 4, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
@@ -1450,7 +1458,8 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
       default: break;
     }
   }
-  gemm_mfma(nt, splitk_ws, splitk_ws_floats, s, tile, chain);
+  if (few >= 0) launch_few(few, nt, s);
+  else nt_tiled(nt, s, tile);                 // (not gemm_mfma: its rule is that of a product on its own)
   gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
 }
 

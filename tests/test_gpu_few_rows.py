@@ -24,3 +24,31 @@ def test_products_of_few_rows(env, orc64, M, kin, out):
 @pytest.mark.parametrize("M,kin,out", [(2200, 64, 1544), (2300, 320, 1160), (2050, 832, 2312)])
 def test_every_tile_shape_at_larger_row_counts(env, orc64, M, kin, out):
     K.test_every_tile_shape_gives_the_same_bits(env, orc64, M, kin, out)
+
+
+# a layer's two gradients together, at rows where a product on its own takes the kernel for few rows and one that can carry
+# the weight gradient does not (768 x 768 up to 128 and at 321 .. 672 rows, 768 from 2304 at 673 .. 1024, 3072 from 768 at 65 .. 160,
+# 384 x 384 up to 1344, 1536 from 384 up to 320), and where both take it: no tile changes a bit
+@pytest.mark.parametrize("M,kin,out", [(32, 768, 768), (128, 768, 768), (400, 768, 768), (1000, 768, 2304), (129, 3072, 768), (536, 384, 384),
+                                       (1343, 384, 384), (67, 1536, 384), (32, 768, 3072)])
+def test_no_tile_changes_the_gradients_of_a_layer(env, orc64, M, kin, out):
+    torch, P = env
+    rng = np.random.default_rng(M + kin + out)
+    dev = lambda a: K.to_dev(torch, a, torch.bfloat16)      # noqa: E731
+    x, dy, u = K.bf16_np(rng, (M, kin)), K.bf16_np(rng, (M, out)), K.bf16_np(rng, (M, kin))
+    w = K.bf16_np(rng, (kin, out), 0.05)
+    xt, dyt, wt, ut = dev(x), dev(dy), dev(w), dev(u)
+
+    def run(tile):
+        got = P.bsr_linear_backward(xt, dyt, wt, u=ut, tile=tile)
+        torch.cuda.synchronize()
+        return [t.float().cpu().numpy() for t in got]
+
+    base = run(0)
+    K.assert_close(base[0], orc64.gelu_bwd(orc64.linear_dgrad(dy, w), u), "dx")
+    dw, db = orc64.linear_wgrad(x, dy)
+    K.assert_close(base[1], dw, "dw")
+    K.assert_close(base[2], db, "db")
+    for tile in P.bsr_gemm_tile_shapes():
+        for name, a, c in zip(("dx", "dw", "db"), base, run(tile)):
+            assert np.array_equal(a, c), f"tile shape {tile}, {name}: {int(np.sum(a != c))} of {a.size} elements differ"
