@@ -103,6 +103,7 @@ struct Tune {
   int cur_batch = 0;
   int cand = -1;                       // >= 0 while tuning: index of the shape every launch is forced to
   int cand_train = -1;                 // >= 0: the trainable part is forced to this shape instead (two-stream tuning)
+  bool aside = false;                  // launches that not every call issues: no place in the order, no pick
   std::vector<TuneRec> recs;
 };
 
@@ -476,7 +477,7 @@ struct TileChoice {
 };
 TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s) {
   TileChoice ch;
-  if (!gemm_nt_tile_is_free(g)) return ch;
+  if (!gemm_nt_tile_is_free(g) || c->tune.aside) return ch;
   Tune& t = c->tune;
   const size_t site = t.site++;
   if (t.cand >= 0) {
@@ -1046,7 +1047,9 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     gemm(c, g1, s);
     const bool cls = cls_last && l == L - 1;
     const bool whole = x_final_out || (sc.moe[l] && (c->experts_out || c->router_logits_out));
+    c->tune.aside = cls;                                 // (the places of a tuned context are those of a call without it)
     if (!cls || whole) block_tail(l, false);
+    c->tune.aside = false;
     if (x_final_out && l == L - 1)
       (void)hipMemcpyAsync(x_final_out, v.xout, (size_t)B * sc.T_last * D * E, hipMemcpyDeviceToDevice, s);
     if (cls) block_tail(l, true);

@@ -44,3 +44,40 @@ def test_last_block_on_class_rows(hip, orc64, name, over, dtype, tol):
         assert hip.rel(grads[n].cpu().numpy(), g) < bar, n
         assert np.array_equal(grads[n].cpu().numpy(), full["grads"][n]), n
     assert float(loss[0]) == full["loss"] and np.array_equal(logits.cpu().numpy(), full["logits"])
+
+
+def products_after_class_attention(torch, call):
+    """Names of the product kernels of a step, in order, from the class rows' attention on"""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    runs = sorted((e for e in prof.events() if e.device_type == torch.autograd.DeviceType.CUDA), key=lambda e: e.time_range.start)
+    names = [e.name for e in runs]
+    first = next(i for i, n in enumerate(names) if "attn_cls_fwd" in n)
+    return [n for n in names[first:] if "gemm_" in n]
+
+
+def test_asking_for_the_output_keeps_the_tuned_shapes(hip):
+    """The last block's whole output takes products of its own; the others keep their measured shapes and bits."""
+    import torch
+    cfg = S.get_config("c2_deit_s", dtype="bf16", batch=8)
+    p = S.make_params(cfg)
+    x, y = S.make_inputs(cfg)
+    import paper_2405_10951_amd as P
+    ctx, dev = P.Context(cfg, p, 8), torch.device("cuda:0")
+    xin, lab = torch.as_tensor(x).to(dev).to(ctx.act_dtype).contiguous(), torch.as_tensor(y, dtype=torch.int32).to(dev)
+    xf = torch.empty((8, ctx.T_f, cfg["dim"]), dtype=ctx.act_dtype, device=dev)
+    xo = torch.empty((8, ctx.T_last, cfg["dim"]), dtype=ctx.act_dtype, device=dev)
+    loss = torch.zeros(4, dtype=torch.float32, device=dev)
+    ctx.bsr_forward_frozen(xin, x_out=xf)
+    grads = [ctx.new_grads() for _ in range(3)]
+    ctx.bsr_train_blocks_fwd_bwd(xf, lab, grads[0], loss_out=loss)
+    ctx.bsr_autotune(xin, lab, xf, loss, grads[1])
+    plain = products_after_class_attention(torch, lambda: ctx.bsr_train_blocks_fwd_bwd(xf, lab, grads[1], loss_out=loss))
+    asked = products_after_class_attention(torch, lambda: ctx.bsr_train_blocks_fwd_bwd(xf, lab, grads[2], loss_out=loss, x_final_out=xo))
+    assert len(plain) > 10 and plain == asked
+    for n in grads[0]:                                         # tuned or not, asked or not: the same bits
+        assert torch.equal(grads[0][n], grads[1][n]) and torch.equal(grads[0][n], grads[2][n]), n
