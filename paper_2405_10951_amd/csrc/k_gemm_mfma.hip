@@ -723,8 +723,13 @@ void launch_ntd(const GemmDesc& g, hipStream_t s) {
   const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   kern<<<tiles, WM * WN * 64, lds_tiles, s>>>(g);
 }
+// The kernels that load straight into LDS hold an operand's row offsets in 32 bits (elements): larger operands, such as the
+// activations of 8192 images, go to the register-staged kernels, whose offsets have 64.
+bool offsets_fit(const GemmDesc& g) {
+  return (int64_t)g.M * g.a_rs <= (int64_t)UINT32_MAX && (int64_t)g.N * g.b_cs <= (int64_t)UINT32_MAX;
+}
 // what the direct-to-LDS kernels take: whole k-tiles, one weight matrix, no folded LayerNorm
-bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.grp_off && !g.ln_colsum; }
+bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.grp_off && !g.ln_colsum && offsets_fit(g); }
 
 // ------------------------------------------------------------------------------------------ NT, few rows
 // The same product where block tiles shared by eight wavefronts would leave most CUs idle.  A workgroup owns
@@ -904,7 +909,7 @@ constexpr float FEW_LEAD = 0.8f;
 // The shape of this kernel for a product and what the model gives it; -1: not one it takes
 int few_pick(const GemmDesc& g, float* us) {
   int pick = -1;
-  if (g.K % 64 == 0 && !g.grp_off)
+  if (g.K % 64 == 0 && !g.grp_off && offsets_fit(g))
     for (int i = 0; i < 3; ++i) {
       const FewShape& f = kFewShapes[i];
       const int64_t tiles = (int64_t)((g.M + 32 * f.mi - 1) / (32 * f.mi)) * ((g.N + 32 * f.ni - 1) / (32 * f.ni));

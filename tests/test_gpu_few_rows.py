@@ -52,3 +52,23 @@ def test_no_tile_changes_the_gradients_of_a_layer(env, orc64, M, kin, out):
     for tile in P.bsr_gemm_tile_shapes():
         for name, a, c in zip(("dx", "dw", "db"), base, run(tile)):
             assert np.array_equal(a, c), f"tile shape {tile}, {name}: {int(np.sum(a != c))} of {a.size} elements differ"
+
+
+# an operand of more than 2^32 elements (8.6 GB): columns for the kernel for few rows, for the direct-to-LDS kernels, and a
+# weight matrix of that size; only its last rows, beyond the 32-bit offsets, are not zero
+@pytest.mark.parametrize("M,kin,out", [(1048600, 4096, 8), (1048600, 4096, 256), (320, 4096, 1048600)])
+def test_operands_of_more_than_2_32_elements(env, M, kin, out):
+    torch, P = env
+    rng = np.random.default_rng(M + out)
+    big, small = max(M, out), min(M, out)
+    a = torch.zeros((big, kin), dtype=torch.bfloat16, device="cuda")
+    tail, b = K.bf16_np(rng, (64, kin)), K.bf16_np(rng, (small, kin), 0.05)
+    a[-64:] = K.to_dev(torch, tail, torch.bfloat16)
+    bt = K.to_dev(torch, b, torch.bfloat16)
+    y, used = P.bsr_linear_forward(*((a, bt) if M > out else (bt, a)), None)
+    torch.cuda.synchronize()
+    assert used == 1
+    if M < out:
+        y = y.T
+    K.assert_close(y[-64:].float().cpu().numpy(), tail.astype(np.float64) @ b.astype(np.float64).T, "last rows")
+    assert not bool(y[:-64].any())
