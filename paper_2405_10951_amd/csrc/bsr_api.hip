@@ -391,7 +391,9 @@ size_t carve(const bsr_config& c, const Schedule& s, char* base, Buffers* out, b
   b.dh = w.take<char>(B * Tmax * D * E);
   b.dqkv = w.take<char>(B * Tmax * 3 * D * E);
   b.delta = w.take<float>(B * H * Tmax);
-  b.partial = w.take<float>(std::max(colsum_partial_floats(0, (int)std::max(3 * D, F)), mean_sq_partial_floats()));
+  // (the head's class sums over its general path leave at most 64 rows of partial sums, an eighth of what the others may)
+  const size_t widest = std::max({3 * D, F, ((size_t)std::max(c.num_classes, 0) + 7) / 8});
+  b.partial = w.take<float>(std::max(colsum_partial_floats(0, (int)widest), mean_sq_partial_floats()));
   int n_ln = 0;
   for (int l = ft; l < L; ++l) n_ln += s.trainable[l] ? 2 : 0;
   if (n_ln > 0 && n_ln <= LN_DEFER_MAX) b.ln_partial = w.take<float>((size_t)n_ln * ln_deferred_partial_floats((int)D));

@@ -166,6 +166,13 @@ def test_saved_bytes_scale_with_batch_dtype_and_fit_the_workspace():
     assert tmoe["moe"] > 0 and all((r["moe"] > 0) == (l in (9, 11)) for l, r in enumerate(pm) if r["total"])
 
 
+def test_workspace_holds_the_class_sums_of_a_wide_head():
+    # beyond 8 x the widest layer, the 64 rows of partial class sums are the longest thing their buffer takes
+    cfg = S.get_config("mini_4blk", num_classes=20000)
+    more = P.bsr_workspace_bytes(P.make_config(dict(cfg, num_classes=40000), 64)) - P.bsr_workspace_bytes(P.make_config(cfg, 64))
+    assert more >= 4 * 20000 * (64 + 2 * 64)               # partial sums, logits and their gradient
+
+
 def test_saved_bytes_errors():
     c = P.make_config(S.get_config("mini_4blk"), 4)
     for bad in (0, 5):
