@@ -516,6 +516,12 @@ void gemm(bsr_ctx* c, const GemmDesc& g, hipStream_t s) {
   else gemm_generic(g, s);
 }
 
+// a product of a classification head that takes the general path
+void head_product(const GemmDesc& g, hipStream_t s) {
+  if (gemm_f32_supported(g)) gemm_f32(g, s);
+  else gemm_small_f32(g, s);
+}
+
 // Eq. 4 for one linear layer: dW = x^T dy and db = column sums of dy.  The MFMA kernels produce db
 // alongside dW; other shapes take the separate column-sum kernels.
 void wgrad(bsr_ctx* c, const void* x, const void* dy, int M, int in, int out, void* dw, void* db, hipStream_t s) {
@@ -1065,7 +1071,7 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
   char* dx_other = b.dxb;
   if (cf.loss == BSR_LOSS_CE) {
     const int C = cf.num_classes;
-    if (head_lds_bytes(D, C) <= 64 * 1024) {
+    if (head_takes(B, D, C, (const float*)c->p.w_head)) {
       head_fwd_bwd(x, B, Tl, D, C, f32, (const float*)c->p.lnf_g, (const float*)c->p.lnf_b, c->eps, (const float*)c->p.w_head,
                    (const float*)c->p.b_head, labels, b.xc, b.z, b.logits, b.dlogits, b.dz, b.loss_rows, dx,
                    (float*)grads->w_head, (float*)grads->b_head, (float*)grads->lnf_g, (float*)grads->lnf_b, loss_out, s);
@@ -1077,17 +1083,17 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     gl.A = b.z; gl.a_rs = D; gl.a_cs = 1; gl.B = c->p.w_head; gl.b_rs = C; gl.b_cs = 1;
     gl.C = b.logits; gl.ldc = C; gl.M = B; gl.N = C; gl.K = D; gl.in_f32 = gl.out_f32 = true;
     gl.bias = (const float*)c->p.b_head;
-    gemm_small_f32(gl, s);
+    head_product(gl, s);
     cross_entropy(b.logits, labels, B, C, b.loss_rows, b.dlogits, loss_out, s);
     if (logits_out) (void)hipMemcpyAsync(logits_out, b.logits, sizeof(float) * (size_t)B * C, hipMemcpyDeviceToDevice, s);
     GemmDesc gz;   // dz = dlogits . W_h^T
     gz.A = b.dlogits; gz.a_rs = C; gz.a_cs = 1; gz.B = c->p.w_head; gz.b_rs = 1; gz.b_cs = C;
     gz.C = b.dz; gz.ldc = D; gz.M = B; gz.N = D; gz.K = C; gz.in_f32 = gz.out_f32 = true;
-    gemm_small_f32(gz, s);
+    head_product(gz, s);
     GemmDesc gw;   // dW_h = z^T . dlogits
     gw.A = b.z; gw.a_rs = 1; gw.a_cs = D; gw.B = b.dlogits; gw.b_rs = C; gw.b_cs = 1;
     gw.C = grads->w_head; gw.ldc = C; gw.M = D; gw.N = C; gw.K = B; gw.in_f32 = gw.out_f32 = true;
-    gemm_small_f32(gw, s);
+    head_product(gw, s);
     colsum(b.dlogits, B, C, C, true, b.partial, (float*)grads->b_head, s);
     layernorm_bwd_params(b.dz, b.xc, b.meanf, b.rstdf, B, D, true, b.partial, (float*)grads->lnf_g, (float*)grads->lnf_b, s);
     layernorm_bwd_dx(b.dz, b.xc, b.meanf, b.rstdf, (const float*)c->p.lnf_g, nullptr, B, D, true, b.dxc, s);

@@ -171,8 +171,8 @@ void scatter_tokens(const void* dy, const int32_t* idx, int B, int T, int k, int
 // Classification head, forward and backward, in two launches (class-token LayerNorm, logits, mean
 // cross-entropy, and the gradients of the head, of the final LayerNorm and of the last block's output
 // dx [B,Tl,D], whose non-class rows are set to zero).  xhat, z, dz: [B,D] fp32 scratch; logits, dlogits:
-// [B,C] fp32; loss_rows [B].  Needs head_lds_bytes(D, C) of LDS per workgroup (caller checks <= 64 KB).
-size_t head_lds_bytes(int D, int C);
+// [B,C] fp32; loss_rows [B].  head_takes: whether these kernels are the ones for a head (by size).
+bool head_takes(int B, int D, int C, const float* w_head);
 void head_fwd_bwd(const void* x, int B, int Tl, int D, int C, bool f32, const float* gamma, const float* beta, float eps,
                   const float* w_head, const float* b_head, const int32_t* labels, float* xhat, float* z, float* logits,
                   float* dlogits, float* dz, float* loss_rows, void* dx, float* dw, float* db, float* dgamma, float* dbeta,

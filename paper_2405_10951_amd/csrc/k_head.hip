@@ -20,6 +20,7 @@ namespace {
 
 constexpr int HT = 1024, HW = HT / WAVE;               // threads and wavefronts per workgroup of the row kernel
 constexpr int SCRATCH = 8192;                          // floats of LDS for partial sums
+constexpr int WIDE_G = 128, PARTS = 8;                 // groups of VEC classes that make a wide head; its ranges of rows
 constexpr int ZERO_PARTS = 4;                          // workgroups per image that clear the other token rows
 constexpr int BT = 256;                                // threads per workgroup of the batch kernel
 constexpr int TD = 16, TC = 64, BCH = 32;              // batch kernel: rows x classes of W_h per workgroup, images per chunk
@@ -57,7 +58,7 @@ __device__ __forceinline__ void zero_rows(T* dst, int64_t n, int part) {
   }
 }
 
-template <typename T, int VEC>
+template <typename T, int VEC, bool WIDE>
 __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, int Tl, int D, int C, int B,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
                                                        float eps, const float* __restrict__ w_head,
@@ -93,16 +94,29 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     z_out[(int64_t)b * D + d] = z;
   }
   __syncthreads();
-  // logits: G groups of VEC classes, R rows of W_h at a time; thread (r, group) adds rows r, r + R, ...
-  const int G = C / VEC, R = max(1, HT / G);
-  for (int i = tid; i < R * G; i += HT) {
-    const int r = i / G, g = i % G;
-    const float* wp = w_head + g * VEC;
-    vecf a = (vecf)0.f;
+  // logits: G groups of VEC classes, R rows of W_h at a time; thread (r, group) adds rows r, r + R, ...  WIDE: a wavefront adds
+  // up one of R ranges of rows, its lanes along the classes, 64 groups at a time.
+  const int G = C / VEC, R = WIDE ? PARTS : max(1, HT / G);
+  if constexpr (WIDE) {
+    const int part = tid / WAVE % PARTS, n = D / PARTS;           // (D is a multiple of 8)
+    for (int g = tid / WAVE / PARTS * WAVE + tid % WAVE; g < G; g += HT / PARTS) {
+      const float* wp = w_head + (int64_t)part * n * C + g * VEC;
+      vecf a = (vecf)0.f;
 #pragma unroll 8
-    for (int d = r; d < D; d += R) a += zs[d] * *(const vecf*)(wp + (int64_t)d * C);
+      for (int d = 0; d < n; ++d) a += zs[part * n + d] * *(const vecf*)(wp + (int64_t)d * C);
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) scr[r * C + g * VEC + v] = a[v];
+      for (int v = 0; v < VEC; ++v) scr[part * C + g * VEC + v] = a[v];
+    }
+  } else {
+    for (int i = tid; i < R * G; i += HT) {
+      const int r = i / G, g = i % G;
+      const float* wp = w_head + g * VEC;
+      vecf a = (vecf)0.f;
+#pragma unroll 8
+      for (int d = r; d < D; d += R) a += zs[d] * *(const vecf*)(wp + (int64_t)d * C);
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) scr[r * C + g * VEC + v] = a[v];
+    }
   }
   __syncthreads();
   for (int i = tid / 8; i < C; i += HT / 8) {          // eight threads per class
@@ -133,33 +147,57 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
   }
   __syncthreads();
   // dz = dlogits . W_h^T: the same walk, a chunk of rows at a time; each thread leaves the product of its VEC classes, then
-  // eight threads add up a row
-  const int GP = G | 1, DC = max(1, SCRATCH / GP);
-  for (int d0 = 0; d0 < D; d0 += DC) {
-    const int rows = min(DC, D - d0);
-    for (int i = tid; i < R * G; i += HT) {
-      const int g = i % G;
-      float dl[VEC];
+  // eight threads add up a row.  WIDE (a chunk would be a few rows, and adding them up all there is): a wavefront takes four
+  // rows at a time, its lanes along the classes.
+  if constexpr (WIDE) {
+    for (int d0 = tid / WAVE * 4; d0 < D; d0 += HW * 4) {
+      float a[4] = {0.f, 0.f, 0.f, 0.f};
+      const float* wp = w_head + (int64_t)d0 * C;
+#pragma unroll 4
+      for (int g = tid % WAVE; g < G; g += WAVE) {
+        const vecf dl = *(const vecf*)(lg + g * VEC);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) dl[v] = lg[g * VEC + v];
-      const float* wp = w_head + (int64_t)d0 * C + g * VEC;
-#pragma unroll 8
-      for (int r = i / G; r < rows; r += R) {
-        const vecf w = *(const vecf*)(wp + (int64_t)r * C);
-        float a = 0.f;
+        for (int i = 0; i < 4; ++i) {
+          const vecf w = *(const vecf*)(wp + (int64_t)i * C + g * VEC);
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) a = fmaf(dl[v], w[v], a);
-        scr[r * GP + g] = a;
+          for (int v = 0; v < VEC; ++v) a[i] = fmaf(dl[v], w[v], a[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[i] = wave_sum(a[i]);
+        if (tid % WAVE == 0) zs[d0 + i] = a[i];          // raw dz (z is not needed any more)
       }
     }
     __syncthreads();
-    for (int r = tid / 8; r < rows; r += HT / 8) {
-      float a = 0.f;
-      for (int g = tid & 7; g < G; g += 8) a += scr[r * GP + g];
-      a += __shfl_xor(a, 1); a += __shfl_xor(a, 2); a += __shfl_xor(a, 4);
-      if ((tid & 7) == 0) zs[d0 + r] = a;              // raw dz (z is not needed any more)
+  } else {
+    const int GP = G | 1, DC = max(1, SCRATCH / GP);
+    for (int d0 = 0; d0 < D; d0 += DC) {
+      const int rows = min(DC, D - d0);
+      for (int i = tid; i < R * G; i += HT) {
+        const int g = i % G;
+        float dl[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) dl[v] = lg[g * VEC + v];
+        const float* wp = w_head + (int64_t)d0 * C + g * VEC;
+#pragma unroll 8
+        for (int r = i / G; r < rows; r += R) {
+          const vecf w = *(const vecf*)(wp + (int64_t)r * C);
+          float a = 0.f;
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) a = fmaf(dl[v], w[v], a);
+          scr[r * GP + g] = a;
+        }
+      }
+      __syncthreads();
+      for (int r = tid / 8; r < rows; r += HT / 8) {
+        float a = 0.f;
+        for (int g = tid & 7; g < G; g += 8) a += scr[r * GP + g];
+        a += __shfl_xor(a, 1); a += __shfl_xor(a, 2); a += __shfl_xor(a, 4);
+        if ((tid & 7) == 0) zs[d0 + r] = a;
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
   // the LayerNorm backward of the row:
   //   dxhat = dz * gamma;  dx = rstd * (dxhat - mean(dxhat) - xhat * mean(dxhat * xhat))
@@ -251,24 +289,40 @@ __global__ __launch_bounds__(BT) void head_batch_kernel(const float* __restrict_
 
 }  // namespace
 
-size_t head_lds_bytes(int D, int C) { return sizeof(float) * ((size_t)2 * D + (size_t)C + HW + (C > SCRATCH ? C : SCRATCH)); }
+static bool four_classes(int C, const float* w_head) { return C % 4 == 0 && ((uintptr_t)w_head & 15) == 0; }   // (as rows of W_h start)
+static bool wide_head(int C, const float* w_head) { return C / (four_classes(C, w_head) ? 4 : 1) >= WIDE_G; }
+static size_t head_lds_bytes(int D, int C, const float* w_head) {
+  return sizeof(float) * ((size_t)2 * D + (size_t)C + HW + (wide_head(C, w_head) ? (size_t)PARTS * C : (size_t)SCRATCH));
+}
+
+// Whether these kernels take a head, or the general ones do (products of their own, which share W_h among all CUs where here
+// every image's workgroup reads all of it): by LDS, then by what is faster.  Steps of a small model, here / general, in us:
+// 768 x 300 113 .. 169 / 120 .. 162 at 1 .. 128 images, 768 x 600 149 .. 203 / 126 .. 167, 384 x 1000 112 .. 164 /
+// 114 .. 147, 192 x 1640 101 .. 151 / 120 .. 152.  Where the classes are no multiple of four the general products go without
+// the matrix cores and take longer by the image: 768 x 1301 256 .. 317 / 132 .. 602, equal at 40.
+bool head_takes(int B, int D, int C, const float* w_head) {
+  if (head_lds_bytes(D, C, w_head) > 64 * 1024) return false;
+  return (int64_t)D * C < 300000 || (!four_classes(C, w_head) && B > 40);
+}
 
 void head_fwd_bwd(const void* x, int B, int Tl, int D, int C, bool f32, const float* gamma, const float* beta, float eps,
                   const float* w_head, const float* b_head, const int32_t* labels, float* xhat, float* z, float* logits,
                   float* dlogits, float* dz, float* loss_rows, void* dx, float* dw, float* db, float* dgamma, float* dbeta,
                   float* loss, hipStream_t s) {
-  const size_t lds = head_lds_bytes(D, C);
+  const size_t lds = head_lds_bytes(D, C, w_head);
   const dim3 grid(B, Tl > 1 ? 1 + ZERO_PARTS : 1);
-  auto rows = [&](auto zero, auto vec) {
+  auto rows = [&](auto zero, auto vec, auto wide) {
     typedef decltype(zero) T;
-    head_rows_kernel<T, decltype(vec)::value><<<grid, HT, lds, s>>>((const T*)x, Tl, D, C, B, gamma, beta, eps, w_head, b_head, labels,
-                                                                  xhat, z, logits, dlogits, dz, loss_rows, (T*)dx);
+    head_rows_kernel<T, decltype(vec)::value, decltype(wide)::value != 0><<<grid, HT, lds, s>>>(
+        (const T*)x, Tl, D, C, B, gamma, beta, eps, w_head, b_head, labels, xhat, z, logits, dlogits, dz, loss_rows, (T*)dx);
   };
-  const bool four = C % 4 == 0 && ((uintptr_t)w_head & 15) == 0;     // (rows of W_h start at a multiple of 16 bytes)
-  if (f32 && four) rows(0.f, RowC<4>{});
-  else if (f32) rows(0.f, RowC<1>{});
-  else if (four) rows((bf16)0.f, RowC<4>{});
-  else rows((bf16)0.f, RowC<1>{});
+  auto forms = [&](auto zero) {
+    const bool wide = wide_head(C, w_head);
+    if (four_classes(C, w_head)) wide ? rows(zero, RowC<4>{}, RowC<1>{}) : rows(zero, RowC<4>{}, RowC<0>{});
+    else wide ? rows(zero, RowC<1>{}, RowC<1>{}) : rows(zero, RowC<1>{}, RowC<0>{});
+  };
+  if (f32) forms(0.f);
+  else forms((bf16)0.f);
   const int nw = ((D + TD - 1) / TD) * ((C + TC - 1) / TC);
   head_batch_kernel<<<nw + (D + WAVE - 1) / WAVE + 1, BT, 0, s>>>(z, xhat, dlogits, dz, loss_rows, B, D, C, nw, dw, db, dgamma, dbeta,
                                                                 loss);

@@ -41,3 +41,20 @@ def test_long_rows_and_odd_heads(hip, orc64, dtype, tol, dim, heads, classes, fu
     p = S.make_params(cfg, std=0.05 if dim < 1000 else 0.02)
     x, y = S.make_inputs(cfg)
     check_step(hip, orc64, cfg, p, x, y, tol, free_running=False)
+
+
+# heads at the edges of their kernels: one class short of a wide head and the first (groups of four, and single classes),
+# classes that do and do not fill the wavefronts' walk, the first that goes to the general products (300000 weights) with
+# and without groups of four, and 41 images, from where single classes stay here while they fit
+@pytest.mark.parametrize("classes,batch", [(127, 2), (128, 2), (129, 3), (508, 2), (512, 2), (772, 1), (1301, 2), (4684, 2), (4688, 2),
+                                           (4689, 2), (1777, 41)])
+def test_heads_of_many_classes(hip, orc64, classes, batch):
+    cfg = S.get_config("mini_4blk", dtype="fp32", num_classes=classes, batch=batch)
+    p = S.make_params(cfg, std=0.05)
+    x, y = S.make_inputs(cfg)
+    ref = orc64.step(cfg, p, x, y)
+    got = hip.run_hip_step(cfg, p, x, y, forced_idx=ref["kept_idx"])
+    assert abs(got["loss"] - ref["loss"]) <= TOL_FP32 * abs(ref["loss"])
+    assert hip.rel(got["logits"], ref["logits"]) < TOL_FP32
+    for n, g in ref["grads"].items():
+        assert hip.rel(got["grads"][n], g) < TOL_FP32, n
