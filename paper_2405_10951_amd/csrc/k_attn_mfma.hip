@@ -1,6 +1,7 @@
 // bf16 MFMA softmax attention (Eq. 1 of the paper) for head size 64 and up to 1024 tokens: up to 256 tokens (every
-// ViT-B/16 and DeiT-S block at 224 pixels) a head's keys are staged whole, beyond that in chunks (second half of the file).  The CLS row of the softmax map, which
-// Eq. 6 ranks tokens by, leaves the forward kernel in fp32 as a by-product.
+// ViT-B/16 and DeiT-S block at 224 pixels) a head's keys are staged whole and probabilities are bf16 factors of the second
+// product, beyond that keys come in chunks and probabilities stay in fp32 (second half of the file).  The CLS row of the
+// softmax map, which Eq. 6 ranks tokens by, leaves the forward kernel in fp32 as a by-product.
 //
 // Forward.  One workgroup = one (image, head): K and V of the head are staged once, and each of
 // its ceil(T / 32) wavefronts owns 32 queries.  K and V sit in LDS row-major (swizzled 16-byte chunks);
@@ -395,12 +396,25 @@ void launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float*
 // ------------------------------------------------------------------------------------------ more than 256 tokens
 // The same products with the other side of the softmax walked in chunks of LC rows that pass through LDS (fetched
 // into registers while the previous chunk is worked on): a workgroup owns 128 queries (4 wavefronts of 32) and the
-// softmax is kept running, output and sum rescaled when a chunk raises the maximum.  What bounds it is the softmax
-// arithmetic (VALU) beside 16 MFMAs per 32 x 64 block; 128-row chunks leave 32 KB of LDS per workgroup, so four or
-// five of them share a CU and cover each other's waits.  At 577 tokens, 16 images of 6 heads, the one-wavefront-per-
-// query kernels this replaces took 469 us forward and 717 us backward, these 26 and 49 us.
+// softmax is kept running, output and sum rescaled when a chunk raises the maximum.  Probabilities, score gradients and
+// delta stay in fp32 here (Split below), so results are the exact ones rounded to bf16.  What bounds it is the softmax
+// arithmetic (VALU) beside 12 MFMAs per 32 x 32 scores; 128-row chunks leave 32 KB of LDS per workgroup, so four or
+// five of them share a CU and cover each other's waits.  At 577 tokens, 16 images of 6 heads, calls in a loop: 42 us forward and 135
+// backward (732 and 2711 with one wavefront per query, of the same precision; 36 and 100 with bf16 factors, whose dq and dk
+// are 1.4 to 2.6 times as far from the exact ones).
 // Workgroups are numbered head first: the query blocks of a head then run on one XCD and share its L2.
 constexpr int LC = 128, LCB = LC / 32, LONG_T = 1024;
+
+// An fp32 factor as the sum of two bf16 ones, good to 2^-17: the second products of these lengths take probabilities and
+// score gradients in fp32, each as two MFMAs with the same other operand.
+struct Split {
+  bf16x8 hi, lo;
+  __device__ __forceinline__ void set(int i, float v) {
+    const bf16 a = (bf16)v;
+    hi[i] = a;
+    lo[i] = (bf16)(v - (float)a);
+  }
+};
 
 struct ChunkRegs { u32x4 v[4]; };      // a thread's share of one operand's chunk: LC rows of 8 16-byte pieces, 256 threads
 __device__ inline void chunk_fetch(ChunkRegs& c, const bf16* base, int64_t rs, int r0, int T, int tid) {
@@ -485,29 +499,34 @@ __global__ __launch_bounds__(256) void attn_fwd_long_kernel(const bf16* __restri
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));         // finite: a chunk holds at least one key
     const float alpha = __builtin_amdgcn_exp2f((m - mx) * c), mc = mx * c;
     m = mx;
-    float sum = 0.f;
-    bf16x8 pf[2 * LCB];
 #pragma unroll
-    for (int jb = 0; jb < LCB; ++jb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(s[jb][r], c, -mc));
-        sum += p;
-        pf[2 * jb + (r >> 3)][r & 7] = (bf16)p;
-      }
-    l = l * alpha + sum + __shfl_xor(sum, 32, 64);
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
+    for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[nb][r] *= alpha;
+    float sum = 0.f;
 #pragma unroll
-      for (int st = 0; st < 2 * LCB; ++st)
-        o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(Vs, nb, lane, st), pf[st], o[nb], 0, 0, 0);
+    for (int jb = 0; jb < LCB; ++jb) {
+      Split p[2];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float pr = __builtin_amdgcn_exp2f(fmaf(s[jb][r], c, -mc));
+        sum += pr;
+        p[r >> 3].set(r & 7, pr);
+      }
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const bf16x8 vf = lds_frag_t(Vs, nb, lane, 2 * jb + hf);
+          o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p[hf].hi, o[nb], 0, 0, 0);
+          o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p[hf].lo, o[nb], 0, 0, 0);
+        }
     }
+    l = l * alpha + sum + __shfl_xor(sum, 32, 64);
   }
   const float inv = 1.0f / l;
   if (qi < T) {
-    if (lse && lh == 0) lse[((int64_t)b * H + h) * T + qi] = m * 0.125f + __logf(l);
+    if (lse && lh == 0) lse[((int64_t)b * H + h) * T + qi] = m * 0.125f + logf(l);
     bf16* orow = out + ((int64_t)b * T + qi) * D + h * HD + 4 * lh;
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
@@ -529,54 +548,47 @@ __global__ __launch_bounds__(256) void attn_fwd_long_kernel(const bf16* __restri
   }
 }
 
-// Backward beyond 256 tokens, one launch: workgroups of the first half own 128 queries (dQ, chunks of keys), those
-// of the second half 128 keys (dK and dV, chunks of queries; delta is taken from the rows of dO and O as they are
-// staged, so nothing waits for the first half).
-__global__ __launch_bounds__(256) void attn_bwd_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
-                                                            const bf16* __restrict__ dout, const float* __restrict__ lse, int T,
-                                                            int H, int heads_total, bf16* __restrict__ dqkv) {
-  __shared__ u32x4 As[LC * 8], Bs[LC * 8];
-  __shared__ __attribute__((aligned(16))) float lse_s[LC], del_s[LC];
+// Backward beyond 256 tokens, as up to 256: dQ by workgroups that own 128 queries and walk chunks of keys, then dK and dV by
+// workgroups that own 128 keys and walk chunks of queries.  delta_i = sum_j P_ij dP_ij takes a walk of its own before the
+// dQ one: dO . O would be one product, but of an output that has been rounded to bf16.
+__global__ __launch_bounds__(256) void attn_bwd_dq_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dout,
+                                                               const float* __restrict__ lse, int T, int H, int heads_total,
+                                                               float* __restrict__ delta, bf16* __restrict__ dqkv) {
+  __shared__ u32x4 Ks[LC * 8], Vs[LC * 8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
-  const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD, nblk = (T + 127) / 128;
-  const int blk = blockIdx.x / heads_total;
+  const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD;
   const int64_t rs = 3 * (int64_t)D;
   const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
   const bf16* dobase = dout + (int64_t)b * T * D + h * HD;
-  const bf16* obase = out + (int64_t)b * T * D + h * HD;
-  const float* lrow = lse + ((int64_t)b * H + h) * T;
   const float c = 0.125f * 1.44269504088896341f;
-  ChunkRegs ra, rb;
-  if (blk < nblk) {
-    const int q0 = blk * 128 + wave * 32, qc = min(q0 + lr, T - 1);
-    bf16x8 qf[4], dof[4];
-    float dl = 0.f;
+  const int q0 = (blockIdx.x / heads_total) * 128 + wave * 32, qc = min(q0 + lr, T - 1);
+  bf16x8 qf[4], dof[4];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      qf[ks] = *(const bf16x8*)(base + (int64_t)qc * rs + (2 * ks + lh) * 8);
-      dof[ks] = *(const bf16x8*)(dobase + (int64_t)qc * D + (2 * ks + lh) * 8);
-      const bf16x8 of = *(const bf16x8*)(obase + (int64_t)qc * D + (2 * ks + lh) * 8);
+  for (int ks = 0; ks < 4; ++ks) {
+    qf[ks] = *(const bf16x8*)(base + (int64_t)qc * rs + (2 * ks + lh) * 8);
+    dof[ks] = *(const bf16x8*)(dobase + (int64_t)qc * D + (2 * ks + lh) * 8);
+  }
+  const float l2 = lse[((int64_t)b * H + h) * T + qc] * 1.44269504088896341f;
+  float dl = 0.f;
+  f32x16 o[2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dl += (float)dof[ks][e] * (float)of[e];
-    }
-    dl += __shfl_xor(dl, 32, 64);
-    const float l2 = lrow[qc] * 1.44269504088896341f;
-    f32x16 o[2];
+  for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
-    chunk_fetch(ra, base + D, rs, 0, T, tid);
-    chunk_fetch(rb, base + 2 * D, rs, 0, T, tid);
+    for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
+  ChunkRegs kr, vr;
+  auto fetch = [&](int c0) __attribute__((always_inline)) {
+    chunk_fetch(kr, base + D, rs, c0, T, tid);
+    chunk_fetch(vr, base + 2 * D, rs, c0, T, tid);
+  };
+  fetch(0);
+  for (int walk = 0; walk < 2; ++walk) {
     for (int c0 = 0; c0 < T; c0 += LC) {
-      if (c0) __syncthreads();
-      chunk_stash(ra, As, tid);
-      chunk_stash(rb, Bs, tid);
+      if (walk || c0) __syncthreads();
+      chunk_stash(kr, Ks, tid);
+      chunk_stash(vr, Vs, tid);
       __syncthreads();
-      if (c0 + LC < T) {
-        chunk_fetch(ra, base + D, rs, c0 + LC, T, tid);
-        chunk_fetch(rb, base + 2 * D, rs, c0 + LC, T, tid);
-      }
+      if (c0 + LC < T) fetch(c0 + LC);
+      else if (!walk) fetch(0);
 #pragma unroll
       for (int jb = 0; jb < LCB; ++jb) {
         f32x16 sa, dp;
@@ -584,33 +596,58 @@ __global__ __launch_bounds__(256) void attn_bwd_long_kernel(const bf16* __restri
         for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-          sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(As, jb * 32 + lr, 2 * ks + lh), qf[ks], sa, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Bs, jb * 32 + lr, 2 * ks + lh), dof[ks], dp, 0, 0, 0);
+          sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Ks, jb * 32 + lr, 2 * ks + lh), qf[ks], sa, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Vs, jb * 32 + lr, 2 * ks + lh), dof[ks], dp, 0, 0, 0);
         }
-        bf16x8 dsf[2];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          float pr = __builtin_amdgcn_exp2f(sa[r] * c - l2);
-          if (c0 + key_of(jb, r, lh) >= T) pr = 0.f;
-          dsf[r >> 3][r & 7] = (bf16)(pr * (dp[r] - dl) * 0.125f);
+          sa[r] = __builtin_amdgcn_exp2f(sa[r] * c - l2);
+          if (c0 + key_of(jb, r, lh) >= T) sa[r] = 0.f;
         }
+        if (!walk) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dl = fmaf(sa[r], dp[r], dl);
+          continue;
+        }
+        Split ds[2];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ds[r >> 3].set(r & 7, sa[r] * (dp[r] - dl) * 0.125f);
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-          for (int hf = 0; hf < 2; ++hf)
-            o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf[hf], lds_frag_t(As, nb, lane, 2 * jb + hf), o[nb], 0, 0, 0);
+          for (int hf = 0; hf < 2; ++hf) {
+            const bf16x8 kf = lds_frag_t(Ks, nb, lane, 2 * jb + hf);
+            o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds[hf].hi, kf, o[nb], 0, 0, 0);
+            o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds[hf].lo, kf, o[nb], 0, 0, 0);
+          }
       }
     }
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = q0 + 8 * (r >> 2) + 4 * lh + (r & 3);
-        if (i < T) dqkv[((int64_t)b * T + i) * rs + h * HD + nb * 32 + lr] = (bf16)o[nb][r];
-      }
-    return;
+    if (!walk) dl += __shfl_xor(dl, 32, 64);
   }
-  const int j0 = (blk - nblk) * 128 + wave * 32, jc = min(j0 + lr, T - 1);
+  if (lh == 0 && q0 + lr < T) delta[((int64_t)b * H + h) * T + q0 + lr] = dl;
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = q0 + 8 * (r >> 2) + 4 * lh + (r & 3);
+      if (i < T) dqkv[((int64_t)b * T + i) * rs + h * HD + nb * 32 + lr] = (bf16)o[nb][r];
+    }
+}
+
+__global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dout,
+                                                                const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                int T, int H, int heads_total, bf16* __restrict__ dqkv) {
+  __shared__ u32x4 Qs[LC * 8], dOs[LC * 8];
+  __shared__ __attribute__((aligned(16))) float lse_s[LC], del_s[LC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
+  const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD;
+  const int64_t rs = 3 * (int64_t)D;
+  const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
+  const bf16* dobase = dout + (int64_t)b * T * D + h * HD;
+  const float* lrow = lse + ((int64_t)b * H + h) * T;
+  const float* drow = delta + ((int64_t)b * H + h) * T;
+  const float c = 0.125f * 1.44269504088896341f;
+  const int j0 = (blockIdx.x / heads_total) * 128 + wave * 32, jc = min(j0 + lr, T - 1);
   bf16x8 kf[4], vf[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
@@ -622,31 +659,21 @@ __global__ __launch_bounds__(256) void attn_bwd_long_kernel(const bf16* __restri
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { ok[nb][r] = 0.f; ov[nb][r] = 0.f; }
-  ChunkRegs ro;
-  chunk_fetch(ra, base, rs, 0, T, tid);
-  chunk_fetch(rb, dobase, D, 0, T, tid);
-  chunk_fetch(ro, obase, D, 0, T, tid);
+  ChunkRegs qr, dor;
+  chunk_fetch(qr, base, rs, 0, T, tid);
+  chunk_fetch(dor, dobase, D, 0, T, tid);
   for (int c0 = 0; c0 < T; c0 += LC) {
     if (c0) __syncthreads();
-    chunk_stash(ra, As, tid);
-    chunk_stash(rb, Bs, tid);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {                   // delta of the staged rows: 8 lanes hold a row
-      const bf16x8 x = __builtin_bit_cast(bf16x8, rb.v[u]), y = __builtin_bit_cast(bf16x8, ro.v[u]);
-      float d = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) d += (float)x[e] * (float)y[e];
-      d += __shfl_xor(d, 1, 64);
-      d += __shfl_xor(d, 2, 64);
-      d += __shfl_xor(d, 4, 64);
-      if ((tid & 7) == 0) del_s[(tid >> 3) + 32 * u] = d;
+    chunk_stash(qr, Qs, tid);
+    chunk_stash(dor, dOs, tid);
+    if (tid < LC) {
+      lse_s[tid] = c0 + tid < T ? lrow[c0 + tid] * 1.44269504088896341f : INFINITY;
+      del_s[tid] = c0 + tid < T ? drow[c0 + tid] : 0.f;
     }
-    if (tid < LC) lse_s[tid] = c0 + tid < T ? lrow[c0 + tid] * 1.44269504088896341f : INFINITY;
     __syncthreads();
     if (c0 + LC < T) {
-      chunk_fetch(ra, base, rs, c0 + LC, T, tid);
-      chunk_fetch(rb, dobase, D, c0 + LC, T, tid);
-      chunk_fetch(ro, obase, D, c0 + LC, T, tid);
+      chunk_fetch(qr, base, rs, c0 + LC, T, tid);
+      chunk_fetch(dor, dobase, D, c0 + LC, T, tid);
     }
 #pragma unroll
     for (int ib = 0; ib < LCB; ++ib) {
@@ -655,10 +682,10 @@ __global__ __launch_bounds__(256) void attn_bwd_long_kernel(const bf16* __restri
       for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
-        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(As, ib * 32 + lr, 2 * ks + lh), kf[ks], sa, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Bs, ib * 32 + lr, 2 * ks + lh), vf[ks], dp, 0, 0, 0);
+        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Qs, ib * 32 + lr, 2 * ks + lh), kf[ks], sa, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(dOs, ib * 32 + lr, 2 * ks + lh), vf[ks], dp, 0, 0, 0);
       }
-      bf16x8 pf[2], dsf[2];
+      Split p[2], ds[2];
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {              // queries c0 + 32 ib + 8 g4 + 4 lh + {0..3}
         const float4 l4 = *(const float4*)(lse_s + ib * 32 + 8 * g4 + 4 * lh);
@@ -669,16 +696,19 @@ __global__ __launch_bounds__(256) void attn_bwd_long_kernel(const bf16* __restri
         for (int e = 0; e < 4; ++e) {
           const int r = g4 * 4 + e;
           const float pr = __builtin_amdgcn_exp2f(sa[r] * c - lv[e]);
-          pf[r >> 3][r & 7] = (bf16)pr;
-          dsf[r >> 3][r & 7] = (bf16)(pr * (dp[r] - dv[e]) * 0.125f);
+          p[r >> 3].set(r & 7, pr);
+          ds[r >> 3].set(r & 7, pr * (dp[r] - dv[e]) * 0.125f);
         }
       }
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
-          ov[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[hf], lds_frag_t(Bs, nb, lane, 2 * ib + hf), ov[nb], 0, 0, 0);
-          ok[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf[hf], lds_frag_t(As, nb, lane, 2 * ib + hf), ok[nb], 0, 0, 0);
+          const bf16x8 gf = lds_frag_t(dOs, nb, lane, 2 * ib + hf), qf = lds_frag_t(Qs, nb, lane, 2 * ib + hf);
+          ov[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[hf].hi, gf, ov[nb], 0, 0, 0);
+          ov[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[hf].lo, gf, ov[nb], 0, 0, 0);
+          ok[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds[hf].hi, qf, ok[nb], 0, 0, 0);
+          ok[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds[hf].lo, qf, ok[nb], 0, 0, 0);
         }
     }
   }
@@ -693,6 +723,12 @@ __global__ __launch_bounds__(256) void attn_bwd_long_kernel(const bf16* __restri
         dst[2 * D] = (bf16)ov[nb][r];
       }
     }
+}
+
+void launch_bwd_long(const bf16* qkv, const bf16* dout, const float* lse, int B, int T, int H, float* delta, bf16* dqkv, hipStream_t s) {
+  const int grid = B * H * ((T + 127) / 128);
+  attn_bwd_dq_long_kernel<<<grid, 256, 0, s>>>(qkv, dout, lse, T, H, B * H, delta, dqkv);
+  attn_bwd_dkv_long_kernel<<<grid, 256, 0, s>>>(qkv, dout, lse, delta, T, H, B * H, dqkv);
 }
 
 }  // namespace
@@ -730,7 +766,7 @@ void attn_bwd_mfma(const void* qkv, const void* out, const void* dout, const flo
     case 6: launch_bwd<6>(q, o, d, lse, B, T, H, delta, g, s); break;
     case 7: launch_bwd<7>(q, o, d, lse, B, T, H, delta, g, s); break;
     case 8: launch_bwd<8>(q, o, d, lse, B, T, H, delta, g, s); break;
-    default: attn_bwd_long_kernel<<<2 * B * H * ((T + 127) / 128), 256, 0, s>>>(q, o, d, lse, T, H, B * H, g); break;
+    default: launch_bwd_long(q, d, lse, B, T, H, delta, g, s); break;
   }
 }
 
