@@ -649,11 +649,10 @@ void attention_cls_fwd(bsr_ctx* c, const void* qkv, int B, int T, void* out, flo
   ProfScope ps(c, BSR_PROF_ATTN_FWD, 4.0 * B * H * T * d, s);
   attn_cls_fwd(qkv, B, T, H, d, c->f32, out, lse, s);
 }
-void attention_cls_bwd(bsr_ctx* c, const void* qkv, const void* out, const void* dout, const float* lse, int B, int T, void* dqkv,
-                       hipStream_t s) {
+void attention_cls_bwd(bsr_ctx* c, const void* qkv, const void* dout, const float* lse, int B, int T, void* dqkv, hipStream_t s) {
   const int H = c->cfg.heads, d = c->cfg.dim / H;
   ProfScope ps(c, BSR_PROF_ATTN_BWD, 10.0 * B * H * T * d, s);
-  attn_cls_bwd(qkv, out, dout, lse, B, T, H, d, c->f32, dqkv, s);
+  attn_cls_bwd(qkv, dout, lse, B, T, H, d, c->f32, dqkv, s);
 }
 
 // Rank the patch tokens of a drop location, hand CLS + the K best to the FFN (Sec. 4.1) and normalise them, in one
@@ -1150,7 +1149,7 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     const GemmDesc d3 = dgrad_desc(c, dx, Mo, D, D, w.w_proj, sh.s_proj, b.dh);
     if (tr) dgrad_wgrad(c, d3, v.o, dx, Mo, D, D, gw.w_proj, gw.b_proj, s);
     else gemm(c, d3, s);
-    if (cls) attention_cls_bwd(c, v.qkv, v.o, b.dh, v.lse, B, Ta, b.dqkv, s);
+    if (cls) attention_cls_bwd(c, v.qkv, b.dh, v.lse, B, Ta, b.dqkv, s);
     else attention_bwd(c, v.qkv, v.o, b.dh, v.lse, B, Ta, b.dqkv, s);
     const GemmDesc d4 = dgrad_desc(c, b.dqkv, M, D, 3 * D, w.w_qkv, sh.s_qkv, b.dh);
     if (tr) dgrad_wgrad(c, d4, v.h1, b.dqkv, M, D, 3 * D, gw.w_qkv, gw.b_qkv, s);

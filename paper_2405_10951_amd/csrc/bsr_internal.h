@@ -103,7 +103,7 @@ size_t gemm_splitk_ws_floats(int dim, int mlp_hidden);
 // [B, T, 3 H d] written whole.  d: whole 16-byte pieces
 bool attn_cls_supported(int T, int d, bool f32);
 void attn_cls_fwd(const void* qkv, int B, int T, int H, int d, bool f32, void* out, float* lse, hipStream_t s);
-void attn_cls_bwd(const void* qkv, const void* out, const void* dout, const float* lse, int B, int T, int H, int d, bool f32,
+void attn_cls_bwd(const void* qkv, const void* dout, const float* lse, int B, int T, int H, int d, bool f32,
                   void* dqkv, hipStream_t s);
 
 bool attn_mfma_supported(int T, int d);

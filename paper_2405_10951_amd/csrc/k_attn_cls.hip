@@ -1,8 +1,8 @@
 // Attention of the class token alone (query 0 of every image and head), forward and backward: all that the last block of
 // a classifier needs, since the head reads nothing else of its output.  fp32 arithmetic on fp32 or bf16 storage.
 //
-// Bound by memory: forward reads K and V once, backward reads them once and writes dQ, dK and dV once, each 16 bytes
-// per lane with eight lanes on a row of 64 bf16 values.  One workgroup per (image, head).
+// Bound by memory: forward reads K and V once, backward reads K twice (for the scores and for dQ) and V once and writes dQ, dK
+// and dV once, each 16 bytes per lane with eight lanes on a row of 64 bf16 values.  One workgroup per (image, head).
 #include "rowops.h"
 
 namespace bsr {
@@ -96,35 +96,36 @@ __global__ __launch_bounds__(NT) void attn_cls_fwd_kernel(const T* __restrict__ 
   }
 }
 
-// Eq. 3, 5 with a gradient dout [B, H d] at query 0 only: P_j = exp(s_j - lse), dP_j = dO . v_j, delta = dO . O,
-// dS_j = P_j (dP_j - delta) / sqrt d; dK_j = dS_j q, dV_j = P_j dO, dQ_0 = sum_j dS_j k_j, dQ_j = 0.
+// Eq. 3, 5 with a gradient dout [B, H d] at query 0 only: P_j = exp(s_j - lse), dP_j = dO . v_j, delta = sum_j P_j dP_j (the
+// stored output is rounded, so not dO . O), dS_j = P_j (dP_j - delta) / sqrt d; dK_j = dS_j q, dV_j = P_j dO,
+// dQ_0 = sum_j dS_j k_j, dQ_j = 0.
 template <typename T>
-__global__ __launch_bounds__(NT) void attn_cls_bwd_kernel(const T* __restrict__ qkv, const T* __restrict__ out,
-                                                          const T* __restrict__ dout, const float* __restrict__ lse, int T_, int H,
-                                                          int d, T* __restrict__ dqkv) {
+__global__ __launch_bounds__(NT) void attn_cls_bwd_kernel(const T* __restrict__ qkv, const T* __restrict__ dout,
+                                                          const float* __restrict__ lse, int T_, int H, int d, T* __restrict__ dqkv) {
   constexpr int V = Chunk<T>::V;
   typedef typename Chunk<T>::vec vec;
-  __shared__ float ds[MAX_T], red[NT * V], rs4[NW];
+  __shared__ float p[MAX_T], dp[MAX_T], red[NT * V], rs4[NW];
   const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * d, nch = d / V, gl = threadIdx.x % GL, grp = threadIdx.x / GL;
   const T* base = qkv + (int64_t)b * T_ * 3 * D + h * d;
   T* dbase = dqkv + (int64_t)b * T_ * 3 * D + h * d;
-  const T* orow = out + (int64_t)b * D + h * d;
   const T* dorow = dout + (int64_t)b * D + h * d;
   const float scale = rsqrtf((float)d), l = lse[blockIdx.x];
   float delta = 0.f;
-  for (int e = threadIdx.x; e < d; e += NT) delta += (float)orow[e] * (float)dorow[e];
-  delta = block_sum(delta, rs4);
   for (int j = grp; j < T_; j += NG) {
     const T* kr = base + (int64_t)j * 3 * D + D;
-    T* dr = dbase + (int64_t)j * 3 * D;
-    float s = 0.f, dp = 0.f;
+    float s = 0.f, t = 0.f;
     for (int c = gl; c < nch; c += GL) {
       const vec q = *(const vec*)(base + c * V), k = *(const vec*)(kr + c * V), v = *(const vec*)(kr + D + c * V), g = *(const vec*)(dorow + c * V);
 #pragma unroll
-      for (int e = 0; e < V; ++e) { s = fmaf((float)q[e], (float)k[e], s); dp = fmaf((float)g[e], (float)v[e], dp); }
+      for (int e = 0; e < V; ++e) { s = fmaf((float)q[e], (float)k[e], s); t = fmaf((float)g[e], (float)v[e], t); }
     }
-    const float pj = expf(group_sum(s) * scale - l), dsj = pj * (group_sum(dp) - delta) * scale;
-    if (gl == 0) ds[j] = dsj;
+    const float pj = expf(group_sum(s) * scale - l), dpj = group_sum(t);
+    if (gl == 0) { p[j] = pj; dp[j] = dpj; delta = fmaf(pj, dpj, delta); }
+  }
+  delta = block_sum(delta, rs4);           // (the barriers in it also publish p and dp)
+  for (int j = grp; j < T_; j += NG) {
+    T* dr = dbase + (int64_t)j * 3 * D;
+    const float pj = p[j], dsj = pj * (dp[j] - delta) * scale;
     for (int c = gl; c < nch; c += GL) {
       const vec q = *(const vec*)(base + c * V), g = *(const vec*)(dorow + c * V);
       vec dk, dv;
@@ -135,7 +136,6 @@ __global__ __launch_bounds__(NT) void attn_cls_bwd_kernel(const T* __restrict__ 
       *(vec*)(dr + 2 * D + c * V) = dv;
     }
   }
-  __syncthreads();
   for (int c0 = 0; c0 < nch; c0 += GL) {
     const int c = c0 + gl;
     float acc[V];
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(NT) void attn_cls_bwd_kernel(const T* __restrict__ 
 #pragma unroll 4
       for (int j = grp; j < T_; j += NG) {
         const vec k = *(const vec*)(base + (int64_t)j * 3 * D + D + c * V);
-        const float w = ds[j];
+        const float w = p[j] * (dp[j] - delta) * scale;
 #pragma unroll
         for (int e = 0; e < V; ++e) acc[e] = fmaf(w, (float)k[e], acc[e]);
       }
@@ -168,10 +168,10 @@ void attn_cls_fwd(const void* qkv, int B, int T, int H, int d, bool f32, void* o
   else attn_cls_fwd_kernel<bf16><<<B * H, NT, 0, s>>>((const bf16*)qkv, T, H, d, (bf16*)out, lse);
 }
 
-void attn_cls_bwd(const void* qkv, const void* out, const void* dout, const float* lse, int B, int T, int H, int d, bool f32,
+void attn_cls_bwd(const void* qkv, const void* dout, const float* lse, int B, int T, int H, int d, bool f32,
                   void* dqkv, hipStream_t s) {
-  if (f32) attn_cls_bwd_kernel<float><<<B * H, NT, 0, s>>>((const float*)qkv, (const float*)out, (const float*)dout, lse, T, H, d, (float*)dqkv);
-  else attn_cls_bwd_kernel<bf16><<<B * H, NT, 0, s>>>((const bf16*)qkv, (const bf16*)out, (const bf16*)dout, lse, T, H, d, (bf16*)dqkv);
+  if (f32) attn_cls_bwd_kernel<float><<<B * H, NT, 0, s>>>((const float*)qkv, (const float*)dout, lse, T, H, d, (float*)dqkv);
+  else attn_cls_bwd_kernel<bf16><<<B * H, NT, 0, s>>>((const bf16*)qkv, (const bf16*)dout, lse, T, H, d, (bf16*)dqkv);
 }
 
 }  // namespace bsr
