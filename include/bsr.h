@@ -225,7 +225,9 @@ int32_t bsr_select_tokens(bsr_ctx* ctx, const float* cls_attn, const void* x_in,
  *   labels       device int32 [B]; may be NULL with BSR_LOSS_MEAN_SQ
  *   loss_out     device fp32 scalar
  *   logits_out   device fp32 [B,classes], may be NULL
- *   x_final_out  device act [B,T_last,D], may be NULL: output of the last block
+ *   x_final_out  device act [B,T_last,D], may be NULL: output of the last block.  (Without it the last block of a
+ *                classifier computes its class rows only, all that the loss depends on; asking for it runs the
+ *                block's other rows as well.  The class rows given are those that loss and gradients came from.)
  *   grads        host struct of device fp32 pointers; every tensor of the trainable blocks, lnf_*
  *                and *_head must be non-NULL; each is overwritten with dLoss/dTensor
  *   kept_idx_out, scores_out, forced_idx: as in bsr_forward_frozen, for the drops in this range
@@ -294,7 +296,8 @@ int32_t bsr_tile_choices(const bsr_ctx* ctx, int32_t part, bsr_tile_choice* choi
  * ascending order, block l holding B * tokens_mlp[l] rows:
  *   forced_experts     int32 [rows, K]   use this choice instead of the ranking (gates still come
  *                                        from the logits); values must lie in 0..E-1, distinct per row
- *   experts_out        int32 [rows, K]   receives the choice
+ *   experts_out        int32 [rows, K]   receives the choice that was used: given back as forced_experts it
+ *                                        reproduces loss and gradients bit for bit
  *   router_logits_out  fp32  [rows, E]   receives the router logits
  * Errors: INVALID_ARG (ctx NULL, misaligned pointer).
  */

@@ -556,8 +556,8 @@ void dgrad_wgrad(bsr_ctx* c, const GemmDesc& dg, const void* x, const void* dy, 
 // Mixture-of-experts FFN of block l on M2 tokens (Sec. 5.3):  x_out = x_res + sum_s gate_s FFN_{e_s}(h),
 // h = LN2(x_res).  Routing, stable sort of the (token, slot) pairs by expert, gather, two grouped
 // GEMMs over the expert ranges (fc1 + GELU, fc2), weighted un-permute.  u (pre-GELU, may be null)
-// and g are [M2*K, F] in expert order.  row_pitch > 0: the M2 tokens are rows 0, row_pitch, ... of the block's tokens (their
-// routing is then not reported).
+// and g are [M2*K, F] in expert order.  row_pitch > 0: the M2 tokens are rows 0, row_pitch, ... of the block's tokens, and
+// so is their routing reported.
 void moe_ffn_forward(bsr_ctx* c, int l, int B, const void* h, const void* x_res, int M2, MoeBuf& m, void* u,
                      void* gbuf, void* x_out, hipStream_t s, int row_pitch = 0) {
   const bsr_config& cf = c->cfg;
@@ -568,11 +568,15 @@ void moe_ffn_forward(bsr_ctx* c, int l, int B, const void* h, const void* x_res,
   GemmDesc gl = fwd_desc(c, h, M2, D, E, nullptr, sh.t_router, m.logits);       // router logits, fp32
   gl.out_f32 = true;
   gemm(c, gl, s);
-  moe_topk(m.logits, M2, E, K, c->forced_experts ? c->forced_experts + row0 * K : nullptr, row_pitch ? row_pitch : 1, m.experts, m.gates, s);
-  if (c->experts_out && !row_pitch)
-    (void)hipMemcpyAsync(c->experts_out + row0 * K, m.experts, sizeof(int32_t) * (size_t)M2 * K, hipMemcpyDeviceToDevice, s);
-  if (c->router_logits_out && !row_pitch)
-    (void)hipMemcpyAsync(c->router_logits_out + row0 * E, m.logits, sizeof(float) * (size_t)M2 * E, hipMemcpyDeviceToDevice, s);
+  const int pitch = row_pitch ? row_pitch : 1;
+  moe_topk(m.logits, M2, E, K, c->forced_experts ? c->forced_experts + row0 * K : nullptr, pitch, m.experts, m.gates, s);
+  auto report = [&](const void* rows, size_t width, void* out) {
+    if (!out) return;
+    if (row_pitch) place_rows(rows, M2, width, row_pitch, out, s);
+    else (void)hipMemcpyAsync(out, rows, width * (size_t)M2, hipMemcpyDeviceToDevice, s);
+  };
+  report(m.experts, sizeof(int32_t) * K, c->experts_out ? c->experts_out + row0 * K : nullptr);
+  report(m.logits, sizeof(float) * E, c->router_logits_out ? c->router_logits_out + row0 * E : nullptr);
   moe_sort(m.experts, M2, E, K, m.off, m.pos, m.perm_tok, s);
   moe_gather_rows(h, m.perm_tok, (int64_t)M2 * K, D, m.xg, s);
   GemmDesc g1 = fwd_desc(c, m.xg, M2 * K, D, F, nullptr, sh.t_fc1, gbuf);
@@ -998,7 +1002,8 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
   // needed there: the query, the projection, the FFN and everything backward of them down to the attention run on one
   // row per image (tensors of B rows).  The gradient of the other rows is exactly zero, so nothing is left out.  When
   // the caller asks for the block's output or for the routing of all its tokens, the block also runs in full, forward,
-  // for those; loss and gradients come from the class rows either way.  (A block that drops tokens runs in full.)
+  // for those; loss and gradients come from the class rows either way, which then stand in what is reported as they were
+  // used.  (A block that drops tokens runs in full.)
   const bool cls_last = cf.loss == BSR_LOSS_CE && L > ft && sc.drop_of[L - 1] < 0 && sc.Ta[L - 1] > 1 &&
                         attn_cls_supported(sc.Ta[L - 1], D / cf.heads, f32);
 
@@ -1060,6 +1065,7 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     if (x_final_out && l == L - 1)
       (void)hipMemcpyAsync(x_final_out, v.xout, (size_t)B * sc.T_last * D * E, hipMemcpyDeviceToDevice, s);
     if (cls) block_tail(l, true);
+    if (cls && x_final_out) place_rows(v.xout, B, (size_t)D * E, sc.T_last, x_final_out, s);
     x = v.xout;
   }
   if (x_final_out && L == ft) (void)hipMemcpyAsync(x_final_out, x, (size_t)B * sc.T_last * D * E, hipMemcpyDeviceToDevice, s);

@@ -178,6 +178,8 @@ void head_fwd_bwd(const void* x, int B, int Tl, int D, int C, bool f32, const fl
                   float* dlogits, float* dz, float* loss_rows, void* dx, float* dw, float* db, float* dgamma, float* dbeta,
                   float* loss, hipStream_t s);
 void extract_cls(const void* x, int B, int T, int D, bool f32, float* out, hipStream_t s);
+// rows [n, row_bytes] -> rows 0, every, 2 every, ... of dst (row_bytes: a multiple of 4)
+void place_rows(const void* rows, int n, size_t row_bytes, int64_t every, void* dst, hipStream_t s);
 void place_cls_grad(const float* dxc, int B, int T, int D, bool f32, void* dx, hipStream_t s);
 void cross_entropy(const float* logits, const int32_t* labels, int B, int C, float* loss_rows,
                    float* dlogits, float* loss, hipStream_t s);

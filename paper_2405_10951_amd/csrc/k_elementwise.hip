@@ -133,6 +133,10 @@ __global__ void place_cls_grad_kernel(const float* __restrict__ dxc, int T_, int
   for (int j = threadIdx.x; j < D; j += blockDim.x) d[j] = (t == 0) ? (T)dxc[(int64_t)b * D + j] : (T)0.f;
 }
 
+__global__ void place_rows_kernel(const uint32_t* __restrict__ rows, int words, int64_t pitch, uint32_t* __restrict__ dst) {
+  for (int j = threadIdx.x; j < words; j += blockDim.x) dst[blockIdx.x * pitch + j] = rows[(int64_t)blockIdx.x * words + j];
+}
+
 // One wavefront per image: loss_b = logsumexp(z) - z[y]; dlogits = (softmax(z) - onehot) / B.
 __global__ __launch_bounds__(WAVE) void cross_entropy_kernel(const float* __restrict__ logits,
                                                              const int32_t* __restrict__ labels, int B,
@@ -349,6 +353,11 @@ void extract_cls(const void* x, int B, int T, int D, bool f32, float* out, hipSt
 void place_cls_grad(const float* dxc, int B, int T, int D, bool f32, void* dx, hipStream_t s) {
   if (f32) place_cls_grad_kernel<float><<<dim3(T, B), 128, 0, s>>>(dxc, T, D, (float*)dx);
   else place_cls_grad_kernel<bf16><<<dim3(T, B), 128, 0, s>>>(dxc, T, D, (bf16*)dx);
+}
+
+void place_rows(const void* rows, int n, size_t row_bytes, int64_t every, void* dst, hipStream_t s) {
+  const int words = (int)(row_bytes / 4);
+  place_rows_kernel<<<n, words < 256 ? 64 : 256, 0, s>>>((const uint32_t*)rows, words, every * words, (uint32_t*)dst);
 }
 
 void cross_entropy(const float* logits, const int32_t* labels, int B, int C, float* loss_rows,

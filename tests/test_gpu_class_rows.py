@@ -70,6 +70,31 @@ def test_class_attention_does_not_see_the_rounding_of_its_output(hip, orc64, T):
         assert hip.rel(got["grads"]["blocks.0.w_qkv"][:, cols], g) < TOL_BF16, name
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_reported_class_rows_are_those_the_loss_came_from(hip, dtype):
+    """Logits from the reported output of the last block: the head's own, up to the order of fp32 sums."""
+    cfg = S.get_config("mini_4blk", dtype=dtype, batch=8, heads=2)
+    p = S.make_params(cfg, std=0.05, peaky=4.0)
+    x, y = S.make_inputs(cfg)
+    got = hip.run_hip_step(cfg, p, x, y)
+    z = got["x_final"][:, 0].astype(np.float64)
+    z = (z - z.mean(1, keepdims=True)) / np.sqrt(z.var(1, keepdims=True) + 1e-6) * p["lnf_g"] + p["lnf_b"]
+    assert hip.rel(got["logits"], z @ p["w_head"].astype(np.float64) + p["b_head"]) < 1e-5
+
+
+def test_recorded_routing_replays_to_the_same_bits(hip):
+    """Among 4096 class tokens some sit on a near-tie of their experts: what a free step reports and a step given that choice
+    have equal loss and gradients."""
+    cfg = S.get_config("mini_moe", batch=4096, image_size=32, moe_top_k=1)
+    p = S.make_params(cfg, std=0.05, peaky=4.0)
+    x, y = S.make_inputs(cfg)
+    free = hip.run_hip_step(cfg, p, x, y)
+    again = hip.run_hip_step(cfg, p, x, y, forced_experts=free["experts"])
+    assert again["loss"] == free["loss"]
+    for n, g in free["grads"].items():
+        assert np.array_equal(again["grads"][n], g), n
+
+
 def products_after_class_attention(torch, call):
     """Names of the product kernels of a step, in order, from the class rows' attention on"""
     from torch.profiler import ProfilerActivity, profile
