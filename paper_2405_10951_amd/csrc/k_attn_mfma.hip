@@ -18,6 +18,8 @@ namespace bsr {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -398,10 +400,10 @@ void launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float*
 // into registers while the previous chunk is worked on): a workgroup owns 128 queries (4 wavefronts of 32) and the
 // softmax is kept running, output and sum rescaled when a chunk raises the maximum.  Probabilities, score gradients and
 // delta stay in fp32 here (Split below), so results are the exact ones rounded to bf16.  What bounds it is the softmax
-// arithmetic (VALU) beside 12 MFMAs per 32 x 32 scores; 128-row chunks leave 32 KB of LDS per workgroup, so four or
-// five of them share a CU and cover each other's waits.  At 577 tokens, 16 images of 6 heads, calls in a loop: 42 us forward and 135
-// backward (732 and 2711 with one wavefront per query, of the same precision; 36 and 100 with bf16 factors, whose dq and dk
-// are 1.4 to 2.6 times as far from the exact ones).
+// arithmetic (VALU) beside 12 MFMAs per 32 x 32 scores and the registers of the accumulators: held to 256 (two workgroups per
+// CU) the kernels run 1.4 times as fast as with the 284 the compiler takes by itself.  At 577 tokens, 16 images of 6 heads, calls
+// in a loop: 29 us forward and 87 backward (732 and 2711 with one wavefront per query, of the same precision; 37 and 100 with
+// bf16 factors at 1 workgroup per CU, dq and dk 1.4 to 2.6 times as far from the exact ones).
 // Workgroups are numbered head first: the query blocks of a head then run on one XCD and share its L2.
 constexpr int LC = 128, LCB = LC / 32, LONG_T = 1024;
 
@@ -409,10 +411,11 @@ constexpr int LC = 128, LCB = LC / 32, LONG_T = 1024;
 // score gradients in fp32, each as two MFMAs with the same other operand.
 struct Split {
   bf16x8 hi, lo;
-  __device__ __forceinline__ void set(int i, float v) {
-    const bf16 a = (bf16)v;
-    hi[i] = a;
-    lo[i] = (bf16)(v - (float)a);
+  __device__ __forceinline__ void set2(int i, float v, float w) {      // elements i, i + 1: conversions come in pairs
+    const bf16x2 a = __builtin_convertvector(f32x2{v, w}, bf16x2);
+    const bf16x2 b = __builtin_convertvector(f32x2{v - (float)a[0], w - (float)a[1]}, bf16x2);
+    hi[i] = a[0]; hi[i + 1] = a[1];
+    lo[i] = b[0]; lo[i + 1] = b[1];
   }
 };
 
@@ -433,7 +436,7 @@ __device__ inline void chunk_stash(const ChunkRegs& c, u32x4* s, int tid) {
   }
 }
 
-__global__ __launch_bounds__(256) void attn_fwd_long_kernel(const bf16* __restrict__ qkv, int T, int H, int heads_total,
+__global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __restrict__ qkv, int T, int H, int heads_total,
                                                             bf16* __restrict__ out, float* __restrict__ lse,
                                                             float* __restrict__ cls_prob) {
   __shared__ u32x4 Ks[LC * 8], Vs[LC * 8];
@@ -508,10 +511,11 @@ __global__ __launch_bounds__(256) void attn_fwd_long_kernel(const bf16* __restri
     for (int jb = 0; jb < LCB; ++jb) {
       Split p[2];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pr = __builtin_amdgcn_exp2f(fmaf(s[jb][r], c, -mc));
-        sum += pr;
-        p[r >> 3].set(r & 7, pr);
+      for (int r = 0; r < 16; r += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[jb][r], c, -mc)), p1 = __builtin_amdgcn_exp2f(fmaf(s[jb][r + 1], c, -mc));
+        sum += p0;
+        sum += p1;
+        p[r >> 3].set2(r & 7, p0, p1);
       }
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
@@ -548,143 +552,176 @@ __global__ __launch_bounds__(256) void attn_fwd_long_kernel(const bf16* __restri
   }
 }
 
-// Backward beyond 256 tokens, as up to 256: dQ by workgroups that own 128 queries and walk chunks of keys, then dK and dV by
-// workgroups that own 128 keys and walk chunks of queries.  delta_i = sum_j P_ij dP_ij takes a walk of its own before the
-// dQ one: dO . O would be one product, but of an output that has been rounded to bf16.
-__global__ __launch_bounds__(256) void attn_bwd_dq_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dout,
-                                                               const float* __restrict__ lse, int T, int H, int heads_total,
-                                                               float* __restrict__ delta, bf16* __restrict__ dqkv) {
-  __shared__ u32x4 Ks[LC * 8], Vs[LC * 8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
-  const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD;
-  const int64_t rs = 3 * (int64_t)D;
-  const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
-  const bf16* dobase = dout + (int64_t)b * T * D + h * HD;
-  const float c = 0.125f * 1.44269504088896341f;
-  const int q0 = (blockIdx.x / heads_total) * 128 + wave * 32, qc = min(q0 + lr, T - 1);
-  bf16x8 qf[4], dof[4];
+// Backward beyond 256 tokens, two launches.  First delta_i = sum_j P_ij dP_ij in fp32, workgroups of 128 queries walking chunks of
+// keys (dO . O would be one product, but of an output that has been rounded to bf16).  Then workgroups of the first half own
+// 128 queries (dQ, chunks of keys), those of the second half 128 keys (dK and dV, chunks of queries).  (delta and dQ in one
+// launch, dK and dV in another: 91 us at 577 tokens, 16 images of 6 heads, and 54 at 2 images; so 87 and 36.)
+struct LongHead {                          // what a workgroup of these kernels works on
+  const bf16 *base, *dobase;               // q of the head's first row (k, v: D and 2 D further), dO
+  int64_t rs, row0;                        // elements from row to row of qkv; index of the head's first row in lse and delta
+  int D, block;
+  __device__ LongHead(const bf16* qkv, const bf16* dout, int T, int H, int heads_total) {
+    const int head = blockIdx.x % heads_total, b = head / H, h = head % H;
+    D = H * HD;
+    rs = 3 * (int64_t)D;
+    base = qkv + (int64_t)b * T * rs + h * HD;
+    dobase = dout + (int64_t)b * T * D + h * HD;
+    row0 = (int64_t)head * T;
+    block = blockIdx.x / heads_total;
+  }
+};
+// four 16-byte pieces of a row: the operand fragments of a wavefront's 32 rows
+__device__ __forceinline__ void row_frags(bf16x8 (&f)[4], const bf16* row, int lh) {
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) f[ks] = *(const bf16x8*)(row + (2 * ks + lh) * 8);
+}
+// scores and dP of 32 staged rows (of xs and ys, from row r0 on) with the fragments xf and yf
+__device__ __forceinline__ void score_products(f32x16& sa, f32x16& dp, const u32x4* xs, const u32x4* ys, int row, int lh, const bf16x8 (&xf)[4],
+                                               const bf16x8 (&yf)[4]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    qf[ks] = *(const bf16x8*)(base + (int64_t)qc * rs + (2 * ks + lh) * 8);
-    dof[ks] = *(const bf16x8*)(dobase + (int64_t)qc * D + (2 * ks + lh) * 8);
+    sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(xs, row, 2 * ks + lh), xf[ks], sa, 0, 0, 0);
+    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(ys, row, 2 * ks + lh), yf[ks], dp, 0, 0, 0);
   }
-  const float l2 = lse[((int64_t)b * H + h) * T + qc] * 1.44269504088896341f;
+}
+constexpr float LOG2E = 1.44269504088896341f, SCORE2 = 0.125f * LOG2E;      // scores are divided by sqrt(64)
+// P of a block of keys k0 .. k0 + 31 in place of the scores; 0 past the last key
+__device__ __forceinline__ void block_probs(f32x16& sa, float l2, int k0, int lh, int T) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sa[r] = __builtin_amdgcn_exp2f(sa[r] * SCORE2 - l2);
+  if (k0 + 32 > T) {                       // uniform: this block reaches past the last key
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (k0 + key_of(0, r, lh) >= T) sa[r] = 0.f;
+  }
+}
+
+__global__ __launch_bounds__(256, 2) void attn_delta_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dout,
+                                                                 const float* __restrict__ lse, int T, int H, int heads_total,
+                                                                 float* __restrict__ delta) {
+  __shared__ u32x4 Ks[LC * 8], Vs[LC * 8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
+  const LongHead hd(qkv, dout, T, H, heads_total);
+  const int qi = hd.block * 128 + wave * 32 + lr, qc = min(qi, T - 1);
+  bf16x8 qf[4], dof[4];
+  row_frags(qf, hd.base + (int64_t)qc * hd.rs, lh);
+  row_frags(dof, hd.dobase + (int64_t)qc * hd.D, lh);
+  const float l2 = lse[hd.row0 + qc] * LOG2E;
   float dl = 0.f;
-  f32x16 o[2];
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
   ChunkRegs kr, vr;
-  auto fetch = [&](int c0) __attribute__((always_inline)) {
-    chunk_fetch(kr, base + D, rs, c0, T, tid);
-    chunk_fetch(vr, base + 2 * D, rs, c0, T, tid);
-  };
-  fetch(0);
-  for (int walk = 0; walk < 2; ++walk) {
+  chunk_fetch(kr, hd.base + hd.D, hd.rs, 0, T, tid);
+  chunk_fetch(vr, hd.base + 2 * hd.D, hd.rs, 0, T, tid);
+  for (int c0 = 0; c0 < T; c0 += LC) {
+    if (c0) __syncthreads();
+    chunk_stash(kr, Ks, tid);
+    chunk_stash(vr, Vs, tid);
+    __syncthreads();
+    if (c0 + LC < T) {
+      chunk_fetch(kr, hd.base + hd.D, hd.rs, c0 + LC, T, tid);
+      chunk_fetch(vr, hd.base + 2 * hd.D, hd.rs, c0 + LC, T, tid);
+    }
+#pragma unroll
+    for (int jb = 0; jb < LCB; ++jb) {
+      f32x16 sa, dp;
+      score_products(sa, dp, Ks, Vs, jb * 32 + lr, lh, qf, dof);
+      block_probs(sa, l2, c0 + jb * 32, lh, T);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dl = fmaf(sa[r], dp[r], dl);
+    }
+  }
+  dl += __shfl_xor(dl, 32, 64);
+  if (lh == 0 && qi < T) delta[hd.row0 + qi] = dl;
+}
+
+__global__ __launch_bounds__(256, 2) void attn_bwd_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dout,
+                                                               const float* __restrict__ lse, const float* __restrict__ delta, int T,
+                                                               int H, int heads_total, bf16* __restrict__ dqkv) {
+  __shared__ u32x4 As[LC * 8], Bs[LC * 8];
+  __shared__ __attribute__((aligned(16))) float lse_s[LC], del_s[LC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
+  const LongHead hd(qkv, dout, T, H, heads_total);
+  const int nblk = (T + 127) / 128;
+  bf16* dst = dqkv + (hd.base - qkv) + lr;           // feature lr of the head's first row of dq
+  ChunkRegs ra, rb;
+  if (hd.block < nblk) {
+    const int q0 = hd.block * 128 + wave * 32, qc = min(q0 + lr, T - 1);
+    bf16x8 qf[4], dof[4];
+    row_frags(qf, hd.base + (int64_t)qc * hd.rs, lh);
+    row_frags(dof, hd.dobase + (int64_t)qc * hd.D, lh);
+    const float l2 = lse[hd.row0 + qc] * LOG2E, dl = delta[hd.row0 + qc];
+    f32x16 o[2];
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
+    chunk_fetch(ra, hd.base + hd.D, hd.rs, 0, T, tid);
+    chunk_fetch(rb, hd.base + 2 * hd.D, hd.rs, 0, T, tid);
     for (int c0 = 0; c0 < T; c0 += LC) {
-      if (walk || c0) __syncthreads();
-      chunk_stash(kr, Ks, tid);
-      chunk_stash(vr, Vs, tid);
+      if (c0) __syncthreads();
+      chunk_stash(ra, As, tid);
+      chunk_stash(rb, Bs, tid);
       __syncthreads();
-      if (c0 + LC < T) fetch(c0 + LC);
-      else if (!walk) fetch(0);
+      if (c0 + LC < T) {
+        chunk_fetch(ra, hd.base + hd.D, hd.rs, c0 + LC, T, tid);
+        chunk_fetch(rb, hd.base + 2 * hd.D, hd.rs, c0 + LC, T, tid);
+      }
 #pragma unroll
       for (int jb = 0; jb < LCB; ++jb) {
         f32x16 sa, dp;
+        score_products(sa, dp, As, Bs, jb * 32 + lr, lh, qf, dof);
+        block_probs(sa, l2, c0 + jb * 32, lh, T);
+        Split ds[2];                                 // (the 1/8 of dS is applied to the sums)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Ks, jb * 32 + lr, 2 * ks + lh), qf[ks], sa, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Vs, jb * 32 + lr, 2 * ks + lh), dof[ks], dp, 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          sa[r] = __builtin_amdgcn_exp2f(sa[r] * c - l2);
-          if (c0 + key_of(jb, r, lh) >= T) sa[r] = 0.f;
-        }
-        if (!walk) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) dl = fmaf(sa[r], dp[r], dl);
-          continue;
-        }
-        Split ds[2];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ds[r >> 3].set(r & 7, sa[r] * (dp[r] - dl) * 0.125f);
+        for (int r = 0; r < 16; r += 2) ds[r >> 3].set2(r & 7, sa[r] * (dp[r] - dl), sa[r + 1] * (dp[r + 1] - dl));
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
           for (int hf = 0; hf < 2; ++hf) {
-            const bf16x8 kf = lds_frag_t(Ks, nb, lane, 2 * jb + hf);
+            const bf16x8 kf = lds_frag_t(As, nb, lane, 2 * jb + hf);
             o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds[hf].hi, kf, o[nb], 0, 0, 0);
             o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds[hf].lo, kf, o[nb], 0, 0, 0);
           }
       }
     }
-    if (!walk) dl += __shfl_xor(dl, 32, 64);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int i = q0 + key_of(0, r, lh);
+        if (i < T) dst[i * hd.rs + nb * 32] = (bf16)(o[nb][r] * 0.125f);
+      }
+    return;
   }
-  if (lh == 0 && q0 + lr < T) delta[((int64_t)b * H + h) * T + q0 + lr] = dl;
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = q0 + 8 * (r >> 2) + 4 * lh + (r & 3);
-      if (i < T) dqkv[((int64_t)b * T + i) * rs + h * HD + nb * 32 + lr] = (bf16)o[nb][r];
-    }
-}
-
-__global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dout,
-                                                                const float* __restrict__ lse, const float* __restrict__ delta,
-                                                                int T, int H, int heads_total, bf16* __restrict__ dqkv) {
-  __shared__ u32x4 Qs[LC * 8], dOs[LC * 8];
-  __shared__ __attribute__((aligned(16))) float lse_s[LC], del_s[LC];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
-  const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD;
-  const int64_t rs = 3 * (int64_t)D;
-  const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
-  const bf16* dobase = dout + (int64_t)b * T * D + h * HD;
-  const float* lrow = lse + ((int64_t)b * H + h) * T;
-  const float* drow = delta + ((int64_t)b * H + h) * T;
-  const float c = 0.125f * 1.44269504088896341f;
-  const int j0 = (blockIdx.x / heads_total) * 128 + wave * 32, jc = min(j0 + lr, T - 1);
+  const int j0 = (hd.block - nblk) * 128 + wave * 32, jc = min(j0 + lr, T - 1);
   bf16x8 kf[4], vf[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    kf[ks] = *(const bf16x8*)(base + D + (int64_t)jc * rs + (2 * ks + lh) * 8);
-    vf[ks] = *(const bf16x8*)(base + 2 * D + (int64_t)jc * rs + (2 * ks + lh) * 8);
-  }
+  row_frags(kf, hd.base + (int64_t)jc * hd.rs + hd.D, lh);
+  row_frags(vf, hd.base + (int64_t)jc * hd.rs + 2 * hd.D, lh);
   f32x16 ok[2], ov[2];
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { ok[nb][r] = 0.f; ov[nb][r] = 0.f; }
-  ChunkRegs qr, dor;
-  chunk_fetch(qr, base, rs, 0, T, tid);
-  chunk_fetch(dor, dobase, D, 0, T, tid);
+  chunk_fetch(ra, hd.base, hd.rs, 0, T, tid);
+  chunk_fetch(rb, hd.dobase, hd.D, 0, T, tid);
   for (int c0 = 0; c0 < T; c0 += LC) {
     if (c0) __syncthreads();
-    chunk_stash(qr, Qs, tid);
-    chunk_stash(dor, dOs, tid);
+    chunk_stash(ra, As, tid);
+    chunk_stash(rb, Bs, tid);
     if (tid < LC) {
-      lse_s[tid] = c0 + tid < T ? lrow[c0 + tid] * 1.44269504088896341f : INFINITY;
-      del_s[tid] = c0 + tid < T ? drow[c0 + tid] : 0.f;
+      lse_s[tid] = c0 + tid < T ? lse[hd.row0 + c0 + tid] * LOG2E : INFINITY;
+      del_s[tid] = c0 + tid < T ? delta[hd.row0 + c0 + tid] : 0.f;
     }
     __syncthreads();
     if (c0 + LC < T) {
-      chunk_fetch(qr, base, rs, c0 + LC, T, tid);
-      chunk_fetch(dor, dobase, D, c0 + LC, T, tid);
+      chunk_fetch(ra, hd.base, hd.rs, c0 + LC, T, tid);
+      chunk_fetch(rb, hd.dobase, hd.D, c0 + LC, T, tid);
     }
 #pragma unroll
     for (int ib = 0; ib < LCB; ++ib) {
       f32x16 sa, dp;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Qs, ib * 32 + lr, 2 * ks + lh), kf[ks], sa, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(dOs, ib * 32 + lr, 2 * ks + lh), vf[ks], dp, 0, 0, 0);
-      }
+      score_products(sa, dp, As, Bs, ib * 32 + lr, lh, kf, vf);
       Split p[2], ds[2];
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {              // queries c0 + 32 ib + 8 g4 + 4 lh + {0..3}
@@ -693,18 +730,18 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const bf16* __re
         const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
         const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < 4; e += 2) {
           const int r = g4 * 4 + e;
-          const float pr = __builtin_amdgcn_exp2f(sa[r] * c - lv[e]);
-          p[r >> 3].set(r & 7, pr);
-          ds[r >> 3].set(r & 7, pr * (dp[r] - dv[e]) * 0.125f);
+          const float p0 = __builtin_amdgcn_exp2f(sa[r] * SCORE2 - lv[e]), p1 = __builtin_amdgcn_exp2f(sa[r + 1] * SCORE2 - lv[e + 1]);
+          p[r >> 3].set2(r & 7, p0, p1);
+          ds[r >> 3].set2(r & 7, p0 * (dp[r] - dv[e]), p1 * (dp[r + 1] - dv[e + 1]));
         }
       }
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
-          const bf16x8 gf = lds_frag_t(dOs, nb, lane, 2 * ib + hf), qf = lds_frag_t(Qs, nb, lane, 2 * ib + hf);
+          const bf16x8 gf = lds_frag_t(Bs, nb, lane, 2 * ib + hf), qf = lds_frag_t(As, nb, lane, 2 * ib + hf);
           ov[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[hf].hi, gf, ov[nb], 0, 0, 0);
           ov[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[hf].lo, gf, ov[nb], 0, 0, 0);
           ok[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ds[hf].hi, qf, ok[nb], 0, 0, 0);
@@ -716,19 +753,18 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_long_kernel(const bf16* __re
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int j = j0 + 8 * (r >> 2) + 4 * lh + (r & 3);
+      const int j = j0 + key_of(0, r, lh);
       if (j < T) {
-        bf16* dst = dqkv + ((int64_t)b * T + j) * rs + h * HD + nb * 32 + lr;
-        dst[D] = (bf16)ok[nb][r];
-        dst[2 * D] = (bf16)ov[nb][r];
+        dst[j * hd.rs + hd.D + nb * 32] = (bf16)(ok[nb][r] * 0.125f);
+        dst[j * hd.rs + 2 * hd.D + nb * 32] = (bf16)ov[nb][r];
       }
     }
 }
 
 void launch_bwd_long(const bf16* qkv, const bf16* dout, const float* lse, int B, int T, int H, float* delta, bf16* dqkv, hipStream_t s) {
   const int grid = B * H * ((T + 127) / 128);
-  attn_bwd_dq_long_kernel<<<grid, 256, 0, s>>>(qkv, dout, lse, T, H, B * H, delta, dqkv);
-  attn_bwd_dkv_long_kernel<<<grid, 256, 0, s>>>(qkv, dout, lse, delta, T, H, B * H, dqkv);
+  attn_delta_long_kernel<<<grid, 256, 0, s>>>(qkv, dout, lse, T, H, B * H, delta);
+  attn_bwd_long_kernel<<<2 * grid, 256, 0, s>>>(qkv, dout, lse, delta, T, H, B * H, dqkv);
 }
 
 }  // namespace
