@@ -246,7 +246,8 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* ctx, const void* x_in, const int32_t* 
  * times every such launch with HIP events in its place in the step, and from then on gives each
  * launch of a batch of the same size B its fastest shape; other batch sizes keep the built-in cost
  * model.  Every shape adds up an output element in the same order, so results do not change by a
- * bit.  Arguments as for the two entry points (x_frozen is the x_out of the first and the x_in of
+ * bit.  (Products of few rows run in a kernel of their own, which adds up in another order; which they are depends on
+ * their sizes alone, so there is nothing to choose and they are only timed.)  Arguments as for the two entry points (x_frozen is the x_out of the first and the x_in of
  * the second; loss_out and grads are overwritten as by a normal step).
  *   launches_out  host, may be NULL: number of launches that now have a measured choice
  *   changed_out   host, may be NULL: how many of them differ from the cost model's choice
@@ -278,7 +279,8 @@ int32_t bsr_autotune_overlapped(bsr_ctx* ctx, const void* input, const int32_t* 
  * The tile choices a context holds after bsr_autotune / bsr_autotune_overlapped, for inspection and reports (host
  * only).  part 0: the launches of bsr_forward_frozen in launch order, part 1: those of bsr_train_blocks_fwd_bwd
  * (a backward launch carries the input gradient named here and, fused with it, the weight gradient of its layer).
- *   rows, out, in  the product: rows x in times in x out      tile  shape id (see bsr_gemm_tile_shapes)
+ *   rows, out, in  the product: rows x in times in x out      tile  shape id (see bsr_gemm_tile_shapes), or
+ *                  9000000 + 1000 rows + columns of a tile of the kernel for products of few rows
  *   microseconds   what bsr_autotune measured for that shape at that launch (0 after bsr_autotune_overlapped,
  *                  which times whole passes)
  * Returns the number of launches of that part (0 without a choice or with bad arguments); writes at most max.
@@ -366,7 +368,8 @@ int32_t bsr_adamw_step(bsr_ctx* ctx, const bsr_params* grads, const bsr_params* 
  *   w_s   bf16 copy of W stored [in,out]        u     [M,in], may be NULL
  * tile (both): 0, or the id of a block-tile shape (bsr_gemm_tile_shapes) the MFMA kernel is to use; a shape that
  *   cannot take the product (a direct-to-LDS shape when `in` / `out` to contract over is not a multiple of 64)
- *   gives way to the default.  Every shape gives the same bits.  An unknown id: INVALID_ARG.
+ *   gives way to the default, and a product of few rows (by its sizes alone: where the kernel for those is clearly
+ *   the faster one) runs that kernel whatever the tile.  Every tile gives the same bits.  An unknown id: INVALID_ARG.
  * bsr_linear_wgrad (Eq. 4): dw[in,out] (fp32) = x[M,in]^T . dy[M,out], summed over all M rows.
  *   db         fp32 [out], may be NULL: the bias gradient, db[o] = sum over rows of dy[:,o], from the
  *              same launch when the MFMA kernel takes the shape (otherwise it needs the workspace)

@@ -93,8 +93,8 @@ struct ProfRec {
 
 // Tile choice per NT GEMM launch, measured on the context's own launches (bsr_autotune).  A launch is
 // identified by the entry point it belongs to and its position in that call's launch order.
-struct TunePick { int M, N, K, tile; float us; };   // us: the chosen shape's measured time (0: not measured)
-struct TuneRec { int kind, cand; size_t site; int M, N, K; hipEvent_t start, stop; };
+struct TunePick { int M, N, K, tile, model; float us; };   // us: the chosen shape's measured time (0: not measured); model: without a choice
+struct TuneRec { int kind, cand; size_t site; int M, N, K, model; hipEvent_t start, stop; };
 struct Tune {
   int batch = 0;                       // the picks hold for this batch size (0: none)
   std::vector<TunePick> pick[2];       // [0] bsr_forward_frozen, [1] bsr_train_blocks_fwd_bwd
@@ -477,7 +477,7 @@ struct TileChoice {
   bool timing = false;
   TuneRec rec{};
 };
-TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s) {
+TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s, bool carries_wgrad = false) {
   TileChoice ch;
   if (!gemm_nt_tile_is_free(g) || c->tune.aside) return ch;
   Tune& t = c->tune;
@@ -485,7 +485,7 @@ TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s) {
   if (t.cand >= 0) {
     const int cand = (t.kind == 1 && t.cand_train >= 0) ? t.cand_train : t.cand;
     ch.tile = gemm_nt_tile_id(cand);
-    ch.rec = TuneRec{t.kind, cand, site, g.M, g.N, g.K, nullptr, nullptr};
+    ch.rec = TuneRec{t.kind, cand, site, g.M, g.N, g.K, gemm_nt_model_tile(g, carries_wgrad), nullptr, nullptr};
     ch.timing = hipEventCreate(&ch.rec.start) == hipSuccess && hipEventCreate(&ch.rec.stop) == hipSuccess;
     if (ch.timing) (void)hipEventRecord(ch.rec.start, s);
   } else if (t.batch == t.cur_batch && site < t.pick[t.kind].size()) {
@@ -548,7 +548,7 @@ void dgrad_wgrad(bsr_ctx* c, const GemmDesc& dg, const void* x, const void* dy, 
   }
   wg.bsum = (float*)db;
   ProfScope ps(c, BSR_PROF_GEMM, 2.0 * dg.M * dg.N * dg.K + 2.0 * wg.M * wg.N * wg.K, s);
-  TileChoice ch = choose_tile(c, dg, s);
+  TileChoice ch = choose_tile(c, dg, s, true);
   gemm_mfma_pair(dg, wg, c->b.splitk, c->b.splitk_floats, s, ch.tile, &c->tn_chain);
   tile_done(c, ch, s);
 }
@@ -1353,12 +1353,12 @@ static int32_t autotune_overlapped(bsr_ctx* c, const void* input, const int32_t*
     size_t sites[2] = {0, 0};
     for (const TuneRec& r : t.recs) sites[r.kind] = std::max(sites[r.kind], r.site + 1);
     for (int k = 0; k < 2; ++k) {
-      t.pick[k].assign(sites[k], TunePick{0, 0, 0, 0, 0.f});
+      t.pick[k].assign(sites[k], TunePick{0, 0, 0, 0, 0, 0.f});
       for (const TuneRec& r : t.recs) {
         if (r.kind != k) continue;
         TunePick& p = t.pick[k][r.site];
-        p.M = r.M; p.N = r.N; p.K = r.K;
-        p.tile = gemm_nt_tile_id(k == 0 ? fz : tr);
+        p.M = r.M; p.N = r.N; p.K = r.K; p.model = r.model;
+        p.tile = r.model >= FEW_ROWS_ID ? r.model : gemm_nt_tile_id(k == 0 ? fz : tr);
       }
       launches += (int)sites[k];
     }
@@ -1375,7 +1375,7 @@ static int32_t autotune_overlapped(bsr_ctx* c, const void* input, const int32_t*
   if (changed_out) {
     int diff = 0;
     for (int k = 0; k < 2; ++k)
-      for (const TunePick& p : t.pick[k]) diff += p.tile != 0 && p.tile != gemm_nt_model_tile(p.M, p.N, p.K);
+      for (const TunePick& p : t.pick[k]) diff += p.tile != 0 && p.tile != p.model;
     *changed_out = diff;
   }
   return check_hip(c, "bsr_autotune_overlapped");
@@ -1408,7 +1408,7 @@ static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, in
     for (const TuneRec& r : t.recs) sites[r.kind] = std::max(sites[r.kind], r.site + 1);
     for (int k = 0; k < 2; ++k) {
       std::vector<float> best(sites[k] * n, -1.f);          // min over the rounds, per (site, shape)
-      t.pick[k].assign(sites[k], TunePick{0, 0, 0, 0, 0.f});
+      t.pick[k].assign(sites[k], TunePick{0, 0, 0, 0, 0, 0.f});
       for (const TuneRec& r : t.recs) {
         if (r.kind != k) continue;
         float ms = 0.f;
@@ -1416,13 +1416,14 @@ static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, in
         float& b = best[r.site * n + r.cand];
         if (b < 0.f || ms < b) b = ms;
         TunePick& p = t.pick[k][r.site];
-        p.M = r.M; p.N = r.N; p.K = r.K;
+        p.M = r.M; p.N = r.N; p.K = r.K; p.model = r.model;
       }
       for (size_t i = 0; i < sites[k]; ++i) {
         int arg = -1;
         for (int j = 0; j < n; ++j)
           if (best[i * n + j] >= 0.f && (arg < 0 || best[i * n + j] < best[i * n + arg])) arg = j;
-        t.pick[k][i].tile = arg < 0 ? 0 : gemm_nt_tile_id(arg);
+        const int model = t.pick[k][i].model;           // (a product of few rows has run its own kernel every time)
+        t.pick[k][i].tile = arg < 0 ? 0 : model >= FEW_ROWS_ID ? model : gemm_nt_tile_id(arg);
         t.pick[k][i].us = arg < 0 ? 0.f : best[i * n + arg] * 1e3f;
         ++launches;
       }
@@ -1441,7 +1442,7 @@ static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, in
     // how many launches now take another shape than the built-in model would give them
     int diff = 0;
     for (int k = 0; k < 2; ++k)
-      for (const TunePick& p : t.pick[k]) diff += p.tile != 0 && p.tile != gemm_nt_model_tile(p.M, p.N, p.K);
+      for (const TunePick& p : t.pick[k]) diff += p.tile != 0 && p.tile != p.model;
     *changed_out = diff;
   }
   return check_hip(c, "bsr_autotune");

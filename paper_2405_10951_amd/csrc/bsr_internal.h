@@ -93,7 +93,8 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
                     int tile = 0, TnChain* chain = nullptr);
 // the block-tile shapes the NT kernel is instantiated for, and whether a GEMM is free to take any of them
 int gemm_nt_tile_count();
-int gemm_nt_model_tile(int M, int N, int K);   // the built-in model's choice
+constexpr int FEW_ROWS_ID = 9000000;           // + 1000 rows + columns: a tile of the kernel for products of few rows
+int gemm_nt_model_tile(const GemmDesc& g, bool carries_wgrad);   // what runs without a measured choice; from FEW_ROWS_ID on: whatever is asked for
 int gemm_nt_tile_id(int i);
 size_t gemm_nt_tile_lds_bytes(int id);          // dynamic LDS a workgroup of that shape holds
 bool gemm_nt_tile_is_free(const GemmDesc& g);

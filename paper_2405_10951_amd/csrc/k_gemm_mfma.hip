@@ -1367,10 +1367,6 @@ static int model_pick(const NtModel (&table)[N], int M, int Nc, int K, bool dire
   return pick;
 }
 static int nt_pick(const GemmDesc& g, float* us) { return model_pick(kNtModel, g.M, g.N, g.K, is_ntd(g), g.ln_colsum != nullptr, us); }
-int gemm_nt_model_tile(int M, int N, int K) {
-  float us = 0.f;
-  return model_pick(kNtModel, M, N, K, K % BK == 0, false, &us);
-}
 size_t gemm_nt_tile_lds_bytes(int id) {
   const int bm = id % 1000000 / 1000, bn = id % 1000, nst = ntd_stages(id);
   return (size_t)(nst ? nst : 2) * (bm + bn) * BK * sizeof(bf16);
@@ -1389,6 +1385,18 @@ static int few_rows_shape(const GemmDesc& g, bool carries_wgrad) {
   if (few < 0) return -1;
   nt_pick(g, &tiled_us);
   return few_us < FEW_LEAD * (tiled_us - EVENTS_US - (carries_wgrad ? TILED_LAUNCH_US : 0.f)) ? few : -1;
+}
+
+static bool can_pair(const GemmDesc& nt) { return is_nt(nt) && !nt.grp_off && nt.K % BK == 0; }
+static int pair_model_tile(const GemmDesc& nt) {
+  float us = 0.f;
+  return model_pick(kPairModel, nt.M, nt.N, nt.K, false, false, &us);
+}
+int gemm_nt_model_tile(const GemmDesc& g, bool carries_wgrad) {
+  const int few = few_rows_shape(g, carries_wgrad);
+  if (few >= 0) return FEW_ROWS_ID + 32000 * kFewShapes[few].mi + 32 * kFewShapes[few].ni;
+  float us = 0.f;
+  return carries_wgrad && can_pair(g) ? pair_model_tile(g) : nt_pick(g, &us);
 }
 
 void gemm_tn_flush(TnChain* chain, hipStream_t s) {
@@ -1448,10 +1456,8 @@ void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hip
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile, TnChain* chain) {
   const int few = few_rows_shape(nt, true);
-  const bool can = few < 0 && is_nt(nt) && is_tn(tn) && !nt.grp_off && !tn.grp_off && nt.K % BK == 0;
-  if (can) {
-    float us = 0.f;
-    switch (tile ? tile : model_pick(kPairModel, nt.M, nt.N, nt.K, false, false, &us)) {
+  if (few < 0 && can_pair(nt) && is_tn(tn) && !tn.grp_off) {
+    switch (tile ? tile : pair_model_tile(nt)) {
       case 128064: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<128, 64, 4, 2, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
       case 64128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<64, 128, 2, 4, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
       case 192128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<192, 128, 2, 4, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }

@@ -72,3 +72,20 @@ def test_operands_of_more_than_2_32_elements(env, M, kin, out):
         y = y.T
     K.assert_close(y[-64:].float().cpu().numpy(), tail.astype(np.float64) @ b.astype(np.float64).T, "last rows")
     assert not bool(y[:-64].any())
+
+
+def test_tuning_reports_what_products_of_few_rows_run(env):
+    """They run one kernel whatever is asked for: no shape is listed for them and none counts as changed."""
+    import bsr_synth as S
+    torch, P = env
+    cfg = S.get_config("c2_deit_s", dtype="bf16", batch=4)
+    x, y = S.make_inputs(cfg)
+    ctx = P.Context(cfg, S.make_params(cfg), 4)
+    xf = torch.empty((4, ctx.T_f, cfg["dim"]), dtype=ctx.act_dtype, device="cuda")
+    launches, changed = ctx.bsr_autotune(torch.as_tensor(x).cuda().to(ctx.act_dtype).contiguous(), torch.as_tensor(y, dtype=torch.int32).cuda(), xf,
+                                         torch.zeros(1, device="cuda"), ctx.new_grads())
+    picks = ctx.bsr_tile_choices(0) + ctx.bsr_tile_choices(1)
+    few = [t for t in picks if t[3] >= 9000000]
+    assert len(picks) == launches and 0 < len(few) < launches and changed <= launches - len(few)
+    assert {t[3] for t in few} <= {9032032, 9064032, 9064064} and all(t[4] > 0 for t in few)
+    assert {t[3] for t in picks} - {t[3] for t in few} <= set(P.bsr_gemm_tile_shapes())
