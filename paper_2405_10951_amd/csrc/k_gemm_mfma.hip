@@ -734,8 +734,9 @@ bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.grp_off && !g.ln_col
 // ------------------------------------------------------------------------------------------ NT, few rows
 // The same product where block tiles shared by eight wavefronts would leave most CUs idle.  A workgroup owns
 // 32 MI x 32 NI outputs and its four wavefronts share k: wavefront w takes the k-groups (of 64) w, w + 4, ..., with a ring
-// of NST stages of its own in LDS, filled by global_load_lds as in the kernel above.  Nobody shares a stage, so there
-// is no barrier in the loop: a wavefront waits for its own loads by count and keeps NST groups in flight.  The four
+// of two stages of its own in LDS, filled by global_load_lds as in the kernel above.  Nobody shares a stage, so there
+// is no barrier in the loop: a wavefront waits for its own loads by count and keeps two groups in flight (three or four brought
+// nothing: 197 x 768 x 3072 6.4 and 6.6 us with two and four, and they keep a second workgroup off the CU).  The four
 // partial tiles are added through LDS in wavefront order (the sum over k has another order than in the tiled
 // kernels, so which products come here depends on their size alone).
 // What bounds it: the CU's path from L2 (about 100 GB/s of operands per CU; a 32 x 32 tile has no reuse to speak of),
@@ -743,10 +744,9 @@ bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.grp_off && !g.ln_col
 // 3072 21.0 -> 6.4, 2304 from 768 8.2 -> 5.2; 788 rows, 384 from 1536 12.6 -> 6.3; 1182 rows, 768 from 3072 21 -> 16.
 // (Fragments straight from global memory, without LDS: 13.5 us for 197 x 768 x 3072; a load then touches 32 lines.)
 // LNF: the folded LayerNorm; a wavefront adds up the rows of its k-groups from its fragments of A.
-template <int MI, int NI, int NST, bool LNF>
+template <int MI, int NI, bool LNF>
 __global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
-  constexpr int NW = 4, BM = 32 * MI, BN = 32 * NI, LDP = BN + 4, LPT = 4 * (MI + NI), STAGE = LPT * 1024;
-  static_assert(NST >= 2 && NST <= 4 && NST * LPT <= 60, "vmcnt has 6 bits");
+  constexpr int NW = 4, NST = 2, BM = 32 * MI, BN = 32 * NI, LDP = BN + 4, LPT = 4 * (MI + NI), STAGE = LPT * 1024;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -782,15 +782,11 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
   for (int mi = 0; mi < MI; ++mi) rsum[mi] = rsq[mi] = 0.f;
   const int sw = swz(lr), ng = g.K / 64;
   const int mine = ng > wave ? (ng - wave + NW - 1) / NW : 0;      // k-groups of this wavefront
-#pragma unroll
-  for (int j = 0; j < NST; ++j)
-    if (j < mine) issue(wave + j * NW, j);
-  int st = 0;
+  if (mine > 0) issue(wave, 0);
+  if (mine > 1) issue(wave + NW, 1);
   for (int i = 0; i < mine; ++i) {
-    const int ahead = min(mine - 1 - i, NST - 1);                  // groups that may stay in flight
-    if (ahead >= 3) wait_vmcnt<(NST > 3 ? 3 : 0) * LPT>();
-    else if (ahead == 2) wait_vmcnt<(NST > 2 ? 2 : 0) * LPT>();
-    else if (ahead == 1) wait_vmcnt<LPT>();
+    const int st = i & 1;
+    if (i + 1 < mine) wait_vmcnt<LPT>();                           // the next group stays in flight
     else wait_vmcnt<0>();
     BSR_SCHED_FENCE();
     const unsigned char* s = ring + st * STAGE;
@@ -829,7 +825,6 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
             rsq[mi] = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, rsq[mi], false);
           }
     }
-    st = st + 1 == NST ? 0 : st + 1;
   }
   __syncthreads();
   float* part = (float*)smem;
@@ -876,26 +871,25 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
   }
 }
 
-template <int MI, int NI, int NST, bool LNF>
+template <int MI, int NI, bool LNF>
 void launch_few_as(const GemmDesc& g, hipStream_t s) {
-  constexpr size_t ring = (size_t)4 * NST * 4 * (MI + NI) * 1024;
+  constexpr size_t ring = (size_t)4 * 2 * 4 * (MI + NI) * 1024;
   constexpr size_t part = (size_t)4 * 32 * MI * ((32 * NI + 4) * sizeof(float) + sizeof(float2));
   constexpr size_t lds = ring > part ? ring : part;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)gemm_nt_few_kernel<MI, NI, NST, LNF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute((const void*)gemm_nt_few_kernel<MI, NI, LNF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr_set = true;
   }
   const int tiles = ((g.M + 32 * MI - 1) / (32 * MI)) * ((g.N + 32 * NI - 1) / (32 * NI));
-  gemm_nt_few_kernel<MI, NI, NST, LNF><<<tiles, 256, lds, s>>>(g);
+  gemm_nt_few_kernel<MI, NI, LNF><<<tiles, 256, lds, s>>>(g);
 }
 template <int MI, int NI>
 void launch_few(const GemmDesc& g, hipStream_t s) {
-  if (g.ln_colsum) launch_few_as<MI, NI, 2, true>(g, s);
-  else launch_few_as<MI, NI, 2, false>(g, s);
+  if (g.ln_colsum) launch_few_as<MI, NI, true>(g, s);
+  else launch_few_as<MI, NI, false>(g, s);
 }
-// Two stages each: three or four brought nothing (197 x 768 x 3072: 6.4 and 6.6 us with two and four) and keep a second
-// workgroup off the CU.  32 x 64 tiles are never ahead of both 64 x 32 and 64 x 64.
+// 32 x 64 tiles are never ahead of both 64 x 32 and 64 x 64.
 // Modelled time of a product here, in microseconds: launch and epilogue, then ceil(tiles / 256) rounds of a start-up
 // and the tile's operand bytes.  Constants fitted to chains of equal launches at 1 .. 2144 rows, N and K of 384 .. 3072
 // (within 15 % where the kernel is the faster one).
@@ -903,7 +897,9 @@ struct FewShape { int mi, ni; float launch_us, round_us, bytes_per_us; };
 const FewShape kFewShapes[] = {{1, 1, 2.6f, 0.5f, 105e3f}, {2, 1, 2.8f, 0.5f, 103e3f}, {2, 2, 3.3f, 1.0f, 65e3f}};
 constexpr float TILED_LAUNCH_US = 2.6f;               // the same fixed part of a tiled launch
 // A product comes here when the model gives it a clear lead over the tiled kernels: inside a step, where every launch
-// follows another kernel, near-ties of the two models (384 columns from 1536 at 2144 rows) went to the tiled ones.
+// follows another kernel, near-ties of the two models (384 columns from 1536 at 2144 rows) went to the tiled ones.  One
+// lead for products on their own and for input gradients that could carry a weight gradient; for the latter the launch they save is
+// added, and the lead itself was chosen on the former.
 constexpr float FEW_LEAD = 0.8f;
 
 // The shape of this kernel for a product and what the model gives it; -1: not one it takes
@@ -1332,7 +1328,8 @@ static int ntd_stages(int id) {
 // fitted to every shape forced in turn on the launches of ViT-B and DeiT-S steps at 1 .. 128 images, keep ratios of 1 and
 // 0.5, 224 and 384 pixels (436 launches of 256 .. 25216 rows, event-bracketed, in their place in the step).  Over these
 // the six shapes' picks take 1.5 % longer than the fastest of all 25 (fitted on half of them, the other half: 1.2 %); the model
-// before, seven register-staged shapes with two constants each, took 7.4 %.  More shapes bring nothing.
+// before, seven register-staged shapes with two constants each, took 7.4 %.  More shapes bring nothing.  All of it at 384, 768,
+// 1152, 1536, 2304 and 3072 columns: at other widths the model extrapolates, and tuning is the way to know.
 struct NtModel { int id, bm, bn; float c[7]; };
 const NtModel kNtModel[] = {
     {64128, 64, 128, {6.508f, 0.000f, 0.142f, 1.061f, 0.000f, 0.000f, 0.353f}},
