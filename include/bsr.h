@@ -27,6 +27,10 @@
  *     of the current batch.  The frozen prefix reads only frozen weights (Fig. 2) and shares no device
  *     scratch with the other two; the caller orders the producer and the consumer of each x_out buffer
  *     with events (two such buffers make a pipeline).  Different contexts are independent.
+ *   - The same calls on the same inputs give the same bits, whatever tiles were chosen (bsr_autotune).  The
+ *     batch size is one of the inputs: the kernels of the matrix products are chosen by their row counts, some add
+ *     up in another order than others, and so an image's own results may differ in rounding with what else is in
+ *     its batch.
  */
 #ifndef BSR_H_
 #define BSR_H_
@@ -434,7 +438,9 @@ int32_t bsr_gemm_tile_shapes(int32_t* ids, int32_t max);
 
 /*
  * Multi-head softmax attention in bf16 (Eq. 1), as the step runs it.  qkv is [B,T,3*H*d] with
- * columns [q|k|v], head h owning columns h*d .. h*d+d-1 of each third.
+ * columns [q|k|v], head h owning columns h*d .. h*d+d-1 of each third.  With d = 64 and up to 256 tokens the
+ * probabilities and score gradients are rounded to bf16 for the products with v, dout, q and k, and the sum over
+ * dP is taken from the rounded out; beyond 256 tokens and for other d all of it is fp32 between inputs and results.
  * bsr_attention_forward:
  *   out      [B,T,H*d] bf16: per-head Softmax(Q K^T / sqrt d) V, heads concatenated
  *   lse      fp32 [B,H,T], may be NULL: log-sum-exp of every score row (what backward keeps instead
