@@ -1,9 +1,11 @@
 """Text summaries of rocprofv3 runs of bench.py, and the per-launch table of the step's GEMMs.
 
-    python -m paper_2405_10951_amd.profile_report trace <kernel_trace.csv> [steps]
+    python -m paper_2405_10951_amd.profile_report trace <kernel_trace.csv> [steps] [first]
         per-kernel table (launches, microseconds per step, share) of the last `steps` steps of a
-        `rocprofv3 --kernel-trace` run; a step starts at its patchify dispatch, what runs before the
-        counted steps (tile tuning, warm-up) is set-up.
+        `rocprofv3 --kernel-trace` run; a step starts at its patchify dispatch (or the one whose name holds
+        `first`), what runs before the counted steps (tile tuning, warm-up) is set-up.
+    python -m paper_2405_10951_amd.profile_report case <name> [passes]
+        needs the GPU: passes through a case of perf/cases.py, for such a run.
     python -m paper_2405_10951_amd.profile_report counters <counter_collection.csv> [steps]
         per kernel class, the average of every counter of a `rocprofv3 --pmc` run over the last `steps` steps;
         where the run holds them, the matrix-core utilisation by rocprofv3's own definition of MfmaUtil
@@ -34,10 +36,10 @@ def _is_gemm(name: str) -> bool:
     return any(k in name for k in ("gemm_nt_kernel", "gemm_ntd_kernel", "gemm_nt_few_kernel", "gemm_tn_kernel"))
 
 
-def trace(path: str, nsteps: int = 20) -> None:
+def trace(path: str, nsteps: int = 20, first: str = "patchify") -> None:
     rows = list(csv.DictReader(open(path)))
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    starts = [i for i, r in enumerate(rows) if "patchify" in r["Kernel_Name"]]
+    starts = [i for i, r in enumerate(rows) if first in r["Kernel_Name"]]
     nsteps = min(nsteps, len(starts))
     sel = rows[starts[-nsteps]:]
     agg: dict = collections.OrderedDict()
@@ -54,6 +56,17 @@ def trace(path: str, nsteps: int = 20) -> None:
     print(f"{'kernel':72s} {'per_step':>8s} {'us/step':>9s} {'avg_us':>8s} {'pct':>6s}")
     for n, (c, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
         print(f"{n[:72]:72s} {c / nsteps:8.1f} {t / nsteps:9.1f} {t / c:8.1f} {100 * t / tot:6.2f}")
+
+
+def case(name: str, passes: int) -> None:
+    import importlib
+    import torch
+    sys.path.insert(0, ".")
+    cases = importlib.import_module("perf.cases")
+    state = cases.prepare(next(c for c in cases.listed() if c["name"] == name), 1)
+    for _ in range(passes):
+        cases.run(state)
+    torch.cuda.synchronize()
 
 
 def _counter_rows(path: str):
@@ -203,7 +216,9 @@ def shapes(argv: list[str]) -> None:
 
 if __name__ == "__main__":
     if len(sys.argv) >= 3 and sys.argv[1] == "trace":
-        trace(sys.argv[2], int(sys.argv[3]) if len(sys.argv) > 3 else 20)
+        trace(sys.argv[2], int(sys.argv[3]) if len(sys.argv) > 3 else 20, *sys.argv[4:5])
+    elif len(sys.argv) >= 3 and sys.argv[1] == "case":
+        case(sys.argv[2], int(sys.argv[3]) if len(sys.argv) > 3 else 25)
     elif len(sys.argv) >= 3 and sys.argv[1] == "counters":
         counters(sys.argv[2], int(sys.argv[3]) if len(sys.argv) > 3 else 5)
     elif len(sys.argv) >= 2 and sys.argv[1] == "shapes":
