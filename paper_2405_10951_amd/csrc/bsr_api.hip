@@ -477,7 +477,7 @@ struct TileChoice {
   bool timing = false;
   TuneRec rec{};
 };
-TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s, bool carries_wgrad = false) {
+TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s, const GemmDesc* wgrad = nullptr) {
   TileChoice ch;
   if (!gemm_nt_tile_is_free(g) || c->tune.aside) return ch;
   Tune& t = c->tune;
@@ -485,7 +485,7 @@ TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s, bool carrie
   if (t.cand >= 0) {
     const int cand = (t.kind == 1 && t.cand_train >= 0) ? t.cand_train : t.cand;
     ch.tile = gemm_nt_tile_id(cand);
-    ch.rec = TuneRec{t.kind, cand, site, g.M, g.N, g.K, gemm_nt_model_tile(g, carries_wgrad), nullptr, nullptr};
+    ch.rec = TuneRec{t.kind, cand, site, g.M, g.N, g.K, gemm_nt_model_tile(g, wgrad, c->b.splitk_floats, true), nullptr, nullptr};
     ch.timing = hipEventCreate(&ch.rec.start) == hipSuccess && hipEventCreate(&ch.rec.stop) == hipSuccess;
     if (ch.timing) (void)hipEventRecord(ch.rec.start, s);
   } else if (t.batch == t.cur_batch && site < t.pick[t.kind].size()) {
@@ -548,7 +548,7 @@ void dgrad_wgrad(bsr_ctx* c, const GemmDesc& dg, const void* x, const void* dy, 
   }
   wg.bsum = (float*)db;
   ProfScope ps(c, BSR_PROF_GEMM, 2.0 * dg.M * dg.N * dg.K + 2.0 * wg.M * wg.N * wg.K, s);
-  TileChoice ch = choose_tile(c, dg, s, true);
+  TileChoice ch = choose_tile(c, dg, s, &wg);
   gemm_mfma_pair(dg, wg, c->b.splitk, c->b.splitk_floats, s, ch.tile, &c->tn_chain);
   tile_done(c, ch, s);
 }

@@ -68,7 +68,7 @@ void ln_fold_weights(const float* w, const float* bias, const float* gamma, cons
 bool gemm_mfma_supported(const GemmDesc& g);
 // splitk_ws: fp32 scratch for the partial sums of split-K weight gradients (may be null: no split)
 // A split-K weight gradient leaves fp32 partials that one more pass has to add up.  With a chain, that
-// pass does not get a launch of its own: it rides as extra workgroups on the NEXT weight-gradient launch
+// pass does not get a launch of its own: it rides on the NEXT weight-gradient launch
 // (which works on the other half of the workspace), and gemm_tn_flush runs the last one.  The sums and
 // their order are the same either way.
 struct TnReduce {
@@ -88,13 +88,15 @@ struct TnChain {
 void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile = 0,
                TnChain* chain = nullptr);
 void gemm_tn_flush(TnChain* chain, hipStream_t s);
-// input gradient (NT) + weight gradient (TN) of one layer, in one launch when the NT tile shape allows it
+// input gradient (NT) + weight gradient (TN) of one layer, in one launch when the NT tile shape has that form
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile = 0, TnChain* chain = nullptr);
 // the block-tile shapes the NT kernel is instantiated for, and whether a GEMM is free to take any of them
 int gemm_nt_tile_count();
 constexpr int FEW_ROWS_ID = 9000000;           // + 1000 rows + columns: a tile of the kernel for products of few rows
-int gemm_nt_model_tile(const GemmDesc& g, bool carries_wgrad);   // what runs without a measured choice; from FEW_ROWS_ID on: whatever is asked for
+// what runs without a measured choice (wgrad: the weight gradient that goes out with g, or null; the workspace as in the
+// call); from FEW_ROWS_ID on: whatever is asked for
+int gemm_nt_model_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained);
 int gemm_nt_tile_id(int i);
 size_t gemm_nt_tile_lds_bytes(int id);          // dynamic LDS a workgroup of that shape holds
 bool gemm_nt_tile_is_free(const GemmDesc& g);

@@ -175,21 +175,6 @@ __device__ __forceinline__ void epilogue(const GemmDesc& g, f32x16 (&acc)[MI][NI
   }
 }
 
-// A weight-gradient launch folded into an input-gradient launch (both read the same dy and neither reads
-// what the other writes): workgroups past nt_tiles do the work of workgroup (i % gx, i / gx) of the
-// gx x gy weight-gradient grid.
-struct TnArgs {
-  GemmDesc g;
-  float *partial, *bpartial;
-  int kt_per, tn_rows;
-  TnReduce red;
-  int gx, gy;
-  int nt_tiles;
-};
-template <int BM, int BN, int WM, int WN>
-__device__ __forceinline__ void tn_body(GemmDesc g, float* partial, float* bpartial, int kt_per, int tn_rows,
-                                        const TnReduce& red, int bx, int by, int gx, int gy);
-
 // ------------------------------------------------------------------------------------------ NT
 // LDS tile: rows of 8 chunks (16 B each), chunk kc of row r stored at position kc ^ swz(r).
 // Software pipeline of one k-tile (4 MFMA steps of k = 16):
@@ -204,17 +189,11 @@ __device__ __forceinline__ void tn_body(GemmDesc g, float* partial, float* bpart
 // never stored.  KTAIL zero-fills chunks beyond K (K % 64 != 0).
 // (A folded 8-wave kernel whose tiles leave room for two workgroups per CU is held to the 128 registers that
 // two workgroups need: the row sums would otherwise push the 192 x 128 shape to 132 and halve its occupancy.)
-template <int BM, int BN, int WM, int WN, bool KTAIL, int PF = 1, bool FUSE = false, bool LNF = false>
+template <int BM, int BN, int WM, int WN, bool KTAIL, int PF = 1, bool LNF = false>
 __global__ __launch_bounds__(WM * WN * 64, (LNF && PF == 1 && WM * WN == 8 && (BM + BN) * 256 <= 80 * 1024) ? 4 : 1)
-void gemm_nt_kernel(GemmDesc g, TnArgs tn) {
-  static_assert(!LNF || (!FUSE && !KTAIL), "the folded LayerNorm reads whole rows of A in whole k-tiles");
+void gemm_nt_kernel(GemmDesc g) {
+  static_assert(!LNF || !KTAIL, "the folded LayerNorm reads whole rows of A in whole k-tiles");
   constexpr int NT = WM * WN * 64;
-  if (FUSE && (int)blockIdx.x >= tn.nt_tiles) {          // uniform over the workgroup
-    static_assert(!FUSE || NT == 512, "the weight-gradient body runs with 8 waves");
-    const int i = blockIdx.x - tn.nt_tiles;
-    tn_body<128, 128, 4, 2>(tn.g, tn.partial, tn.bpartial, tn.kt_per, tn.tn_rows, tn.red, i % tn.gx, i / tn.gx, tn.gx, tn.gy);
-    return;
-  }
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32;
   constexpr int ACH = (BM * 8 + NT - 1) / NT, BCH = (BN * 8 + NT - 1) / NT;   // 16-byte chunks per thread per tile
   constexpr bool AEVEN = (BM * 8) % NT == 0, BEVEN = (BN * 8) % NT == 0;      // else the last chunk is partial
@@ -225,7 +204,7 @@ void gemm_nt_kernel(GemmDesc g, TnArgs tn) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
   const int ntn = (g.N + BN - 1) / BN;
-  const int tile = xcd_remap(blockIdx.x, FUSE ? tn.nt_tiles : (int)gridDim.x);
+  const int tile = xcd_remap(blockIdx.x, (int)gridDim.x);
   int m0 = (tile / ntn) * BM;
   const int n0 = (tile % ntn) * BN;
   if (g.grp_off) {
@@ -438,15 +417,15 @@ void launch_nt(const GemmDesc& g, hipStream_t s) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     (void)hipFuncSetAttribute((const void*)gemm_nt_kernel<BM, BN, WM, WN, true, PF>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)hipFuncSetAttribute((const void*)gemm_nt_kernel<BM, BN, WM, WN, false, PF, false, true>,
+    (void)hipFuncSetAttribute((const void*)gemm_nt_kernel<BM, BN, WM, WN, false, PF, true>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_lnf);
     attr_set = true;
   }
   // grouped: every group may end in one partial row tile
   const int tiles = ((g.M + BM - 1) / BM + (g.grp_off ? g.groups : 0)) * ((g.N + BN - 1) / BN);
-  if (g.ln_colsum) gemm_nt_kernel<BM, BN, WM, WN, false, PF, false, true><<<tiles, WM * WN * 64, lds_lnf, s>>>(g, TnArgs());
-  else if (g.K % BK == 0) gemm_nt_kernel<BM, BN, WM, WN, false, PF><<<tiles, WM * WN * 64, lds, s>>>(g, TnArgs());
-  else gemm_nt_kernel<BM, BN, WM, WN, true, PF><<<tiles, WM * WN * 64, lds, s>>>(g, TnArgs());
+  if (g.ln_colsum) gemm_nt_kernel<BM, BN, WM, WN, false, PF, true><<<tiles, WM * WN * 64, lds_lnf, s>>>(g);
+  else if (g.K % BK == 0) gemm_nt_kernel<BM, BN, WM, WN, false, PF><<<tiles, WM * WN * 64, lds, s>>>(g);
+  else gemm_nt_kernel<BM, BN, WM, WN, true, PF><<<tiles, WM * WN * 64, lds, s>>>(g);
 }
 
 // ------------------------------------------------------------------------------------------ NT, operands straight into LDS
@@ -569,10 +548,9 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
   }
 }
 
-// (a shape whose stages take at most half of the 160 KB is held to the registers that let two workgroups share a CU)
+// The work of one tile (a kernel of its own below, and the input-gradient half of a layer's backward launch).
 template <int BM, int BN, int WM, int WN, int NST>
-__global__ __launch_bounds__(WM * WN * 64, (NST * (BM + BN) * 128 <= 80 * 1024 && WM * WN <= 4) ? 2 : 1)
-void gemm_ntd_kernel(GemmDesc g) {
+__device__ __forceinline__ void ntd_body(const GemmDesc& g, int tile) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, NMF = MI * NI, NFR = MI + NI;
   constexpr int RPI = NT / 8;                       // tile rows one load instruction of the workgroup fills
@@ -581,13 +559,12 @@ void gemm_ntd_kernel(GemmDesc g) {
   constexpr int STAGE = (BM + BN) * 128;            // bytes of a stage: rows of 8 chunks of 16 bytes, A rows first
   static_assert(BM % RPI == 0 && BN % RPI == 0 && RPI % 16 == 0, "a load instruction covers whole groups of 16 rows");
   static_assert(NST >= 2 && NST <= 4 && (NST - 1) * LPT <= 60, "vmcnt has 6 bits");
-  static_assert(NMF >= NFR && NMF <= 16 && MI >= 1 && NI >= 1, "");
+  static_assert(NMF >= 2 && NMF <= 16, "");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int ntn = (g.N + BN - 1) / BN;
-  const int tile = xcd_remap(blockIdx.x, (int)gridDim.x);
   const int m0 = (tile / ntn) * BM, n0 = (tile % ntn) * BN;
   const bf16* __restrict__ A = (const bf16*)g.A;
   const bf16* __restrict__ Bt = (const bf16*)g.B;
@@ -641,7 +618,11 @@ void gemm_ntd_kernel(GemmDesc g) {
     sfor<NMF>([&](auto J) __attribute__((always_inline)) {
       constexpr int j = decltype(J)::value;
       mf1(IC<set>{}, J);
-      if constexpr (j < NFR) rd1(IC<set ^ 1>{}, J, st, ks);
+      constexpr int RPM = (NFR + NMF - 1) / NMF;         // reads behind an MFMA
+      sfor<RPM>([&](auto R) __attribute__((always_inline)) {
+        constexpr int r = j * RPM + decltype(R)::value;
+        if constexpr (r < NFR) rd1(IC<set ^ 1>{}, IC<r>{}, st, ks);
+      });
       BSR_SCHED_FENCE();
     });
   };
@@ -707,6 +688,13 @@ void gemm_ntd_kernel(GemmDesc g) {
   }
   // every wavefront is past the last barrier, i.e. has read its last fragments: the stages are free
   epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)));
+}
+
+// (a shape whose stages take at most half of the 160 KB is held to the registers that let two workgroups share a CU)
+template <int BM, int BN, int WM, int WN, int NST>
+__global__ __launch_bounds__(WM * WN * 64, (NST * (BM + BN) * 128 <= 80 * 1024 && WM * WN <= 4) ? 2 : 1)
+void gemm_ntd_kernel(GemmDesc g) {
+  ntd_body<BM, BN, WM, WN, NST>(g, xcd_remap(blockIdx.x, (int)gridDim.x));
 }
 
 template <int BM, int BN, int WM, int WN, int NST>
@@ -924,16 +912,24 @@ void launch_few(int pick, const GemmDesc& g, hipStream_t s) {
 // Weight gradient dW[Mo,No] = sum_t X[t,Mo]^T dY[t,No] (Eq. 4): both operands have the contraction
 // index t (tokens) as their row index, so an MFMA fragment (8 consecutive t for one column) is
 // strided in memory.  The tiles are staged in LDS as they lie in memory - 64 token rows of 16-byte
-// chunks, plain 16-byte writes - and the fragments are read with the LDS transpose read
+// chunks - and the fragments are read with the LDS transpose read
 // (ds_read_b64_tr_b16): within every 16 lanes, lane 4e+q passes the address of 4 columns of token
 // row e, and lane j receives column j of the four rows, i.e. 4 consecutive tokens of one column.
 // A fragment is two such reads (token rows r..r+3 and r+4..r+7).  One half-wave reads 4 rows x 64
 // bytes; the 64-byte segments of a row are permuted by segment ^ (row & 3) so that those four land
 // in four different bank groups (a row of 128 columns spans all 64 banks exactly once).
-// Split-K: workgroup z handles k-tiles [z*kt_per, (z+1)*kt_per) and writes its own fp32 partial;
-// a second kernel adds the partials in a fixed order (bit-reproducible, no atomics).
+// Loads and arithmetic are two kinds of wavefront.  Four loaders fill a ring of NST stages with global_load_lds and wait
+// for them by count; eight others only read fragments and multiply; one barrier per k-tile hands a landed stage over and a
+// read one back.  A wavefront that did both would wait for every load in flight in front of each transpose read: the
+// compiler cannot tell that such a read does not touch what a load is writing (measured so, 768 x 3072 over 25216 tokens:
+// 167 us; register-staged 201; loaders of their own 141).  Two loaders are too few (154), a higher priority for them is worth
+// up to 2 %.  What bounds it then is the path from L2 (64 bytes a clock into LDS) and, at many tokens, memory: the loads
+// alone take 119 of those 141 us.
+// The MFMA operands are swapped as in the direct-to-LDS NT kernel, so the two share their epilogue.
+// Split-K: workgroup z handles k-tiles [z*kt_per, (z+1)*kt_per) and writes its own fp32 partial; they are added in a fixed
+// order (bit-reproducible, no atomics) by wavefronts of the next such launch.
 // Bias gradient: the workgroups of the first row of tiles also multiply every dY fragment by an
-// all-ones A fragment, which leaves the column sums of dY (db = 1^T dY) in one more accumulator per
+// all-ones fragment, which leaves the column sums of dY (db = 1^T dY) in one more accumulator per
 // 32 columns; they travel through the same partial / reduce path as dW.
 #define BSR_LDS_PTR(T, p) ((T __attribute__((address_space(3)))*)(p))
 
@@ -959,97 +955,125 @@ __device__ inline void splitk_reduce_item(const TnReduce& r, int64_t item) {
 __device__ inline int64_t splitk_reduce_items(const TnReduce& r) { return r.n / 4 + (r.nb + 3) / 4; }
 inline int64_t splitk_reduce_items_host(const TnReduce& r) { return r.n / 4 + (r.nb + 3) / 4; }
 
-// Grid rows [0, tn_rows) multiply; rows past them (if any) add up the partials of the previous weight
-// gradient (red), a bandwidth-bound job that overlaps with this launch's matrix work.
-// The work of workgroup (bx, by) of a gx x gy grid (the kernel below passes its own block index; the fused
-// input-gradient + weight-gradient launch passes the coordinates of its extra workgroups).
-template <int BM, int BN, int WM, int WN>
-__device__ __forceinline__ void tn_body(GemmDesc g, float* partial, float* bpartial, int kt_per, int tn_rows,
-                                        const TnReduce& red, int bx, int by, int gx, int gy) {
-  constexpr int NT = WM * WN * 64;
-  if (by >= tn_rows) {
-    const int64_t nthreads = (int64_t)(gy - tn_rows) * gx * NT;
-    const int64_t first = ((int64_t)(by - tn_rows) * gx + bx) * NT + threadIdx.x;
-    const int64_t items = splitk_reduce_items(red);
-    for (int64_t it = first; it < items; it += nthreads) splitk_reduce_item(red, it);
-    return;
-  }
-  constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32;
-  constexpr int ACPR = BM / 8, BCPR = BN / 8;                  // 16-byte chunks per token row
-  constexpr int ACH = BK * ACPR / NT, BCH = BK * BCPR / NT;    // chunks per thread per k-tile
+constexpr int TN_LOADERS = 4, TN_THREADS = (8 + TN_LOADERS) * 64;
+
+// What a weight gradient needs in a launch: its product and split, and the sums of the previous one.
+struct TnArgs {
+  GemmDesc g;
+  float *partial, *bpartial;
+  int kt_per;                    // k-tiles of a split
+  int gx;                        // tiles
+  int blocks;                    // tiles x splits (or groups)
+  TnReduce red;                  // partials of an earlier launch to add up; splits == 0: none
+};
+
+// Workgroup lin of gx tiles x splits (grouped: x groups), tile fastest.
+template <int BM, int BN, int WM, int WN, int NST>
+__device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
+  constexpr int NP = TN_LOADERS, NC = WM * WN;
+  constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, NMF = MI * NI, NFR = MI + NI;
+  constexpr int ABYTES = 64 * BM * 2, STAGE = (BM + BN) * 128;       // a stage: 64 token rows of A columns, then of B columns
   static_assert(BM % 128 == 0 && BN % 128 == 0, "the segment permutation needs a multiple of 4 segments per row");
-  static_assert(ACH >= 1 && BCH >= 1 && (BK * ACPR) % NT == 0 && (BK * BCPR) % NT == 0 && MI >= 1 && NI >= 1, "");
+  static_assert(NC == 8 && NMF >= 2 && NMF <= 16, "");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* As = smem;                            // [2][64 token rows][BM columns] bf16
-  unsigned char* Bs = smem + 2 * BK * BM * 2;          // [2][64 token rows][BN columns] bf16
-  constexpr int ABUF = BK * BM * 2, BBUF = BK * BN * 2;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int ntn = (g.N + BN - 1) / BN;
-  const int ntiles = gx;
-  const int tile = xcd_remap(bx, ntiles);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  GemmDesc g = a.g;
+  const int ntn = (g.N + BN - 1) / BN, ntm = (g.M + BM - 1) / BM;
+  const int tile = lin % a.gx, by = lin / a.gx;
   // an XCD's contiguous range of tiles runs along the side with fewer tiles first, so that it spans that side
   // and its L2 fetches the longer operand's token rows once instead of once per XCD
-  const int ntm = (g.M + BM - 1) / BM;
   const bool mfast = ntm < ntn;
   const int m0 = (mfast ? tile % ntm : tile / ntn) * BM, n0 = (mfast ? tile / ntm : tile % ntn) * BN;
+  float *partial = a.partial, *bpartial = a.bpartial;
+  int kt0 = by * a.kt_per, nk = min(a.kt_per, (g.K + BK - 1) / BK - kt0);
   if (g.grp_off) {
-    // grouped form: by is the group; the contraction runs over its token rows only
-    const int e = by, r0 = g.grp_off[e], r1 = g.grp_off[e + 1];
+    // grouped form: by is the group; the contraction runs over its token rows only (perhaps none)
+    const int r0 = g.grp_off[by], r1 = g.grp_off[by + 1];
     g.A = (const bf16*)g.A + (int64_t)r0 * g.a_cs;
     g.B = (const bf16*)g.B + (int64_t)r0 * g.b_rs;
     g.K = r1 - r0;
-    g.C = (float*)g.C + (int64_t)e * g.c_gs;
-    if (g.bsum) g.bsum += (int64_t)e * g.bsum_gs;
-    partial = nullptr;
-    bpartial = nullptr;
-    kt_per = (g.K + BK - 1) / BK;
+    g.C = (float*)g.C + (int64_t)by * g.c_gs;
+    if (g.bsum) g.bsum += (int64_t)by * g.bsum_gs;
+    kt0 = 0;
+    nk = (g.K + BK - 1) / BK;
   }
-  const int nk_all = (g.K + BK - 1) / BK;
-  const int kt0 = g.grp_off ? 0 : by * kt_per, kt1 = min(kt0 + kt_per, nk_all);
-  const bf16* __restrict__ X = (const bf16*)g.A;     // [K tokens, Mo], row stride a_cs
-  const bf16* __restrict__ Y = (const bf16*)g.B;     // [K tokens, No], row stride b_rs
-
-  // chunk c of a tile: token row c / chunks-per-row, chunk position c % chunks-per-row
-  int ar[ACH], br[BCH], sa[ACH], sb[BCH];
-  const bf16* pa[ACH];
-  const bf16* pb[BCH];
+  if (wave >= NC) {                                    // ---- loaders
+    __builtin_amdgcn_s_setprio(3);
+    constexpr int AR = 1024 / (BM * 2), BR = 1024 / (BN * 2);        // token rows one load instruction of a wavefront fills
+    constexpr int AI = 64 / AR / NP, BI = 64 / BR / NP, LPP = AI + BI;   // load instructions of a loader per k-tile
+    static_assert((AR == 4 || AR == 2) && (BR == 4 || BR == 2) && (NST - 1) * LPP <= 63, "vmcnt has 6 bits");
+    const int pw = wave - NC;
+    const bf16* X = (const bf16*)g.A + (int64_t)kt0 * BK * g.a_cs;     // [K tokens, Mo], row stride a_cs
+    const bf16* Y = (const bf16*)g.B + (int64_t)kt0 * BK * g.b_rs;     // [K tokens, No], row stride b_rs
+    const int rows = g.K - kt0 * BK;                                   // token rows from here on
+    const int ra = lane / (BM / 8), pa = lane % (BM / 8), rb = lane / (BN / 8), pb = lane % (BN / 8);
+    // LDS slot p of token row r holds the chunk whose segment is permuted to it (columns past the end repeat valid ones: never stored)
+    auto chunk = [](int r, int p) { return ((((p >> 2) ^ (r & 3)) << 2) | (p & 3)) * 8; };
+    auto acol = [&](int r) { return min(m0 + chunk(r, pa), g.M - 8); };
+    auto bcol = [&](int r) { return min(n0 + chunk(r, pb), g.N - 8); };
+    // instruction i of loader pw holds rows (i NP + pw) AR + ra: r & 3 takes one value for four rows an instruction; with
+    // two it depends on the parity of pw (NP is even)
+    const int64_t aoff = (int64_t)ra * g.a_cs + acol(AR == 2 ? 2 * (pw & 1) + ra : ra);
+    const int64_t boff = (int64_t)rb * g.b_rs + bcol(BR == 2 ? 2 * (pw & 1) + rb : rb);
+    auto issue = [&](int kt, int st) __attribute__((always_inline)) {
+      unsigned char* d = smem + st * STAGE + pw * 1024;
+      if ((kt + 1) * BK <= rows) {
+        const bf16* xb = X + ((int64_t)kt * BK + pw * AR) * g.a_cs;
+        const bf16* yb = Y + ((int64_t)kt * BK + pw * BR) * g.b_rs;
 #pragma unroll
-  for (int i = 0; i < ACH; ++i) {
-    const int c = tid + NT * i, r = c / ACPR, q = c % ACPR;
-    ar[i] = r;
-    pa[i] = X + min(m0 + q * 8, g.M - 8);              // columns past Mo repeat valid ones: never stored
-    sa[i] = r * (BM * 2) + ((((q >> 2) ^ (r & 3)) << 2) + (q & 3)) * 16;
-  }
+        for (int i = 0; i < AI; ++i, xb += (int64_t)AR * NP * g.a_cs)
+          __builtin_amdgcn_global_load_lds(BSR_GLOBAL_PTR(xb + aoff), BSR_LDS_VOID(d + i * NP * 1024), 16, 0, 0);
 #pragma unroll
-  for (int i = 0; i < BCH; ++i) {
-    const int c = tid + NT * i, r = c / BCPR, q = c % BCPR;
-    br[i] = r;
-    pb[i] = Y + min(n0 + q * 8, g.N - 8);
-    sb[i] = r * (BN * 2) + ((((q >> 2) ^ (r & 3)) << 2) + (q & 3)) * 16;
-  }
-  u32x4 ra[ACH], rb[BCH];
-  auto fetch = [&](int kt) {                           // token rows past K are zero
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      const int t = kt * BK + ar[i];
-      ra[i] = *(const u32x4*)(pa[i] + (int64_t)min(t, g.K - 1) * g.a_cs);
-      if (t >= g.K) ra[i] = u32x4{0u, 0u, 0u, 0u};
+        for (int i = 0; i < BI; ++i, yb += (int64_t)BR * NP * g.b_rs)
+          __builtin_amdgcn_global_load_lds(BSR_GLOBAL_PTR(yb + boff), BSR_LDS_VOID(d + ABYTES + i * NP * 1024), 16, 0, 0);
+      } else {                                         // the last tokens: rows past them repeat the last one (cleared below)
+#pragma unroll 1
+        for (int i = 0; i < AI; ++i) {
+          const int r = (i * NP + pw) * AR + ra;
+          __builtin_amdgcn_global_load_lds(BSR_GLOBAL_PTR(X + (int64_t)min(kt * BK + r, rows - 1) * g.a_cs + acol(r)),
+                                           BSR_LDS_VOID(d + i * NP * 1024), 16, 0, 0);
+        }
+#pragma unroll 1
+        for (int i = 0; i < BI; ++i) {
+          const int r = (i * NP + pw) * BR + rb;
+          __builtin_amdgcn_global_load_lds(BSR_GLOBAL_PTR(Y + (int64_t)min(kt * BK + r, rows - 1) * g.b_rs + bcol(r)),
+                                           BSR_LDS_VOID(d + ABYTES + i * NP * 1024), 16, 0, 0);
+        }
+      }
+    };
+    // k-tile kt is in LDS, up to `later` k-tiles behind it may still be on their way; token rows past the last are zero
+    auto landed = [&](int kt, int st, int later) __attribute__((always_inline)) {
+      if (NST >= 4 && later >= 3) wait_vmcnt<(NST >= 4 ? 3 : 0) * LPP>();
+      else if (NST >= 3 && later >= 2) wait_vmcnt<(NST >= 3 ? 2 : 0) * LPP>();
+      else if (later >= 1) wait_vmcnt<LPP>();
+      else wait_vmcnt<0>();
+      const int valid = rows - kt * BK;
+      if (kt == nk - 1 && valid < BK) {                // each loader clears what it loaded
+        unsigned char* d = smem + st * STAGE + pw * 1024 + lane * 16;
+        for (int i = 0; i < AI; ++i)
+          if ((i * NP + pw) * AR + ra >= valid) *(u32x4*)(d + i * NP * 1024) = u32x4{0u, 0u, 0u, 0u};
+        for (int i = 0; i < BI; ++i)
+          if ((i * NP + pw) * BR + rb >= valid) *(u32x4*)(d + ABYTES + i * NP * 1024) = u32x4{0u, 0u, 0u, 0u};
+        wait_lgkmcnt0();
+      }
+    };
+    if (nk <= 0) return;
+    for (int j = 0; j < NST && j < nk; ++j) issue(j, j);
+    landed(0, 0, min(nk, NST) - 1);
+    __builtin_amdgcn_s_barrier();
+    for (int kt = 0, st = 0; kt < nk; ++kt) {
+      const int stn = st + 1 == NST ? 0 : st + 1;
+      if (kt + 1 < nk) landed(kt + 1, stn, min(nk - 2 - kt, NST - 2));
+      __builtin_amdgcn_s_barrier();                    // k-tile kt has been read, k-tile kt + 1 may be
+      if (kt + NST < nk) issue(kt + NST, st);
+      st = stn;
     }
-#pragma unroll
-    for (int i = 0; i < BCH; ++i) {
-      const int t = kt * BK + br[i];
-      rb[i] = *(const u32x4*)(pb[i] + (int64_t)min(t, g.K - 1) * g.b_rs);
-      if (t >= g.K) rb[i] = u32x4{0u, 0u, 0u, 0u};
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) *(u32x4*)(As + buf * ABUF + sa[i]) = ra[i];
-#pragma unroll
-    for (int i = 0; i < BCH; ++i) *(u32x4*)(Bs + buf * BBUF + sb[i]) = rb[i];
-  };
+    return;
+  }
 
+  // ---- wavefronts that multiply
+  const int wm = wave / WN, wn = wave % WN;
   f32x16 acc[MI][NI];
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi)
@@ -1059,22 +1083,27 @@ __device__ __forceinline__ void tn_body(GemmDesc g, float* partial, float* bpart
       for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 
   // transpose-read coordinates of this lane: j = lane % 16 inside its block of 16 lanes, the block
-  // covers columns cb*16 .. +16 of the 32-column fragment for k-group kg (tokens kg*8 .. +8 of a k-step)
-  const int lr = lane & 31, lh = lane >> 5;
-  const int j = lane & 15, cb = (lane >> 4) & 1, kg = lh;
-  const int rj = j >> 2;                               // token row inside a group of four (= row & 3)
-  int oa[MI], ob[NI];                                  // byte offset inside a token row, segment-permuted
+  // covers columns cb*16 .. +16 of the 32-column fragment for k-group lh (tokens lh*8 .. +8 of a k-step);
+  // fragments in the order A0, B0 .. B(NI-1), A1 .. A(MI-1) as in the NT kernel
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  union Frag { bf16x8 v; s16x4 h[2]; };
+  const int lh = lane >> 5, cb = (lane >> 4) & 1, rj = (lane & 15) >> 2;    // rj: token row inside a group of four (= row & 3)
+  int offr[NFR];
+  Frag fr[2][NFR];
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    const int off = (wm * TM + mi * 32 + cb * 16 + (j & 3) * 4) * 2, q = off >> 4;
-    oa[mi] = ((((q >> 2) ^ rj) << 2) + (q & 3)) * 16 + (off & 15);
+  for (int j = 0; j < NFR; ++j) {
+    const bool isA = j == 0 || j > NI;
+    const int idx = j == 0 ? 0 : (j <= NI ? j - 1 : j - NI);
+    const int o = ((isA ? wm * TM : wn * TN) + idx * 32 + cb * 16 + (lane & 3) * 4) * 2, q = o >> 4;
+    offr[j] = (isA ? 0 : ABYTES) + (lh * 8 + rj) * (isA ? BM : BN) * 2 + ((((q >> 2) ^ rj) << 2) + (q & 3)) * 16 + (o & 15);
   }
-#pragma unroll
-  for (int ni = 0; ni < NI; ++ni) {
-    const int off = (wn * TN + ni * 32 + cb * 16 + (j & 3) * 4) * 2, q = off >> 4;
-    ob[ni] = ((((q >> 2) ^ rj) << 2) + (q & 3)) * 16 + (off & 15);
-  }
-
+  auto rd1 = [&](auto SET, auto J, int st, int ks) __attribute__((always_inline)) {
+    constexpr int set = decltype(SET)::value, j = decltype(J)::value;
+    constexpr int rowb = ((j == 0 || j > NI) ? BM : BN) * 2;
+    const unsigned char* p = smem + st * STAGE + offr[j] + ks * 16 * rowb;       // and row + 4: both have (row & 3) == rj
+    fr[set][j].h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(BSR_LDS_PTR(s16x4, p));
+    fr[set][j].h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(BSR_LDS_PTR(s16x4, p + 4 * rowb));
+  };
   const bool do_bsum = g.bsum && m0 == 0 && wm == 0;     // uniform over the wavefront
   f32x16 accb[NI];
   bf16x8 ones;
@@ -1084,84 +1113,121 @@ __device__ __forceinline__ void tn_body(GemmDesc g, float* partial, float* bpart
   for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
     for (int r = 0; r < 16; ++r) accb[ni][r] = 0.f;
-
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  union Frag { bf16x8 v; s16x4 h[2]; };
-  Frag fa[2][MI], fb[2][NI];
-  auto load_frags = [&](int set, const unsigned char* Ab, const unsigned char* Bb, int ks) {
-    const int row = ks * 16 + kg * 8 + rj;             // and row + 4: both have (row & 3) == rj
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-      const unsigned char* a = Ab + row * (BM * 2) + oa[mi];
-      fa[set][mi].h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(BSR_LDS_PTR(s16x4, a));
-      fa[set][mi].h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(BSR_LDS_PTR(s16x4, a + 4 * BM * 2));
-    }
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const unsigned char* bp = Bb + row * (BN * 2) + ob[ni];
-      fb[set][ni].h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(BSR_LDS_PTR(s16x4, bp));
-      fb[set][ni].h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(BSR_LDS_PTR(s16x4, bp + 4 * BN * 2));
-    }
+  auto mf1 = [&](auto SET, auto J) __attribute__((always_inline)) {
+    constexpr int set = decltype(SET)::value, j = decltype(J)::value, mi = j / NI, ni = j % NI;
+    constexpr int ja = mi == 0 ? 0 : NI + mi, jb = 1 + ni;
+    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[set][jb].v, fr[set][ja].v, acc[mi][ni], 0, 0, 0);
+    if (mi == MI - 1 && do_bsum) accb[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[set][jb].v, ones, accb[ni], 0, 0, 0);
   };
-  auto mma = [&](int set) {
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][mi].v, fb[set][ni].v, acc[mi][ni], 0, 0, 0);
-    if (do_bsum) {
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-        accb[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fb[set][ni].v, accb[ni], 0, 0, 0);
-    }
+  auto kstep = [&](auto SET, int st, int ks) __attribute__((always_inline)) {
+    constexpr int set = decltype(SET)::value, RPM = (NFR + NMF - 1) / NMF;
+    sfor<NMF>([&](auto J) __attribute__((always_inline)) {
+      constexpr int j = decltype(J)::value;
+      mf1(IC<set>{}, J);
+      sfor<RPM>([&](auto R) __attribute__((always_inline)) {
+        constexpr int r = j * RPM + decltype(R)::value;
+        if constexpr (r < NFR) rd1(IC<set ^ 1>{}, IC<r>{}, st, ks);
+      });
+      BSR_SCHED_FENCE();
+    });
   };
-
-  const int nk = kt1 - kt0;
+  // the last k-step of a k-tile (fragments in set 1) with the barrier; behind it the first fragments of the next k-tile
+  // are read (after the last one they are idle)
+  auto klast = [&](int stn) __attribute__((always_inline)) {
+    constexpr int PRE = NMF >= 16 ? 4 : (NMF >= 8 ? 2 : 1), POST = NMF - PRE, RPP = (NFR + POST - 1) / POST;
+    sfor<PRE>([&](auto J) __attribute__((always_inline)) { mf1(IC<1>{}, J); BSR_SCHED_FENCE(); });
+    wait_lgkmcnt0();                                   // this wavefront's reads of the stage are done
+    __builtin_amdgcn_s_barrier();
+    BSR_SCHED_FENCE();
+    sfor<POST>([&](auto P) __attribute__((always_inline)) {
+      constexpr int p = decltype(P)::value;
+      mf1(IC<1>{}, IC<PRE + p>{});
+      sfor<RPP>([&](auto R) __attribute__((always_inline)) {
+        constexpr int r = p * RPP + decltype(R)::value;
+        if constexpr (r < NFR) rd1(IC<0>{}, IC<r>{}, stn, 0);
+      });
+      BSR_SCHED_FENCE();
+    });
+  };
   if (nk > 0) {
-    fetch(kt0);
-    stash(0);
-    if (nk > 1) fetch(kt0 + 1);
-    __syncthreads();
-    load_frags(0, As, Bs, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-      const int buf = kt & 1;
-      const unsigned char* Ab = As + buf * ABUF;
-      const unsigned char* Bb = Bs + buf * BBUF;
-      load_frags(1, Ab, Bb, 1);
-      mma(0);
-      load_frags(0, Ab, Bb, 2);
-      mma(1);
-      load_frags(1, Ab, Bb, 3);
-      if (kt + 1 < nk) stash(buf ^ 1);
-      if (kt + 2 < nk) fetch(kt0 + kt + 2);
-      mma(0);
-      __syncthreads();
-      if (kt + 1 < nk) load_frags(0, As + (buf ^ 1) * ABUF, Bs + (buf ^ 1) * BBUF, 0);
-      mma(1);
+    __builtin_amdgcn_s_barrier();
+    sfor<NFR>([&](auto J) __attribute__((always_inline)) { rd1(IC<0>{}, J, 0, 0); });
+    for (int kt = 0, st = 0; kt < nk; ++kt) {
+      const int stn = st + 1 == NST ? 0 : st + 1;
+      kstep(IC<0>{}, st, 1);
+      kstep(IC<1>{}, st, 2);
+      kstep(IC<0>{}, st, 3);
+      klast(stn);
+      st = stn;
     }
-    __syncthreads();
   }
-  GemmDesc o = g;
-  if (partial) {                                   // split-K: plain fp32 partial, no epilogue terms
-    o.C = partial + (int64_t)by * g.M * g.N;
-    o.ldc = g.N; o.bias = nullptr; o.act = ACT_NONE; o.res = nullptr; o.remap_np = 0; o.out_f32 = true;
+  if (partial) {                                   // split-K: this split's fp32 partial
+    g.C = partial + (int64_t)by * g.M * g.N;
+    g.ldc = g.N;
   }
-  float* patch = (float*)smem + wave * (32 * (TN + 4));
-  epilogue<MI, NI>(o, acc, m0 + wm * TM, n0 + wn * TN, lane, patch);
-  if (do_bsum && lh == 0) {                        // every row of accb holds the column sums
+  epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)));
+  if (do_bsum && (lane & 31) == 0) {               // every column of accb holds the column sums
     float* dst = bpartial ? bpartial + (int64_t)by * g.N : g.bsum;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const int col = n0 + wn * TN + ni * 32 + lr;
-      if (col < g.N) dst[col] = accb[ni][0];
-    }
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int col = n0 + wn * TN + ni * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+        if (col < g.N) dst[col] = accb[ni][r];
+      }
   }
 }
 
-template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_tn_kernel(GemmDesc g, float* partial, float* bpartial, int kt_per,
-                                                              int tn_rows, TnReduce red) {
-  tn_body<BM, BN, WM, WN>(g, partial, bpartial, kt_per, tn_rows, red, blockIdx.x, blockIdx.y, gridDim.x, gridDim.y);
+// Tiles of a weight gradient: 128 x 128, four stages, or 256 x 128, three.
+template <int T> struct TnTile;
+template <> struct TnTile<0> { static constexpr int BM = 128, BN = 128, WM = 2, WN = 4, NST = 4; };
+template <> struct TnTile<1> { static constexpr int BM = 256, BN = 128, WM = 4, WN = 2, NST = 3; };
+template <class T> constexpr size_t tile_lds() { return (size_t)T::NST * (T::BM + T::BN) * 128; }
+template <class T> constexpr size_t tile_patch_lds() { return (size_t)T::WM * T::WN * 32 * ((T::BN / T::WN) * 4 + 16); }
+
+// A weight gradient on its own.  Workgroups past a.blocks add up the partials of an earlier one.
+template <int T>
+__global__ __launch_bounds__(TN_THREADS, 1) void gemm_tn_kernel(TnArgs a) {
+  using S = TnTile<T>;
+  if ((int)blockIdx.x >= a.blocks) {
+    const int64_t step = (int64_t)(gridDim.x - a.blocks) * TN_THREADS, items = splitk_reduce_items(a.red);
+    for (int64_t it = (int64_t)(blockIdx.x - a.blocks) * TN_THREADS + threadIdx.x; it < items; it += step) splitk_reduce_item(a.red, it);
+    return;
+  }
+  tn_body<S::BM, S::BN, S::WM, S::WN, S::NST>(a, xcd_remap(blockIdx.x, a.blocks));
+}
+
+// Tiles of the input gradient in a launch that computes a layer's weight gradient as well.
+template <int I> struct PairTile;
+template <> struct PairTile<0> { static constexpr int BM = 128, BN = 64, WM = 2, WN = 2, NST = 4; };
+template <> struct PairTile<1> { static constexpr int BM = 128, BN = 128, WM = 2, WN = 4, NST = 4; };
+template <> struct PairTile<2> { static constexpr int BM = 192, BN = 128, WM = 2, WN = 4, NST = 3; };
+template <> struct PairTile<3> { static constexpr int BM = 256, BN = 128, WM = 4, WN = 2, NST = 3; };
+
+// Both gradients of a layer (Eq. 2 and Eq. 4): they read the same dy and neither reads what the other writes.  One
+// workgroup per CU; the weight gradient's workgroups, which are the longest, come first, the input gradient's tiles fill
+// the CUs they leave.  Its workgroups have wavefronts to spare: those add up the partials of the previous weight gradient.
+// (Workgroups of their own for these sums hold a CU each: 768 x 768 over 2144 tokens 13.0 -> 16.1 us where they no longer
+// fit beside the tiles.)  Against the register-staged pair that this replaces, both gradients, launches in a row: 2144
+// tokens 768 x 3072 39.2 -> 27.7 us, 3072 x 768 with GELU' 45.5 -> 38.4, 768 x 768 17.6 -> 13.0, 768 x 2304 33.2 -> 24.7,
+// 384 x 1536 17.9 -> 13.2; 25216 tokens 768 x 3072 310 -> 244, 768 x 2304 238 -> 183; 1.28x over 112 shapes of 197 .. 25216 tokens.
+template <int I, int T>
+__global__ __launch_bounds__(TN_THREADS, 1) void gemm_pair_kernel(GemmDesc g, TnArgs a, int nt_tiles) {
+  using N = PairTile<I>;
+  using S = TnTile<T>;
+  constexpr int NTHR = N::WM * N::WN * 64;
+  if ((int)blockIdx.x < a.blocks) {
+    tn_body<S::BM, S::BN, S::WM, S::WN, S::NST>(a, xcd_remap(blockIdx.x, a.blocks));
+    return;
+  }
+  const int tile = blockIdx.x - a.blocks;
+  if (threadIdx.x >= NTHR) {
+    const int64_t items = a.red.splits > 0 ? splitk_reduce_items(a.red) : 0;
+    for (int64_t it = (int64_t)tile * (TN_THREADS - NTHR) + threadIdx.x - NTHR; it < items; it += (int64_t)nt_tiles * (TN_THREADS - NTHR))
+      splitk_reduce_item(a.red, it);
+    return;
+  }
+  ntd_body<N::BM, N::BN, N::WM, N::WN, N::NST>(g, xcd_remap(tile, nt_tiles));
 }
 
 // the same reduction as a launch of its own
@@ -1180,105 +1246,149 @@ bool is_tn(const GemmDesc& g) {
          g.remap_np == 0 && (((uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C) & 15) == 0;
 }
 
-constexpr int TN_BM = 128, TN_BN = 128, TN_WM = 4, TN_WN = 2, TN_THREADS = TN_WM * TN_WN * 64;
-constexpr size_t TN_LDS_TILES = (size_t)2 * (TN_BM + TN_BN) * BK * sizeof(bf16);
-constexpr size_t TN_LDS_PATCH = (size_t)TN_WM * TN_WN * 32 * (TN_BN / TN_WN + 4) * sizeof(float);   // epilogue patches
-constexpr size_t TN_LDS = TN_LDS_TILES > TN_LDS_PATCH ? TN_LDS_TILES : TN_LDS_PATCH;
+// How a weight gradient is split over its tokens and tiled, and which tile its input gradient takes where nothing was
+// measured: the combination that a model of the launch finishes first.  With one workgroup per CU a workgroup takes
+// c0 + c1 k-tiles (an input gradient with GELU' gelu more; a split that leaves a partial sum another `partial` a million floats);
+// the launch takes what list scheduling over 256 CUs takes (weight gradient first), a start, and the bytes of the partial
+// sums.  Constants fitted to every combination on 112 layers (384 and 768 wide, 197 .. 25216 tokens, 1 .. 16 splits, launches in a
+// row); its choices take 1.0 % longer than the fastest.
+struct PairCost { int bm, bn; float c0, c1, gelu; };
+const PairCost kPairNt[] = {{128, 64, 2.00f, 0.365f, 2.88f}, {128, 128, 2.66f, 0.606f, 3.76f},
+                            {192, 128, 4.43f, 0.621f, 4.70f}, {256, 128, 3.96f, 0.746f, 6.78f}};
+struct TnCost { int bm, bn; float c0, c1, partial; };
+const TnCost kTn[] = {{128, 128, 2.35f, 0.503f, 0.109f}, {256, 128, 3.57f, 0.864f, 0.359f}};
+constexpr float PAIR_START_US = 2.08f, PAIR_PARTIAL_US = 2.02f;     // the latter per million floats of partial sums
+constexpr int PAIR_CUS = 256;
 
-// Everything a weight-gradient launch needs beyond the kernel itself: the split, the workspace half, the
-// reduction of the previous launch that rides along (taken from the chain) and the one this launch leaves.
-struct TnPlan {
-  GemmDesc g;
-  float *partial = nullptr, *bpartial = nullptr;
-  int kt_per = 0, tn_rows = 1, grid_x = 0, grid_y = 1;
-  TnReduce prev;                 // added up by the extra grid rows of this launch
-  TnReduce mine;                 // what this launch leaves to add up (mine.splits == 0: nothing)
+// list scheduling: T workgroups of lt first, then N of ln
+float pair_span(int64_t T, float lt, int64_t N, float ln) {
+  const int64_t q = T / PAIR_CUS, r = T % PAIR_CUS;         // r CUs have q + 1 of the long ones, the others q
+  const float base[2] = {q * lt, (q + 1) * lt}, least = (T * lt + N * ln) / PAIR_CUS;
+  const int64_t cus[2] = {PAIR_CUS - r, r};
+  float best = 0.f;
+  bool found = N == 0;
+  for (int f = 0; f < 2 && N > 0; ++f) {
+    if (!cus[f]) continue;
+    for (int64_t j = std::max<int64_t>(0, (int64_t)((least - base[f]) / ln)); ; ++j) {
+      const float x = base[f] + j * ln;
+      if (found && x >= best) break;
+      const float other = x - base[1 - f];
+      if (cus[f] * j + (other > 0.f ? cus[1 - f] * (int64_t)(other / ln + 1e-4f) : 0) >= N) { best = x; found = true; break; }
+    }
+  }
+  return std::max(best, base[r > 0]);
+}
+
+struct TnSplit {
+  int tile = 0, splits = 1, nt = 1;    // tile of the weight gradient, its splits, tile of the input gradient
+  float us = 0.f;                      // what the model gives the launch
+  size_t room = 0;                     // floats for partial sums that the choice could count on
 };
+// floats of the split-K workspace that one launch may fill
+size_t tn_room(size_t ws_floats, bool chained) { return chained ? (ws_floats / 2) & ~(size_t)3 : ws_floats; }
 
-TnPlan plan_tn(const GemmDesc& g, float* ws, size_t ws_floats, TnChain* chain) {
-  TnPlan p;
-  p.g = g;
-  const int tiles = ((g.M + TN_BM - 1) / TN_BM) * ((g.N + TN_BN - 1) / TN_BN);
-  p.grid_x = tiles;
-  if (chain) {       // this launch takes one half of the workspace, the pending reduction reads the other
-    ws_floats /= 2;
-    ws_floats &= ~(size_t)3;
-    if (ws) ws += (size_t)chain->slot * ws_floats;
-  }
+// nt: the input gradient of the same launch, or null.  (Sizes only: a tile that was measured or asked for changes no split.)
+TnSplit tn_split(const GemmDesc* nt, const GemmDesc& g, size_t room) {
+  TnSplit best;
+  best.room = room;
   const int nk = (g.K + BK - 1) / BK;
-  // enough splits for about 1.5 workgroups per CU, each with at least 4 k-tiles (measured with the launch
-  // sharing the chip with an input-gradient product: at 35 - 49 k-tiles of tokens, 384 workgroups beat 512
-  // and 320 by 1 % of the step); two per CU once the token dimension is long (at 138 - 194 k-tiles 512 beat
-  // 384 by 3 % and 256 by 12 %)
-  int splits = 1;
-  const size_t mn = (size_t)g.M * g.N;
-  const size_t per_split = mn + (g.bsum ? (size_t)g.N : 0);   // partial dW, then partial column sums
-  if (ws && mn % 4 == 0) {
-    const int target = nk >= 96 ? 512 : 384;
-    splits = std::max(1, std::min({target / tiles, nk / 4, (int)(ws_floats / per_split), 16}));
+  const size_t mn = (size_t)g.M * g.N, per_split = mn + (g.bsum ? (size_t)g.N : 0);   // partial dW, then partial column sums
+  const int most = std::max(1, (int)std::min<size_t>(std::min(nk / 4, 16), room / per_split));
+  bool any = false;
+  for (int s = 1; s <= most; ++s) {
+    const int per = (nk + s - 1) / s, splits = (nk + per - 1) / per;
+    if (splits != s) continue;                              // the same k-tiles a split as with fewer of them
+    const float parts = s > 1 ? (float)s * mn * 1e-6f : 0.f;
+    for (int t = 0; t < 2; ++t) {
+      const int64_t T = (int64_t)((g.M + kTn[t].bm - 1) / kTn[t].bm) * ((g.N + kTn[t].bn - 1) / kTn[t].bn) * s;
+      const float lt = kTn[t].c0 + kTn[t].c1 * per + kTn[t].partial * (s > 1 ? 1.f : 0.f);
+      for (int i = 0; i < (nt ? 4 : 1); ++i) {
+        if (nt && t == 1 && i < 2) continue;                // (small tiles beside large ones: never the fastest)
+        const PairCost& c = kPairNt[i];
+        const int64_t N = nt ? (int64_t)((nt->M + c.bm - 1) / c.bm) * ((nt->N + c.bn - 1) / c.bn) : 0;
+        const float ln = c.c0 + c.c1 * (nt ? nt->K / BK : 0) + (nt && nt->act == ACT_GELU_BWD ? c.gelu : 0.f);
+        const float us = PAIR_START_US + PAIR_PARTIAL_US * parts + pair_span(T, lt, N, ln);
+        if (!any || us < best.us) { best.tile = t; best.splits = s; best.nt = nt ? i : 1; best.us = us; any = true; }
+      }
+    }
   }
-  p.kt_per = (nk + splits - 1) / splits;
-  splits = (nk + p.kt_per - 1) / p.kt_per;
-  p.tn_rows = splits;
-  // the previous weight gradient's reduction rides along: about four items per thread
-  int red_rows = 0;
-  if (chain && chain->pending.splits > 0) {
-    p.prev = chain->pending;
+  return best;
+}
+
+// Arguments of a weight-gradient launch: workspace half, the sums that wait in the chain (which it takes over) and the ones
+// it leaves (in the chain, or in *mine without one).
+TnArgs plan_tn(const GemmDesc& g, const TnSplit& sp, float* ws, size_t ws_floats, TnChain* chain, TnReduce* mine) {
+  TnArgs a;
+  a.g = g;
+  a.partial = a.bpartial = nullptr;
+  const int nk = (g.K + BK - 1) / BK;
+  a.kt_per = (nk + sp.splits - 1) / sp.splits;
+  a.gx = ((g.M + kTn[sp.tile].bm - 1) / kTn[sp.tile].bm) * ((g.N + kTn[sp.tile].bn - 1) / kTn[sp.tile].bn);
+  a.blocks = a.gx * sp.splits;
+  *mine = TnReduce();
+  if (chain) {       // this launch takes one half of the workspace, the pending reduction reads the other
+    if (ws) ws += (size_t)chain->slot * tn_room(ws_floats, true);
+    a.red = chain->pending;
     chain->pending = TnReduce();
-    const int64_t per_row = (int64_t)tiles * TN_THREADS * 4;
-    red_rows = (int)std::min<int64_t>(8, std::max<int64_t>(1, (splitk_reduce_items_host(p.prev) + per_row - 1) / per_row));
   }
-  p.grid_y = splits + red_rows;
-  if (splits > 1) {
-    p.partial = ws;
-    p.bpartial = g.bsum ? ws + (size_t)splits * mn : nullptr;
-    p.mine.partial = ws; p.mine.n = (int64_t)mn; p.mine.splits = splits; p.mine.out = (float*)g.C;
-    p.mine.bpartial = p.bpartial; p.mine.nb = g.bsum ? g.N : 0; p.mine.bout = g.bsum;
+  if (sp.splits > 1) {
+    const size_t mn = (size_t)g.M * g.N;
+    a.partial = ws;
+    a.bpartial = g.bsum ? ws + (size_t)sp.splits * mn : nullptr;
+    mine->partial = ws; mine->n = (int64_t)mn; mine->splits = sp.splits; mine->out = (float*)g.C;
+    mine->bpartial = a.bpartial; mine->nb = g.bsum ? g.N : 0; mine->bout = g.bsum;
     if (chain) {
-      chain->pending = p.mine;
+      chain->pending = *mine;
       chain->slot ^= 1;
     }
   }
-  return p;
+  return a;
 }
 
-void launch_tn(const GemmDesc& g, float* ws, size_t ws_floats, hipStream_t s, TnChain* chain) {
+template <int T>
+void launch_tn_as(const TnArgs& a, hipStream_t s) {
   static bool attr_set = false;
-  auto kern = gemm_tn_kernel<TN_BM, TN_BN, TN_WM, TN_WN>;
+  constexpr size_t lds = tile_lds<TnTile<T>>();
+  static_assert(tile_patch_lds<TnTile<T>>() <= lds, "the epilogue patches live in the stage buffers");
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)TN_LDS);
+    (void)hipFuncSetAttribute((const void*)gemm_tn_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr_set = true;
   }
-  if (g.grp_off) {   // one grid row per group, no split: tiles x groups already fills the machine
-    gemm_tn_flush(chain, s);
-    const int tiles = ((g.M + TN_BM - 1) / TN_BM) * ((g.N + TN_BN - 1) / TN_BN);
-    kern<<<dim3(tiles, g.groups), TN_THREADS, TN_LDS, s>>>(g, nullptr, nullptr, 0, g.groups, TnReduce());
-    return;
-  }
-  const TnPlan p = plan_tn(g, ws, ws_floats, chain);
-  kern<<<dim3(p.grid_x, p.grid_y), TN_THREADS, TN_LDS, s>>>(p.g, p.partial, p.bpartial, p.kt_per, p.tn_rows, p.prev);
-  if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s);
+  // sums of an earlier launch: about four items per thread
+  const int64_t per = (int64_t)TN_THREADS * 4;
+  const int red = a.red.splits > 0 ? (int)std::min<int64_t>(512, (splitk_reduce_items_host(a.red) + per - 1) / per) : 0;
+  gemm_tn_kernel<T><<<a.blocks + red, TN_THREADS, lds, s>>>(a);
 }
 
-// One launch for an input gradient (NT, tile BM x BN) and the weight gradient of the same layer.
-template <int BM, int BN, int WM, int WN, int PF>
-void launch_nt_fused(const GemmDesc& g, const TnPlan& p, hipStream_t s) {
-  static_assert(WM * WN * 64 == TN_THREADS, "");
+void launch_tn(const GemmDesc& g, const TnSplit& sp, float* ws, size_t ws_floats, hipStream_t s, TnChain* chain) {
+  TnReduce mine;
+  TnArgs a = plan_tn(g, sp, ws, ws_floats, chain, &mine);
+  if (g.grp_off) a.blocks = a.gx * g.groups;   // a group per split: tiles x groups already fills the machine
+  if (sp.tile) launch_tn_as<1>(a, s);
+  else launch_tn_as<0>(a, s);
+  if (!chain && mine.splits > 0) launch_reduce(mine, s);
+}
+
+template <int I, int T>
+void launch_pair_as(const GemmDesc& g, const TnArgs& a, hipStream_t s) {
+  using N = PairTile<I>;
   static bool attr_set = false;
-  constexpr size_t lds_tiles = (size_t)2 * (BM + BN) * BK * sizeof(bf16);
-  constexpr size_t lds_patch = (size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float);
-  constexpr size_t lds_nt = lds_tiles > lds_patch ? lds_tiles : lds_patch;
-  constexpr size_t lds = lds_nt > TN_LDS ? lds_nt : TN_LDS;
-  auto kern = gemm_nt_kernel<BM, BN, WM, WN, false, PF, true>;
+  constexpr size_t lds = tile_lds<N>() > tile_lds<TnTile<T>>() ? tile_lds<N>() : tile_lds<TnTile<T>>();
+  static_assert(tile_patch_lds<N>() <= lds && tile_patch_lds<TnTile<T>>() <= lds, "the epilogue patches live in the stage buffers");
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute((const void*)gemm_pair_kernel<I, T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr_set = true;
   }
-  TnArgs t;
-  t.g = p.g; t.partial = p.partial; t.bpartial = p.bpartial; t.kt_per = p.kt_per; t.tn_rows = p.tn_rows;
-  t.red = p.prev; t.gx = p.grid_x; t.gy = p.grid_y;
-  t.nt_tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  kern<<<t.nt_tiles + p.grid_x * p.grid_y, TN_THREADS, lds, s>>>(g, t);
+  const int tiles = ((g.M + N::BM - 1) / N::BM) * ((g.N + N::BN - 1) / N::BN);
+  gemm_pair_kernel<I, T><<<a.blocks + tiles, TN_THREADS, lds, s>>>(g, a, tiles);
+}
+template <int I>
+void launch_pair(const GemmDesc& g, const GemmDesc& t, const TnSplit& sp, float* ws, size_t ws_floats, hipStream_t s, TnChain* chain) {
+  TnReduce mine;
+  const TnArgs a = plan_tn(t, sp, ws, ws_floats, chain, &mine);
+  if (sp.tile) launch_pair_as<I, 1>(g, a, s);
+  else launch_pair_as<I, 0>(g, a, s);
+  if (!chain && mine.splits > 0) launch_reduce(mine, s);
 }
 
 bool is_nt(const GemmDesc& g) {
@@ -1312,13 +1422,13 @@ static const int kNtShapes[] = {
     3128064, 3064128, 2192128, 2256128, 2128128,
     // operands straight into LDS (id = 7000000 + shape; K a multiple of 64, one weight matrix, no folded LayerNorm:
     // a launch outside that takes the model's shape instead)
-    7256256, 7320256, 7192256, 7256192, 7256128, 7128256, 7192128, 7128128,
+    7256256, 7320256, 7192256, 7256192, 7256128, 7128256, 7192128, 7128128, 7128064,
 };
 // stages of the direct-to-LDS shapes (0: not one of them)
 static int ntd_stages(int id) {
   switch (id) {
     case 7256256: case 7320256: case 7192256: case 7256192: case 7192128: case 7128128: return 2;
-    case 7256128: case 7128256: return 3;
+    case 7256128: case 7128256: case 7128064: return 3;
     default: return 0;
   }
 }
@@ -1338,13 +1448,6 @@ const NtModel kNtModel[] = {
     {3128064, 128, 64, {6.542f, 0.794f, 0.173f, 0.773f, 0.052f, 0.000f, 0.222f}},
     {7256256, 256, 256, {0.000f, 8.827f, 1.173f, 1.403f, 0.332f, 5.356f, 0.142f}},
     {7320256, 320, 256, {10.479f, 4.369f, 1.469f, 3.163f, 0.515f, 0.945f, 0.009f}},
-};
-// A launch that carries the layer's weight gradient as well: three shapes, 2.6 % above the fastest (shapes chosen by the
-// model of the input gradient alone: 9.6 %).
-const NtModel kPairModel[] = {
-    {128064, 128, 64, {10.593f, 0.000f, 0.213f, 3.588f, 0.481f, 0.000f, 0.079f}},
-    {192128, 192, 128, {9.635f, 0.000f, 0.405f, 12.419f, 1.218f, 0.000f, 0.112f}},
-    {3128064, 128, 64, {10.966f, 0.000f, 0.188f, 3.563f, 0.555f, 0.000f, 0.006f}},
 };
 constexpr float EVENTS_US = 4.5f;      // the part of c0 that a launch inside a chain does not take (the event pair)
 
@@ -1373,27 +1476,35 @@ int gemm_nt_tile_id(int i) { return kNtShapes[i]; }
 bool gemm_nt_tile_is_free(const GemmDesc& g) { return is_nt(g) && !g.grp_off; }
 
 // The one rule that sends a product to the kernel for few rows: the shape of that kernel, or -1 for the tiled ones.  It
-// looks at the product's sizes, and at whether the launch could carry the layer's weight gradient as well (tiled kernels
-// do that in one launch; here it costs another one), and at nothing else: the kernel for few rows adds over k in another
-// order, so with the tile choice in the rule, tuning would change bits.
-static int few_rows_shape(const GemmDesc& g, bool carries_wgrad) {
+// looks at the product's sizes and, for an input gradient, at those of the layer's weight gradient (which a tiled product
+// carries in its own launch, and which takes another one here), and at nothing else: the kernel for few rows adds over k in
+// another order, so with the tile choice in the rule, tuning would change bits.
+static int few_rows_shape(const GemmDesc& g) {
   float few_us = 0.f, tiled_us = 0.f;
   const int few = few_pick(g, &few_us);
   if (few < 0) return -1;
   nt_pick(g, &tiled_us);
-  return few_us < FEW_LEAD * (tiled_us - EVENTS_US - (carries_wgrad ? TILED_LAUNCH_US : 0.f)) ? few : -1;
+  return few_us < FEW_LEAD * (tiled_us - EVENTS_US) ? few : -1;
+}
+static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && is_tn(tn) && !tn.grp_off; }
+static int few_rows_shape(const GemmDesc& nt, const GemmDesc& tn, const TnSplit& pair) {
+  if (!can_pair(nt, tn)) return few_rows_shape(nt);
+  float few_us = 0.f;
+  const int few = few_pick(nt, &few_us);
+  if (few < 0) return -1;
+  const TnSplit alone = tn_split(nullptr, tn, pair.room);
+  return few_us + alone.us < pair.us ? few : -1;
 }
 
-static bool can_pair(const GemmDesc& nt) { return is_nt(nt) && !nt.grp_off && nt.K % BK == 0; }
-static int pair_model_tile(const GemmDesc& nt) {
+// id of the tile that the model gives the input gradient of a layer's backward launch
+static int pair_model_tile(const TnSplit& pair) { return 7000000 + 1000 * kPairNt[pair.nt].bm + kPairNt[pair.nt].bn; }
+int gemm_nt_model_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained) {
   float us = 0.f;
-  return model_pick(kPairModel, nt.M, nt.N, nt.K, false, false, &us);
-}
-int gemm_nt_model_tile(const GemmDesc& g, bool carries_wgrad) {
-  const int few = few_rows_shape(g, carries_wgrad);
+  TnSplit pair;
+  if (wgrad) pair = tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained));
+  const int few = wgrad ? few_rows_shape(g, *wgrad, pair) : few_rows_shape(g);
   if (few >= 0) return FEW_ROWS_ID + 32000 * kFewShapes[few].mi + 32 * kFewShapes[few].ni;
-  float us = 0.f;
-  return carries_wgrad && can_pair(g) ? pair_model_tile(g) : nt_pick(g, &us);
+  return wgrad && can_pair(g, *wgrad) ? pair_model_tile(pair) : nt_pick(g, &us);
 }
 
 void gemm_tn_flush(TnChain* chain, hipStream_t s) {
@@ -1417,6 +1528,7 @@ static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
     case 7128256: launch_ntd<128, 256, 2, 4, 3>(g, s); break;
     case 7192128: launch_ntd<192, 128, 2, 2, 2>(g, s); break;
     case 7128128: launch_ntd<128, 128, 2, 2, 2>(g, s); break;
+    case 7128064: launch_ntd<128, 64, 2, 2, 3>(g, s); break;
     case 256256: launch_nt<256, 256, 2, 4>(g, s); break;
     case 256128: launch_nt<256, 128, 4, 4>(g, s); break;
     case 192128: launch_nt<192, 128, 2, 4>(g, s); break;
@@ -1439,36 +1551,39 @@ static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
 
 void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile, TnChain* chain) {
   if (is_tn(g)) {
-    launch_tn(g, splitk_ws, splitk_ws_floats, s, chain);
+    const TnSplit split = g.grp_off ? TnSplit() : tn_split(nullptr, g, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
+    launch_tn(g, split, splitk_ws, splitk_ws_floats, s, chain);
     return;
   }
-  const int few = few_rows_shape(g, false);
+  const int few = few_rows_shape(g);
   if (few >= 0) launch_few(few, g, s);
   else nt_tiled(g, s, tile);
 }
 
-// The input gradient (NT) and the weight gradient (TN) of one layer.  When the tile shape chosen for the
-// NT part runs with 8 waves they go out as one launch (the weight-gradient workgroups fill the machine
-// behind the input-gradient tiles), otherwise as two.  Which kernel multiplies does not depend on the tile either way.
+// The input gradient (NT) and the weight gradient (TN) of one layer: one launch, unless the tile asked for is none of
+// the shapes that the joint kernel has.  Which kernel multiplies, and how the weight gradient is split, does not depend
+// on the tile.
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile, TnChain* chain) {
-  const int few = few_rows_shape(nt, true);
-  if (few < 0 && can_pair(nt) && is_tn(tn) && !tn.grp_off) {
-    switch (tile ? tile : pair_model_tile(nt)) {
-      case 128064: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<128, 64, 4, 2, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
-      case 64128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<64, 128, 2, 4, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
-      case 192128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<192, 128, 2, 4, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
-      case 128128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<128, 128, 4, 2, 1>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
-      case 3128064: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<128, 64, 4, 2, 3>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
-      case 3064128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<64, 128, 2, 4, 3>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
-      case 2192128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<192, 128, 2, 4, 2>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
-      case 2128128: { const TnPlan p = plan_tn(tn, splitk_ws, splitk_ws_floats, chain); launch_nt_fused<128, 128, 4, 2, 2>(nt, p, s); if (!chain && p.mine.splits > 0) launch_reduce(p.mine, s); return; }
+  const TnSplit split = tn_split(is_ntd(nt) ? &nt : nullptr, tn, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
+  const int few = few_rows_shape(nt, tn, split);
+  if (few >= 0) {
+    launch_few(few, nt, s);
+    gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
+    return;
+  }
+  if (can_pair(nt, tn)) {
+    switch ((tile ? tile : pair_model_tile(split)) % 1000000) {
+      case 128064: launch_pair<0>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
+      case 128128: launch_pair<1>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
+      case 192128: launch_pair<2>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
+      case 256128: launch_pair<3>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
       default: break;
     }
   }
-  if (few >= 0) launch_few(few, nt, s);
-  else nt_tiled(nt, s, tile);                 // (not gemm_mfma: its rule is that of a product on its own)
-  gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
+  nt_tiled(nt, s, tile);                 // (not gemm_mfma: its rule is that of a product on its own)
+  if (is_tn(tn)) launch_tn(tn, split, splitk_ws, splitk_ws_floats, s, chain);
+  else gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
 }
 
 }  // namespace bsr
