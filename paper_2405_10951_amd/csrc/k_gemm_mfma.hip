@@ -439,8 +439,11 @@ void launch_nt(const GemmDesc& g, hipStream_t s) {
 // (s_waitcnt vmcnt counts such a load when its data is in LDS), so behind the barrier k-tile kt + NST can go into
 // the stage of k-tile kt; (3) the order of the k-loop is written out, every MFMA followed by at most one fragment
 // read or a few loads, and pinned with scheduling barriers (the compiler's own order bunches the reads in front
-// of the MFMAs and waits for them).  Wave tiles are at least 64 x 64 (128 x 64 in the 256 x 256 shape): per MFMA
-// a wavefront reads 0.75 - 1 KB of fragments instead of the 1.5 KB of a 64 x 32 wave tile.
+// of the MFMAs and waits for them).  Large shapes have wave tiles of 64 x 64 and
+// more (128 x 64 in the 256 x 256 shape): per MFMA a wavefront reads 0.75 - 1 KB of fragments instead of the 1.5 KB of a 64 x 32
+// wave tile.  Shapes that leave a CU one workgroup of few tiles run eight wavefronts on small wave tiles and three stages:
+// there two wavefronts a SIMD and k-tiles in flight count for more (6304 x 768 x 3072, 192 x 128: four wavefronts and two stages
+// 42.4 us, eight and three 35.1; 4416 x 768 x 3072, 128 x 128: 34.6 and 27.0; the loads alone take 23 of those 27).
 // The MFMA operands are swapped (weight rows first), so an accumulator holds the TRANSPOSED 32 x 32 output tile:
 // a lane owns one output row and four runs of four consecutive columns.  That lets the epilogue round to bf16
 // before the tile goes through LDS whenever nothing has to be added in fp32 afterwards (8-byte LDS writes of four
@@ -733,7 +736,7 @@ __device__ __forceinline__ void ntd_body(const GemmDesc& g, int tile) {
 
 // (a shape whose stages take at most half of the 160 KB is held to the registers that let two workgroups share a CU)
 template <int BM, int BN, int WM, int WN, int NST>
-__global__ __launch_bounds__(WM * WN * 64, (NST * (BM + BN) * 128 <= 80 * 1024 && WM * WN <= 4) ? 2 : 1)
+__global__ __launch_bounds__(WM * WN * 64, NST * (BM + BN) * 128 <= 80 * 1024 ? WM * WN / 2 : 1)
 void gemm_ntd_kernel(GemmDesc g) {
   ntd_body<BM, BN, WM, WN, NST>(g, xcd_remap(blockIdx.x, (int)gridDim.x));
 }
@@ -924,11 +927,9 @@ void launch_few(const GemmDesc& g, hipStream_t s) {
 // (within 15 % where the kernel is the faster one).
 struct FewShape { int mi, ni; float launch_us, round_us, bytes_per_us; };
 const FewShape kFewShapes[] = {{1, 1, 2.6f, 0.5f, 105e3f}, {2, 1, 2.8f, 0.5f, 103e3f}, {2, 2, 3.3f, 1.0f, 65e3f}};
-constexpr float TILED_LAUNCH_US = 2.6f;               // the same fixed part of a tiled launch
-// A product comes here when the model gives it a clear lead over the tiled kernels: inside a step, where every launch
-// follows another kernel, near-ties of the two models (384 columns from 1536 at 2144 rows) went to the tiled ones.  One
-// lead for products on their own and for input gradients that could carry a weight gradient; for the latter the launch they save is
-// added, and the lead itself was chosen on the former.
+// A product on its own comes here when the model gives it this lead over the tiled kernels' model.  Chains of equal launches
+// at 32 .. 2144 rows (108 products, 384 and 768 wide): 0.8 loses 0.04 % to the faster of the two, 0.7 2.1 %, 0.9 1.7 %, 1.0 2.9 % (the
+// model of this kernel is short by half where a launch takes several rounds).
 constexpr float FEW_LEAD = 0.8f;
 
 // The shape of this kernel for a product and what the model gives it; -1: not one it takes
@@ -1458,56 +1459,70 @@ bool gemm_mfma_supported(const GemmDesc& g) { return is_nt(g) || is_tn(g); }
 // has measured to be (bsr_autotune).  Every shape accumulates an output element over k in the same order, so the choice
 // never changes a result.
 static const int kNtShapes[] = {
-    256128, 128128, 192128, 160256, 256256, 128064, 96128, 64128, 128256, 192256, 256064, 96256,
-    // with deeper register prefetch (id = PF * 1000000 + shape)
-    3128064, 3064128, 2192128, 2256128, 2128128,
-    // operands straight into LDS (id = 7000000 + shape; K a multiple of 64, one weight matrix, no folded LayerNorm:
-    // a launch outside that takes the model's shape instead)
-    7256256, 7320256, 7192256, 7256192, 7256128, 7128256, 7192128, 7128128, 7128064,
+    // staged through registers; what folds a LayerNorm, has a ragged K or runs group by group has these only
+    256128, 128128, 192128, 160256, 256256, 128064, 64128,
+    3128064,                              // with deeper register prefetch (id = PF * 1000000 + shape)
+    // operands straight into LDS (id = 7000000 + shape, 8000000 + shape with one stage more; K a multiple of 64, one weight
+    // matrix, no folded LayerNorm: a launch outside that takes the model's shape instead)
+    7256256, 7320256, 7192256, 7256192, 7256128, 7128256, 7192128, 7128128, 7128064, 7064128, 7096128, 8192128, 8128128,
 };
 // stages of the direct-to-LDS shapes (0: not one of them)
 static int ntd_stages(int id) {
   switch (id) {
     case 7256256: case 7320256: case 7192256: case 7256192: case 7192128: case 7128128: return 2;
-    case 7256128: case 7128256: case 7128064: return 3;
+    case 7256128: case 7128256: case 7128064: case 7064128: case 7096128: case 8192128: case 8128128: return 3;
     default: return 0;
   }
 }
 
 // The model: with t tiles, time = c0 + ceil(t / 256) (c1 + c2 K / 64) + t / 256 (c3 + c4 K / 64) + ceil(t / 512) (c5 + c6 K / 64)
-// microseconds: a fixed part, rounds of one workgroup per CU, what scales with the work, rounds of two per CU.  Constants
-// fitted to every shape forced in turn on the launches of ViT-B and DeiT-S steps at 1 .. 128 images, keep ratios of 1 and
-// 0.5, 224 and 384 pixels (436 launches of 256 .. 25216 rows, event-bracketed, in their place in the step).  Over these
-// the six shapes' picks take 1.5 % longer than the fastest of all 25 (fitted on half of them, the other half: 1.2 %); the model
-// before, seven register-staged shapes with two constants each, took 7.4 %.  More shapes bring nothing.  All of it at 384, 768,
-// 1152, 1536, 2304 and 3072 columns: at other widths the model extrapolates, and tuning is the way to know.
-struct NtModel { int id, bm, bn; float c[7]; };
+// microseconds, and where a GELU is applied ceil(t / 256) c7 + t / 256 c8 more: a fixed part, rounds of one workgroup per CU,
+// what scales with the work, rounds of two per CU.
+struct NtModel { int id, bm, bn; float c[9]; };
+// Direct-to-LDS shapes: constants fitted to chains of equal launches over twelve weight matrices (88 products of 400 .. 25216
+// rows; 384, 768, 1152, 1536, 2304 and 3072 columns).  Of 32 shapes measured there these nine lose 0.8 %, and the model's
+// picks among them 1.2 %, to the fastest of all; the best of the shapes before them (four-wavefront and register-staged
+// ones) took 6.5 % longer, the model's picks of those 14 %.  At other widths the model extrapolates, and tuning is the way to know.
 const NtModel kNtModel[] = {
-    {64128, 64, 128, {6.508f, 0.000f, 0.142f, 1.061f, 0.000f, 0.000f, 0.353f}},
-    {192128, 192, 128, {7.783f, 1.559f, 0.501f, 1.705f, 0.104f, 0.000f, 0.182f}},
-    {256128, 256, 128, {3.608f, 3.854f, 0.664f, 2.056f, 0.342f, 2.154f, 0.001f}},
-    {3128064, 128, 64, {6.542f, 0.794f, 0.173f, 0.773f, 0.052f, 0.000f, 0.222f}},
-    {7256256, 256, 256, {0.000f, 8.827f, 1.173f, 1.403f, 0.332f, 5.356f, 0.142f}},
-    {7320256, 320, 256, {10.479f, 4.369f, 1.469f, 3.163f, 0.515f, 0.945f, 0.009f}},
+    {7128064, 128, 64, {2.231f, 0.226f, 0.225f, 0.244f, 0.063f, 1.485f, 0.040f, 1.032f, 0.000f}},
+    {7192128, 192, 128, {3.692f, 0.495f, 0.423f, 1.425f, 0.145f, 0.000f, 0.241f, 2.731f, 0.000f}},
+    {8128128, 128, 128, {1.293f, 2.977f, 0.363f, 0.000f, 0.181f, 0.000f, 0.000f, 1.970f, 0.623f}},
+    {7128128, 128, 128, {2.632f, 0.784f, 0.200f, 0.475f, 0.149f, 0.273f, 0.363f, 1.768f, 0.000f}},
+    {7320256, 320, 256, {0.696f, 7.695f, 0.752f, 0.000f, 1.252f, 1.771f, 0.190f, 10.720f, 0.381f}},
+    {8192128, 192, 128, {1.428f, 3.720f, 0.438f, 0.000f, 0.294f, 0.000f, 0.000f, 2.450f, 1.429f}},
+    {7192256, 192, 256, {1.340f, 5.269f, 0.721f, 0.000f, 0.597f, 0.321f, 0.000f, 6.615f, 0.367f}},
+    {7256256, 256, 256, {0.390f, 6.475f, 0.912f, 0.000f, 0.791f, 1.970f, 0.000f, 7.088f, 1.735f}},
+    {7256128, 256, 128, {0.000f, 4.160f, 0.564f, 0.268f, 0.342f, 1.936f, 0.000f, 3.777f, 0.839f}},
 };
-constexpr float EVENTS_US = 4.5f;      // the part of c0 that a launch inside a chain does not take (the event pair)
+// Register-staged shapes, for products that only they take: fitted to every shape forced in turn on the launches of ViT-B
+// and DeiT-S steps (436 launches, event-bracketed, in their place in the step, the event pair included).
+const NtModel kNtStagedModel[] = {
+    {64128, 64, 128, {6.508f, 0.000f, 0.142f, 1.061f, 0.000f, 0.000f, 0.353f, 0.f, 0.f}},
+    {192128, 192, 128, {7.783f, 1.559f, 0.501f, 1.705f, 0.104f, 0.000f, 0.182f, 0.f, 0.f}},
+    {256128, 256, 128, {3.608f, 3.854f, 0.664f, 2.056f, 0.342f, 2.154f, 0.001f, 0.f, 0.f}},
+    {3128064, 128, 64, {6.542f, 0.794f, 0.173f, 0.773f, 0.052f, 0.000f, 0.222f, 0.f, 0.f}},
+};
+constexpr float EVENTS_US = 4.5f;      // the part of their c0 that a launch inside a chain does not take (the event pair)
 
-// the model's pick and its time, event pair included; direct_ok: direct-to-LDS shapes are allowed, folded: the LayerNorm is
-// folded in (64 columns per tile would double its dot instructions per MFMA)
-template <int N>
-static int model_pick(const NtModel (&table)[N], int M, int Nc, int K, bool direct_ok, bool folded, float* us_out) {
+// the model's pick and the time it gives it in a chain of launches.  (With the LayerNorm folded in, 64 columns per tile would
+// double its dot instructions per MFMA.)
+static int nt_pick(const GemmDesc& g, float* us_out) {
+  const bool direct = is_ntd(g);
+  const NtModel* table = direct ? kNtModel : kNtStagedModel;
+  const int n = direct ? (int)(sizeof(kNtModel) / sizeof(kNtModel[0])) : (int)(sizeof(kNtStagedModel) / sizeof(kNtStagedModel[0]));
   int pick = 0;
-  const float k = (float)((K + BK - 1) / BK);
-  for (const NtModel& e : table) {
-    if ((ntd_stages(e.id) && !direct_ok) || (folded && e.bn < 128)) continue;
-    const int64_t t = (int64_t)((M + e.bm - 1) / e.bm) * ((Nc + e.bn - 1) / e.bn);
+  const float k = (float)((g.K + BK - 1) / BK), gelu = g.act == ACT_NONE ? 0.f : 1.f;
+  for (int i = 0; i < n; ++i) {
+    const NtModel& e = table[i];
+    if (g.ln_colsum && e.bn < 128) continue;
+    const int64_t t = (int64_t)((g.M + e.bm - 1) / e.bm) * ((g.N + e.bn - 1) / e.bn);
     const float r1 = (float)((t + 255) / 256), w = (float)t / 256.f, r2 = (float)((t + 511) / 512);
-    const float us = e.c[0] + r1 * (e.c[1] + e.c[2] * k) + w * (e.c[3] + e.c[4] * k) + r2 * (e.c[5] + e.c[6] * k);
+    const float us = e.c[0] + r1 * (e.c[1] + e.c[2] * k + e.c[7] * gelu) + w * (e.c[3] + e.c[4] * k + e.c[8] * gelu) +
+                     r2 * (e.c[5] + e.c[6] * k) - (direct ? 0.f : EVENTS_US);
     if (!pick || us < *us_out) { pick = e.id; *us_out = us; }
   }
   return pick;
 }
-static int nt_pick(const GemmDesc& g, float* us) { return model_pick(kNtModel, g.M, g.N, g.K, is_ntd(g), g.ln_colsum != nullptr, us); }
 size_t gemm_nt_tile_lds_bytes(int id) {
   const int bm = id % 1000000 / 1000, bn = id % 1000, nst = ntd_stages(id);
   return (size_t)(nst ? nst : 2) * (bm + bn) * BK * sizeof(bf16);
@@ -1525,7 +1540,7 @@ static int few_rows_shape(const GemmDesc& g) {
   const int few = few_pick(g, &few_us);
   if (few < 0) return -1;
   nt_pick(g, &tiled_us);
-  return few_us < FEW_LEAD * (tiled_us - EVENTS_US) ? few : -1;
+  return few_us < FEW_LEAD * tiled_us ? few : -1;
 }
 static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && is_tn(tn) && !tn.grp_off; }
 static int few_rows_shape(const GemmDesc& nt, const GemmDesc& tn, const TnSplit& pair) {
@@ -1567,25 +1582,20 @@ static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
     case 7256192: launch_ntd<256, 192, 4, 2, 2>(g, s); break;
     case 7256128: launch_ntd<256, 128, 4, 2, 3>(g, s); break;
     case 7128256: launch_ntd<128, 256, 2, 4, 3>(g, s); break;
-    case 7192128: launch_ntd<192, 128, 2, 2, 2>(g, s); break;
-    case 7128128: launch_ntd<128, 128, 2, 2, 2>(g, s); break;
+    case 7192128: launch_ntd<192, 128, 2, 4, 2>(g, s); break;
+    case 8192128: launch_ntd<192, 128, 2, 4, 3>(g, s); break;
+    case 7128128: launch_ntd<128, 128, 2, 4, 2>(g, s); break;
+    case 8128128: launch_ntd<128, 128, 2, 4, 3>(g, s); break;
     case 7128064: launch_ntd<128, 64, 2, 2, 3>(g, s); break;
+    case 7064128: launch_ntd<64, 128, 2, 2, 3>(g, s); break;
+    case 7096128: launch_ntd<96, 128, 1, 4, 3>(g, s); break;
     case 256256: launch_nt<256, 256, 2, 4>(g, s); break;
     case 256128: launch_nt<256, 128, 4, 4>(g, s); break;
     case 192128: launch_nt<192, 128, 2, 4>(g, s); break;
     case 160256: launch_nt<160, 256, 1, 8>(g, s); break;
     case 128064: launch_nt<128, 64, 4, 2>(g, s); break;
-    case 96128: launch_nt<96, 128, 1, 4>(g, s); break;
     case 64128: launch_nt<64, 128, 2, 4>(g, s); break;
-    case 128256: launch_nt<128, 256, 2, 4>(g, s); break;
-    case 192256: launch_nt<192, 256, 2, 4>(g, s); break;
-    case 256064: launch_nt<256, 64, 4, 2>(g, s); break;
-    case 96256: launch_nt<96, 256, 1, 8>(g, s); break;
     case 3128064: launch_nt<128, 64, 4, 2, 3>(g, s); break;
-    case 3064128: launch_nt<64, 128, 2, 4, 3>(g, s); break;
-    case 2192128: launch_nt<192, 128, 2, 4, 2>(g, s); break;
-    case 2256128: launch_nt<256, 128, 4, 4, 2>(g, s); break;
-    case 2128128: launch_nt<128, 128, 4, 2, 2>(g, s); break;
     default: launch_nt<128, 128, 4, 2>(g, s); break;
   }
 }
