@@ -8,14 +8,13 @@
 // every k-tile) and 32 x 32 (8 wavefronts, each an eighth of every k-tile); the partial sums of the wavefronts that
 // share a tile are added through LDS in a fixed order (bit-reproducible).
 //
-// Measured, DeiT-S step of 8 images: the products 11.5 ms as vector-unit kernels, 1.4 ms here (81 launches; 0.41 ms is
-// what a large fp32 product on this chip would take); one 192-wide block of 130 rows: 60 -> 4.5 .. 7.7 us a product.
+// Measured, chains of launches, operands staged through registers -> straight into LDS: 1576 x 384 x 1536 42.4 -> 30.5 us,
+// 536 x 384 x 1536 16.9 -> 12.8, 1576 x 1536 x 384 30.6 -> 28.6 (65 TFLOP/s; the matrix cores alone 23).
 //
 // The contraction index of an MFMA is a dummy: MFMA j of a group of 8 uses k = 4 h + j for wave half h, so a lane's
-// four operands of four MFMAs are four consecutive floats.  An operand whose k is contiguous in memory is staged as
-// it lies, rows of KT floats (+4: the 16-byte reads of 16 rows then hit every bank once), and read with one 16-byte
-// LDS read per four MFMAs; an operand whose row index is contiguous is staged [k][row] (+8 per k-row: the two wave
-// halves, four k-rows apart, hit different banks) and read with four 4-byte reads.
+// four operands of four MFMAs are four consecutive floats.  An operand whose k is contiguous in memory is read with one
+// 16-byte LDS read per four MFMAs; an operand whose row index is contiguous lies as [k][row] and is read with four 4-byte
+// reads.
 #include <algorithm>
 
 #include "bsr_internal.h"
@@ -39,62 +38,83 @@ __device__ inline int xcd_range(int pid, int n) {
   return x * base + min(x, rem) + pid / 8;
 }
 
+// Loads that go straight into LDS: lane l of a wavefront writes 16 bytes at the wavefront's LDS address + 16 l
+#define BSR_GLOBAL_PTR(p) ((const void __attribute__((address_space(1)))*)(p))
+#define BSR_LDS_VOID(p) ((void __attribute__((address_space(3)))*)(p))
+template <int N> __device__ __forceinline__ void wait_vmcnt() { __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8)); }
+__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4)); }
+
 // k-tile: long where the wavefronts share it, since a tile that is alone on its CU is done with 32 k long before the
 // next loads return (64 x 64 tiles at M = 1576, K = 384: 30 us with k-tiles of 32 fetched one ahead)
 __host__ __device__ constexpr int f32_kt(int wk) { return wk == 1 ? 32 : wk == 2 ? 64 : 128; }
 
-// One operand's tile in LDS: R rows (of the output index) x KT; KC: k contiguous in memory
+// One operand's tile in LDS: R rows (of the output index) x KT; KC: k contiguous in memory.  KC tiles lie as panels of 32 k,
+// rows of eight 16-byte chunks, chunk c of row r at position c ^ swz(r) (16 rows that read the same chunk then hit every bank
+// once; the permutation is applied to the global address a lane loads from); the others lie as [k][row].
+__device__ inline int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 template <int R, int KT, bool KC, int NT>
 struct Tile {
-  static constexpr int LD = KC ? KT + 4 : R + 8;                 // floats per LDS row
-  static constexpr int FLOATS = KC ? R * LD : KT * LD;
-  static constexpr int CPR = (KC ? KT : R) / 4;                  // 16-byte chunks per memory row
-  static constexpr int NCH = R * KT / 4 / NT;                    // chunks per thread
+  static constexpr int FLOATS = R * KT;
+  static constexpr int NCH = R * KT / 4 / NT;                    // load instructions per thread
   static_assert(R * KT / 4 % NT == 0 && NCH >= 1, "every thread carries whole chunks");
-  f32x4 v[NCH];
-  // p: operand, ld: floats between memory rows, r0: first output row of the tile, rows / K: extents
-  __device__ __forceinline__ void fetch(const float* __restrict__ p, int64_t ld, int r0, int rows, int k0, int K, int tid) {
+  // output row (or first of four) and k of the chunk that thread tid's load i brings, relative to the tile
+  __device__ static __forceinline__ void where(int tid, int i, int& r, int& k) {
+    const int c = tid + NT * i;
+    if (KC) { r = c / 8 % R; k = c / (8 * R) * 32 + (c % 8 ^ swz(r)) * 4; }
+    else { r = c % (R / 4) * 4; k = c / (R / 4); }
+  }
+  // p: operand, ld: floats between memory rows, r0: first output row of the tile, rows / K: extents.  Rows past the end
+  // repeat valid ones (never stored), k past the end too (cleared below).
+  __device__ static __forceinline__ void load(float* s, const float* __restrict__ p, int64_t ld, int r0, int rows, int k0, int K, int tid) {
+    float* dst = s + __builtin_amdgcn_readfirstlane(tid >> 6) * 256;
+    const bool whole = k0 + KT <= K;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-      const int c = tid + NT * i, a = c / CPR, q = (c % CPR) * 4;
-      const int r = KC ? r0 + a : r0 + q, k = KC ? k0 + q : k0 + a;
-      // rows past the end repeat valid ones (never stored); k past the end is zero
-      const float* src = KC ? p + (int64_t)min(r, rows - 1) * ld + min(k, K - 4) : p + (int64_t)min(k, K - 1) * ld + min(r, rows - 4);
-      v[i] = *(const f32x4*)src;
-      if (k >= K) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      int r, k;
+      where(tid, i, r, k);
+      r += r0;
+      k += k0;
+      if (!whole) k = min(k, K - (KC ? 4 : 1));
+      __builtin_amdgcn_global_load_lds(BSR_GLOBAL_PTR(KC ? p + (int64_t)min(r, rows - 1) * ld + k : p + (int64_t)k * ld + min(r, rows - 4)),
+                                       BSR_LDS_VOID(dst + NT * 4 * i), 16, 0, 0);
     }
   }
-  __device__ __forceinline__ void stash(float* s, int tid) const {
+  // what this thread has loaded of k >= K becomes zero
+  __device__ static __forceinline__ void clear(float* s, int k0, int K, int tid) {
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-      const int c = tid + NT * i;
-      *(f32x4*)(s + (c / CPR) * LD + (c % CPR) * 4) = v[i];
+      int r, k;
+      where(tid, i, r, k);
+      if (k0 + k >= K) *(f32x4*)(s + (tid + NT * i) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   }
   // four consecutive k of output row r: k-group grp of 8, wave half h
   __device__ static __forceinline__ f32x4 frag(const float* s, int r, int grp, int h) {
-    const int k = grp * 8 + h * 4;
     if constexpr (KC) {
-      return *(const f32x4*)(s + r * LD + k);
+      const int chunk = grp * 2 + h;
+      return *(const f32x4*)(s + (chunk / 8 * R + r) * 32 + (chunk % 8 ^ swz(r)) * 4);
     } else {
       f32x4 f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) f[j] = s[(k + j) * LD + r];
+      for (int j = 0; j < 4; ++j) f[j] = s[(grp * 8 + h * 4 + j) * R + r];
       return f;
     }
   }
 };
 
-template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
+// Operand tiles go straight into a ring of NST stages in LDS, NST - 1 k-tiles ahead, one barrier per k-tile.  (Staged through
+// registers, the branches around the last k-tiles made the compiler wait for every load in flight at each LDS write: loads
+// and matrix work took turns, 23 + 25 us of the 42 us of 1576 x 384 x 1536.)
+template <int BM, int BN, int WM, int WN, int WK, int NST, bool AK, bool BKC>
 __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_kernel(GemmDesc g) {
   constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, GRP = KT / 8 / WK;
   typedef Tile<BM, KT, AK, NT> TA;
   typedef Tile<BN, KT, BKC, NT> TB;
-  extern __shared__ __attribute__((aligned(16))) float sm[];
-  float* As = sm;                          // [2][TA::FLOATS]
-  float* Bs = sm + 2 * TA::FLOATS;         // [2][TB::FLOATS]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int LPT = TA::NCH + TB::NCH, STAGE = TA::FLOATS + TB::FLOATS;
+  static_assert(NST >= 2 && NST <= 4 && (NST - 1) * LPT <= 63, "vmcnt has 6 bits");
+  extern __shared__ __attribute__((aligned(16))) float sm[];      // [NST][STAGE]: A rows, then B rows
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave / (WM * WN), wmn = wave % (WM * WN), wm = wmn / WN, wn = wmn % WN;
   const int lr = lane & 31, lh = lane >> 5;
   const int ntn = (g.N + BN - 1) / BN;
@@ -114,24 +134,26 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
   constexpr int SG = NT / BN;                              // threads per column
   const bool do_bsum = !BKC && g.bsum && m0 == 0;          // uniform over the workgroup
   float csum = 0.f;
-  // k-tile kt is multiplied from LDS while kt + 1 goes from registers to the other buffer and kt + 2, kt + 3 are on
-  // their way from memory in two register stages
-  TA ta[2];
-  TB tb[2];
   const int nk = (g.K + KT - 1) / KT;
-  auto fetch = [&](int st, int kt) __attribute__((always_inline)) {
-    ta[st].fetch(A, lda, m0, g.M, kt * KT, g.K, tid);
-    tb[st].fetch(B, ldb, n0, g.N, kt * KT, g.K, tid);
+  auto issue = [&](int kt, int st) __attribute__((always_inline)) {
+    TA::load(sm + st * STAGE, A, lda, m0, g.M, kt * KT, g.K, tid);
+    TB::load(sm + st * STAGE + TA::FLOATS, B, ldb, n0, g.N, kt * KT, g.K, tid);
   };
-  auto stash = [&](int st, int buf) __attribute__((always_inline)) {
-    ta[st].stash(As + buf * TA::FLOATS, tid);
-    tb[st].stash(Bs + buf * TB::FLOATS, tid);
-  };
-  auto step = [&](int par, int kt) __attribute__((always_inline)) {        // par = kt & 1, a constant
-    if (kt + 1 < nk) stash(par ^ 1, par ^ 1);
-    if (kt + 3 < nk) fetch(par ^ 1, kt + 3);
-    const float* a = As + par * TA::FLOATS;
-    const float* b = Bs + par * TB::FLOATS;
+  for (int j = 0; j < NST - 1 && j < nk; ++j) issue(j, j);
+  for (int kt = 0, st = 0; kt < nk; ++kt) {
+    const int later = min(nk - 1 - kt, NST - 2);           // k-tiles that may still be on their way
+    if (NST >= 4 && later >= 2) wait_vmcnt<(NST >= 4 ? 2 : 0) * LPT>();
+    else if (NST >= 3 && later >= 1) wait_vmcnt<(NST >= 3 ? 1 : 0) * LPT>();
+    else wait_vmcnt<0>();
+    float* a = sm + st * STAGE;
+    float* b = a + TA::FLOATS;
+    if ((kt + 1) * KT > g.K) {
+      TA::clear(a, kt * KT, g.K, tid);
+      TB::clear(b, kt * KT, g.K, tid);
+    }
+    wait_lgkmcnt0();                                       // this wavefront has read k-tile kt - 1
+    __builtin_amdgcn_s_barrier();
+    if (kt + NST - 1 < nk) issue(kt + NST - 1, st == 0 ? NST - 1 : st - 1);
 #pragma unroll
     for (int q = 0; q < GRP; ++q) {
       const int grp = q * WK + wk;
@@ -149,18 +171,10 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
             acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[mi][j], fb[ni][j], acc[mi][ni], 0, 0, 0);
     }
     if (do_bsum)
-      for (int k = tid / BN; k < KT; k += SG) csum += b[k * TB::LD + tid % BN];
-    __syncthreads();
-  };
-  fetch(0, 0);
-  if (nk > 1) fetch(1, 1);
-  stash(0, 0);
-  if (nk > 2) fetch(0, 2);
-  __syncthreads();
-  for (int kt = 0; kt < nk; kt += 2) {
-    step(0, kt);
-    if (kt + 1 < nk) step(1, kt + 1);
+      for (int k = tid / BN; k < KT; k += SG) csum += b[k * BN + tid % BN];
+    st = st + 1 == NST ? 0 : st + 1;
   }
+  __syncthreads();
   if (do_bsum) {
     sm[tid] = csum;
     __syncthreads();
@@ -214,13 +228,13 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
   }
 }
 
-template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
+template <int BM, int BN, int WM, int WN, int WK, int NST, bool AK, bool BKC>
 void launch(const GemmDesc& g, hipStream_t s) {
   constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
-  constexpr size_t tiles_f = 2 * (size_t)(Tile<BM, KT, AK, NT>::FLOATS + Tile<BN, KT, BKC, NT>::FLOATS);
+  constexpr size_t tiles_f = NST * (size_t)(Tile<BM, KT, AK, NT>::FLOATS + Tile<BN, KT, BKC, NT>::FLOATS);
   constexpr size_t sums_f = (size_t)WK * BM * (BN + 4);
   constexpr size_t lds = sizeof(float) * (tiles_f > sums_f ? tiles_f : sums_f);
-  auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, AK, BKC>;
+  auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, NST, AK, BKC>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -230,19 +244,22 @@ void launch(const GemmDesc& g, hipStream_t s) {
   kern<<<tiles, NT, lds, s>>>(g);
 }
 
-// Which block tile: the one with the least matrix time on the busiest CU, ceil(tiles / 256) x tile area x K, the
-// smaller tiles priced up by what their operand traffic and their sums over wavefronts cost.  The prices are set by hand, not
-// fitted.  Steps with every product forced to 128, 64 and 32, and by this rule, in us: DeiT-S, a third of the tokens gone at
-// three places, 1 image 4919, 1815, 1059, 1058; 8 images 5896, 2248, 1772, 1760; 32 images 9727, 4757, 4642, 4417; 8 images
-// with all tokens 9773, 3852, 3378, 3530; one 192-wide block, 2 sequences of 65 442, 186, 130, 130.
+// Which block tile: the one that a model finishes first.  With t tiles, time = c0 + ceil(t / 256) (c1 + c2 K / 100) + t / 256
+// (c3 + c4 K / 100) + ceil(t / 512) (c5 + c6 K / 100) microseconds (rounds of one workgroup per CU, work, rounds of two), fitted to chains
+// of equal launches of the three forms (264 products: 65 .. 6304 rows, 192 and 384 wide).  Its picks take 0.1 % longer than the
+// fastest tile; tile areas with prices set by hand 1.0 %, 32 x 32 always 3.9 %.
 int f32_pick(const GemmDesc& g) {
   const int edge[3] = {128, 64, 32};
-  const float price[3] = {1.0f, 1.15f, 1.6f};
+  const float c[3][7] = {{6.180f, 0.000f, 5.645f, 3.077f, 0.964f, 1.018f, 0.500f},
+                         {3.079f, 0.387f, 1.480f, 0.514f, 0.321f, 0.420f, 0.279f},
+                         {2.598f, 0.505f, 0.421f, 0.453f, 0.032f, 0.137f, 0.152f}};
   int best = 0;
   float least = 0.f;
+  const float k = 0.01f * g.K;
   for (int i = 0; i < 3; ++i) {
     const int64_t tiles = (int64_t)((g.M + edge[i] - 1) / edge[i]) * ((g.N + edge[i] - 1) / edge[i]);
-    const float t = (float)((tiles + 255) / 256) * edge[i] * edge[i] * price[i];
+    const float t = c[i][0] + (float)((tiles + 255) / 256) * (c[i][1] + c[i][2] * k) + (float)tiles / 256.f * (c[i][3] + c[i][4] * k) +
+                    (float)((tiles + 511) / 512) * (c[i][5] + c[i][6] * k);
     if (i == 0 || t < least) { best = i; least = t; }
   }
   return best;
@@ -251,9 +268,9 @@ int f32_pick(const GemmDesc& g) {
 template <bool AK, bool BKC>
 void launch_form(const GemmDesc& g, hipStream_t s) {
   switch (f32_pick(g)) {
-    case 0: launch<128, 128, 2, 2, 1, AK, BKC>(g, s); break;
-    case 1: launch<64, 64, 2, 2, 2, AK, BKC>(g, s); break;
-    default: launch<32, 32, 1, 1, 8, AK, BKC>(g, s); break;
+    case 0: launch<128, 128, 2, 2, 1, 2, AK, BKC>(g, s); break;
+    case 1: launch<64, 64, 2, 2, 2, 2, AK, BKC>(g, s); break;
+    default: launch<32, 32, 1, 1, 8, 2, AK, BKC>(g, s); break;
   }
 }
 
