@@ -207,15 +207,32 @@ void launch_fwd(const bf16* qkv, int B, int T, int H, bf16* out, float* lse, flo
 //   dK_j = sum_i dS_ij q_i,  dV_j = sum_i P_ij dO_i   (kernel "dkv": a wave owns 32 keys, sweeps
 //                                                      the query blocks)
 // Both recompute S with MFMAs; nothing T x T is stored or exchanged between wavefronts, and no
-// atomics are used.  As in the forward kernel the lane that owns the output row keeps the
+// atomics are used.  What bounds them is how many wavefronts a CU has to cover the chain read - MFMA - exp - MFMA.  "dq" runs all
+// ceil(T / 32) wavefronts of a head in one workgroup, in 128 registers, so that two heads share a CU, and writes 8-byte pieces:
+// 128 images of 12 heads at 197 tokens 89 -> 67 us (four wavefronts a workgroup, a head staged twice, 2-byte stores).  "dkv" has
+// four accumulators and needs 124 registers with its loop written out; held to 128 in workgroups of seven wavefronts it spills
+// (135 us), with the loop kept it takes 108, and 8-byte stores alone make it 93: so it stays at 84.  As in the forward kernel the lane that owns the output row keeps the
 // contraction index in accumulator order and the transposed operand in LDS is read in that order.
 
 __device__ inline bf16x8 lds_frag(const u32x4* rows, int row, int chunk) {
   return *(const bf16x8*)(rows + row * 8 + (chunk ^ swz(row)));
 }
 
+// 64 features of one row, features as rows of the accumulators, lane = row
+__device__ __forceinline__ void store_row(bf16* row, const f32x16 (&o)[2], int lh) {
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int rq = 0; rq < 4; ++rq) {
+      bf16x4 v4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v4[e] = (bf16)o[nb][4 * rq + e];
+      *(bf16x4*)(row + nb * 32 + 8 * rq + 4 * lh) = v4;
+    }
+}
+
 template <int NJ>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
+__global__ __launch_bounds__(NJ * 64, 4) void attn_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out,
                                                           const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                           int T, int H, float* __restrict__ delta,
                                                           bf16* __restrict__ dqkv) {
@@ -225,15 +242,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16* __restrict
   u32x4* Vs = Ks + Tpad * 8;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 31, lh = lane >> 5;
-  const int b = blockIdx.y / H, h = blockIdx.y % H;
+  const int b = blockIdx.x / H, h = blockIdx.x % H;
   const int D = H * HD;
   const int64_t rs = 3 * (int64_t)D;
   const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
-  load_k(base + D, rs, T, Tpad, Ks, tid);
-  load_k(base + 2 * D, rs, T, Tpad, Vs, tid);
+  load_k(base + D, rs, T, Tpad, Ks, tid, NJ * 64);
+  load_k(base + 2 * D, rs, T, Tpad, Vs, tid, NJ * 64);
   __syncthreads();
-  const int q0 = blockIdx.x * 128 + wave * 32;
-  if (q0 >= T) return;
+  const int q0 = wave * 32;
   const int qi = q0 + lr, qc = min(qi, T - 1);
   bf16x8 qf[4], dof[4];
   float dl = 0.f;
@@ -259,7 +275,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16* __restrict
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
-#pragma unroll
+#pragma nounroll
   for (int jb = 0; jb < NJ; ++jb) {
     f32x16 sa, dp;
 #pragma unroll
@@ -273,22 +289,16 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16* __restrict
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       float pr = __builtin_amdgcn_exp2f(sa[r] * c - l2);
-      if (key_of(jb, r, lh) >= T) pr = 0.f;
+      if (jb == NJ - 1 && key_of(jb, r, lh) >= T) pr = 0.f;
       dsf[r >> 3][r & 7] = (bf16)(pr * (dp[r] - dl) * 0.125f);
     }
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)
-        o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dsf[hf], lds_frag_t(Ks, nb, lane, 2 * jb + hf), o[nb], 0, 0, 0);
+        o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(Ks, nb, lane, 2 * jb + hf), dsf[hf], o[nb], 0, 0, 0);
   }
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = q0 + 8 * (r >> 2) + 4 * lh + (r & 3);
-      if (i < T) dqkv[((int64_t)b * T + i) * rs + h * HD + nb * 32 + lr] = (bf16)o[nb][r];
-    }
+  if (qi < T) store_row(dqkv + ((int64_t)b * T + qi) * rs + h * HD, o, lh);
 }
 
 template <int NJ>
@@ -391,7 +401,7 @@ void launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float*
     attr_set = true;
   }
   const dim3 grid((T + 127) / 128, B * H);
-  attn_bwd_dq_kernel<NJ><<<grid, 256, lds_q, s>>>(qkv, out, dout, lse, T, H, delta, dqkv);
+  attn_bwd_dq_kernel<NJ><<<B * H, NJ * 64, lds_q, s>>>(qkv, out, dout, lse, T, H, delta, dqkv);
   attn_bwd_dkv_kernel<NJ><<<grid, 256, lds_kv, s>>>(qkv, dout, lse, delta, T, H, dqkv);
 }
 
