@@ -71,6 +71,24 @@ __device__ inline int xcd_remap(int pid, int nblocks) {
   return x * base + min(x, rem) + local;
 }
 
+// Grouped form: row tiles count group after group (a group's last tile may be partial).  Row tile mt belongs to the group whose
+// weights, bias and rows (from m0 on, up to g.M) g then describes; false: past the last group, nothing to do.
+template <int BM>
+__device__ __forceinline__ bool group_tile(GemmDesc& g, int mt, int& m0) {
+  for (int e = 0; e < g.groups; ++e) {
+    const int r0 = g.grp_off[e], r1 = g.grp_off[e + 1], n = (r1 - r0 + BM - 1) / BM;
+    if (mt < n) {
+      m0 = r0 + mt * BM;
+      g.M = r1;
+      g.B = (const bf16*)g.B + (int64_t)e * g.b_gs;
+      if (g.bias) g.bias += (int64_t)e * g.bias_gs;
+      return true;
+    }
+    mt -= n;
+  }
+  return false;
+}
+
 // Eight consecutive columns of output row m, accumulated in fp32: the statistics of a folded LayerNorm, bias,
 // positional embedding (with the row remap of the patch embedding), GELU with its stored pre-activation or
 // GELU', the residual, and the store (16 bytes of bf16, or 32 bytes of fp32).
@@ -207,25 +225,7 @@ void gemm_nt_kernel(GemmDesc g) {
   const int tile = xcd_remap(blockIdx.x, (int)gridDim.x);
   int m0 = (tile / ntn) * BM;
   const int n0 = (tile % ntn) * BN;
-  if (g.grp_off) {
-    // grouped form: the tile index counts row tiles group after group (a group's last tile may be
-    // partial); workgroups past the last group have nothing to do
-    int mt = tile / ntn, e = 0, found = 0;
-    for (; e < g.groups; ++e) {
-      const int r0 = g.grp_off[e], r1 = g.grp_off[e + 1];
-      const int nt_e = (r1 - r0 + BM - 1) / BM;
-      if (mt < nt_e) {
-        m0 = r0 + mt * BM;
-        g.M = r1;                                   // rows of this tile stop at the end of its group
-        found = 1;
-        break;
-      }
-      mt -= nt_e;
-    }
-    if (!found) return;
-    g.B = (const bf16*)g.B + (int64_t)e * g.b_gs;
-    if (g.bias) g.bias += (int64_t)e * g.bias_gs;
-  }
+  if (g.grp_off && !group_tile<BM>(g, tile / ntn, m0)) return;
   const bf16* __restrict__ A = (const bf16*)g.A;
   const bf16* __restrict__ Bt = (const bf16*)g.B;
 
@@ -594,7 +594,7 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
 
 // The work of one tile (a kernel of its own below, and the input-gradient half of a layer's backward launch).
 template <int BM, int BN, int WM, int WN, int NST>
-__device__ __forceinline__ void ntd_body(const GemmDesc& g, int tile) {
+__device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, NMF = MI * NI, NFR = MI + NI;
   constexpr int RPI = NT / 8;                       // tile rows one load instruction of the workgroup fills
@@ -609,7 +609,9 @@ __device__ __forceinline__ void ntd_body(const GemmDesc& g, int tile) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int ntn = (g.N + BN - 1) / BN;
-  const int m0 = (tile / ntn) * BM, n0 = (tile % ntn) * BN;
+  int m0 = (tile / ntn) * BM;
+  const int n0 = (tile % ntn) * BN;
+  if (g.grp_off && !group_tile<BM>(g, tile / ntn, m0)) return;
   const bf16* __restrict__ A = (const bf16*)g.A;
   const bf16* __restrict__ Bt = (const bf16*)g.B;
 
@@ -752,7 +754,8 @@ void launch_ntd(const GemmDesc& g, hipStream_t s) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_tiles);
     attr_set = true;
   }
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  // grouped: every group may end in one partial row tile
+  const int tiles = ((g.M + BM - 1) / BM + (g.grp_off ? g.groups : 0)) * ((g.N + BN - 1) / BN);
   kern<<<tiles, WM * WN * 64, lds_tiles, s>>>(g);
 }
 // The kernels that load straight into LDS hold an operand's row offsets in 32 bits (elements): larger operands, such as the
@@ -760,8 +763,8 @@ void launch_ntd(const GemmDesc& g, hipStream_t s) {
 bool offsets_fit(const GemmDesc& g) {
   return (int64_t)g.M * g.a_rs <= (int64_t)UINT32_MAX && (int64_t)g.N * g.b_cs <= (int64_t)UINT32_MAX;
 }
-// what the direct-to-LDS kernels take: whole k-tiles, one weight matrix, no folded LayerNorm
-bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.grp_off && !g.ln_colsum && offsets_fit(g); }
+// what the direct-to-LDS kernels take: whole k-tiles, no folded LayerNorm
+bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.ln_colsum && offsets_fit(g); }
 
 // ------------------------------------------------------------------------------------------ NT, few rows
 // The same product where block tiles shared by eight wavefronts would leave most CUs idle.  A workgroup owns
@@ -1459,11 +1462,11 @@ bool gemm_mfma_supported(const GemmDesc& g) { return is_nt(g) || is_tn(g); }
 // has measured to be (bsr_autotune).  Every shape accumulates an output element over k in the same order, so the choice
 // never changes a result.
 static const int kNtShapes[] = {
-    // staged through registers; what folds a LayerNorm, has a ragged K or runs group by group has these only
+    // staged through registers; what folds a LayerNorm or has a ragged K has these only
     256128, 128128, 192128, 160256, 256256, 128064, 64128,
     3128064,                              // with deeper register prefetch (id = PF * 1000000 + shape)
-    // operands straight into LDS (id = 7000000 + shape, 8000000 + shape with one stage more; K a multiple of 64, one weight
-    // matrix, no folded LayerNorm: a launch outside that takes the model's shape instead)
+    // operands straight into LDS (id = 7000000 + shape, 8000000 + shape with one stage more; K a multiple of 64, no
+    // folded LayerNorm: a launch outside that takes the model's shape instead)
     7256256, 7320256, 7192256, 7256192, 7256128, 7128256, 7192128, 7128128, 7128064, 7064128, 7096128, 8192128, 8128128,
 };
 // stages of the direct-to-LDS shapes (0: not one of them)
@@ -1515,7 +1518,8 @@ static int nt_pick(const GemmDesc& g, float* us_out) {
   for (int i = 0; i < n; ++i) {
     const NtModel& e = table[i];
     if (g.ln_colsum && e.bn < 128) continue;
-    const int64_t t = (int64_t)((g.M + e.bm - 1) / e.bm) * ((g.N + e.bn - 1) / e.bn);
+    // (a group ends in a partial row tile: half a tile each)
+    const int64_t t = (int64_t)((g.M + e.bm - 1) / e.bm + (g.grp_off ? g.groups / 2 : 0)) * ((g.N + e.bn - 1) / e.bn);
     const float r1 = (float)((t + 255) / 256), w = (float)t / 256.f, r2 = (float)((t + 511) / 512);
     const float us = e.c[0] + r1 * (e.c[1] + e.c[2] * k + e.c[7] * gelu) + w * (e.c[3] + e.c[4] * k + e.c[8] * gelu) +
                      r2 * (e.c[5] + e.c[6] * k) - (direct ? 0.f : EVENTS_US);
@@ -1542,7 +1546,7 @@ static int few_rows_shape(const GemmDesc& g) {
   nt_pick(g, &tiled_us);
   return few_us < FEW_LEAD * tiled_us ? few : -1;
 }
-static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && is_tn(tn) && !tn.grp_off; }
+static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && !nt.grp_off && is_tn(tn) && !tn.grp_off; }
 static int few_rows_shape(const GemmDesc& nt, const GemmDesc& tn, const TnSplit& pair) {
   if (!can_pair(nt, tn)) return few_rows_shape(nt);
   float few_us = 0.f;
@@ -1571,9 +1575,7 @@ void gemm_tn_flush(TnChain* chain, hipStream_t s) {
 
 // The tiled kernels, in the shape asked for or, for 0 and for a shape that cannot take the product, the model's.
 static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
-  // groups are a few hundred rows and each ends in a partial row tile: 128-row tiles, 64-row ones where a group
-  // averages under four of those (the last tile of a 268-row group is 9 % full at 128 rows, 19 % at 64)
-  int pick = g.grp_off ? (g.M < 512 * g.groups ? 64128 : 128128) : tile;
+  int pick = g.grp_off ? 0 : tile;
   if (!pick || (ntd_stages(pick) && !is_ntd(g))) { float us = 0.f; pick = nt_pick(g, &us); }
   switch (pick) {
     case 7256256: launch_ntd<256, 256, 2, 4, 2>(g, s); break;
