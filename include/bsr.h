@@ -269,7 +269,7 @@ int32_t bsr_autotune(bsr_ctx* ctx, const void* input, const int32_t* labels, int
  * iteration ahead of the trainable part on `side_stream` (reading x_frozen), ordered as
  * bsr_pipeline_step orders them, every launch with the shape under test; in place of the optimizer
  * step the bf16 copies of the trainable weights are rebuilt (no weight changes).  Three runs per shape,
- * over the shapes whose workgroups leave room for a second one on a compute unit.  The fastest shape
+ * over the shapes whose workgroups leave room for a second one on a compute unit, and once more with the model's shapes.  The fastest
  * is then used for every launch of a batch of size B.  The choice replaces the one of bsr_autotune (a
  * context holds one).  BLOCKS until both streams have drained.
  * Errors: as bsr_autotune; INVALID_ARG for a missing second buffer or stream; BAD_CONFIG when the

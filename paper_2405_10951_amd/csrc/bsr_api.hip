@@ -484,7 +484,7 @@ TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s, const GemmD
   const size_t site = t.site++;
   if (t.cand >= 0) {
     const int cand = (t.kind == 1 && t.cand_train >= 0) ? t.cand_train : t.cand;
-    ch.tile = gemm_nt_tile_id(cand);
+    ch.tile = cand < gemm_nt_tile_count() ? gemm_nt_tile_id(cand) : 0;
     ch.rec = TuneRec{t.kind, cand, site, g.M, g.N, g.K, gemm_nt_model_tile(g, wgrad, c->b.splitk_floats, true), nullptr, nullptr};
     ch.timing = hipEventCreate(&ch.rec.start) == hipSuccess && hipEventCreate(&ch.rec.stop) == hipSuccess;
     if (ch.timing) (void)hipEventRecord(ch.rec.start, s);
@@ -1257,11 +1257,11 @@ static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_par
 // The two-stream schedule is not tuned launch by launch.  Side by side, a launch cannot be judged by its own
 // time: a shape whose workgroup fills the LDS of a CU is quick by itself and stalls whatever runs on the other
 // stream, and with the GPU always full it is the work per CU-second that counts, not how evenly one launch
-// alone fills the chip.  (Measured on a ViT-B/16 step, batch 32: the per-launch best of all shapes timed alone gives
-// 2.13 ms pipelined, 192 x 128 forced everywhere 2.03 ms; per-launch event times taken side by side chose
-// worse than that, too.)  So the choice is one shape for all launches, among the shapes that leave room for a
-// second workgroup on a CU (two tile buffers of at most 80 KB; the shape id is [prefetch depth] BM BN in
-// decimal), and what is timed is a whole side-by-side pass.
+// alone fills the chip.  So what is timed is a whole side-by-side pass: with one shape for all launches, among the shapes that
+// leave room for a second workgroup on a CU (stages of at most 80 KB; the shape id is [family] BM BN in
+// decimal), and with every launch in the shape the model gives it, which since the backward launches hold a CU by themselves
+// is mostly the fastest (ViT-B/16: batch 32 1784 us, best single shape 1910, every launch's own best timed alone 1794; batch 12 1123,
+// 1141, 1132; batch 64 2962, 3064, 2964; DeiT-S batch 32 860, 858, 870).
 static bool shares_a_cu(int tile_id) { return gemm_nt_tile_lds_bytes(tile_id) <= 80 * 1024; }
 
 static int32_t autotune_overlapped(bsr_ctx* c, const void* input, const int32_t* labels, int32_t B, void* x_frozen,
@@ -1330,6 +1330,7 @@ static int32_t autotune_overlapped(bsr_ctx* c, const void* input, const int32_t*
   std::vector<int> cands;
   for (int j = 0; j < n; ++j)
     if (shares_a_cu(gemm_nt_tile_id(j))) cands.push_back(j);
+  cands.push_back(n);                                     // every launch in the shape that the model gives it
   // the shape with the shortest pass, three tries each.  (Refining it into one shape for the prefix and another
   // for the trainable part was tried: the passes differ by less than they scatter, and the refined pairs ran
   // 4 - 6 % slower in the pipeline than the single shape.)
@@ -1358,7 +1359,8 @@ static int32_t autotune_overlapped(bsr_ctx* c, const void* input, const int32_t*
         if (r.kind != k) continue;
         TunePick& p = t.pick[k][r.site];
         p.M = r.M; p.N = r.N; p.K = r.K; p.model = r.model;
-        p.tile = r.model >= FEW_ROWS_ID ? r.model : gemm_nt_tile_id(k == 0 ? fz : tr);
+        const int shape = k == 0 ? fz : tr;
+        p.tile = r.model >= FEW_ROWS_ID || shape == n ? r.model : gemm_nt_tile_id(shape);
       }
       launches += (int)sites[k];
     }
