@@ -3,8 +3,8 @@
 // product, beyond that keys come in chunks and probabilities stay in fp32 (second half of the file).  The CLS row of the
 // softmax map, which Eq. 6 ranks tokens by, leaves the forward kernel in fp32 as a by-product.
 //
-// Forward.  One workgroup = one (image, head): K and V of the head are staged once, and each of
-// its ceil(T / 32) wavefronts owns 32 queries.  K and V sit in LDS row-major (swizzled 16-byte chunks);
+// Forward.  One workgroup = one (image, head), or half the queries of one where there are few: K and V of the head are staged
+// once, and each of its wavefronts owns 32 queries.  K and V sit in LDS row-major (swizzled 16-byte chunks);
 // V^T fragments come from the LDS transpose read.  The wave computes S^T = K Q^T with 32x32x16 MFMAs, so that a
 // lane owns one query and the softmax reductions over keys are in-register (plus one exchange between
 // the two halves of the wave).  The normalised P^T accumulators are, as they lie in registers, an
@@ -39,10 +39,8 @@ __device__ inline int swz(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2
 // key index of accumulator element r (of key block jb) held by a lane of wave half lh
 __device__ inline int key_of(int jb, int r, int lh) { return jb * 32 + 8 * (r >> 2) + 4 * lh + (r & 3); }
 
-// K rows [T,64] of one head -> LDS chunks; rows >= T are zero.
-__device__ inline void load_k(const bf16* base, int64_t row_stride, int T, int Tpad, u32x4* Ks, int tid,
-                              int nthreads = 256) {
-  // four loads in flight per thread before the first LDS write: one trip to memory instead of four
+// Rows [T,64] of one operand of one head -> LDS chunks; rows >= T are zero.
+__device__ inline void load_one(const bf16* base, int64_t row_stride, int T, int Tpad, u32x4* Ks, int tid, int nthreads) {
   const int total = Tpad * 8;
   for (int c0 = tid; c0 < total; c0 += 4 * nthreads) {
     u32x4 v[4];
@@ -56,6 +54,32 @@ __device__ inline void load_k(const bf16* base, int64_t row_stride, int T, int T
     for (int u = 0; u < 4; ++u) {
       const int c = c0 + u * nthreads, row = c >> 3, kc = c & 7;
       if (c < total) Ks[row * 8 + (kc ^ swz(row))] = v[u];
+    }
+  }
+}
+// K and V of one head together
+__device__ inline void load_two(const bf16* x, int64_t xs, const bf16* y, int64_t ys, int T, int Tpad, u32x4* Xs, u32x4* Ys, int tid,
+                                int nthreads) {
+  // four loads of either operand in flight per thread before the first LDS write: one trip to memory
+  const int total = Tpad * 8;
+  for (int c0 = tid; c0 < total; c0 += 4 * nthreads) {
+    u32x4 v[4], w[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = c0 + u * nthreads, row = c >> 3, kc = c & 7;
+      v[u] = w[u] = u32x4{0u, 0u, 0u, 0u};
+      if (c < total && row < T) {
+        v[u] = *(const u32x4*)(x + (int64_t)row * xs + kc * 8);
+        w[u] = *(const u32x4*)(y + (int64_t)row * ys + kc * 8);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = c0 + u * nthreads, row = c >> 3, kc = c & 7;
+      if (c < total) {
+        Xs[row * 8 + (kc ^ swz(row))] = v[u];
+        Ys[row * 8 + (kc ^ swz(row))] = w[u];
+      }
     }
   }
 }
@@ -82,7 +106,7 @@ template <int NJ>
 __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, int T, int H,
                                                                bf16* __restrict__ out, float* __restrict__ lse,
                                                                float* __restrict__ cls_prob) {
-  constexpr int Tpad = NJ * 32, NTH = NJ * 64;
+  constexpr int Tpad = NJ * 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u32x4* Ks = (u32x4*)smem;                         // [Tpad][8 chunks]
   u32x4* Vs = Ks + Tpad * 8;                        // [Tpad][8 chunks]
@@ -92,7 +116,7 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
   const int D = H * HD;
   const int64_t rs = 3 * (int64_t)D;
   const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
-  const int q0 = wave * 32;                         // wave w owns queries 32 w .. 32 w + 31 (q0 < T always)
+  const int q0 = (blockIdx.y * (blockDim.x >> 6) + wave) * 32;      // a wave owns 32 queries
   // Q fragments straight from global memory, requested before K and V are staged so that their
   // latency is hidden: lane (query lr, half lh) needs chunks 2 ks + lh
   bf16x8 qf[4];
@@ -101,9 +125,9 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) qf[ks] = *(const bf16x8*)(qrow + (2 * ks + lh) * 8);
   }
-  load_k(base + D, rs, T, Tpad, Ks, tid, NTH);
-  load_k(base + 2 * D, rs, T, Tpad, Vs, tid, NTH);
+  load_two(base + D, rs, base + 2 * D, rs, T, Tpad, Ks, Vs, tid, blockDim.x);
   __syncthreads();
+  if (q0 >= T) return;
 
   // S^T[key, query] = K Q^T
   f32x16 s[NJ];
@@ -195,7 +219,10 @@ void launch_fwd(const bf16* qkv, int B, int T, int H, bf16* out, float* lse, flo
     (void)hipFuncSetAttribute((const void*)attn_fwd_mfma_kernel<NJ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr_set = true;
   }
-  attn_fwd_mfma_kernel<NJ><<<B * H, NJ * 64, lds, s>>>(qkv, T, H, out, lse, cls_prob);
+  // Few heads leave CUs idle: their queries go to two workgroups then, which both stage K and V: one image of
+  // 12 heads, 197 tokens 8.0 -> 7.4 us.  (From 128 heads on two workgroups a head are more than one a CU.)
+  const int parts = NJ > 1 && B * H <= 128 ? 2 : 1;
+  attn_fwd_mfma_kernel<NJ><<<dim3(B * H, parts), (NJ + parts - 1) / parts * 64, lds, s>>>(qkv, T, H, out, lse, cls_prob);
 }
 
 
@@ -246,8 +273,7 @@ __global__ __launch_bounds__(NJ * 64, 4) void attn_bwd_dq_kernel(const bf16* __r
   const int D = H * HD;
   const int64_t rs = 3 * (int64_t)D;
   const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
-  load_k(base + D, rs, T, Tpad, Ks, tid, NJ * 64);
-  load_k(base + 2 * D, rs, T, Tpad, Vs, tid, NJ * 64);
+  load_two(base + D, rs, base + 2 * D, rs, T, Tpad, Ks, Vs, tid, NJ * 64);
   __syncthreads();
   const int q0 = wave * 32;
   const int qi = q0 + lr, qc = min(qi, T - 1);
@@ -318,8 +344,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16* __restric
   const int64_t rs = 3 * (int64_t)D;
   const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
   const bf16* dobase = dout + (int64_t)b * T * D + h * HD;
-  load_k(base, rs, T, Tpad, Qs, tid);
-  load_k(dobase, D, T, Tpad, dOs, tid);
+  load_one(base, rs, T, Tpad, Qs, tid, 256);        // (both at once: registers that this kernel needs, 84 -> 88 us)
+  load_one(dobase, D, T, Tpad, dOs, tid, 256);
   for (int i = tid; i < Tpad; i += 256) {
     lse_s[i] = (i < T) ? lse[((int64_t)b * H + h) * T + i] * 1.44269504088896341f : INFINITY;
     del_s[i] = (i < T) ? delta[((int64_t)b * H + h) * T + i] : 0.f;
