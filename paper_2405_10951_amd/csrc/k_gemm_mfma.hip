@@ -925,15 +925,16 @@ void launch_few(const GemmDesc& g, hipStream_t s) {
   else launch_few_as<MI, NI, false>(g, s);
 }
 // 32 x 64 tiles are never ahead of both 64 x 32 and 64 x 64.
-// Modelled time of a product here, in microseconds: launch and epilogue, then ceil(tiles / 256) rounds of a start-up
-// and the tile's operand bytes.  Constants fitted to chains of equal launches at 1 .. 2144 rows, N and K of 384 .. 3072
-// (within 15 % where the kernel is the faster one).
-struct FewShape { int mi, ni; float launch_us, round_us, bytes_per_us; };
-const FewShape kFewShapes[] = {{1, 1, 2.6f, 0.5f, 105e3f}, {2, 1, 2.8f, 0.5f, 103e3f}, {2, 2, 3.3f, 1.0f, 65e3f}};
-// A product on its own comes here when the model gives it this lead over the tiled kernels' model.  Chains of equal launches
-// at 32 .. 2144 rows (108 products, 384 and 768 wide): 0.8 loses 0.04 % to the faster of the two, 0.7 2.1 %, 0.9 1.7 %, 1.0 2.9 % (the
-// model of this kernel is short by half where a launch takes several rounds).
-constexpr float FEW_LEAD = 0.8f;
+// Modelled time of a product here, in microseconds, in the form of the tiled kernels' model: with t tiles, c0 +
+// ceil(t / 256) (c1 + c2 K / 64) + t / 256 (c3 + c4 K / 64) + ceil(t / 512) (c5 + c6 K / 64), and t / 256 c7 where a GELU is applied.
+// Constants fitted to chains of equal launches at 32 .. 2144 rows, N and K of 384 .. 3072 (108 products): the picks take 0.4 % longer than the
+// fastest of the three (a rate per CU and whole rounds of tiles: 5.5 %; 32 x 32 tiles share a CU, which that left out).
+struct FewShape { int mi, ni; float c[8]; };
+const FewShape kFewShapes[] = {{1, 1, {1.870f, 0.140f, 0.068f, 0.000f, 0.022f, 0.841f, 0.000f, 0.102f}},
+                               {2, 1, {1.672f, 1.466f, 0.090f, 0.000f, 0.072f, 0.000f, 0.000f, 0.143f}},
+                               {2, 2, {1.598f, 2.827f, 0.154f, 0.039f, 0.092f, 0.000f, 0.000f, 0.414f}}};
+// A product on its own comes here when this model gives it less than that of the tiled kernels: 0.2 % over the faster of the
+// two on the same products (with a lead of 0.9 asked for 0.5 %, of 0.8 1.9 %).
 
 // The shape of this kernel for a product and what the model gives it; -1: not one it takes
 int few_pick(const GemmDesc& g, float* us) {
@@ -942,7 +943,9 @@ int few_pick(const GemmDesc& g, float* us) {
     for (int i = 0; i < 3; ++i) {
       const FewShape& f = kFewShapes[i];
       const int64_t tiles = (int64_t)((g.M + 32 * f.mi - 1) / (32 * f.mi)) * ((g.N + 32 * f.ni - 1) / (32 * f.ni));
-      const float t = f.launch_us + (float)((tiles + 255) / 256) * (f.round_us + 64.f * (f.mi + f.ni) * g.K / f.bytes_per_us);
+      const float k = g.K / 64, w = (float)tiles / 256.f;
+      const float t = f.c[0] + (float)((tiles + 255) / 256) * (f.c[1] + f.c[2] * k) + w * (f.c[3] + f.c[4] * k + (g.act == ACT_NONE ? 0.f : f.c[7])) +
+                      (float)((tiles + 511) / 512) * (f.c[5] + f.c[6] * k);
       if (pick < 0 || t < *us) { pick = i; *us = t; }
     }
   return pick;
@@ -1544,7 +1547,7 @@ static int few_rows_shape(const GemmDesc& g) {
   const int few = few_pick(g, &few_us);
   if (few < 0) return -1;
   nt_pick(g, &tiled_us);
-  return few_us < FEW_LEAD * tiled_us ? few : -1;
+  return few_us < tiled_us ? few : -1;
 }
 static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && !nt.grp_off && is_tn(tn) && !tn.grp_off; }
 static int few_rows_shape(const GemmDesc& nt, const GemmDesc& tn, const TnSplit& pair) {
