@@ -9,7 +9,7 @@
 // group of 8 features uses feature 4 h + j for wave half h and a lane reads four consecutive floats; and the
 // accumulator of the scores, whose element r holds row 8 (r / 4) + 4 h + r % 4, is itself the operand of the second
 // product, with the other operand read in that row order.
-// 8 images of 6 heads at 197 .. 67 tokens: forward 53 -> 12 us on average, backward 72 -> 23 us, against one wavefront
+// 8 images of 6 heads at 197 .. 67 tokens: forward 53 -> 12 us on average, backward 72 -> 18 us, against one wavefront
 // per row on the vector unit.
 #include "bsr_internal.h"
 
@@ -151,10 +151,23 @@ __device__ inline void reduce_store(const f32x16 (&o)[2], float (*os)[2][16][64]
   }
 }
 
+// the 32 x 64 operand of the second product as its MFMAs take it: row row_of(r), feature 32 nb + lane % 32
+__device__ __forceinline__ void load_rows_t(const float* base, int64_t rs, int r0, int T, int lr, int lh, float (&v)[2][16]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float* row = base + (int64_t)min(r0 + row_of(r, lh), T - 1) * rs + lr;
+    v[0][r] = row[0];
+    v[1][r] = row[32];
+  }
+}
+
 // Backward (Eq. 3, 5): P = exp(s / 8 - lse), dP = dO . v, delta = dO . O, dS = P (dP - delta) / 8.
 // Workgroups [0, nb): dQ of 32 queries, the wavefronts share the keys; [nb, 2 nb): dK and dV of 32 keys, the
 // wavefronts share the queries (delta is taken again from rows they read anyway, so both run in one launch).
-__global__ __launch_bounds__(NW * 64) void attn_f32_bwd_kernel(const float* __restrict__ qkv, const float* __restrict__ out,
+// Bound by the wait for a block's rows before each of its products: the operands of all four are asked for ahead of
+// the first that needs them, so one wait is left per block.  8 images of 6 heads, 197 tokens and the selected ones
+// after them, three launches: 70 -> 53 us; 2 images of 3 heads at 65 tokens: 15.1 -> 12.7 us.
+__global__ __launch_bounds__(NW * 64, 2) void attn_f32_bwd_kernel(const float* __restrict__ qkv, const float* __restrict__ out,
                                                               const float* __restrict__ dout, const float* __restrict__ lse, int T,
                                                               int H, float* __restrict__ dqkv) {
   __shared__ float os[NW][2][16][64];
@@ -187,21 +200,21 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_bwd_kernel(const float* __re
     zero(o[1]);
     for (int k0 = wave * 32; k0 < T; k0 += NW * 32) {
       const float* krow = base + D + (int64_t)min(k0 + lr, T - 1) * rs;
-      f32x4 f[8];
+      f32x4 f[8], f2[8];
       load_row(krow, lh, f);
+      load_row(krow + D, lh, f2);
       f32x16 s = row_products(f, qf);                          // row = key, lane = query
-      load_row(krow + D, lh, f);
-      const f32x16 dp = row_products(f, dof);
+      float kt[2][16];                                         // on its way while dP is multiplied
+      load_rows_t(base + D, rs, k0, T, lr, lh, kt);
+      const f32x16 dp = row_products(f2, dof);
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         s[r] = k0 + row_of(r, lh) < T ? expf(s[r] * 0.125f - ls) * (dp[r] - dl) * 0.125f : 0.f;
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float k = base[D + (int64_t)min(k0 + row_of(r, lh), T - 1) * rs + nb * 32 + lr];
-          o[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(s[r], k, o[nb], 0, 0, 0);      // row = query, lane = feature
-        }
+        for (int r = 0; r < 16; ++r)
+          o[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(s[r], kt[nb][r], o[nb], 0, 0, 0);      // row = query, lane = feature
     }
     reduce_store(o, os, dbase, rs, q0, T, wave, lane);
     return;
@@ -214,12 +227,14 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_bwd_kernel(const float* __re
   zero(ok[0]); zero(ok[1]); zero(ov[0]); zero(ov[1]);
   for (int i0 = wave * 32; i0 < T; i0 += NW * 32) {
     const int ic = min(i0 + lr, T - 1);
-    f32x4 f[8];
+    f32x4 f[8], f2[8];
     load_row(base + (int64_t)ic * rs, lh, f);
+    load_row(dobase + (int64_t)ic * D, lh, f2);
     f32x16 s = row_products(f, kf);                            // row = query, lane = key
-    load_row(dobase + (int64_t)ic * D, lh, f);
-    f32x16 dp = row_products(f, vf);
-    const float dl = delta_of(ic, f), ls = lrow[ic];
+    const float dl = delta_of(ic, f2), ls = lrow[ic];
+    f32x16 dp = row_products(f2, vf);
+    float gt[2][16], qt[2][16];                                // dO and Q as the second products take them
+    load_rows_t(dobase, D, i0, T, lr, lh, gt);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int i = row_of(r, lh);
@@ -228,13 +243,13 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_bwd_kernel(const float* __re
       s[r] = p;
       dp[r] = p * (dp[r] - di) * 0.125f;
     }
+    load_rows_t(base, rs, i0, T, lr, lh, qt);
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int64_t i = min(i0 + row_of(r, lh), T - 1);
-        ov[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(s[r], dobase[i * D + nb * 32 + lr], ov[nb], 0, 0, 0);
-        ok[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dp[r], base[i * rs + nb * 32 + lr], ok[nb], 0, 0, 0);
+        ov[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(s[r], gt[nb][r], ov[nb], 0, 0, 0);
+        ok[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(dp[r], qt[nb][r], ok[nb], 0, 0, 0);
       }
   }
   reduce_store(ok, os, dbase + D, rs, j0, T, wave, lane);
