@@ -269,8 +269,8 @@ int32_t bsr_autotune(bsr_ctx* ctx, const void* input, const int32_t* labels, int
  * iteration ahead of the trainable part on `side_stream` (reading x_frozen), ordered as
  * bsr_pipeline_step orders them, every launch with the shape under test; in place of the optimizer
  * step the bf16 copies of the trainable weights are rebuilt (no weight changes).  Three runs per shape,
- * over the shapes whose workgroups leave room for a second one on a compute unit, and once more with the model's shapes.  The fastest
- * is then used for every launch of a batch of size B.  The choice replaces the one of bsr_autotune (a
+ * over the shapes whose workgroups leave room for a second one on a compute unit, and once more with the
+ * model's shape at every launch.  The fastest is then used for every launch of a batch of size B.  The choice replaces the one of bsr_autotune (a
  * context holds one).  BLOCKS until both streams have drained.
  * Errors: as bsr_autotune; INVALID_ARG for a missing second buffer or stream; BAD_CONFIG when the
  * model has no frozen prefix.
@@ -282,7 +282,7 @@ int32_t bsr_autotune_overlapped(bsr_ctx* ctx, const void* input, const int32_t* 
 /*
  * The tile choices a context holds after bsr_autotune / bsr_autotune_overlapped, for inspection and reports (host
  * only).  part 0: the launches of bsr_forward_frozen in launch order, part 1: those of bsr_train_blocks_fwd_bwd
- * (a backward launch carries the input gradient named here and, fused with it, the weight gradient of its layer).
+ * (a backward launch carries the input gradient named here and, in the same launch, the weight gradient of its layer).
  *   rows, out, in  the product: rows x in times in x out      tile  shape id (see bsr_gemm_tile_shapes), or
  *                  9000000 + 1000 rows + columns of a tile of the kernel for products of few rows
  *   microseconds   what bsr_autotune measured for that shape at that launch (0 after bsr_autotune_overlapped,
@@ -372,7 +372,7 @@ int32_t bsr_adamw_step(bsr_ctx* ctx, const bsr_params* grads, const bsr_params* 
  *   w_s   bf16 copy of W stored [in,out]        u     [M,in], may be NULL
  * tile (both): 0, or the id of a block-tile shape (bsr_gemm_tile_shapes) the MFMA kernel is to use; a shape that
  *   cannot take the product (a direct-to-LDS shape when `in` / `out` to contract over is not a multiple of 64)
- *   gives way to the default, and a product of few rows (by its sizes alone: where the kernel for those is clearly
+ *   gives way to the default, as do ids of shapes that earlier versions listed, and a product of few rows (by its sizes alone: where the kernel for those is clearly
  *   the faster one) runs that kernel whatever the tile.  Every tile gives the same bits.  An unknown id: INVALID_ARG.
  * bsr_linear_wgrad (Eq. 4): dw[in,out] (fp32) = x[M,in]^T . dy[M,out], summed over all M rows.
  *   db         fp32 [out], may be NULL: the bias gradient, db[o] = sum over rows of dy[:,o], from the

@@ -98,6 +98,8 @@ constexpr int FEW_ROWS_ID = 9000000;           // + 1000 rows + columns: a tile 
 // call); from FEW_ROWS_ID on: whatever is asked for
 int gemm_nt_model_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained);
 int gemm_nt_tile_id(int i);
+// an id that the entry points take: 0, a shape above, or one that was a shape once (the model chooses in its place)
+bool gemm_nt_tile_known(int id);
 size_t gemm_nt_tile_lds_bytes(int id);          // dynamic LDS a workgroup of that shape holds
 bool gemm_nt_tile_is_free(const GemmDesc& g);
 size_t gemm_splitk_ws_floats(int dim, int mlp_hidden);

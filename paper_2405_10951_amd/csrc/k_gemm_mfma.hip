@@ -1,6 +1,6 @@
 // bf16 MFMA GEMMs for gfx950 (CDNA4), the hot kernels of the BSR step.
 //
-// Two kernels, both C = epilogue(sum_k A(m,k) B(k,n)) with fp32 accumulation in
+// Two forms, both C = epilogue(sum_k A(m,k) B(k,n)) with fp32 accumulation in
 // v_mfma_f32_32x32x16_bf16 tiles staged through LDS:
 //   NT: A[M,K] and B^T[N,K] both have the contraction index contiguous.  Covers the forward linears
 //       (activations x bf16 weight copy stored [out,in]) and the input gradients of Eq. 2
@@ -9,11 +9,14 @@
 //       weight gradients of Eq. 4, dW = X^T dY, contraction over all tokens of the batch.
 //
 // Block tile BM x BN x 64 shared by WM x WN wavefronts, each owning a wave tile of 32x32 MFMA tiles.
-// LDS is double buffered; the next k-tile waits in registers while the current one feeds the
-// matrix cores.  Workgroups are renumbered so that each XCD (the hardware deals consecutive
+// Tiles come straight from global memory into two to four stages of LDS (gemm_ntd_kernel: every wavefront
+// loads; gemm_pair_kernel and gemm_tn_kernel: wavefronts of their own do); products whose k-tiles cannot be
+// loaded that way wait in registers while the k-tile before feeds the matrix cores (gemm_nt_kernel), and
+// products of few rows share k between wavefronts (gemm_nt_few_kernel).  Workgroups are renumbered so that each XCD (the hardware deals consecutive
 // workgroup ids round-robin over 8 XCDs) works on a contiguous range of tiles and its L2 sees whole
 // operand panels.
 #include <algorithm>
+#include <iterator>
 #include <utility>
 
 #include "bsr_internal.h"
@@ -1472,6 +1475,9 @@ static const int kNtShapes[] = {
     // folded LayerNorm: a launch outside that takes the model's shape instead)
     7256256, 7320256, 7192256, 7256192, 7256128, 7128256, 7192128, 7128128, 7128064, 7064128, 7096128, 8192128, 8128128,
 };
+// ids that callers may still hold, of register-staged shapes that no product was fastest on: they take the model's shape
+static const int kNtRetired[] = {96128, 128256, 192256, 256064, 96256, 3064128, 2192128, 2256128, 2128128};
+static bool is_retired(int id) { return std::find(std::begin(kNtRetired), std::end(kNtRetired), id) != std::end(kNtRetired); }
 // stages of the direct-to-LDS shapes (0: not one of them)
 static int ntd_stages(int id) {
   switch (id) {
@@ -1536,6 +1542,7 @@ size_t gemm_nt_tile_lds_bytes(int id) {
 }
 int gemm_nt_tile_count() { return (int)(sizeof(kNtShapes) / sizeof(kNtShapes[0])); }
 int gemm_nt_tile_id(int i) { return kNtShapes[i]; }
+bool gemm_nt_tile_known(int id) { return id == 0 || std::find(std::begin(kNtShapes), std::end(kNtShapes), id) != std::end(kNtShapes) || is_retired(id); }
 bool gemm_nt_tile_is_free(const GemmDesc& g) { return is_nt(g) && !g.grp_off; }
 
 // The one rule that sends a product to the kernel for few rows: the shape of that kernel, or -1 for the tiled ones.  It
@@ -1579,7 +1586,7 @@ void gemm_tn_flush(TnChain* chain, hipStream_t s) {
 // The tiled kernels, in the shape asked for or, for 0 and for a shape that cannot take the product, the model's.
 static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
   int pick = g.grp_off ? 0 : tile;
-  if (!pick || (ntd_stages(pick) && !is_ntd(g))) { float us = 0.f; pick = nt_pick(g, &us); }
+  if (!pick || is_retired(pick) || (ntd_stages(pick) && !is_ntd(g))) { float us = 0.f; pick = nt_pick(g, &us); }
   switch (pick) {
     case 7256256: launch_ntd<256, 256, 2, 4, 2>(g, s); break;
     case 7320256: launch_ntd<320, 256, 2, 4, 2>(g, s); break;
