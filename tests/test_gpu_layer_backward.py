@@ -1,0 +1,51 @@
+"""GPU parity of a layer's two gradients where the joint launch can go wrong: token counts around the k-tiles of the weight
+gradient (64 tokens) and around its splits, both of its tiles, widths that end inside a tile, and scratch too small for the
+splits.  And attention forward: a head by one workgroup or by two is the same bits."""
+import numpy as np
+import pytest
+
+import test_gpu_kernels as K
+from test_gpu_kernels import env  # noqa: F401  (a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+# one token .. a few k-tiles; 8 .. 264 columns; splits with a ragged last one (788, 1000, 2111); the 256 x 128 tile (4416 and
+# 6304 tokens at 768 x 3072)
+@pytest.mark.parametrize("M,kin,out", [(1, 64, 8), (63, 192, 136), (64, 136, 264), (65, 264, 72), (191, 768, 64), (197, 768, 776),
+                                       (788, 384, 1536), (1000, 264, 520), (2111, 768, 2304), (4416, 768, 3072), (6304, 3072, 768)])
+def test_both_gradients_within_the_rounding_of_their_sums(env, M, kin, out):
+    """Products of bf16 numbers are exact in fp32 and each of n additions errs by at most 2^-23 of what it adds up to, so an
+    fp32 sum is within n 2^-23 of the sum of the terms' magnitudes; dX is then rounded to bf16 (2^-8 of its value)."""
+    torch, P = env
+    rng = np.random.default_rng(5 * M + kin + out)
+    x, dy, w = (K.to_dev(torch, K.bf16_np(rng, s), torch.bfloat16) for s in ((M, kin), (M, out), (kin, out)))
+    X, DY, W = x.double(), dy.double(), w.double()
+    dx_ref, dw_ref, db_ref = DY @ W.t().contiguous(), X.t().contiguous() @ DY, DY.sum(0)
+    dx_mag, dw_mag, db_mag = DY.abs() @ W.abs().t().contiguous(), X.abs().t().contiguous() @ DY.abs(), DY.abs().sum(0)
+    per = (kin + 1) * out
+    for floats in (0, 2 * per, 16 * per):                   # no room for a split, for two, for all
+        ws = torch.full((floats,), float("nan"), device="cuda") if floats else None
+        dx, dw, db = P.bsr_linear_backward(x, dy, w, workspace=ws)
+        alone, _ = P.bsr_linear_wgrad(x, dy, workspace=ws)
+        torch.cuda.synchronize()
+        for name, got, ref, mag, n, rounding in (("dx", dx, dx_ref, dx_mag, out, 2.0 ** -8), ("dw", dw, dw_ref, dw_mag, M, 0.0),
+                                                 ("db", db, db_ref, db_mag, M, 0.0), ("dw alone", alone, dw_ref, dw_mag, M, 0.0)):
+            over = ((got.double() - ref).abs() - n * 2.0 ** -23 * mag * (1 + rounding) - rounding * ref.abs()).max().item()
+            assert over <= 1e-30, f"{name}, scratch for {floats} numbers: {over:.3g} beyond the bound"
+    for tile in (96256, 3064128):                           # ids that are no longer shapes: still taken, the same bits
+        again = P.bsr_linear_backward(x, dy, w, workspace=ws, tile=tile)
+        assert all(torch.equal(a, b) for a, b in zip((dx, dw, db), again)), f"tile {tile}"
+
+
+@pytest.mark.parametrize("T", [1, 33, 64, 65, 128, 197, 256])
+def test_attention_of_few_heads_is_the_same_bits(env, T):
+    """24 heads (two workgroups share a head) against the same heads among 132 (one workgroup each)."""
+    torch, P = env
+    rng = np.random.default_rng(T)
+    qkv = K.to_dev(torch, K.bf16_np(rng, (11, T, 3 * 12 * 64), 1.5), torch.bfloat16)
+    many = P.bsr_attention_forward(qkv, 12)
+    few = P.bsr_attention_forward(qkv[:2].contiguous(), 12)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("out", "lse", "CLS row"), many, few):
+        assert torch.equal(a[:2], b), name
