@@ -33,7 +33,7 @@ def _short(name: str) -> str:
 
 
 def _is_gemm(name: str) -> bool:
-    return any(k in name for k in ("gemm_nt_kernel", "gemm_ntd_kernel", "gemm_nt_few_kernel", "gemm_tn_kernel"))
+    return any(k in name for k in ("gemm_nt_kernel", "gemm_ntd_kernel", "gemm_pair_kernel", "gemm_nt_few_kernel", "gemm_tn_kernel"))
 
 
 def trace(path: str, nsteps: int = 20, first: str = "patchify") -> None:
@@ -52,7 +52,7 @@ def trace(path: str, nsteps: int = 20, first: str = "patchify") -> None:
     span = (int(sel[-1]["End_Timestamp"]) - int(sel[0]["Start_Timestamp"])) / 1e3
     print(f"# last {nsteps} steps: {len(sel)} dispatches ({len(sel) / nsteps:.1f} per step), kernel time "
           f"{tot / nsteps:.1f} us per step, span {span / nsteps:.1f} us per step")
-    print(f"# GEMM launches (gemm_nt / gemm_ntd / gemm_nt_few / gemm_tn kernels): {gemm / nsteps:.1f} us per step, summed durations")
+    print(f"# GEMM launches (gemm_nt / gemm_ntd / gemm_pair / gemm_nt_few / gemm_tn kernels): {gemm / nsteps:.1f} us per step, summed durations")
     print(f"{'kernel':72s} {'per_step':>8s} {'us/step':>9s} {'avg_us':>8s} {'pct':>6s}")
     for n, (c, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
         print(f"{n[:72]:72s} {c / nsteps:8.1f} {t / nsteps:9.1f} {t / c:8.1f} {100 * t / tot:6.2f}")
@@ -91,8 +91,10 @@ def counters(path: str, nsteps: int = 5) -> None:
             return "gemm_nt_few (few rows)"
         if "gemm_ntd_kernel" in n:
             return "gemm_ntd (operands straight into LDS)"
+        if "gemm_pair_kernel" in n or "gemm_tn_kernel" in n:
+            return "gemm_pair / gemm_tn (a layer's input and weight gradient in one launch, or the weight gradient alone)"
         if _is_gemm(n):
-            return "gemm_nt / gemm_tn (register-staged; fused launches carry a weight gradient)"
+            return "gemm_nt (register-staged)"
         if "attn_fwd" in n:
             return "attention forward"
         if "attn_bwd" in n:

@@ -34,7 +34,7 @@ def per_kernel(path: str, counter: str, last_steps: int):
     starts = [i for i, r in enumerate(rows) if "patchify" in r[1]]
     first = starts[-last_steps] if 0 < last_steps <= len(starts) else 0
     gemm = [v for _, n, v in rows[first:]
-            if "gemm_nt_kernel" in n or "gemm_ntd_kernel" in n or "gemm_tn_kernel" in n or "gemm_nt_few_kernel" in n]
+            if any(k in n for k in ("gemm_nt_kernel", "gemm_ntd_kernel", "gemm_pair_kernel", "gemm_tn_kernel", "gemm_nt_few_kernel"))]
     copy = [v for _, n, v in rows if "copybuffer" in n.lower()]    # the runtime's plain device-to-device copy kernel
     return gemm, copy
 
