@@ -928,29 +928,32 @@ void launch_few(const GemmDesc& g, hipStream_t s) {
   else launch_few_as<MI, NI, false>(g, s);
 }
 // 32 x 64 tiles are never ahead of both 64 x 32 and 64 x 64.
-// Modelled time of a product here, in microseconds, in the form of the tiled kernels' model: with t tiles, c0 +
+// c: modelled time of a product here, in microseconds, in the form of the tiled kernels' model: with t tiles, c0 +
 // ceil(t / 256) (c1 + c2 K / 64) + t / 256 (c3 + c4 K / 64) + ceil(t / 512) (c5 + c6 K / 64), and t / 256 c7 where a GELU is applied.
 // Constants fitted to chains of equal launches at 32 .. 2144 rows, N and K of 384 .. 3072 (108 products): the picks take 0.4 % longer than the
-// fastest of the three (a rate per CU and whole rounds of tiles: 5.5 %; 32 x 32 tiles share a CU, which that left out).
-struct FewShape { int mi, ni; float c[8]; };
-const FewShape kFewShapes[] = {{1, 1, {1.870f, 0.140f, 0.068f, 0.000f, 0.022f, 0.841f, 0.000f, 0.102f}},
-                               {2, 1, {1.672f, 1.466f, 0.090f, 0.000f, 0.072f, 0.000f, 0.000f, 0.143f}},
-                               {2, 2, {1.598f, 2.827f, 0.154f, 0.039f, 0.092f, 0.000f, 0.000f, 0.414f}}};
-// A product on its own comes here when this model gives it less than that of the tiled kernels: 0.2 % over the faster of the
-// two on the same products (with a lead of 0.9 asked for 0.5 %, of 0.8 1.9 %).
+// fastest of the three.
+// The other three are what the rule for coming here at all goes by (few_rows_shape): launch and epilogue, then ceil(t / 256) rounds of a
+// start-up and the tile's operand bytes (within 15 % where this kernel is the faster one; its tiles would take 5.5 % longer than the fastest).
+struct FewShape { int mi, ni; float c[8], launch_us, round_us, bytes_per_us; };
+const FewShape kFewShapes[] = {{1, 1, {1.870f, 0.140f, 0.068f, 0.000f, 0.022f, 0.841f, 0.000f, 0.102f}, 2.6f, 0.5f, 105e3f},
+                               {2, 1, {1.672f, 1.466f, 0.090f, 0.000f, 0.072f, 0.000f, 0.000f, 0.143f}, 2.8f, 0.5f, 103e3f},
+                               {2, 2, {1.598f, 2.827f, 0.154f, 0.039f, 0.092f, 0.000f, 0.000f, 0.414f}, 3.3f, 1.0f, 65e3f}};
 
-// The shape of this kernel for a product and what the model gives it; -1: not one it takes
-int few_pick(const GemmDesc& g, float* us) {
+// The shape of this kernel for a product, or -1: not one it takes; *rule_us: the time that the rule compares
+int few_pick(const GemmDesc& g, float* rule_us) {
+  if (g.K % 64 || g.grp_off || !offsets_fit(g)) return -1;
   int pick = -1;
-  if (g.K % 64 == 0 && !g.grp_off && offsets_fit(g))
-    for (int i = 0; i < 3; ++i) {
-      const FewShape& f = kFewShapes[i];
-      const int64_t tiles = (int64_t)((g.M + 32 * f.mi - 1) / (32 * f.mi)) * ((g.N + 32 * f.ni - 1) / (32 * f.ni));
-      const float k = g.K / 64, w = (float)tiles / 256.f;
-      const float t = f.c[0] + (float)((tiles + 255) / 256) * (f.c[1] + f.c[2] * k) + w * (f.c[3] + f.c[4] * k + (g.act == ACT_NONE ? 0.f : f.c[7])) +
-                      (float)((tiles + 511) / 512) * (f.c[5] + f.c[6] * k);
-      if (pick < 0 || t < *us) { pick = i; *us = t; }
-    }
+  float least = 0.f;
+  for (int i = 0; i < 3; ++i) {
+    const FewShape& f = kFewShapes[i];
+    const int64_t tiles = (int64_t)((g.M + 32 * f.mi - 1) / (32 * f.mi)) * ((g.N + 32 * f.ni - 1) / (32 * f.ni));
+    const float k = g.K / 64, w = (float)tiles / 256.f, rounds = (float)((tiles + 255) / 256);
+    const float t = f.c[0] + rounds * (f.c[1] + f.c[2] * k) + w * (f.c[3] + f.c[4] * k + (g.act == ACT_NONE ? 0.f : f.c[7])) +
+                    (float)((tiles + 511) / 512) * (f.c[5] + f.c[6] * k);
+    const float r = f.launch_us + rounds * (f.round_us + 64.f * (f.mi + f.ni) * g.K / f.bytes_per_us);
+    if (pick < 0 || t < least) { pick = i; least = t; }
+    if (i == 0 || r < *rule_us) *rule_us = r;
+  }
   return pick;
 }
 void launch_few(int pick, const GemmDesc& g, hipStream_t s) {
@@ -1333,7 +1336,6 @@ float pair_span(int64_t T, float lt, int64_t N, float ln) {
 struct TnSplit {
   int tile = 0, splits = 1, nt = 1;    // tile of the weight gradient, its splits, tile of the input gradient
   float us = 0.f;                      // what the model gives the launch
-  size_t room = 0;                     // floats for partial sums that the choice could count on
 };
 // floats of the split-K workspace that one launch may fill
 size_t tn_room(size_t ws_floats, bool chained) { return chained ? (ws_floats / 2) & ~(size_t)3 : ws_floats; }
@@ -1341,7 +1343,6 @@ size_t tn_room(size_t ws_floats, bool chained) { return chained ? (ws_floats / 2
 // nt: the input gradient of the same launch, or null.  (Sizes only: a tile that was measured or asked for changes no split.)
 TnSplit tn_split(const GemmDesc* nt, const GemmDesc& g, size_t room) {
   TnSplit best;
-  best.room = room;
   const int nk = (g.K + BK - 1) / BK;
   const size_t mn = (size_t)g.M * g.N, per_split = mn + (g.bsum ? (size_t)g.N : 0);   // partial dW, then partial column sums
   const int most = std::max(1, (int)std::min<size_t>(std::min(nk / 4, 16), room / per_split));
@@ -1506,35 +1507,39 @@ const NtModel kNtModel[] = {
     {7256256, 256, 256, {0.390f, 6.475f, 0.912f, 0.000f, 0.791f, 1.970f, 0.000f, 7.088f, 1.735f}},
     {7256128, 256, 128, {0.000f, 4.160f, 0.564f, 0.268f, 0.342f, 1.936f, 0.000f, 3.777f, 0.839f}},
 };
-// Register-staged shapes, for products that only they take: fitted to every shape forced in turn on the launches of ViT-B
-// and DeiT-S steps (436 launches, event-bracketed, in their place in the step, the event pair included).
-const NtModel kNtStagedModel[] = {
+// Fitted to every shape forced in turn on the launches of ViT-B and DeiT-S steps (436 launches, event-bracketed, in their place
+// in the step, the event pair included).  The register-staged ones, which come first, are picked from for products that only they
+// take; all of them together are what the rule for products of few rows takes a tiled launch in a step for.
+const NtModel kNtStepModel[] = {
     {64128, 64, 128, {6.508f, 0.000f, 0.142f, 1.061f, 0.000f, 0.000f, 0.353f, 0.f, 0.f}},
     {192128, 192, 128, {7.783f, 1.559f, 0.501f, 1.705f, 0.104f, 0.000f, 0.182f, 0.f, 0.f}},
     {256128, 256, 128, {3.608f, 3.854f, 0.664f, 2.056f, 0.342f, 2.154f, 0.001f, 0.f, 0.f}},
     {3128064, 128, 64, {6.542f, 0.794f, 0.173f, 0.773f, 0.052f, 0.000f, 0.222f, 0.f, 0.f}},
+    {7256256, 256, 256, {0.000f, 8.827f, 1.173f, 1.403f, 0.332f, 5.356f, 0.142f, 0.f, 0.f}},
+    {7320256, 320, 256, {10.479f, 4.369f, 1.469f, 3.163f, 0.515f, 0.945f, 0.009f, 0.f, 0.f}},
 };
 constexpr float EVENTS_US = 4.5f;      // the part of their c0 that a launch inside a chain does not take (the event pair)
 
-// the model's pick and the time it gives it in a chain of launches.  (With the LayerNorm folded in, 64 columns per tile would
+// the fastest by a table of models, and the time it gives it.  (With the LayerNorm folded in, 64 columns per tile would
 // double its dot instructions per MFMA.)
-static int nt_pick(const GemmDesc& g, float* us_out) {
-  const bool direct = is_ntd(g);
-  const NtModel* table = direct ? kNtModel : kNtStagedModel;
-  const int n = direct ? (int)(sizeof(kNtModel) / sizeof(kNtModel[0])) : (int)(sizeof(kNtStagedModel) / sizeof(kNtStagedModel[0]));
+template <int N>
+static int model_pick(const NtModel (&table)[N], const GemmDesc& g, bool direct_ok, float* us_out) {
   int pick = 0;
   const float k = (float)((g.K + BK - 1) / BK), gelu = g.act == ACT_NONE ? 0.f : 1.f;
-  for (int i = 0; i < n; ++i) {
-    const NtModel& e = table[i];
-    if (g.ln_colsum && e.bn < 128) continue;
+  for (const NtModel& e : table) {
+    if ((ntd_stages(e.id) && !direct_ok) || (g.ln_colsum && e.bn < 128)) continue;
     // (a group ends in a partial row tile: half a tile each)
     const int64_t t = (int64_t)((g.M + e.bm - 1) / e.bm + (g.grp_off ? g.groups / 2 : 0)) * ((g.N + e.bn - 1) / e.bn);
     const float r1 = (float)((t + 255) / 256), w = (float)t / 256.f, r2 = (float)((t + 511) / 512);
     const float us = e.c[0] + r1 * (e.c[1] + e.c[2] * k + e.c[7] * gelu) + w * (e.c[3] + e.c[4] * k + e.c[8] * gelu) +
-                     r2 * (e.c[5] + e.c[6] * k) - (direct ? 0.f : EVENTS_US);
+                     r2 * (e.c[5] + e.c[6] * k);
     if (!pick || us < *us_out) { pick = e.id; *us_out = us; }
   }
   return pick;
+}
+static int nt_pick(const GemmDesc& g) {
+  float us = 0.f;
+  return is_ntd(g) ? model_pick(kNtModel, g, true, &us) : model_pick(kNtStepModel, g, false, &us);
 }
 size_t gemm_nt_tile_lds_bytes(int id) {
   const int bm = id % 1000000 / 1000, bn = id % 1000, nst = ntd_stages(id);
@@ -1546,35 +1551,29 @@ bool gemm_nt_tile_known(int id) { return id == 0 || std::find(std::begin(kNtShap
 bool gemm_nt_tile_is_free(const GemmDesc& g) { return is_nt(g) && !g.grp_off; }
 
 // The one rule that sends a product to the kernel for few rows: the shape of that kernel, or -1 for the tiled ones.  It
-// looks at the product's sizes and, for an input gradient, at those of the layer's weight gradient (which a tiled product
-// carries in its own launch, and which takes another one here), and at nothing else: the kernel for few rows adds over k in
-// another order, so with the tile choice in the rule, tuning would change bits.
-static int few_rows_shape(const GemmDesc& g) {
+// looks at the product's sizes, and at whether the launch could carry the layer's weight gradient as well (tiled kernels
+// do that in one launch; here it costs another one), and at nothing else: the kernel for few rows adds over k in another
+// order, so with the tile choice in the rule, tuning would change bits, and so does every shift of the line itself.
+// A product goes there when it leads clearly over the tiled kernels as they run in a step, where every launch follows another
+// kernel: near-ties went to the tiled ones there.  (A line without that lead, between the models fitted to chains of equal launches, came
+// to 1.000x over 20 steps, 0.984 .. 1.019, and moved every gradient behind a product that changed sides by up to 1 %.)
+constexpr float FEW_LEAD = 0.8f, TILED_LAUNCH_US = 2.6f;      // the latter: the launch that a weight gradient carried along saves
+static int few_rows_shape(const GemmDesc& g, bool carries_wgrad) {
   float few_us = 0.f, tiled_us = 0.f;
   const int few = few_pick(g, &few_us);
   if (few < 0) return -1;
-  nt_pick(g, &tiled_us);
-  return few_us < tiled_us ? few : -1;
+  model_pick(kNtStepModel, g, is_ntd(g), &tiled_us);
+  return few_us < FEW_LEAD * (tiled_us - EVENTS_US - (carries_wgrad ? TILED_LAUNCH_US : 0.f)) ? few : -1;
 }
 static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && !nt.grp_off && is_tn(tn) && !tn.grp_off; }
-static int few_rows_shape(const GemmDesc& nt, const GemmDesc& tn, const TnSplit& pair) {
-  if (!can_pair(nt, tn)) return few_rows_shape(nt);
-  float few_us = 0.f;
-  const int few = few_pick(nt, &few_us);
-  if (few < 0) return -1;
-  const TnSplit alone = tn_split(nullptr, tn, pair.room);
-  return few_us + alone.us < pair.us ? few : -1;
-}
 
 // id of the tile that the model gives the input gradient of a layer's backward launch
 static int pair_model_tile(const TnSplit& pair) { return 7000000 + 1000 * kPairNt[pair.nt].bm + kPairNt[pair.nt].bn; }
 int gemm_nt_model_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained) {
-  float us = 0.f;
-  TnSplit pair;
-  if (wgrad) pair = tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained));
-  const int few = wgrad ? few_rows_shape(g, *wgrad, pair) : few_rows_shape(g);
+  const int few = few_rows_shape(g, wgrad != nullptr);
   if (few >= 0) return FEW_ROWS_ID + 32000 * kFewShapes[few].mi + 32 * kFewShapes[few].ni;
-  return wgrad && can_pair(g, *wgrad) ? pair_model_tile(pair) : nt_pick(g, &us);
+  if (wgrad && can_pair(g, *wgrad)) return pair_model_tile(tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained)));
+  return nt_pick(g);
 }
 
 void gemm_tn_flush(TnChain* chain, hipStream_t s) {
@@ -1586,7 +1585,7 @@ void gemm_tn_flush(TnChain* chain, hipStream_t s) {
 // The tiled kernels, in the shape asked for or, for 0 and for a shape that cannot take the product, the model's.
 static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
   int pick = g.grp_off ? 0 : tile;
-  if (!pick || is_retired(pick) || (ntd_stages(pick) && !is_ntd(g))) { float us = 0.f; pick = nt_pick(g, &us); }
+  if (!pick || is_retired(pick) || (ntd_stages(pick) && !is_ntd(g))) pick = nt_pick(g);
   switch (pick) {
     case 7256256: launch_ntd<256, 256, 2, 4, 2>(g, s); break;
     case 7320256: launch_ntd<320, 256, 2, 4, 2>(g, s); break;
@@ -1618,7 +1617,7 @@ void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hip
     launch_tn(g, split, splitk_ws, splitk_ws_floats, s, chain);
     return;
   }
-  const int few = few_rows_shape(g);
+  const int few = few_rows_shape(g, false);
   if (few >= 0) launch_few(few, g, s);
   else nt_tiled(g, s, tile);
 }
@@ -1628,13 +1627,13 @@ void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hip
 // on the tile.
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile, TnChain* chain) {
-  const TnSplit split = tn_split(is_ntd(nt) ? &nt : nullptr, tn, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
-  const int few = few_rows_shape(nt, tn, split);
+  const int few = few_rows_shape(nt, true);
   if (few >= 0) {
     launch_few(few, nt, s);
     gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
     return;
   }
+  const TnSplit split = tn_split(is_ntd(nt) ? &nt : nullptr, tn, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
   if (can_pair(nt, tn)) {
     switch ((tile ? tile : pair_model_tile(split)) % 1000000) {
       case 128064: launch_pair<0>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;

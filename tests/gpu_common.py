@@ -124,6 +124,24 @@ def run_hip_step(cfg, params, x, labels, forced_idx=None, max_batch=None, sgd=No
     return out
 
 
+def product_kernels(call):
+    """Names of the matrix product kernels that call() launches, in order: what really ran."""
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    runs = sorted((e for e in prof.events() if e.device_type == torch.autograd.DeviceType.CUDA), key=lambda e: e.time_range.start)
+    return [e.name for e in runs if "gemm_" in e.name]
+
+
+def families(names):
+    """few: k shared by wavefronts; joint: a layer's two gradients; wgrad: one of them alone; tiled: the others"""
+    kinds = (("gemm_nt_few", "few"), ("gemm_pair", "joint"), ("gemm_tn", "wgrad"), ("gemm_nt", "tiled"))
+    return [next(k for part, k in kinds if part in n) for n in names]
+
+
 def gap_ok(scores_row, k, rel_gap):
     """True when the oracle's k-th and (k+1)-th largest scores are separated by more than rel_gap
     (relative to the k-th): only then is the kept set required to match exactly."""

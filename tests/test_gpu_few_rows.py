@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import test_gpu_kernels as K
+from gpu_common import families, product_kernels
 from test_gpu_kernels import env  # noqa: F401  (a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -18,6 +19,24 @@ def test_products_of_few_rows(env, orc64, M, kin, out):
     if kin % 64 == 0 and out % 64 == 0:
         K.test_linear_dgrad(env, orc64, M, kin, out)
     K.test_layernorm_folded_into_linear(env, orc64, M, kin, out)
+
+
+# The two families add over k in different orders, so the line between them is part of the results.  Products of a step (768 wide: class
+# rows, half the tokens of 27 images; 384 wide) and ragged ones, on either side; a layer's two gradients likewise
+@pytest.mark.parametrize("M,kin,out,kernel", [(128, 768, 3072, "few"), (300, 448, 392, "few"), (729, 3072, 768, "few"), (702, 768, 768, "tiled"),
+                                              (729, 768, 768, "tiled"), (1300, 448, 584, "tiled"), (65, 192, 576, "tiled")])
+def test_which_kernel_multiplies(env, M, kin, out, kernel):
+    torch, P = env
+    x, w = (torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((M, kin), (out, kin)))
+    assert families(product_kernels(lambda: P.bsr_linear_forward(x, w, None))) == [kernel]
+
+
+@pytest.mark.parametrize("M,kin,out,kernels", [(32, 768, 768, ["joint"]), (128, 768, 768, ["joint"]), (129, 3072, 768, ["joint"]), (67, 1536, 384, ["joint"]),
+                                               (32, 768, 3072, ["few", "wgrad"]), (128, 768, 3072, ["few", "wgrad"])])
+def test_which_kernel_takes_the_gradients_of_a_layer(env, M, kin, out, kernels):
+    torch, P = env
+    x, dy, w = (torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((M, kin), (M, out), (kin, out)))
+    assert families(product_kernels(lambda: P.bsr_linear_backward(x, dy, w))) == kernels
 
 
 # row counts that stay with the tiled kernels whatever the tile shape (of the sizes that test has, 300 x 448 x 392 and
