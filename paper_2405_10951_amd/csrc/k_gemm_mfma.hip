@@ -1633,6 +1633,7 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
     gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
     return;
   }
+  if (is_retired(tile)) tile = 0;
   const TnSplit split = tn_split(is_ntd(nt) ? &nt : nullptr, tn, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
   if (can_pair(nt, tn)) {
     switch ((tile ? tile : pair_model_tile(split)) % 1000000) {

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import test_gpu_kernels as K
+from gpu_common import product_kernels
 from test_gpu_kernels import env  # noqa: F401  (a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -33,9 +34,19 @@ def test_both_gradients_within_the_rounding_of_their_sums(env, M, kin, out):
                                                  ("db", db, db_ref, db_mag, M, 0.0), ("dw alone", alone, dw_ref, dw_mag, M, 0.0)):
             over = ((got.double() - ref).abs() - n * 2.0 ** -23 * mag * (1 + rounding) - rounding * ref.abs()).max().item()
             assert over <= 1e-30, f"{name}, scratch for {floats} numbers: {over:.3g} beyond the bound"
-    for tile in (96256, 3064128):                           # ids that are no longer shapes: still taken, the same bits
+    for tile in (160256, 7320256):                          # shapes that the joint launch does not have: two launches, the same bits
         again = P.bsr_linear_backward(x, dy, w, workspace=ws, tile=tile)
         assert all(torch.equal(a, b) for a, b in zip((dx, dw, db), again)), f"tile {tile}"
+
+
+@pytest.mark.parametrize("tile", [96128, 128256, 192256, 256064, 96256, 3064128, 2192128, 2256128, 2128128])
+def test_ids_that_are_no_longer_shapes_run_what_no_id_runs(env, tile):
+    torch, P = env
+    x, dy, w = (torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((1000, 768), (1000, 768), (768, 768)))
+    default = product_kernels(lambda: P.bsr_linear_backward(x, dy, w))
+    assert len(default) == 1 and product_kernels(lambda: P.bsr_linear_backward(x, dy, w, tile=tile)) == default
+    default = product_kernels(lambda: P.bsr_linear_forward(x, w, None))
+    assert product_kernels(lambda: P.bsr_linear_forward(x, w, None, tile=tile)) == default
 
 
 @pytest.mark.parametrize("T", [1, 33, 64, 65, 128, 197, 256])
