@@ -270,7 +270,8 @@ int32_t bsr_autotune(bsr_ctx* ctx, const void* input, const int32_t* labels, int
  * bsr_pipeline_step orders them, every launch with the shape under test; in place of the optimizer
  * step the bf16 copies of the trainable weights are rebuilt (no weight changes).  Three runs per shape,
  * over the shapes whose workgroups leave room for a second one on a compute unit, and once more with the
- * model's shape at every launch.  The fastest is then used for every launch of a batch of size B.  The choice replaces the one of bsr_autotune (a
+ * model's shape at every launch.  (A layer's backward launch holds a compute unit by itself whatever the shape.)
+ * The fastest is then used for every launch of a batch of size B.  The choice replaces the one of bsr_autotune (a
  * context holds one).  BLOCKS until both streams have drained.
  * Errors: as bsr_autotune; INVALID_ARG for a missing second buffer or stream; BAD_CONFIG when the
  * model has no frozen prefix.
@@ -283,7 +284,8 @@ int32_t bsr_autotune_overlapped(bsr_ctx* ctx, const void* input, const int32_t* 
  * The tile choices a context holds after bsr_autotune / bsr_autotune_overlapped, for inspection and reports (host
  * only).  part 0: the launches of bsr_forward_frozen in launch order, part 1: those of bsr_train_blocks_fwd_bwd
  * (a backward launch carries the input gradient named here and, in the same launch, the weight gradient of its layer).
- *   rows, out, in  the product: rows x in times in x out      tile  shape id (see bsr_gemm_tile_shapes), or
+ *   rows, out, in  the product: rows x in times in x out      tile  id of the shape that runs (see bsr_gemm_tile_shapes; ids that
+ *                  name the same kernel for a launch are one choice there), or
  *                  9000000 + 1000 rows + columns of a tile of the kernel for products of few rows
  *   microseconds   what bsr_autotune measured for that shape at that launch (0 after bsr_autotune_overlapped,
  *                  which times whole passes)
@@ -372,16 +374,16 @@ int32_t bsr_adamw_step(bsr_ctx* ctx, const bsr_params* grads, const bsr_params* 
  *   w_s   bf16 copy of W stored [in,out]        u     [M,in], may be NULL
  * tile (both): 0, or the id of a block-tile shape (bsr_gemm_tile_shapes) the MFMA kernel is to use; a shape that
  *   cannot take the product (a direct-to-LDS shape when `in` / `out` to contract over is not a multiple of 64)
- *   gives way to the default, as do ids of shapes that earlier versions listed, and a product of few rows (by its sizes alone: where the kernel for those is clearly
- *   the faster one) runs that kernel whatever the tile.  Every tile gives the same bits.  An unknown id: INVALID_ARG.
+ *   gives way to the default, as do ids of shapes that earlier versions listed, and a product of few rows (by its
+ *   sizes alone: where the kernel for those is clearly the faster one) runs that kernel whatever the tile.  Every tile gives the same bits.  An unknown id: INVALID_ARG.
  * bsr_linear_wgrad (Eq. 4): dw[in,out] (fp32) = x[M,in]^T . dy[M,out], summed over all M rows.
  *   db         fp32 [out], may be NULL: the bias gradient, db[o] = sum over rows of dy[:,o], from the
  *              same launch when the MFMA kernel takes the shape (otherwise it needs the workspace)
  *   workspace  device fp32 scratch of workspace_floats elements, may be NULL.  With at least
- *              2*(in+1)*out floats the sum over M is split over several workgroups per output tile
+ *              2*(in+1)*out floats the sum over M may be split over several workgroups per output tile
  *              (partial sums are added in a fixed order: results are bit-reproducible).
  * bsr_linear_backward: bsr_linear_dgrad and bsr_linear_wgrad of one layer as the step issues them, in one launch where
- *   the block-tile shape allows it.  Arguments as for the two; `in` and `out` multiples of 8 (others: INVALID_ARG).  dx, dw
+ *   the sizes and the block-tile shape allow it.  Arguments as for the two; `in` and `out` multiples of 8 (others: INVALID_ARG).  dx, dw
  *   and db have the same bits whatever the tile.
  */
 int32_t bsr_linear_forward(const void* x, int32_t M, int32_t in, int32_t out, const void* w_t,

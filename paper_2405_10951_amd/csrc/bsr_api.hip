@@ -94,7 +94,7 @@ struct ProfRec {
 // Tile choice per NT GEMM launch, measured on the context's own launches (bsr_autotune).  A launch is
 // identified by the entry point it belongs to and its position in that call's launch order.
 struct TunePick { int M, N, K, tile, model; float us; };   // us: the chosen shape's measured time (0: not measured); model: without a choice
-struct TuneRec { int kind, cand; size_t site; int M, N, K, model; hipEvent_t start, stop; };
+struct TuneRec { int kind, cand; size_t site; int M, N, K, model, ran; hipEvent_t start, stop; };   // ran: the shape that the launch took
 struct Tune {
   int batch = 0;                       // the picks hold for this batch size (0: none)
   std::vector<TunePick> pick[2];       // [0] bsr_forward_frozen, [1] bsr_train_blocks_fwd_bwd
@@ -485,7 +485,8 @@ TileChoice choose_tile(bsr_ctx* c, const GemmDesc& g, hipStream_t s, const GemmD
   if (t.cand >= 0) {
     const int cand = (t.kind == 1 && t.cand_train >= 0) ? t.cand_train : t.cand;
     ch.tile = cand < gemm_nt_tile_count() ? gemm_nt_tile_id(cand) : 0;
-    ch.rec = TuneRec{t.kind, cand, site, g.M, g.N, g.K, gemm_nt_model_tile(g, wgrad, c->b.splitk_floats, true), nullptr, nullptr};
+    const size_t room = c->b.splitk_floats;
+    ch.rec = TuneRec{t.kind, cand, site, g.M, g.N, g.K, gemm_nt_runs_tile(g, wgrad, room, true, 0), gemm_nt_runs_tile(g, wgrad, room, true, ch.tile), nullptr, nullptr};
     ch.timing = hipEventCreate(&ch.rec.start) == hipSuccess && hipEventCreate(&ch.rec.stop) == hipSuccess;
     if (ch.timing) (void)hipEventRecord(ch.rec.start, s);
   } else if (t.batch == t.cur_batch && site < t.pick[t.kind].size()) {
@@ -1259,7 +1260,7 @@ static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_par
 // stream, and with the GPU always full it is the work per CU-second that counts, not how evenly one launch
 // alone fills the chip.  So what is timed is a whole side-by-side pass: with one shape for all launches, among the shapes that
 // leave room for a second workgroup on a CU (stages of at most 80 KB; the shape id is [family] BM BN in
-// decimal), and with every launch in the shape the model gives it, which since the backward launches hold a CU by themselves
+// decimal; a backward launch holds a CU by itself whatever the id), and with every launch in the shape the model gives it, which since the backward launches hold a CU by themselves
 // is mostly the fastest (ViT-B/16: batch 32 1784 us, best single shape 1910, every launch's own best timed alone 1794; batch 12 1123,
 // 1141, 1132; batch 64 2962, 3064, 2964; DeiT-S batch 32 860, 858, 870).
 static bool shares_a_cu(int tile_id) { return gemm_nt_tile_lds_bytes(tile_id) <= 80 * 1024; }
@@ -1359,8 +1360,7 @@ static int32_t autotune_overlapped(bsr_ctx* c, const void* input, const int32_t*
         if (r.kind != k) continue;
         TunePick& p = t.pick[k][r.site];
         p.M = r.M; p.N = r.N; p.K = r.K; p.model = r.model;
-        const int shape = k == 0 ? fz : tr;
-        p.tile = r.model >= FEW_ROWS_ID || shape == n ? r.model : gemm_nt_tile_id(shape);
+        if (r.cand == (k == 0 ? fz : tr)) p.tile = r.ran;
       }
       launches += (int)sites[k];
     }
@@ -1413,6 +1413,9 @@ static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, in
       t.pick[k].assign(sites[k], TunePick{0, 0, 0, 0, 0, 0.f});
       for (const TuneRec& r : t.recs) {
         if (r.kind != k) continue;
+        // a shape that stands in for another here (several ids name one joint kernel, some shapes cannot take the product) is timed
+        // under that one's own id and not again: more draws would favour it
+        if (r.ran < FEW_ROWS_ID && r.ran != gemm_nt_tile_id(r.cand)) continue;
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, r.start, r.stop) != hipSuccess) continue;
         float& b = best[r.site * n + r.cand];

@@ -94,9 +94,9 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
 // the block-tile shapes the NT kernel is instantiated for, and whether a GEMM is free to take any of them
 int gemm_nt_tile_count();
 constexpr int FEW_ROWS_ID = 9000000;           // + 1000 rows + columns: a tile of the kernel for products of few rows
-// what runs without a measured choice (wgrad: the weight gradient that goes out with g, or null; the workspace as in the
-// call); from FEW_ROWS_ID on: whatever is asked for
-int gemm_nt_model_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained);
+// id of the shape that really runs when `tile` is asked for (0: without a measured choice; wgrad: the weight gradient that goes out
+// with g, or null; the workspace as in the call); from FEW_ROWS_ID on: whatever is asked for
+int gemm_nt_runs_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained, int tile);
 int gemm_nt_tile_id(int i);
 // an id that the entry points take: 0, a shape above, or one that was a shape once (the model chooses in its place)
 bool gemm_nt_tile_known(int id);

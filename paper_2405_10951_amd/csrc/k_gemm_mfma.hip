@@ -1567,13 +1567,27 @@ static int few_rows_shape(const GemmDesc& g, bool carries_wgrad) {
 }
 static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && !nt.grp_off && is_tn(tn) && !tn.grp_off; }
 
-// id of the tile that the model gives the input gradient of a layer's backward launch
-static int pair_model_tile(const TnSplit& pair) { return 7000000 + 1000 * kPairNt[pair.nt].bm + kPairNt[pair.nt].bn; }
-int gemm_nt_model_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained) {
+// Tile of the input gradient (index into kPairNt) in a layer's backward launch that is asked to take a shape; -1: the joint kernel
+// has no such tile, two launches.  Several ids name one tile here: loads are straight into LDS whatever the id says, in one depth.
+static int joint_tile(int tile, const TnSplit& pair) {
+  if (!tile || is_retired(tile)) return pair.nt;
+  for (int i = 0; i < 4; ++i)
+    if (tile % 1000000 == 1000 * kPairNt[i].bm + kPairNt[i].bn) return i;
+  return -1;
+}
+// Shape of a product on its own that is asked to take a shape: the model's for 0, for an id that was a shape once and for a shape that
+// cannot take the product.
+static int nt_tile(const GemmDesc& g, int tile) {
+  return !tile || is_retired(tile) || (ntd_stages(tile) && !is_ntd(g)) ? nt_pick(g) : tile;
+}
+int gemm_nt_runs_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained, int tile) {
   const int few = few_rows_shape(g, wgrad != nullptr);
   if (few >= 0) return FEW_ROWS_ID + 32000 * kFewShapes[few].mi + 32 * kFewShapes[few].ni;
-  if (wgrad && can_pair(g, *wgrad)) return pair_model_tile(tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained)));
-  return nt_pick(g);
+  if (wgrad && can_pair(g, *wgrad)) {
+    const int i = joint_tile(tile, tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained)));
+    if (i >= 0) return 7000000 + 1000 * kPairNt[i].bm + kPairNt[i].bn;
+  }
+  return nt_tile(g, tile);
 }
 
 void gemm_tn_flush(TnChain* chain, hipStream_t s) {
@@ -1584,9 +1598,7 @@ void gemm_tn_flush(TnChain* chain, hipStream_t s) {
 
 // The tiled kernels, in the shape asked for or, for 0 and for a shape that cannot take the product, the model's.
 static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
-  int pick = g.grp_off ? 0 : tile;
-  if (!pick || is_retired(pick) || (ntd_stages(pick) && !is_ntd(g))) pick = nt_pick(g);
-  switch (pick) {
+  switch (nt_tile(g, g.grp_off ? 0 : tile)) {
     case 7256256: launch_ntd<256, 256, 2, 4, 2>(g, s); break;
     case 7320256: launch_ntd<320, 256, 2, 4, 2>(g, s); break;
     case 7192256: launch_ntd<192, 256, 2, 4, 2>(g, s); break;
@@ -1633,14 +1645,13 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
     gemm_mfma(tn, splitk_ws, splitk_ws_floats, s, 0, chain);
     return;
   }
-  if (is_retired(tile)) tile = 0;
   const TnSplit split = tn_split(is_ntd(nt) ? &nt : nullptr, tn, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
   if (can_pair(nt, tn)) {
-    switch ((tile ? tile : pair_model_tile(split)) % 1000000) {
-      case 128064: launch_pair<0>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
-      case 128128: launch_pair<1>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
-      case 192128: launch_pair<2>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
-      case 256128: launch_pair<3>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
+    switch (joint_tile(tile, split)) {
+      case 0: launch_pair<0>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
+      case 1: launch_pair<1>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
+      case 2: launch_pair<2>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
+      case 3: launch_pair<3>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
       default: break;
     }
   }

@@ -1,5 +1,7 @@
 """GPU parity of the products of few rows (wavefronts of a workgroup share k, rings of their own in LDS) at the edges of
 their tiles and k-groups, and the tiled kernels' own edges at row counts that stay with them."""
+import re
+
 import numpy as np
 import pytest
 
@@ -109,3 +111,52 @@ def test_tuning_reports_what_products_of_few_rows_run(env):
     assert len(picks) == launches and 0 < len(few) < launches and changed <= launches - len(few)
     assert {t[3] for t in few} <= {9032032, 9064032, 9064064} and all(t[4] > 0 for t in few)
     assert {t[3] for t in picks} - {t[3] for t in few} <= set(P.bsr_gemm_tile_shapes())
+
+
+def shape_id(name):
+    """Shape id of a product kernel's instance, from its name; None for kernels that have none"""
+    kind, args = re.match(r".*?(gemm_\w+)<([^>]*)>", name).groups() if "<" in name else ("", "")
+    v = [{"true": 1, "false": 0}.get(a.strip(), a.strip()) for a in args.split(",")]
+    if kind == "gemm_nt_few_kernel":
+        return 9000000 + 32000 * int(v[0]) + 32 * int(v[1])
+    if kind == "gemm_pair_kernel":
+        return (7128064, 7128128, 7192128, 7256128)[int(v[0])]
+    if kind == "gemm_ntd_kernel":
+        deep = (v[0], v[1], v[4]) in (("192", "128", "3"), ("128", "128", "3"))
+        return (8000000 if deep else 7000000) + 1000 * int(v[0]) + int(v[1])
+    if kind == "gemm_nt_kernel":
+        return (1000000 * int(v[5]) if int(v[5]) > 1 else 0) + 1000 * int(v[0]) + int(v[1])
+    return None
+
+
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("two_streams", [False, True])
+def test_tuning_reports_the_shapes_that_run(env, two_streams, fold):
+    """Several ids name one kernel in a backward launch, and some shapes cannot take some products: what is reported is what
+    runs, and compared with the model's choice as such."""
+    import bsr_synth as S
+    torch, P = env
+    cfg = S.get_config("c2_deit_s", dtype="bf16", batch=16, fold_frozen_layernorm=int(fold))
+    x, y = S.make_inputs(cfg)
+    ctx = P.Context(cfg, S.make_params(cfg), 16)
+    xin, lab = torch.as_tensor(x).cuda().to(ctx.act_dtype).contiguous(), torch.as_tensor(y, dtype=torch.int32).cuda()
+    xf, xs = (torch.empty((16, ctx.T_f, cfg["dim"]), dtype=ctx.act_dtype, device="cuda") for _ in range(2))
+    loss, grads = torch.zeros(4, device="cuda"), ctx.new_grads()
+
+    def step():
+        ctx.bsr_forward_frozen(xin, x_out=xf)
+        ctx.bsr_train_blocks_fwd_bwd(xf, lab, grads, loss_out=loss)
+
+    model = [i for i in map(shape_id, product_kernels(step)) if i]
+    if two_streams:
+        frozen, train = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(frozen):
+            launches, changed = ctx.bsr_autotune_overlapped(xin, lab, xf, xs, loss, grads, train)
+        torch.cuda.synchronize()
+    else:
+        launches, changed = ctx.bsr_autotune(xin, lab, xf, loss, grads)
+    reported = [t[3] for t in ctx.bsr_tile_choices(0) + ctx.bsr_tile_choices(1)]
+    ran = [i for i in map(shape_id, product_kernels(step)) if i]
+    assert len(ran) == launches and reported == ran
+    assert changed == sum(a != b for a, b in zip(model, ran))
