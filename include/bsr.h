@@ -380,7 +380,7 @@ int32_t bsr_adamw_step(bsr_ctx* ctx, const bsr_params* grads, const bsr_params* 
  *   db         fp32 [out], may be NULL: the bias gradient, db[o] = sum over rows of dy[:,o], from the
  *              same launch when the MFMA kernel takes the shape (otherwise it needs the workspace)
  *   workspace  device fp32 scratch of workspace_floats elements, may be NULL.  With at least
- *              2*(in+1)*out floats the sum over M may be split over several workgroups per output tile
+ *              2*(in+1)*out floats the sum over M is taken in parts (their number by the sizes alone), by one or more workgroups per output tile
  *              (partial sums are added in a fixed order: results are bit-reproducible).
  * bsr_linear_backward: bsr_linear_dgrad and bsr_linear_wgrad of one layer as the step issues them, in one launch where
  *   the sizes and the block-tile shape allow it.  Arguments as for the two; `in` and `out` multiples of 8 (others: INVALID_ARG).  dx, dw

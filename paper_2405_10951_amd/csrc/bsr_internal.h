@@ -67,14 +67,14 @@ void ln_fold_weights(const float* w, const float* bias, const float* gamma, cons
 // ---- bf16 MFMA paths --------------------------------------------------------------------------
 bool gemm_mfma_supported(const GemmDesc& g);
 // splitk_ws: fp32 scratch for the partial sums of split-K weight gradients (may be null: no split)
-// A split-K weight gradient leaves fp32 partials that one more pass has to add up.  With a chain, that
+// A weight gradient whose tokens several workgroups share leaves fp32 partials that one more pass has to add up.  With a chain, that
 // pass does not get a launch of its own: it rides on the NEXT weight-gradient launch
 // (which works on the other half of the workspace), and gemm_tn_flush runs the last one.  The sums and
 // their order are the same either way.
 struct TnReduce {
   const float* partial = nullptr;   // [splits][n]
   int64_t n = 0;
-  int splits = 0;
+  int splits = 0;                   // partials
   float* out = nullptr;
   const float* bpartial = nullptr;  // [splits][nb] column sums (bias gradient), may be null
   int nb = 0;

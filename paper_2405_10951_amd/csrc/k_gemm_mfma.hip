@@ -980,15 +980,18 @@ void launch_few(int pick, const GemmDesc& g, hipStream_t s) {
 // up to 2 %.  What bounds it then is the path from L2 (64 bytes a clock into LDS) and, at many tokens, memory: the loads
 // alone take 119 of those 141 us.
 // The MFMA operands are swapped as in the direct-to-LDS NT kernel, so the two share their epilogue.
-// Split-K: workgroup z handles k-tiles [z*kt_per, (z+1)*kt_per) and writes its own fp32 partial; they are added in a fixed
-// order (bit-reproducible, no atomics) by wavefronts of the next such launch.
+// The tokens are cut into parts of kt_per k-tiles, by the sizes alone (tn_kt_per): each part is summed from zero and the parts
+// are added up in ascending order, whichever workgroups they were summed by (bit-reproducible, no atomics).  A sum in parts is also the
+// more precise one: over 6304 tokens dW is 2.4e-7 off its value in 64 bits (768 x 2304, three parts), summed in one chain 5.0e-7.
+// A workgroup takes one part or, with 128 x 128 tiles, `run` of them in a row: the first one of a tile adds its parts up in
+// registers, the others leave a partial each, and wavefronts of the next such launch add these to the first's.
 // Bias gradient: the workgroups of the first row of tiles also multiply every dY fragment by an
 // all-ones fragment, which leaves the column sums of dY (db = 1^T dY) in one more accumulator per
 // 32 columns; they travel through the same partial / reduce path as dW.
 #define BSR_LDS_PTR(T, p) ((T __attribute__((address_space(3)))*)(p))
 
-// four elements of a split-K sum (or, past the matrix, up to four of the column sums): partials added in
-// ascending split order
+// four elements of a sum of partials (or, past the matrix, up to four of the column sums): added in
+// ascending order
 __device__ inline void splitk_reduce_item(const TnReduce& r, int64_t item) {
   const int64_t i = item * 4;
   if (i >= r.n) {
@@ -1011,17 +1014,18 @@ inline int64_t splitk_reduce_items_host(const TnReduce& r) { return r.n / 4 + (r
 
 constexpr int TN_LOADERS = 4, TN_THREADS = (8 + TN_LOADERS) * 64;
 
-// What a weight gradient needs in a launch: its product and split, and the sums of the previous one.
+// What a weight gradient needs in a launch: its product, its parts, and the sums of the previous one.
 struct TnArgs {
   GemmDesc g;
-  float *partial, *bpartial;
-  int kt_per;                    // k-tiles of a split
+  float *partial, *bpartial;     // [1 + parts - run], null where a workgroup takes them all
+  int kt_per;                    // k-tiles of a part
+  int run;                       // parts of a workgroup
   int gx;                        // tiles
-  int blocks;                    // tiles x splits (or groups)
+  int blocks;                    // tiles x runs (or groups)
   TnReduce red;                  // partials of an earlier launch to add up; splits == 0: none
 };
 
-// Workgroup lin of gx tiles x splits (grouped: x groups), tile fastest.
+// Workgroup lin of gx tiles x runs (grouped: x groups), tile fastest.
 template <int BM, int BN, int WM, int WN, int NST>
 __device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
   constexpr int NP = TN_LOADERS, NC = WM * WN;
@@ -1029,6 +1033,7 @@ __device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
   constexpr int ABYTES = 64 * BM * 2, STAGE = (BM + BN) * 128;       // a stage: 64 token rows of A columns, then of B columns
   static_assert(BM % 128 == 0 && BN % 128 == 0, "the segment permutation needs a multiple of 4 segments per row");
   static_assert(NC == 8 && NMF >= 2 && NMF <= 16, "");
+  constexpr bool RUNS = NMF == 2;                      // registers for a sum beside the one that is being taken
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1040,7 +1045,7 @@ __device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
   const bool mfast = ntm < ntn;
   const int m0 = (mfast ? tile % ntm : tile / ntn) * BM, n0 = (mfast ? tile / ntm : tile % ntn) * BN;
   float *partial = a.partial, *bpartial = a.bpartial;
-  int kt0 = by * a.kt_per, nk = min(a.kt_per, (g.K + BK - 1) / BK - kt0);
+  int kt0 = by * a.run * a.kt_per, nk = min(a.run * a.kt_per, (g.K + BK - 1) / BK - kt0);
   if (g.grp_off) {
     // grouped form: by is the group; the contraction runs over its token rows only (perhaps none)
     const int r0 = g.grp_off[by], r1 = g.grp_off[by + 1];
@@ -1203,25 +1208,8 @@ __device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
       BSR_SCHED_FENCE();
     });
   };
-  if (nk > 0) {
-    __builtin_amdgcn_s_barrier();
-    sfor<NFR>([&](auto J) __attribute__((always_inline)) { rd1(IC<0>{}, J, 0, 0); });
-    for (int kt = 0, st = 0; kt < nk; ++kt) {
-      const int stn = st + 1 == NST ? 0 : st + 1;
-      kstep(IC<0>{}, st, 1);
-      kstep(IC<1>{}, st, 2);
-      kstep(IC<0>{}, st, 3);
-      klast(stn);
-      st = stn;
-    }
-  }
-  if (partial) {                                   // split-K: this split's fp32 partial
-    g.C = partial + (int64_t)by * g.M * g.N;
-    g.ldc = g.N;
-  }
-  epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)));
-  if (do_bsum && (lane & 31) == 0) {               // every column of accb holds the column sums
-    float* dst = bpartial ? bpartial + (int64_t)by * g.N : g.bsum;
+  auto store_bsum = [&](float* dst) __attribute__((always_inline)) {
+    if (!do_bsum || (lane & 31) != 0) return;          // every column of accb holds the column sums
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
@@ -1229,7 +1217,85 @@ __device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
         const int col = n0 + wn * TN + ni * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
         if (col < g.N) dst[col] = accb[ni][r];
       }
+  };
+  int slot = by == 0 ? 0 : 1 + (by - 1) * a.run;       // partial of the part that is being summed
+  // what the first workgroup of a tile has added up so far (-0 + x is x, whatever x)
+  f32x16 sum[RUNS ? MI : 1][RUNS ? NI : 1], sumb[RUNS ? NI : 1];
+  if constexpr (RUNS) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sumb[ni][r] = -0.f;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) sum[mi][ni][r] = -0.f;
+      }
   }
+  // a part that is not this workgroup's last has been summed
+  auto next_part = [&]() __attribute__((always_inline)) {
+    if (by == 0) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) sum[mi][ni] += acc[mi][ni];
+        sumb[ni] += accb[ni];
+      }
+    } else {
+      float* dst = partial + (int64_t)slot * g.M * g.N;
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int row = m0 + wm * TM + mi * 32 + (lane & 31), col = n0 + wn * TN + ni * 32 + 8 * q + 4 * lh;
+            if (row < g.M && col < g.N)
+              *(f32x4*)(dst + (int64_t)row * g.N + col) = f32x4{acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2], acc[mi][ni][4 * q + 3]};
+          }
+      if (bpartial) store_bsum(bpartial + (int64_t)slot * g.N);
+      ++slot;
+    }
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        accb[ni][r] = 0.f;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) acc[mi][ni][r] = 0.f;
+      }
+  };
+  if (nk > 0) {
+    __builtin_amdgcn_s_barrier();
+    sfor<NFR>([&](auto J) __attribute__((always_inline)) { rd1(IC<0>{}, J, 0, 0); });
+    for (int kt = 0, st = 0, left = a.kt_per; kt < nk; ++kt) {
+      const int stn = st + 1 == NST ? 0 : st + 1;
+      kstep(IC<0>{}, st, 1);
+      kstep(IC<1>{}, st, 2);
+      kstep(IC<0>{}, st, 3);
+      klast(stn);
+      st = stn;
+      if constexpr (RUNS)
+        if (--left == 0 && kt + 1 < nk) {
+          next_part();
+          left = a.kt_per;
+        }
+    }
+  }
+  if constexpr (RUNS)
+    if (by == 0) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) acc[mi][ni] = sum[mi][ni] + acc[mi][ni];
+        accb[ni] = sumb[ni] + accb[ni];
+      }
+    }
+  if (partial) {
+    g.C = partial + (int64_t)slot * g.M * g.N;
+    g.ldc = g.N;
+  }
+  epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)));
+  store_bsum(bpartial ? bpartial + (int64_t)slot * g.N : g.bsum);
 }
 
 // Tiles of a weight gradient: 128 x 128, four stages, or 256 x 128, three.
@@ -1300,12 +1366,22 @@ bool is_tn(const GemmDesc& g) {
          g.remap_np == 0 && (((uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C) & 15) == 0;
 }
 
-// How a weight gradient is split over its tokens and tiled, and which tile its input gradient takes where nothing was
+// k-tiles of a part of a weight gradient's tokens: parts for 384 workgroups of 128 x 128 (512 from 96 k-tiles on), none
+// below four k-tiles, at most 16, as many as the workspace has room for.  Sizes alone: it is the order of the sum.
+int tn_kt_per(const GemmDesc& g, size_t room) {
+  const int nk = (g.K + BK - 1) / BK;
+  const int64_t tiles = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
+  const size_t per_part = (size_t)g.M * g.N + (g.bsum ? (size_t)g.N : 0);             // partial dW, then partial column sums
+  const int parts = (int)std::min<int64_t>({(nk >= 96 ? 512 : 384) / tiles, nk / 4, (int64_t)std::min<size_t>(room / per_part, 16), 16});
+  return parts > 1 ? (nk + parts - 1) / parts : nk;
+}
+
+// How many parts a workgroup of a weight gradient takes, its tile, and which tile its input gradient takes where nothing was
 // measured: the combination that a model of the launch finishes first.  With one workgroup per CU a workgroup takes
-// c0 + c1 k-tiles (an input gradient with GELU' gelu more; a split that leaves a partial sum another `partial` a million floats);
+// c0 + c1 k-tiles (an input gradient with GELU' gelu more; `partial` more for each partial sum that it leaves);
 // the launch takes what list scheduling over 256 CUs takes (weight gradient first), a start, and the bytes of the partial
-// sums.  Constants fitted to every combination on 112 layers (384 and 768 wide, 197 .. 25216 tokens, 1 .. 16 splits, launches in a
-// row); its choices take 1.0 % longer than the fastest.
+// sums.  Constants fitted to every combination on 112 layers (384 and 768 wide, 197 .. 25216 tokens, 1 .. 16 partials, launches in a
+// row, one part a workgroup).
 struct PairCost { int bm, bn; float c0, c1, gelu; };
 const PairCost kPairNt[] = {{128, 64, 2.00f, 0.365f, 2.88f}, {128, 128, 2.66f, 0.606f, 3.76f},
                             {192, 128, 4.43f, 0.621f, 4.70f}, {256, 128, 3.96f, 0.746f, 6.78f}};
@@ -1334,33 +1410,31 @@ float pair_span(int64_t T, float lt, int64_t N, float ln) {
 }
 
 struct TnSplit {
-  int tile = 0, splits = 1, nt = 1;    // tile of the weight gradient, its splits, tile of the input gradient
-  float us = 0.f;                      // what the model gives the launch
+  int tile = 0, kt_per = 0, run = 1, nt = 1;     // tile of the weight gradient, k-tiles of a part, parts of a workgroup, tile of the input gradient
+  int runs = 1, partials = 0;                    // workgroups of a tile, what they leave to be added up (0: nothing)
 };
 // floats of the split-K workspace that one launch may fill
 size_t tn_room(size_t ws_floats, bool chained) { return chained ? (ws_floats / 2) & ~(size_t)3 : ws_floats; }
 
-// nt: the input gradient of the same launch, or null.  (Sizes only: a tile that was measured or asked for changes no split.)
+// nt: the input gradient of the same launch, or null
 TnSplit tn_split(const GemmDesc* nt, const GemmDesc& g, size_t room) {
   TnSplit best;
-  const int nk = (g.K + BK - 1) / BK;
-  const size_t mn = (size_t)g.M * g.N, per_split = mn + (g.bsum ? (size_t)g.N : 0);   // partial dW, then partial column sums
-  const int most = std::max(1, (int)std::min<size_t>(std::min(nk / 4, 16), room / per_split));
+  const int nk = (g.K + BK - 1) / BK, per = tn_kt_per(g, room), parts = (nk + per - 1) / per;
+  float least = 0.f;
   bool any = false;
-  for (int s = 1; s <= most; ++s) {
-    const int per = (nk + s - 1) / s, splits = (nk + per - 1) / per;
-    if (splits != s) continue;                              // the same k-tiles a split as with fewer of them
-    const float parts = s > 1 ? (float)s * mn * 1e-6f : 0.f;
-    for (int t = 0; t < 2; ++t) {
-      const int64_t T = (int64_t)((g.M + kTn[t].bm - 1) / kTn[t].bm) * ((g.N + kTn[t].bn - 1) / kTn[t].bn) * s;
-      const float lt = kTn[t].c0 + kTn[t].c1 * per + kTn[t].partial * (s > 1 ? 1.f : 0.f);
+  for (int run = 1; run <= parts; ++run) {
+    const int runs = (parts + run - 1) / run, partials = runs > 1 ? 1 + parts - run : 0;
+    const float sums = PAIR_PARTIAL_US * partials * ((float)g.M * g.N * 1e-6f);
+    for (int t = 0; t < (run == 1 ? 2 : 1); ++t) {
+      const int64_t T = (int64_t)((g.M + kTn[t].bm - 1) / kTn[t].bm) * ((g.N + kTn[t].bn - 1) / kTn[t].bn) * runs;
+      const float lt = kTn[t].c0 + kTn[t].c1 * per * run + kTn[t].partial * (runs > 1 ? run : 0);
       for (int i = 0; i < (nt ? 4 : 1); ++i) {
         if (nt && t == 1 && i < 2) continue;                // (small tiles beside large ones: never the fastest)
         const PairCost& c = kPairNt[i];
         const int64_t N = nt ? (int64_t)((nt->M + c.bm - 1) / c.bm) * ((nt->N + c.bn - 1) / c.bn) : 0;
         const float ln = c.c0 + c.c1 * (nt ? nt->K / BK : 0) + (nt && nt->act == ACT_GELU_BWD ? c.gelu : 0.f);
-        const float us = PAIR_START_US + PAIR_PARTIAL_US * parts + pair_span(T, lt, N, ln);
-        if (!any || us < best.us) { best.tile = t; best.splits = s; best.nt = nt ? i : 1; best.us = us; any = true; }
+        const float us = PAIR_START_US + sums + pair_span(T, lt, N, ln);
+        if (!any || us < least) { best = TnSplit{t, per, run, nt ? i : 1, runs, partials}; least = us; any = true; }
       }
     }
   }
@@ -1373,21 +1447,21 @@ TnArgs plan_tn(const GemmDesc& g, const TnSplit& sp, float* ws, size_t ws_floats
   TnArgs a;
   a.g = g;
   a.partial = a.bpartial = nullptr;
-  const int nk = (g.K + BK - 1) / BK;
-  a.kt_per = (nk + sp.splits - 1) / sp.splits;
+  a.kt_per = sp.kt_per;
+  a.run = sp.run;
   a.gx = ((g.M + kTn[sp.tile].bm - 1) / kTn[sp.tile].bm) * ((g.N + kTn[sp.tile].bn - 1) / kTn[sp.tile].bn);
-  a.blocks = a.gx * sp.splits;
+  a.blocks = a.gx * (g.grp_off ? g.groups : sp.runs);      // (grouped: tiles x groups already fills the machine)
   *mine = TnReduce();
   if (chain) {       // this launch takes one half of the workspace, the pending reduction reads the other
     if (ws) ws += (size_t)chain->slot * tn_room(ws_floats, true);
     a.red = chain->pending;
     chain->pending = TnReduce();
   }
-  if (sp.splits > 1) {
+  if (sp.partials > 0) {
     const size_t mn = (size_t)g.M * g.N;
     a.partial = ws;
-    a.bpartial = g.bsum ? ws + (size_t)sp.splits * mn : nullptr;
-    mine->partial = ws; mine->n = (int64_t)mn; mine->splits = sp.splits; mine->out = (float*)g.C;
+    a.bpartial = g.bsum ? ws + (size_t)sp.partials * mn : nullptr;
+    mine->partial = ws; mine->n = (int64_t)mn; mine->splits = sp.partials; mine->out = (float*)g.C;
     mine->bpartial = a.bpartial; mine->nb = g.bsum ? g.N : 0; mine->bout = g.bsum;
     if (chain) {
       chain->pending = *mine;
@@ -1414,8 +1488,7 @@ void launch_tn_as(const TnArgs& a, hipStream_t s) {
 
 void launch_tn(const GemmDesc& g, const TnSplit& sp, float* ws, size_t ws_floats, hipStream_t s, TnChain* chain) {
   TnReduce mine;
-  TnArgs a = plan_tn(g, sp, ws, ws_floats, chain, &mine);
-  if (g.grp_off) a.blocks = a.gx * g.groups;   // a group per split: tiles x groups already fills the machine
+  const TnArgs a = plan_tn(g, sp, ws, ws_floats, chain, &mine);
   if (sp.tile) launch_tn_as<1>(a, s);
   else launch_tn_as<0>(a, s);
   if (!chain && mine.splits > 0) launch_reduce(mine, s);
@@ -1625,7 +1698,9 @@ static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
 
 void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile, TnChain* chain) {
   if (is_tn(g)) {
-    const TnSplit split = g.grp_off ? TnSplit() : tn_split(nullptr, g, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
+    TnSplit split;
+    if (g.grp_off) split.kt_per = (g.K + BK - 1) / BK;     // (all tokens of a group in one part)
+    else split = tn_split(nullptr, g, tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr));
     launch_tn(g, split, splitk_ws, splitk_ws_floats, s, chain);
     return;
   }
@@ -1635,7 +1710,7 @@ void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hip
 }
 
 // The input gradient (NT) and the weight gradient (TN) of one layer: one launch, unless the tile asked for is none of
-// the shapes that the joint kernel has.  Which kernel multiplies, and how the weight gradient is split, does not depend
+// the shapes that the joint kernel has.  Which kernel multiplies, and which tokens are summed together, does not depend
 // on the tile.
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile, TnChain* chain) {

@@ -39,6 +39,36 @@ def test_both_gradients_within_the_rounding_of_their_sums(env, M, kin, out):
         assert all(torch.equal(a, b) for a, b in zip((dx, dw, db), again)), f"tile {tile}"
 
 
+# parts of at least four k-tiles (64 tokens each), for 384 or, from 96 k-tiles on, 512 workgroups of 128 x 128, at most 16
+def tokens_per_part(M, kin, out):
+    nk, tiles = -(-M // 64), -(-kin // 128) * -(-out // 128)
+    parts = max(1, min((512 if nk >= 96 else 384) // tiles, nk // 4, 16))
+    return 64 * -(-nk // parts)
+
+
+# a part a workgroup (1000, 4 parts), all of a tile's parts in one (2111: 3; 2144: 2), runs of 3, 2 (1337), 3, 3, 1 (2144) and 4, 4, 3
+# (6305) parts, the 256 x 128 tile (13000: 6); ragged tokens and columns
+@pytest.mark.parametrize("M,kin,out", [(255, 264, 192), (1000, 264, 192), (2111, 768, 2304), (2144, 3072, 768), (1337, 776, 704), (2144, 768, 768),
+                                       (6305, 776, 768), (13000, 1544, 768)])
+def test_weight_gradients_are_sums_of_parts(env, M, kin, out):
+    """Which tokens are summed together depends on the sizes alone, and the parts are added up in order: the same bits as the parts on
+    their own, added up one after the other."""
+    torch, P = env
+    rng = np.random.default_rng(M + kin + out)
+    x, dy, w = (K.to_dev(torch, K.bf16_np(rng, s), torch.bfloat16) for s in ((M, kin), (M, out), (kin, out)))
+    ws = torch.full((16 * (kin + 1) * out,), float("nan"), device="cuda")
+    _, dw, db = P.bsr_linear_backward(x, dy, w, workspace=ws)
+    alone, _ = P.bsr_linear_wgrad(x, dy, workspace=ws)
+    step = tokens_per_part(M, kin, out)
+    parts = [P.bsr_linear_backward(x[i:i + step], dy[i:i + step], w)[1:] for i in range(0, M, step)]
+    dw_ref, db_ref = parts[0]
+    for p in parts[1:]:
+        dw_ref, db_ref = dw_ref + p[0], db_ref + p[1]
+    torch.cuda.synchronize()
+    assert torch.equal(dw, dw_ref) and torch.equal(db, db_ref), "with the input gradient"
+    assert torch.equal(alone, dw_ref), "on its own"
+
+
 @pytest.mark.parametrize("tile", [96128, 128256, 192256, 256064, 96256, 3064128, 2192128, 2256128, 2128128])
 def test_ids_that_are_no_longer_shapes_run_what_no_id_runs(env, tile):
     torch, P = env
