@@ -595,6 +595,38 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
   }
 }
 
+// The same for results that leave as plain fp32, as weight gradients do.  (Through epilogue_t, whose other paths the compiler cannot
+// rule out, the kernels with the 256 x 128 weight-gradient tile spilled 25 - 29 registers and were 5 KB longer.)
+template <int MI, int NI>
+__device__ __forceinline__ void epilogue_f32(float* c, int64_t ldc, int M, int N, const f32x16 (&acc)[MI][NI], int row0, int col0, int lane,
+                                             unsigned char* patch) {
+  constexpr int TN = NI * 32, LDF = TN * 4 + 16, CPR = TN / 4, RPP = 64 / CPR;     // 4-column chunks per row, rows per pass of the wave
+  static_assert(32 % RPP == 0, "whole passes");
+  const int lm = lane & 31, lh = lane >> 5, my_chunk = lane % CPR, my_row = lane / CPR, col = col0 + my_chunk * 4;
+#pragma nounroll
+  for (int mi = 0; mi < MI; ++mi) {
+    sfor<MI>([&](auto I) __attribute__((always_inline)) {
+      constexpr int i = decltype(I)::value;
+      if (mi != i) return;
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg)
+          *(f32x4*)(patch + lm * LDF + (ni * 32 + 8 * rg + 4 * lh) * 4) =
+              f32x4{acc[i][ni][4 * rg], acc[i][ni][4 * rg + 1], acc[i][ni][4 * rg + 2], acc[i][ni][4 * rg + 3]};
+    });
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+    for (int p = 0; p < 32 / RPP; ++p) {
+      const int lr = p * RPP + my_row, m = row0 + mi * 32 + lr;
+      if (m < M && col < N) *(f32x4*)(c + (int64_t)m * ldc + col) = *(const f32x4*)(patch + lr * LDF + my_chunk * 16);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // The work of one tile (a kernel of its own below, and the input-gradient half of a layer's backward launch).
 template <int BM, int BN, int WM, int WN, int NST>
 __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
@@ -979,7 +1011,7 @@ void launch_few(int pick, const GemmDesc& g, hipStream_t s) {
 // 167 us; register-staged 201; loaders of their own 141).  Two loaders are too few (154), a higher priority for them is worth
 // up to 2 %.  What bounds it then is the path from L2 (64 bytes a clock into LDS) and, at many tokens, memory: the loads
 // alone take 119 of those 141 us.
-// The MFMA operands are swapped as in the direct-to-LDS NT kernel, so the two share their epilogue.
+// The MFMA operands are swapped as in the direct-to-LDS NT kernel: accumulators hold transposed tiles.
 // The tokens are cut into parts of kt_per k-tiles, by the sizes alone (tn_kt_per): each part is summed from zero and the parts
 // are added up in ascending order, whichever workgroups they were summed by (bit-reproducible, no atomics).  A sum in parts is also the
 // more precise one: over 6304 tokens dW is 2.4e-7 off its value in 64 bits (768 x 2304, three parts), summed in one chain 5.0e-7.
@@ -1290,11 +1322,8 @@ __device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
         accb[ni] = sumb[ni] + accb[ni];
       }
     }
-  if (partial) {
-    g.C = partial + (int64_t)slot * g.M * g.N;
-    g.ldc = g.N;
-  }
-  epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)));
+  epilogue_f32<MI, NI>(partial ? partial + (int64_t)slot * g.M * g.N : (float*)g.C, partial ? g.N : g.ldc, g.M, g.N, acc, m0 + wm * TM,
+                       n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)));
   store_bsum(bpartial ? bpartial + (int64_t)slot * g.N : g.bsum);
 }
 
