@@ -247,20 +247,28 @@ void launch(const GemmDesc& g, hipStream_t s) {
 // Which block tile: the one that a model finishes first.  With t tiles, time = c0 + ceil(t / 256) (c1 + c2 K / 100) + t / 256
 // (c3 + c4 K / 100) + ceil(t / 512) (c5 + c6 K / 100) microseconds (rounds of one workgroup per CU, work, rounds of two), fitted to chains
 // of equal launches of the three forms (264 products: 65 .. 6304 rows, 192 and 384 wide).  Its picks take 0.1 % longer than the
-// fastest tile; tile areas with prices set by hand 1.0 %, 32 x 32 always 3.9 %.
+// fastest tile; tile areas with prices set by hand 1.0 %, 32 x 32 always 3.9 %.  At other widths the model extrapolates.
+// The fewer k of a tile a wavefront adds up, the closer a sum is to its value in 64 bits, so no product takes a larger tile than `most`, the
+// least of tile area x rounds of the CUs with those prices (DeiT-S steps of 1 .. 8 images: weight gradients over a few dozen tokens).
 int f32_pick(const GemmDesc& g) {
   const int edge[3] = {128, 64, 32};
   const float c[3][7] = {{6.180f, 0.000f, 5.645f, 3.077f, 0.964f, 1.018f, 0.500f},
                          {3.079f, 0.387f, 1.480f, 0.514f, 0.321f, 0.420f, 0.279f},
                          {2.598f, 0.505f, 0.421f, 0.453f, 0.032f, 0.137f, 0.152f}};
-  int best = 0;
+  const float price[3] = {1.0f, 1.15f, 1.6f};
+  int64_t tiles[3];
+  int most = 0, best = 0;
   float least = 0.f;
-  const float k = 0.01f * g.K;
   for (int i = 0; i < 3; ++i) {
-    const int64_t tiles = (int64_t)((g.M + edge[i] - 1) / edge[i]) * ((g.N + edge[i] - 1) / edge[i]);
-    const float t = c[i][0] + (float)((tiles + 255) / 256) * (c[i][1] + c[i][2] * k) + (float)tiles / 256.f * (c[i][3] + c[i][4] * k) +
-                    (float)((tiles + 511) / 512) * (c[i][5] + c[i][6] * k);
-    if (i == 0 || t < least) { best = i; least = t; }
+    tiles[i] = (int64_t)((g.M + edge[i] - 1) / edge[i]) * ((g.N + edge[i] - 1) / edge[i]);
+    const float area = (float)((tiles[i] + 255) / 256) * edge[i] * edge[i] * price[i];
+    if (i == 0 || area < least) { most = i; least = area; }
+  }
+  const float k = 0.01f * g.K;
+  for (int i = most; i < 3; ++i) {
+    const float t = c[i][0] + (float)((tiles[i] + 255) / 256) * (c[i][1] + c[i][2] * k) + (float)tiles[i] / 256.f * (c[i][3] + c[i][4] * k) +
+                    (float)((tiles[i] + 511) / 512) * (c[i][5] + c[i][6] * k);
+    if (i == most || t < least) { best = i; least = t; }
   }
   return best;
 }
