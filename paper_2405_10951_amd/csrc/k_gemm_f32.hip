@@ -41,7 +41,7 @@ __device__ inline int xcd_range(int pid, int n) {
 // Loads that go straight into LDS: lane l of a wavefront writes 16 bytes at the wavefront's LDS address + 16 l
 #define BSR_GLOBAL_PTR(p) ((const void __attribute__((address_space(1)))*)(p))
 #define BSR_LDS_VOID(p) ((void __attribute__((address_space(3)))*)(p))
-template <int N> __device__ __forceinline__ void wait_vmcnt() { __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8)); }
+__device__ __forceinline__ void wait_vmcnt0() { __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8)); }
 __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4)); }
 
 // k-tile: long where the wavefronts share it, since a tile that is alone on its CU is done with 32 k long before the
@@ -102,18 +102,18 @@ struct Tile {
   }
 };
 
-// Operand tiles go straight into a ring of NST stages in LDS, NST - 1 k-tiles ahead, one barrier per k-tile.  (Staged through
+// Operand tiles go straight into two stages in LDS, one k-tile ahead, one barrier per k-tile.  (Staged through
 // registers, the branches around the last k-tiles made the compiler wait for every load in flight at each LDS write: loads
-// and matrix work took turns, 23 + 25 us of the 42 us of 1576 x 384 x 1536.)
-template <int BM, int BN, int WM, int WN, int WK, int NST, bool AK, bool BKC>
+// and matrix work took turns, 23 + 25 us of the 42 us of 1576 x 384 x 1536.  A ring with its depth as a parameter, always two: fp32 steps
+// of 1 .. 8 images of DeiT-S and of the 192-wide block took 2 % longer, DeiT-S of 8 images 1571 -> 1544 us.)
+template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
 __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_kernel(GemmDesc g) {
   constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, GRP = KT / 8 / WK;
   typedef Tile<BM, KT, AK, NT> TA;
   typedef Tile<BN, KT, BKC, NT> TB;
-  constexpr int LPT = TA::NCH + TB::NCH, STAGE = TA::FLOATS + TB::FLOATS;
-  static_assert(NST >= 2 && NST <= 4 && (NST - 1) * LPT <= 63, "vmcnt has 6 bits");
-  extern __shared__ __attribute__((aligned(16))) float sm[];      // [NST][STAGE]: A rows, then B rows
+  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  extern __shared__ __attribute__((aligned(16))) float sm[];      // [2][STAGE]: A rows, then B rows
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave / (WM * WN), wmn = wave % (WM * WN), wm = wmn / WN, wn = wmn % WN;
   const int lr = lane & 31, lh = lane >> 5;
@@ -139,12 +139,10 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
     TA::load(sm + st * STAGE, A, lda, m0, g.M, kt * KT, g.K, tid);
     TB::load(sm + st * STAGE + TA::FLOATS, B, ldb, n0, g.N, kt * KT, g.K, tid);
   };
-  for (int j = 0; j < NST - 1 && j < nk; ++j) issue(j, j);
-  for (int kt = 0, st = 0; kt < nk; ++kt) {
-    const int later = min(nk - 1 - kt, NST - 2);           // k-tiles that may still be on their way
-    if (NST >= 4 && later >= 2) wait_vmcnt<(NST >= 4 ? 2 : 0) * LPT>();
-    else if (NST >= 3 && later >= 1) wait_vmcnt<(NST >= 3 ? 1 : 0) * LPT>();
-    else wait_vmcnt<0>();
+  issue(0, 0);
+  for (int kt = 0; kt < nk; ++kt) {
+    const int st = kt & 1;
+    wait_vmcnt0();
     float* a = sm + st * STAGE;
     float* b = a + TA::FLOATS;
     if ((kt + 1) * KT > g.K) {
@@ -153,7 +151,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
     }
     wait_lgkmcnt0();                                       // this wavefront has read k-tile kt - 1
     __builtin_amdgcn_s_barrier();
-    if (kt + NST - 1 < nk) issue(kt + NST - 1, st == 0 ? NST - 1 : st - 1);
+    if (kt + 1 < nk) issue(kt + 1, st ^ 1);
 #pragma unroll
     for (int q = 0; q < GRP; ++q) {
       const int grp = q * WK + wk;
@@ -172,7 +170,6 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
     }
     if (do_bsum)
       for (int k = tid / BN; k < KT; k += SG) csum += b[k * BN + tid % BN];
-    st = st + 1 == NST ? 0 : st + 1;
   }
   __syncthreads();
   if (do_bsum) {
@@ -228,13 +225,13 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
   }
 }
 
-template <int BM, int BN, int WM, int WN, int WK, int NST, bool AK, bool BKC>
+template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
 void launch(const GemmDesc& g, hipStream_t s) {
   constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
-  constexpr size_t tiles_f = NST * (size_t)(Tile<BM, KT, AK, NT>::FLOATS + Tile<BN, KT, BKC, NT>::FLOATS);
+  constexpr size_t tiles_f = 2 * (size_t)(Tile<BM, KT, AK, NT>::FLOATS + Tile<BN, KT, BKC, NT>::FLOATS);
   constexpr size_t sums_f = (size_t)WK * BM * (BN + 4);
   constexpr size_t lds = sizeof(float) * (tiles_f > sums_f ? tiles_f : sums_f);
-  auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, NST, AK, BKC>;
+  auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, AK, BKC>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -276,9 +273,9 @@ int f32_pick(const GemmDesc& g) {
 template <bool AK, bool BKC>
 void launch_form(const GemmDesc& g, hipStream_t s) {
   switch (f32_pick(g)) {
-    case 0: launch<128, 128, 2, 2, 1, 2, AK, BKC>(g, s); break;
-    case 1: launch<64, 64, 2, 2, 2, 2, AK, BKC>(g, s); break;
-    default: launch<32, 32, 1, 1, 8, 2, AK, BKC>(g, s); break;
+    case 0: launch<128, 128, 2, 2, 1, AK, BKC>(g, s); break;
+    case 1: launch<64, 64, 2, 2, 2, AK, BKC>(g, s); break;
+    default: launch<32, 32, 1, 1, 8, AK, BKC>(g, s); break;
   }
 }
 
