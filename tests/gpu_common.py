@@ -124,8 +124,9 @@ def run_hip_step(cfg, params, x, labels, forced_idx=None, max_batch=None, sgd=No
     return out
 
 
-def product_kernels(call):
-    """Names of the matrix product kernels that call() launches, in order: what really ran."""
+def product_kernels(call, *parts):
+    """Names of the matrix product kernels that call() launches (or of those with one of `parts` in their name), in order: what
+    really ran."""
     from torch.profiler import ProfilerActivity, profile
     call()
     torch.cuda.synchronize()
@@ -133,7 +134,7 @@ def product_kernels(call):
         call()
         torch.cuda.synchronize()
     runs = sorted((e for e in prof.events() if e.device_type == torch.autograd.DeviceType.CUDA), key=lambda e: e.time_range.start)
-    return [e.name for e in runs if "gemm_" in e.name]
+    return [e.name for e in runs if any(p in e.name for p in parts or ("gemm_",))]
 
 
 def families(names):

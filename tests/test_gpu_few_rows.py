@@ -61,11 +61,16 @@ def test_no_tile_changes_the_gradients_of_a_layer(env, orc64, M, kin, out):
     w = K.bf16_np(rng, (kin, out), 0.05)
     xt, dyt, wt, ut = dev(x), dev(dy), dev(w), dev(u)
 
+    ws = torch.full((16 * (kin + 1) * out,), float("nan"), device="cuda")
+
     def run(tile):
-        got = P.bsr_linear_backward(xt, dyt, wt, u=ut, tile=tile)
+        got = P.bsr_linear_backward(xt, dyt, wt, u=ut, workspace=ws, tile=tile)
         torch.cuda.synchronize()
         return [t.float().cpu().numpy() for t in got]
 
+    assert families(product_kernels(lambda: run(0))) == (["few", "wgrad"] if (M, out) == (32, 3072) else ["joint"])
+    if (M, out) != (32, 3072):
+        assert families(product_kernels(lambda: P.bsr_linear_dgrad(dyt, wt))) == ["few"]
     base = run(0)
     K.assert_close(base[0], orc64.gelu_bwd(orc64.linear_dgrad(dy, w), u), "dx")
     dw, db = orc64.linear_wgrad(x, dy)

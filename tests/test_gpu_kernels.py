@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import bsr_synth as S
+from gpu_common import families, product_kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -72,7 +73,7 @@ def test_every_tile_shape_gives_the_same_bits(env, orc64, M, kin, out):
     """Both kernel families, every block-tile shape, every epilogue form (bias; GELU with the stored pre-activation;
     residual; GELU' of a stored tensor in the input-gradient product of Eq. 2), on products whose rows and columns end
     inside a tile and whose contraction is 1 .. 24 k-tiles: the same bits as the default shape, which is checked
-    against the oracle."""
+    against the oracle.  (Products of few rows run one kernel whatever the tile.)"""
     torch, P = env
     rng = np.random.default_rng(M * 3 + kin + out)
     x = bf16_np(rng, (M, kin)); w = bf16_np(rng, (kin, out), 0.05); b = rng.standard_normal(out).astype(np.float32)
@@ -93,6 +94,8 @@ def test_every_tile_shape_gives_the_same_bits(env, orc64, M, kin, out):
         assert used == 1
         return [bits(t) for t in (y, u, g, r, d)]
 
+    few = (M, kin, out) in ((300, 448, 392), (333, 1536, 264))
+    assert families(product_kernels(lambda: forms(0))) == ["few" if few else "tiled"] * 4
     base = forms(0)
     ref = orc64.linear(x, w, b)
     assert_close(torch.from_numpy(base[0]).view(torch.bfloat16).float().numpy(), ref, "linear")

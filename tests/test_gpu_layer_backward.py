@@ -1,21 +1,29 @@
 """GPU parity of a layer's two gradients where the joint launch can go wrong: token counts around the k-tiles of the weight
-gradient (64 tokens) and around its splits, both of its tiles, widths that end inside a tile, and scratch too small for the
-splits.  And attention forward: a head by one workgroup or by two is the same bits."""
+gradient (64 tokens) and around its parts, both of its tiles, widths that end inside a tile, and scratch too small for the
+parts.  And attention forward: a head by one workgroup or by two is the same bits."""
+import re
+
 import numpy as np
 import pytest
 
 import test_gpu_kernels as K
-from gpu_common import product_kernels
+from gpu_common import families, product_kernels
 from test_gpu_kernels import env  # noqa: F401  (a fixture)
 
 pytestmark = pytest.mark.gpu
 
 
-# one token .. a few k-tiles; 8 .. 264 columns; splits with a ragged last one (788, 1000, 2111); the 256 x 128 tile (4416 and
-# 6304 tokens at 768 x 3072)
-@pytest.mark.parametrize("M,kin,out", [(1, 64, 8), (63, 192, 136), (64, 136, 264), (65, 264, 72), (191, 768, 64), (197, 768, 776),
-                                       (788, 384, 1536), (1000, 264, 520), (2111, 768, 2304), (4416, 768, 3072), (6304, 3072, 768)])
-def test_both_gradients_within_the_rounding_of_their_sums(env, M, kin, out):
+# the joint launch: one token .. a few k-tiles, on either side of a k-tile's 64 tokens; columns that end inside its tiles of 64 and 128;
+# several parts, the last one ragged, in one workgroup (2111) or more (450 and above), the 256 x 128 tile (13000)
+JOINT = [(1, 136, 64), (33, 264, 192), (63, 264, 128), (64, 392, 192), (65, 264, 192), (191, 264, 192), (320, 392, 448), (450, 392, 384), (520, 136, 64),
+         (1000, 776, 320), (1337, 776, 704), (2111, 776, 2304), (6305, 776, 768), (13000, 1544, 768),
+         (191, 768, 64), (788, 384, 1536), (2111, 768, 2304), (4416, 768, 3072), (6304, 3072, 768)]
+# two launches, since the input gradient has no whole k-tiles
+TWO = [(1, 64, 8), (63, 192, 136), (64, 136, 264), (65, 264, 72), (197, 768, 776), (1000, 264, 520)]
+
+
+@pytest.mark.parametrize("M,kin,out,kernels", [s + (["joint"],) for s in JOINT] + [s + (["tiled", "wgrad"],) for s in TWO])
+def test_both_gradients_within_the_rounding_of_their_sums(env, M, kin, out, kernels):
     """Products of bf16 numbers are exact in fp32 and each of n additions errs by at most 2^-23 of what it adds up to, so an
     fp32 sum is within n 2^-23 of the sum of the terms' magnitudes; dX is then rounded to bf16 (2^-8 of its value)."""
     torch, P = env
@@ -25,8 +33,12 @@ def test_both_gradients_within_the_rounding_of_their_sums(env, M, kin, out):
     dx_ref, dw_ref, db_ref = DY @ W.t().contiguous(), X.t().contiguous() @ DY, DY.sum(0)
     dx_mag, dw_mag, db_mag = DY.abs() @ W.abs().t().contiguous(), X.abs().t().contiguous() @ DY.abs(), DY.abs().sum(0)
     per = (kin + 1) * out
-    for floats in (0, 2 * per, 16 * per):                   # no room for a split, for two, for all
+    for floats in (0, 2 * per, 16 * per):                   # no room for a second part, for two, for all
         ws = torch.full((floats,), float("nan"), device="cuda") if floats else None
+        names = product_kernels(lambda: P.bsr_linear_backward(x, dy, w, workspace=ws))
+        assert families(names) == kernels
+        if M == 13000 and floats == 16 * per:
+            assert re.search(r"gemm_pair_kernel<\d, 1>", names[0]), names
         dx, dw, db = P.bsr_linear_backward(x, dy, w, workspace=ws)
         alone, _ = P.bsr_linear_wgrad(x, dy, workspace=ws)
         torch.cuda.synchronize()
@@ -37,6 +49,28 @@ def test_both_gradients_within_the_rounding_of_their_sums(env, M, kin, out):
     for tile in (160256, 7320256):                          # shapes that the joint launch does not have: two launches, the same bits
         again = P.bsr_linear_backward(x, dy, w, workspace=ws, tile=tile)
         assert all(torch.equal(a, b) for a, b in zip((dx, dw, db), again)), f"tile {tile}"
+
+
+def test_sums_added_up_by_the_next_launch_are_the_same_bits(env):
+    """With one block trained, the partial sums of its last weight gradient are added up by a launch of their own; with two, by spare
+    wavefronts of the next block's first joint launch."""
+    import bsr_synth as S
+    torch, P = env
+    grads = []
+    for first in (2, 1):
+        cfg = S.get_config("c1_block_fp32", dtype="bf16", depth=3, first_trainable=first, drop_blocks=[], tokens_in=130, batch=8)
+        x, _ = S.make_inputs(cfg)
+        ctx = P.Context(cfg, S.make_params(cfg), 8)
+        xf = torch.empty((8, ctx.T_f, cfg["dim"]), dtype=ctx.act_dtype, device="cuda")
+        ctx.bsr_forward_frozen(torch.as_tensor(x).cuda().to(ctx.act_dtype).contiguous(), x_out=xf)
+        loss, g = torch.zeros(4, device="cuda"), ctx.new_grads()
+        names = product_kernels(lambda: ctx.bsr_train_blocks_fwd_bwd(xf, None, g, loss_out=loss), "splitk_reduce", "gemm_pair")
+        # (the layer from 192 to 768 takes the kernel for few rows)
+        assert ["splitk_reduce" in n for n in names] == [False] * 3 * (3 - first) + [True]
+        grads.append({n: t.clone() for n, t in g.items() if n.startswith("blocks.2.")})
+    assert len(grads[0]) == 12
+    for n, t in grads[0].items():
+        assert torch.equal(t, grads[1][n]), n
 
 
 # parts of at least four k-tiles (64 tokens each), for 384 or, from 96 k-tiles on, 512 workgroups of 128 x 128, at most 16
