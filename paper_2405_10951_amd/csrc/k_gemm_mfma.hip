@@ -1356,10 +1356,11 @@ template <> struct PairTile<3> { static constexpr int BM = 256, BN = 128, WM = 4
 // Both gradients of a layer (Eq. 2 and Eq. 4): they read the same dy and neither reads what the other writes.  One
 // workgroup per CU; the weight gradient's workgroups, which are the longest, come first, the input gradient's tiles fill
 // the CUs they leave.  Its workgroups have wavefronts to spare: those add up the partials of the previous weight gradient.
-// (Workgroups of their own for these sums hold a CU each: 768 x 768 over 2144 tokens 13.0 -> 16.1 us where they no longer
-// fit beside the tiles.)  Against the register-staged pair that this replaces, both gradients, launches in a row: 2144
-// tokens 768 x 3072 39.2 -> 27.7 us, 3072 x 768 with GELU' 45.5 -> 38.4, 768 x 768 17.6 -> 13.0, 768 x 2304 33.2 -> 24.7,
-// 384 x 1536 17.9 -> 13.2; 25216 tokens 768 x 3072 310 -> 244, 768 x 2304 238 -> 183; 1.28x over 112 shapes of 197 .. 25216 tokens.
+// (Workgroups of their own for these sums hold a CU each: 768 x 768 over 2144 tokens took 1.24 times as long where they no longer
+// fitted beside the tiles.)  Against the register-staged pair that this replaces, both gradients, calls in a row that add their partials up in a
+// launch of their own: 2144 tokens 768 x 3072 43.6 -> 28.0 us, 3072 x 768 with GELU' 52.6 -> 38.0, 768 x 2304 41.8 -> 24.6; where the partials are
+// most of it 768 x 768 21.6 -> 22.6, 384 x 1536 23.5 -> 22.9; 25216 tokens 768 x 3072 325 -> 238, 768 x 2304 247 -> 181; 1.18x over 112 shapes of
+// 197 .. 25216 tokens (0.87 .. 1.71).
 template <int I, int T>
 __global__ __launch_bounds__(TN_THREADS, 1) void gemm_pair_kernel(GemmDesc g, TnArgs a, int nt_tiles) {
   using N = PairTile<I>;
@@ -1410,7 +1411,9 @@ int tn_kt_per(const GemmDesc& g, size_t room) {
 // c0 + c1 k-tiles (an input gradient with GELU' gelu more; `partial` more for each partial sum that it leaves);
 // the launch takes what list scheduling over 256 CUs takes (weight gradient first), a start, and the bytes of the partial
 // sums.  Constants fitted to every combination on 112 layers (384 and 768 wide, 197 .. 25216 tokens, 1 .. 16 partials, launches in a
-// row, one part a workgroup).
+// row, one part a workgroup).  Steps with the parts of a workgroup forced to 1, 2, 3, 4 and all, and by the model, in us: ViT-B, 32 images
+// 2320, 2256, 2226, 2231, 2241 and 2232, 128 images 5687, 5765, 5709, 5644, 5791 and 5633; DeiT-S, 32 images with AdamW 1348, 1308, 1290, 1300, 1370
+// and 1271, 577 tokens 1740, 1715, 1709, 1716, 1831 and 1680.
 struct PairCost { int bm, bn; float c0, c1, gelu; };
 const PairCost kPairNt[] = {{128, 64, 2.00f, 0.365f, 2.88f}, {128, 128, 2.66f, 0.606f, 3.76f},
                             {192, 128, 4.43f, 0.621f, 4.70f}, {256, 128, 3.96f, 0.746f, 6.78f}};
