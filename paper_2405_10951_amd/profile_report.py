@@ -16,6 +16,9 @@
         shape chosen, its measured time, TFLOP/s, % of the bf16 MFMA peak and the algorithmic bytes (operands
         and result once); with the two counter files of a --pmc FETCH_SIZE / WRITE_SIZE run of
         `bench.py --no-pipeline --calibrate-copy --no-sweep`, also the HBM-side bytes each launch moved.
+    python -m paper_2405_10951_amd.profile_report tiles
+        needs the GPU: forward products and layer gradients of 384- and 768-wide models in every tile shape, in chains over twelve
+        sets of operands: the model's pick against the fastest.
 """
 from __future__ import annotations
 
@@ -216,6 +219,54 @@ def shapes(argv: list[str]) -> None:
           f"({100 * tot_fl / tot_us / 1e6 / PEAK_BF16_TFLOPS:.1f} % of the bf16 MFMA peak)")
 
 
+def tiles() -> None:
+    import torch
+    import paper_2405_10951_amd as P
+    ids = [0] + list(P.bsr_gemm_tile_shapes())
+    rand = lambda *s: torch.randn(s, device="cuda").to(torch.bfloat16)      # noqa: E731
+
+    def fastest(call) -> dict:
+        """id -> microseconds of a launch, the least of five rounds over all ids, graphs of 24 launches"""
+        graphs, us = {}, dict.fromkeys(ids, float("inf"))
+        for t in ids:
+            call(0, t)
+            torch.cuda.synchronize()
+            graphs[t] = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graphs[t]):
+                for i in range(24):
+                    call(i % 12, t)
+        for _ in range(6):
+            for t in ids:
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                graphs[t].replay()
+                b.record()
+                b.synchronize()
+                us[t] = min(us[t], a.elapsed_time(b) / 24 * 1e3)
+        return us
+
+    for what in ("product", "gradients"):
+        lost = n = 0
+        print(f"# {what}: us in the model's shape, in the fastest of {len(ids) - 1}, its id (none: all within 3 %, as where the kernel for few rows runs)")
+        print(f"{'rows':>6s} {'in':>5s} {'out':>5s} {'model':>8s} {'fastest':>8s} {'id':>8s} {'ratio':>6s}")
+        for D in (384, 768):
+            for M in (197, 400, 788, 1072, 2144, 3072, 4416, 6304, 12608, 25216):
+                for kin, out in ((D, 3 * D), (D, D), (D, 4 * D), (4 * D, D)):
+                    x, dy, w = rand(M, kin), rand(M, out), [rand(out, kin) for _ in range(12)]
+                    if what == "product":
+                        y = torch.empty((M, out), dtype=torch.bfloat16, device="cuda")
+                        us = fastest(lambda i, t: P.bsr_linear_forward(x, w[i], None, y=y, tile=t))      # noqa: B023
+                    else:
+                        w = [v.t().contiguous() for v in w]
+                        ws = torch.empty(8 * max(3 * D * D, 4 * D * D) + 64 * D, device="cuda")
+                        us = fastest(lambda i, t: P.bsr_linear_backward(x, dy, w[i], workspace=ws, tile=t))      # noqa: B023
+                    best = min(ids[1:], key=us.get)
+                    same = max(us.values()) < 1.03 * min(us.values())
+                    lost, n = lost + us[0] / min(us.values()) - 1.0, n + 1
+                    print(f"{M:6d} {kin:5d} {out:5d} {us[0]:8.1f} {us[best]:8.1f} {'none' if same else best:>8} {us[0] / us[best]:6.3f}", flush=True)
+        print(f"# over {n}: the model's shape takes {100 * lost / n:.1f} % longer than the fastest")
+
+
 if __name__ == "__main__":
     if len(sys.argv) >= 3 and sys.argv[1] == "trace":
         trace(sys.argv[2], int(sys.argv[3]) if len(sys.argv) > 3 else 20, *sys.argv[4:5])
@@ -225,5 +276,7 @@ if __name__ == "__main__":
         counters(sys.argv[2], int(sys.argv[3]) if len(sys.argv) > 3 else 5)
     elif len(sys.argv) >= 2 and sys.argv[1] == "shapes":
         shapes(sys.argv[2:])
+    elif len(sys.argv) >= 2 and sys.argv[1] == "tiles":
+        tiles()
     else:
         sys.exit(__doc__)
