@@ -11,10 +11,6 @@ namespace {
 
 constexpr int MAX_T = 1024, NT = 256, NW = NT / WAVE, GL = 8, NG = NT / GL;   // eight lanes per key, NG keys at a time
 
-__device__ inline float group_sum(float v) {       // over the eight lanes of a key
-  v += __shfl_xor(v, 1); v += __shfl_xor(v, 2); v += __shfl_xor(v, 4);
-  return v;
-}
 __device__ inline float block_sum(float v, float* red) {
   v = wave_sum(v);
   __syncthreads();
@@ -59,7 +55,7 @@ __global__ __launch_bounds__(NT) void attn_cls_fwd_kernel(const T* __restrict__ 
 #pragma unroll
       for (int e = 0; e < V; ++e) s = fmaf((float)q[e], (float)k[e], s);
     }
-    s = group_sum(s) * scale;
+    s = eight_sum(s) * scale;
     if (gl == 0) p[j] = s;
     mx = fmaxf(mx, s);
   }
@@ -119,7 +115,7 @@ __global__ __launch_bounds__(NT) void attn_cls_bwd_kernel(const T* __restrict__ 
 #pragma unroll
       for (int e = 0; e < V; ++e) { s = fmaf((float)q[e], (float)k[e], s); t = fmaf((float)g[e], (float)v[e], t); }
     }
-    const float pj = expf(group_sum(s) * scale - l), dpj = group_sum(t);
+    const float pj = expf(eight_sum(s) * scale - l), dpj = eight_sum(t);
     if (gl == 0) { p[j] = pj; dp[j] = dpj; delta = fmaf(pj, dpj, delta); }
   }
   delta = block_sum(delta, rs4);           // (the barriers in it also publish p and dp)

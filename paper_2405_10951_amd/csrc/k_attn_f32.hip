@@ -11,7 +11,7 @@
 // product, with the other operand read in that row order.
 // 8 images of 6 heads at 197 .. 67 tokens: forward 53 -> 12 us on average, backward 72 -> 18 us, against one wavefront
 // per row on the vector unit.
-#include "bsr_internal.h"
+#include "rowops.h"
 
 namespace bsr {
 
@@ -73,13 +73,13 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_fwd_kernel(const float* __re
       if (want_cls && lr == 0 && key < T) cls_s[key] = s[r];
       mx = fmaxf(mx, s[r]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));                    // finite: a block holds at least one key
+    mx = half_max(mx);                    // finite: a block holds at least one key
     const float alpha = expf(m - mx);
     m = mx;
     float sum = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) { s[r] = expf(s[r] - mx); sum += s[r]; }
-    l = l * alpha + sum + __shfl_xor(sum, 32, 64);
+    l = l * alpha + sum + half_other(sum);
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
 #pragma unroll
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_bwd_kernel(const float* _
     for (int g = 0; g < 8; ++g)
 #pragma unroll
       for (int e = 0; e < 4; ++e) d = fmaf(dof[g][e], of[g][e], d);
-    return d + __shfl_xor(d, 32, 64);
+    return half_sum(d);
   };
   if ((int)blockIdx.x < nblk) {
     const int q0 = blockIdx.x * 32, qc = min(q0 + lr, T - 1);

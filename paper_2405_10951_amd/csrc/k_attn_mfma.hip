@@ -11,7 +11,7 @@
 // operand of the second product O^T = V^T P^T: MFMA contracts over a dummy index, so the key order
 // that the accumulator layout dictates is simply applied to the V^T reads as well.  No T x T tensor
 // ever leaves registers.
-#include "bsr_internal.h"
+#include "rowops.h"
 
 namespace bsr {
 
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
 #pragma unroll
     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[jb][r]);
   }
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = half_max(mx);
   const float mc = mx * c;
   float sum = 0.f;
   bf16x8 pf[2 * NJ];
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
       sum += p;
       pf[2 * jb + (r >> 3)][r & 7] = (bf16)p;
     }
-  sum += __shfl_xor(sum, 32, 64);
+  sum = half_sum(sum);
   const float inv = 1.0f / sum;
   const int qi = q0 + lr;
   if (lse && lh == 0 && qi < T) lse[((int64_t)b * H + h) * T + qi] = mx * 0.125f + __logf(sum);
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(NJ * 64, 4) void attn_bwd_dq_kernel(const bf16* __r
       for (int e = 0; e < 8; ++e) dl += (float)dof[ks][e] * (float)of[e];
     }
   }
-  dl += __shfl_xor(dl, 32, 64);
+  dl = half_sum(dl);
   const float l2 = lse[((int64_t)b * H + h) * T + qc] * 1.44269504088896341f;
   if (lh == 0 && qi < T) delta[((int64_t)b * H + h) * T + qi] = dl;
   const float c = 0.125f * 1.44269504088896341f;
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __res
           if (j < T) cls_s[j] = s[jb][r];
         }
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));         // finite: a chunk holds at least one key
+    mx = half_max(mx);         // finite: a chunk holds at least one key
     const float alpha = __builtin_amdgcn_exp2f((m - mx) * c), mc = mx * c;
     m = mx;
 #pragma unroll
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __res
           o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, p[hf].lo, o[nb], 0, 0, 0);
         }
     }
-    l = l * alpha + sum + __shfl_xor(sum, 32, 64);
+    l = l * alpha + sum + half_other(sum);
   }
   const float inv = 1.0f / l;
   if (qi < T) {
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(256, 2) void attn_delta_long_kernel(const bf16* __r
       for (int r = 0; r < 16; ++r) dl = fmaf(sa[r], dp[r], dl);
     }
   }
-  dl += __shfl_xor(dl, 32, 64);
+  dl = half_sum(dl);
   if (lh == 0 && qi < T) delta[hd.row0 + qi] = dl;
 }
 

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
   for (int i = tid / 8; i < C; i += HT / 8) {          // eight threads per class
     float a = 0.f;
     for (int r = tid & 7; r < R; r += 8) a += scr[r * C + i];
-    a += __shfl_xor(a, 1); a += __shfl_xor(a, 2); a += __shfl_xor(a, 4);
+    a = eight_sum(a);
     if ((tid & 7) == 0) {
       if (b_head) a += b_head[i];
       lg[i] = a;
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
       for (int r = tid / 8; r < rows; r += HT / 8) {
         float a = 0.f;
         for (int g = tid & 7; g < G; g += 8) a += scr[r * GP + g];
-        a += __shfl_xor(a, 1); a += __shfl_xor(a, 2); a += __shfl_xor(a, 4);
+        a = eight_sum(a);
         if ((tid & 7) == 0) zs[d0 + r] = a;
       }
       __syncthreads();

@@ -16,22 +16,15 @@ template <typename T, int MAXC>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, int64_t M, int D, const float* __restrict__ gamma,
                                                      const float* __restrict__ beta, float eps, T* __restrict__ y,
                                                      float* __restrict__ mean, float* __restrict__ rstd) {
-  constexpr int V = Chunk<T>::V;
   const int lane = threadIdx.x % WAVE;
   const int64_t m = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
   if (m >= M) return;
-  const T* xr = x + m * D;
-  float v[MAXC][V];
-#pragma unroll
-  for (int i = 0; i < MAXC; ++i) {
-    const int c = lane + i * WAVE;
-    if (c < D / V) {
-      const typename Chunk<T>::vec t = *(const typename Chunk<T>::vec*)(xr + c * V);
-#pragma unroll
-      for (int e = 0; e < V; ++e) v[i][e] = (float)t[e];
-    }
-  }
-  layernorm_row<T, MAXC>(v, D, lane, gamma, beta, eps, y + m * D, mean ? mean + m : nullptr, rstd ? rstd + m : nullptr);
+  typename Chunk<T>::vec raw[MAXC];
+  float v[MAXC][Chunk<T>::V];
+  load_row<T, MAXC>(x + m * D, D / Chunk<T>::V, lane, raw, v);
+  RowParams<T, MAXC> par;
+  par.ahead(gamma, beta, D / Chunk<T>::V, lane);
+  layernorm_row(v, par, D, lane, gamma, beta, eps, y + m * D, mean ? mean + m : nullptr, rstd ? rstd + m : nullptr);
 }
 
 // any row length

@@ -2,20 +2,13 @@
 // A router activates K of E expert MLPs per token and their outputs are added, weighted by the
 // softmax over the K selected router logits.  The (token, slot) pairs are sorted by expert so that
 // each expert sees a contiguous range of rows; the expert FFNs then run as grouped MFMA GEMMs.
-#include "bsr_internal.h"
+#include "rowops.h"
 
 namespace bsr {
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-constexpr int WAVE = 64;
-
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 // Expert choice of one token per thread, from the router logits [M,E] (a GEMM wrote them): the K
 // largest logits (ties: lower index) in descending order, or the forced choice (clamped into

@@ -103,9 +103,12 @@ __global__ __launch_bounds__(SEL_WAVES * WAVE) void select_kernel(SelectArgs a, 
   const T* xb = (const T*)a.x + (int64_t)b * a.T * D;
   const int64_t out0 = (int64_t)b * T_out;
   auto layernorm = [&](const float (&v)[MC][V], int64_t m) __attribute__((always_inline)) {
-    if constexpr (MAXC > 0)
-      layernorm_row<T, MAXC>(v, D, lane, a.gamma, a.beta, a.eps, (T*)a.y + m * D, a.mean ? a.mean + m : nullptr,
+    if constexpr (MAXC > 0) {
+      RowParams<T, MAXC, MAXC == 1> par;
+      par.ahead(a.gamma, a.beta, nch, lane);
+      layernorm_row(v, par, D, lane, a.gamma, a.beta, a.eps, (T*)a.y + m * D, a.mean ? a.mean + m : nullptr,
                              a.rstd ? a.rstd + m : nullptr);
+    }
   };
   if (part < row_parts) {
     const int end = min((part + 1) * rows, k + 1);
@@ -117,16 +120,11 @@ __global__ __launch_bounds__(SEL_WAVES * WAVE) void select_kernel(SelectArgs a, 
         for (int c = lane; c < nch; c += WAVE) *(vec*)(dst + c * V) = *(const vec*)(src + c * V);
       } else {
         float v[MC][V];
+        vec raw[MC];
+        load_row<T, MC>(src, nch, lane, raw, v);
 #pragma unroll
-        for (int q = 0; q < MC; ++q) {
-          const int c = lane + q * WAVE;
-          if (c < nch) {
-            const vec t = *(const vec*)(src + c * V);
-            *(vec*)(dst + c * V) = t;
-#pragma unroll
-            for (int e = 0; e < V; ++e) v[q][e] = (float)t[e];
-          }
-        }
+        for (int q = 0; q < MC; ++q)
+          if (lane + q * WAVE < nch) *(vec*)(dst + (lane + q * WAVE) * V) = raw[q];
         layernorm(v, m);
       }
     }
@@ -141,7 +139,7 @@ __global__ __launch_bounds__(SEL_WAVES * WAVE) void select_kernel(SelectArgs a, 
   const float inv = 1.0f / wave_sum(s);
   for (int j = tid; j < n; j += SEL_WAVES * WAVE) a.fw[(int64_t)b * n + j] = sc[j] * inv;
   const int64_t m = out0 + k + 1;
-  float v[MC][V];
+  float v[MC][V] = {};
   // 64 chunks of the row at a time: every wavefront adds its share of the tokens, wavefront 0 the eight shares
   auto chunks = [&](int q, float (&o)[V]) __attribute__((always_inline)) {
     const int c = q * WAVE + lane;
