@@ -5,9 +5,10 @@
 // What bounds it: launches (the rows are a few MB).  So every workgroup of an image finds the kept set by itself, which
 // takes one wavefront about a microsecond, and goes on with its share of the rows; ranking, gather, fusion and
 // LayerNorm took four launches (8 + 5 + 60 + 6 us at 27 images of 197 tokens, 768 wide).
-// The kept set is found by bisection over the bits of the scores: 32 steps fix, from the top bit down, the largest
-// value that at least k scores reach, each step one compare and one ballot per 64 scores.  (Counting for every
-// score how many beat it takes n^2 compares: 32 us at 576 tokens.)
+// The kept set is found by bisection over the bits of the scores: steps fix, from the top down, one or two bits each of the largest
+// value that at least k scores reach, each a compare and ballot per 64 scores and candidate, and stop once exactly k do (mostly half
+// way down).  (Calls in a row, one bit a step to the last bit -> this: 128 images of 196 tokens, 768 wide, 13.3 -> 10.8 us, 32 of 576 14.3 -> 11.5,
+// 4 of 1023 15.2 -> 11.4; in a step with its LayerNorm, 32 images of 196 tokens 10.8 -> 7.9.)  (Counting for every score how many beat it takes n^2 compares: 32 us at 576 tokens.)
 #include <algorithm>
 
 #include "rowops.h"
@@ -26,32 +27,44 @@ __device__ inline unsigned score_key(float v) {
   return (u & 0x80000000u) ? ~u : u | 0x80000000u;
 }
 
-// One wavefront: ascending indices of the k best of sc[0 .. n) into list, equal scores to the lower index.
+// One wavefront: ascending indices of the k best of sc[0 .. n) into list, equal scores to the lower index.  n <= 64 NC; BITS are fixed
+// per step (with 16 chunks of scores three counts a step take longer than two steps).
+template <int NC, int BITS>
 __device__ __forceinline__ void select_wave(const float* sc, int n, int k, int lane, int32_t* list) {
-  unsigned key[MAX_N / WAVE];
+  unsigned key[NC];
 #pragma unroll
-  for (int c = 0; c < MAX_N / WAVE; ++c) key[c] = c * WAVE + lane < n ? score_key(sc[c * WAVE + lane]) : 0u;
+  for (int c = 0; c < NC; ++c) key[c] = c * WAVE + lane < n ? score_key(sc[c * WAVE + lane]) : 0u;
   auto count = [&](auto better) __attribute__((always_inline)) {
     int cnt = 0;
 #pragma unroll
-    for (int c = 0; c < MAX_N / WAVE; ++c) {
-      if (c * WAVE >= n) break;
+    for (int c = 0; c < NC; ++c) {
+      if (NC > 4 && c * WAVE >= n) break;
       cnt += __popcll(__ballot(better(key[c])));
     }
     return cnt;
   };
-  unsigned kth = 0;                         // the k-th largest key
+  unsigned kth = 0;                         // in the end the k-th largest key, or a value that exactly the k best reach
 #pragma unroll 1
-  for (int bit = 31; bit >= 0; --bit) {
-    const unsigned cand = kth | (1u << bit);
-    if (count([&](unsigned x) { return x >= cand; }) >= k) kth = cand;
+  for (int bit = 32 - BITS; bit >= 0; bit -= BITS) {
+    constexpr int ND = (1 << BITS) - 1;
+    int reach[ND], d = 0, at = 0;           // scores that reach digit 1, 2, ..; the largest digit that k reach, and how many do
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const unsigned cand = kth | ((unsigned)(i + 1) << bit);
+      reach[i] = count([&](unsigned x) { return x >= cand; });
+    }
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+      if (reach[i] >= k) { d = i + 1; at = reach[i]; }
+    kth |= (unsigned)d << bit;
+    if (d && at == k) break;
   }
   int ties = k - count([&](unsigned x) { return x > kth; });      // of the equal ones, the first so many
   int base = 0;
   const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
-  for (int c = 0; c < MAX_N / WAVE; ++c) {
-    if (c * WAVE >= n) break;
+  for (int c = 0; c < NC; ++c) {
+    if (NC > 4 && c * WAVE >= n) break;
     const bool eq = key[c] == kth;
     const unsigned long long em = __ballot(eq);
     const bool keep = key[c] > kth || (eq && __popcll(em & below) < ties);
@@ -63,9 +76,10 @@ __device__ __forceinline__ void select_wave(const float* sc, int n, int k, int l
 }
 
 // Workgroup (image b, part y): y < row_parts hands on rows y * rows .. of [class; kept]; y == row_parts (only with
-// a.fw) makes the fused token.  MAXC == 0: rows are copied only; otherwise LayerNorm follows.
+// a.fw) makes the fused token.  MAXC == 0: rows are copied only; otherwise LayerNorm follows.  Held to the registers of four workgroups
+// a CU, which launch() counts on (at three, 16 images of 576 tokens took a second round: 12 -> 18 us).
 template <typename T, int MAXC>
-__global__ __launch_bounds__(SEL_WAVES * WAVE) void select_kernel(SelectArgs a, int rows, int row_parts) {
+__global__ __launch_bounds__(SEL_WAVES * WAVE, MAXC <= 2 ? 8 : 1) void select_kernel(SelectArgs a, int rows, int row_parts) {
   constexpr int V = Chunk<T>::V, MC = MAXC ? MAXC : 1;
   typedef typename Chunk<T>::vec vec;
   __shared__ float sc[MAX_N];
@@ -76,9 +90,16 @@ __global__ __launch_bounds__(SEL_WAVES * WAVE) void select_kernel(SelectArgs a, 
   const bool first = part == 0;
   if (a.cls_prob) {                         // heads in ascending order, then divided by H
     for (int j = tid; j < n; j += SEL_WAVES * WAVE) {
+      const float* p = a.cls_prob + (int64_t)b * a.H * a.T + 1 + j;
       float v = 0.f;
-#pragma unroll 4
-      for (int h = 0; h < a.H; ++h) v += a.cls_prob[((int64_t)b * a.H + h) * a.T + 1 + j];
+      for (int h0 = 0; h0 < a.H; h0 += 12) {            // (twelve loads at a time)
+        float t[12];
+#pragma unroll
+        for (int u = 0; u < 12; ++u) t[u] = p[(int64_t)min(h0 + u, a.H - 1) * a.T];
+#pragma unroll
+        for (int u = 0; u < 12; ++u)
+          if (h0 + u < a.H) v += t[u];
+      }
       v /= (float)a.H;
       sc[j] = v;
       if (first && a.scores) a.scores[(int64_t)b * n + j] = v;
@@ -90,7 +111,10 @@ __global__ __launch_bounds__(SEL_WAVES * WAVE) void select_kernel(SelectArgs a, 
     for (int i = tid; i < k; i += SEL_WAVES * WAVE) list[i] = a.forced[(int64_t)b * k + i];
   __syncthreads();
   if (!a.forced) {
-    if (wave == 0) select_wave(sc, n, k, lane, list);
+    if (wave == 0) {
+      if (n <= 4 * WAVE) select_wave<4, 2>(sc, n, k, lane, list);
+      else select_wave<MAX_N / WAVE, 1>(sc, n, k, lane, list);
+    }
     __syncthreads();
   }
   if (first)

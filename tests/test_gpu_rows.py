@@ -61,3 +61,9 @@ def test_heads_of_many_classes(hip, orc64, dtype, tol, dim, classes, batch):
     assert hip.rel(got["logits"], ref["logits"]) < tol
     for n, g in ref["grads"].items():
         assert hip.rel(got["grads"][n], g) < tol, n
+
+
+# the largest count that takes two bits a step, one less and the first that takes one
+@pytest.mark.parametrize("n", [255, 256, 257])
+def test_selection_where_its_two_forms_meet(hip, orc32, n):
+    test_selection_at_the_edges(hip, orc32, n)
