@@ -95,8 +95,17 @@ __device__ __forceinline__ bool group_tile(GemmDesc& g, int mt, int& m0) {
 // Eight consecutive columns of output row m, accumulated in fp32: the statistics of a folded LayerNorm, bias,
 // positional embedding (with the row remap of the patch embedding), GELU with its stored pre-activation or
 // GELU', the residual, and the store (16 bytes of bf16, or 32 bytes of fp32).
+// extra: what it would read of memory for them (the stored input of a GELU', the residual), read ahead.
+struct Extra8 {
+  bf16x8 u, r;
+  __device__ __forceinline__ void fetch(const GemmDesc& g, int m, int col) {
+    const int64_t row = g.remap_np > 0 ? (int64_t)m + m / g.remap_np + 1 : m;
+    if (g.act == ACT_GELU_BWD) u = *(const bf16x8*)((const bf16*)g.aux + row * g.ldc + col);
+    if (!g.out_f32 && g.res) r = *(const bf16x8*)((const bf16*)g.res + row * (g.ldr ? g.ldr : g.ldc) + col);
+  }
+};
 __device__ __forceinline__ void finish8(const GemmDesc& g, float (&v)[8], int m, int col, const float (&bias)[8],
-                                        const float (&cs)[8], const float2* st) {
+                                        const float (&cs)[8], const float2* st, const Extra8* extra = nullptr) {
   if (st) {
     const float2 ms = *st;
 #pragma unroll
@@ -122,7 +131,7 @@ __device__ __forceinline__ void finish8(const GemmDesc& g, float (&v)[8], int m,
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = gelu_f(v[j]);
   } else if (g.act == ACT_GELU_BWD) {
-    const bf16x8 u = *(const bf16x8*)((const bf16*)g.aux + off);
+    const bf16x8 u = extra ? extra->u : *(const bf16x8*)((const bf16*)g.aux + off);
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] *= gelu_grad_f((float)u[j]);
   }
@@ -132,7 +141,7 @@ __device__ __forceinline__ void finish8(const GemmDesc& g, float (&v)[8], int m,
     *(float4*)(c + 4) = make_float4(v[4], v[5], v[6], v[7]);
   } else {
     if (g.res) {
-      const bf16x8 rr = *(const bf16x8*)((const bf16*)g.res + (g.ldr ? row * g.ldr + col : off));
+      const bf16x8 rr = extra ? extra->r : *(const bf16x8*)((const bf16*)g.res + (g.ldr ? row * g.ldr + col : off));
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] += (float)rr[j];
     }
@@ -469,31 +478,73 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // this epilogue with every row block and pass written out (13 700 of the kernel's 14 400 instructions) cost a
 // launch about 3 us.  So the row blocks are a loop (the accumulators of block mi are picked by a switch, which
 // is all that has to be written out per block) and so are the passes: the finishing code exists once.
+template <int NI> struct EpiLanes {
+  static constexpr int TN = NI * 32;
+  static constexpr int CPR = TN / 8, RPP = 64 / CPR;       // 8-column chunks per row, rows per pass of the wave
+  static constexpr int NPASS = (32 + RPP - 1) / RPP;       // (with 12 chunks per row 60 lanes work and the last pass is partial)
+};
+// What an epilogue adds or multiplies, asked for when the last loads of k-tiles are out: the bias, and the first row block's residual or stored input of a
+// GELU'.  Behind the k-loop they are one more trip to memory of every tile
+// (steps of 32 images: DeiT-S 1250 -> 1234 us, ViT-B the same; asked for ahead of the first tiles instead, those land later: ViT-B 0.3 % longer).
+// A slot is 16 bytes: with nothing but a bias to add (`direct`) the bias in the order of the accumulators (where the registers allow that
+// beside the k-loop), else the bias of the lane's eight columns in two slots and a slot for every pass of a row block.
+template <int MI, int NI> struct EpiAhead {
+  using L = EpiLanes<NI>;
+  static constexpr bool EARLY = MI * NI <= 8;      // (the 320 x 256 shape would spill 27 registers: it asks behind the k-loop)
+  static constexpr int SLOTS = EARLY && 4 * NI > 2 + L::NPASS ? 4 * NI : 2 + L::NPASS;
+  f32x4 slot[SLOTS];
+  const bf16* extra;
+  int64_t lde;
+  bool direct, on, bwd;              // only a bias to add; something to read ahead; and that it is for a GELU'
+  template <class P> __device__ __forceinline__ void one(const GemmDesc& g, int row0, int col, int my_row, bool col_ok, P) {
+    constexpr int p = P::value;
+    const int m = row0 + p * L::RPP + my_row;
+    if (p * L::RPP + my_row < 32 && m < g.M && col_ok) slot[2 + p] = *(const f32x4*)(extra + (int64_t)m * lde + col);
+  }
+  // bias of columns col0 + 32 (i / 4) + 8 (i % 4) + 4 lh ..
+  __device__ static __forceinline__ f32x4 direct_bias(const GemmDesc& g, int col0, int lane, int i) {
+    const int c = col0 + (i >> 2) * 32 + 8 * (i & 3) + 4 * (lane >> 5);
+    return g.bias && c < g.N ? *(const f32x4*)(g.bias + c) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ void fetch(const GemmDesc& g, int row0, int col0, int lane) {
+    direct = !g.out_f32 && !g.res && g.remap_np == 0 && g.act == ACT_NONE;
+    bwd = g.act == ACT_GELU_BWD;
+    on = !direct && !g.out_f32 && g.remap_np == 0 && (bwd ? !g.res : g.act == ACT_NONE);
+    extra = bwd ? (const bf16*)g.aux : (const bf16*)g.res;
+    lde = bwd || !g.ldr ? g.ldc : g.ldr;
+    if (direct) {
+      if constexpr (EARLY)
+#pragma unroll
+        for (int i = 0; i < 4 * NI; ++i) slot[i] = direct_bias(g, col0, lane, i);
+      return;
+    }
+    const int my_row = lane / L::CPR, col = col0 + lane % L::CPR * 8;
+    const bool ok = col < g.N;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) slot[i] = g.bias && ok ? *(const f32x4*)(g.bias + col + 4 * i) : f32x4{0.f, 0.f, 0.f, 0.f};
+    if (on) sfor<L::NPASS>([&](auto P) __attribute__((always_inline)) { one(g, row0, col, my_row, ok && my_row < L::RPP, P); });
+  }
+};
 template <int MI, int NI>
 __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][NI], int row0, int col0, int lane,
-                                           unsigned char* patch) {
-  constexpr int TN = NI * 32;
-  constexpr int CPR = TN / 8, RPP = 64 / CPR;       // 8-column chunks per row, rows per pass of the wave
-  constexpr int NPASS = (32 + RPP - 1) / RPP;       // (with 12 chunks per row 60 lanes work and the last pass is partial)
+                                           unsigned char* patch, EpiAhead<MI, NI>& early) {
+  using L = EpiLanes<NI>;
+  constexpr int TN = L::TN, CPR = L::CPR, RPP = L::RPP, NPASS = L::NPASS;
   const int lm = lane & 31, lh = lane >> 5;
   const int my_chunk = lane % CPR, my_row = lane / CPR;
   const int col = col0 + my_chunk * 8;
   const bool col_ok = col < g.N && my_row < RPP;    // N is a multiple of 8 on this path
   // nothing but the bias to add: round first, move half the bytes
-  const bool direct = !g.out_f32 && !g.res && g.remap_np == 0 && g.act == ACT_NONE;
-  if (direct) {
+  if (early.direct) {
     constexpr int LDB = TN * 2 + 16;                // bytes per patch row
     bf16* dst = (bf16*)g.C;
 #pragma nounroll
     for (int mi = 0; mi < MI; ++mi) {
-      f32x4 bq[NI][4];                              // bias of the columns this lane holds (read per row block: the
-#pragma unroll                                      // accumulators leave no registers to keep it in)
-      for (int ni = 0; ni < NI; ++ni)
+      f32x4 bq[4 * NI];                             // bias of the columns this lane holds
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int c = col0 + ni * 32 + 8 * rg + 4 * lh;
-          bq[ni][rg] = (g.bias && c < g.N) ? *(const f32x4*)(g.bias + c) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+      for (int i = 0; i < 4 * NI; ++i)
+        if constexpr (EpiAhead<MI, NI>::EARLY) bq[i] = early.slot[i];
+        else bq[i] = EpiAhead<MI, NI>::direct_bias(g, col0, lane, i);
       sfor<MI>([&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value;
         if (mi != i) return;
@@ -503,7 +554,7 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
           for (int rg = 0; rg < 4; ++rg) {
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[i][ni][4 * rg + e] + bq[ni][rg][e]);
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[i][ni][4 * rg + e] + bq[4 * ni + rg][e]);
             *(bf16x4*)(patch + lm * LDB + (ni * 32 + 8 * rg + 4 * lh) * 2) = o;
           }
       });
@@ -524,21 +575,11 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
   constexpr int LDF = TN * 4 + 16;
   float bias[8], cs[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) { bias[j] = (g.bias && col_ok) ? g.bias[col + j] : 0.f; cs[j] = 0.f; }
+  for (int j = 0; j < 8; ++j) { bias[j] = early.slot[j / 4][j % 4]; cs[j] = 0.f; }
   // A residual or the stored input of a GELU' is read NPASS passes ahead (the passes written out for it): read where it is
   // used, every pass of a wavefront waits for memory, 8 - 20 times a tile: 6304 x 768 x 768 19.1 -> 16.2 us (192 x 128),
   // 25216 x 768 x 768 41.9 -> 36.7 (320 x 256), launches in a row.
-  const bool bwd = g.act == ACT_GELU_BWD;
-  const bool ahead = !g.out_f32 && g.remap_np == 0 && (bwd ? !g.res : g.act == ACT_NONE);
-  const bf16* extra = bwd ? (const bf16*)g.aux : (const bf16*)g.res;
-  const int64_t lde = bwd || !g.ldr ? g.ldc : g.ldr;
-  bf16x8 ext[NPASS];
-  auto fetch_extra = [&](int mi, auto P) __attribute__((always_inline)) {
-    constexpr int p = decltype(P)::value;
-    const int m = row0 + mi * 32 + p * RPP + my_row;
-    if (p * RPP + my_row < 32 && m < g.M && col_ok) ext[p] = *(const bf16x8*)(extra + (int64_t)m * lde + col);
-  };
-  if (ahead) sfor<NPASS>([&](auto P) __attribute__((always_inline)) { fetch_extra(0, P); });
+  const bool bwd = early.bwd;
 #pragma nounroll
   for (int mi = 0; mi < MI; ++mi) {
     sfor<MI>([&](auto I) __attribute__((always_inline)) {
@@ -553,14 +594,14 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
     });
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    if (ahead) {
+    if (early.on) {
       sfor<NPASS>([&](auto P) __attribute__((always_inline)) {
         constexpr int p = decltype(P)::value;
         const int lr = p * RPP + my_row;
         const int m = row0 + mi * 32 + lr;
         const bool mine = lr < 32 && m < g.M && col_ok;
-        const bf16x8 e = ext[p];
-        if (mi + 1 < MI) fetch_extra(mi + 1, P);
+        const bf16x8 e = __builtin_bit_cast(bf16x8, early.slot[2 + p]);
+        if (mi + 1 < MI) early.one(g, row0 + (mi + 1) * 32, col, my_row, col_ok, P);
         if (mine) {
           const f32x4 p0 = *(const f32x4*)(patch + lr * LDF + my_chunk * 32);
           const f32x4 p1 = *(const f32x4*)(patch + lr * LDF + my_chunk * 32 + 16);
@@ -740,6 +781,7 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
   };
 
   const int nk = g.K / BK;
+  EpiAhead<MI, NI> early;
   // prologue: every stage filled (k-tiles 0 .. NST-1), k-tile 0 landed
 #pragma unroll
   for (int j = 0; j < NST; ++j)
@@ -759,6 +801,7 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
     klast(IC<(NST - 2) * LPT>{}, kt, st, stn, 0);
     st = stn;
   }
+  if constexpr (early.EARLY) early.fetch(g, m0 + wm * TM, n0 + wn * TN, lane);
   for (; kt < nk; ++kt) {                // the last NST k-tiles: nothing left to issue
     const int stn = (st + 1 == NST) ? 0 : st + 1;
     kstep(IC<0>{}, st, 1);
@@ -767,8 +810,9 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
     klast(IC<-1>{}, kt, st, stn, nk - 1 - kt);
     st = stn;
   }
+  if constexpr (!early.EARLY) early.fetch(g, m0 + wm * TM, n0 + wn * TN, lane);
   // every wavefront is past the last barrier, i.e. has read its last fragments: the stages are free
-  epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)));
+  epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)), early);
 }
 
 // (a shape whose stages take at most half of the 160 KB is held to the registers that let two workgroups share a CU)
@@ -854,6 +898,19 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
   const int mine = ng > wave ? (ng - wave + NW - 1) / NW : 0;      // k-groups of this wavefront
   if (mine > 0) issue(wave, 0);
   if (mine > 1) issue(wave + NW, 1);
+  // what the epilogue adds, asked for behind the first loads (as in EpiAhead above): thread tid finishes eight columns of rows tid / (BN / 8) + i * STEP
+  constexpr int STEP = 256 / (BN / 8), ITEMS = (BM * BN / 8 + 255) / 256;
+  const int erow = tid / (BN / 8), ecol = n0 + tid % (BN / 8) * 8;
+  float bias[8], cs[8];
+  Extra8 extra[ITEMS];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    bias[j] = g.bias && ecol < g.N ? g.bias[ecol + j] : 0.f;
+    cs[j] = LNF && ecol < g.N ? g.ln_colsum[ecol + j] : 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (erow + i * STEP < BM && m0 + erow + i * STEP < g.M && ecol < g.N) extra[i].fetch(g, m0 + erow + i * STEP, ecol);
   for (int i = 0; i < mine; ++i) {
     const int st = i & 1;
     if (i + 1 < mine) wait_vmcnt<LPT>();                           // the next group stays in flight
@@ -915,21 +972,18 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
       for (int r = 0; r < 16; ++r)
         part[(wave * BM + mi * 32 + 8 * (r >> 2) + 4 * lh + (r & 3)) * LDP + ni * 32 + lr] = acc[mi][ni][r];
   __syncthreads();
-#pragma unroll 1
-  for (int it = tid; it < BM * BN / 8; it += 256) {
-    const int row = it / (BN / 8), col8 = it % (BN / 8) * 8, m = m0 + row, col = n0 + col8;
-    if (m >= g.M || col >= g.N) continue;
-    float v[8], bias[8], cs[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      v[j] = part[row * LDP + col8 + j];
-      bias[j] = g.bias ? g.bias[col + j] : 0.f;
-      cs[j] = LNF ? g.ln_colsum[col + j] : 0.f;
-    }
+  for (int i = 0; i < ITEMS; ++i) {
+    const int row = erow + i * STEP, m = m0 + row;
+    if (row >= BM || m >= g.M || ecol >= g.N) continue;
+    const float* p = part + row * LDP + ecol - n0;
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = p[j];
 #pragma unroll
     for (int w = 1; w < NW; ++w)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] += part[(w * BM + row) * LDP + col8 + j];
+      for (int j = 0; j < 8; ++j) v[j] += p[w * BM * LDP + j];
     float2 ms = make_float2(0.f, 0.f);
     if constexpr (LNF) {
 #pragma unroll
@@ -937,7 +991,7 @@ __global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
       const float mean = ms.x / (float)g.K;
       ms = make_float2(mean, rsqrtf(fmaxf(ms.y / (float)g.K - mean * mean, 0.f) + g.ln_eps));
     }
-    finish8(g, v, m, col, bias, cs, LNF ? &ms : nullptr);
+    finish8(g, v, m, ecol, bias, cs, LNF ? &ms : nullptr, &extra[i]);
   }
 }
 
