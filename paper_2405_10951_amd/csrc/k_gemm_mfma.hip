@@ -486,12 +486,13 @@ template <int NI> struct EpiLanes {
 // What an epilogue adds or multiplies, asked for when the last loads of k-tiles are out: the bias, and the first row block's residual or stored input of a
 // GELU'.  Behind the k-loop they are one more trip to memory of every tile
 // (steps of 32 images: DeiT-S 1250 -> 1234 us, ViT-B the same; asked for ahead of the first tiles instead, those land later: ViT-B 0.3 % longer).
-// A slot is 16 bytes: with nothing but a bias to add (`direct`) the bias in the order of the accumulators (where the registers allow that
-// beside the k-loop), else the bias of the lane's eight columns in two slots and a slot for every pass of a row block.
+// A slot is 16 bytes: with nothing but a bias to add (`direct`) the bias in the order of the accumulators (wave tiles 32 columns wide), else
+// the bias of the lane's eight columns in two slots and a slot for every pass of a row block.
 template <int MI, int NI> struct EpiAhead {
   using L = EpiLanes<NI>;
   static constexpr bool EARLY = MI * NI <= 8;      // (the 320 x 256 shape would spill 27 registers: it asks behind the k-loop)
-  static constexpr int SLOTS = EARLY && 4 * NI > 2 + L::NPASS ? 4 * NI : 2 + L::NPASS;
+  static constexpr bool BIAS_EARLY = NI == 1;       // (as many slots either way)
+  static constexpr int SLOTS = 2 + L::NPASS;
   f32x4 slot[SLOTS];
   const bf16* extra;
   int64_t lde;
@@ -513,7 +514,7 @@ template <int MI, int NI> struct EpiAhead {
     extra = bwd ? (const bf16*)g.aux : (const bf16*)g.res;
     lde = bwd || !g.ldr ? g.ldc : g.ldr;
     if (direct) {
-      if constexpr (EARLY)
+      if constexpr (BIAS_EARLY)
 #pragma unroll
         for (int i = 0; i < 4 * NI; ++i) slot[i] = direct_bias(g, col0, lane, i);
       return;
@@ -538,13 +539,18 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
   if (early.direct) {
     constexpr int LDB = TN * 2 + 16;                // bytes per patch row
     bf16* dst = (bf16*)g.C;
+    f32x4 bq[4 * NI];                               // bias of the columns this lane holds
+    auto read_bias = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 4 * NI; ++i) bq[i] = EpiAhead<MI, NI>::direct_bias(g, col0, lane, i);
+    };
+    if constexpr (EpiAhead<MI, NI>::BIAS_EARLY)
+#pragma unroll
+      for (int i = 0; i < 4 * NI; ++i) bq[i] = early.slot[i];
+    else if constexpr (EpiAhead<MI, NI>::EARLY) read_bias();
 #pragma nounroll
     for (int mi = 0; mi < MI; ++mi) {
-      f32x4 bq[4 * NI];                             // bias of the columns this lane holds
-#pragma unroll
-      for (int i = 0; i < 4 * NI; ++i)
-        if constexpr (EpiAhead<MI, NI>::EARLY) bq[i] = early.slot[i];
-        else bq[i] = EpiAhead<MI, NI>::direct_bias(g, col0, lane, i);
+      if constexpr (!EpiAhead<MI, NI>::EARLY) read_bias();     // (once per row block: no registers to keep it in)
       sfor<MI>([&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value;
         if (mi != i) return;
