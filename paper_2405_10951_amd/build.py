@@ -13,6 +13,7 @@ LIB = os.path.join(HERE, "libbsr_hip.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=fast",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",       # kernel arguments in registers from a wavefront's first instruction
          "-Wno-unused-command-line-argument"]
 
 

@@ -107,7 +107,9 @@ struct Tile {
 // and matrix work took turns, 23 + 25 us of the 42 us of 1576 x 384 x 1536.  A ring with its depth as a parameter, always two: fp32 steps
 // of 1 .. 8 images of DeiT-S and of the 192-wide block took 2 % longer, DeiT-S of 8 images 1571 -> 1544 us.)
 template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
-__global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_kernel(GemmDesc g) {
+__global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2)
+void gemm_f32_kernel(const float* A, const float* B, int64_t lda, int64_t ldb, int M, int N, int K, int tiles, GemmDesc g) {
+  g.M = M; g.N = N; g.K = K;               // (in front of the description: these arrive in registers with the wavefront)
   constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, GRP = KT / 8 / WK;
   typedef Tile<BM, KT, AK, NT> TA;
@@ -118,11 +120,8 @@ __global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2) void gemm_f32_ke
   const int wk = wave / (WM * WN), wmn = wave % (WM * WN), wm = wmn / WN, wn = wmn % WN;
   const int lr = lane & 31, lh = lane >> 5;
   const int ntn = (g.N + BN - 1) / BN;
-  const int tile = xcd_range(blockIdx.x, gridDim.x);
+  const int tile = xcd_range(blockIdx.x, tiles);
   const int m0 = (tile / ntn) * BM, n0 = (tile % ntn) * BN;
-  const float* A = (const float*)g.A;
-  const float* B = (const float*)g.B;
-  const int64_t lda = AK ? g.a_rs : g.a_cs, ldb = BKC ? g.b_cs : g.b_rs;
   f32x16 acc[MI][NI];
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi)
@@ -238,7 +237,7 @@ void launch(const GemmDesc& g, hipStream_t s) {
     attr_set = true;
   }
   const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  kern<<<tiles, NT, lds, s>>>(g);
+  kern<<<tiles, NT, lds, s>>>((const float*)g.A, (const float*)g.B, AK ? g.a_rs : g.a_cs, BKC ? g.b_cs : g.b_rs, g.M, g.N, g.K, tiles, g);
 }
 
 // Which block tile: the one that a model finishes first.  With t tiles, time = c0 + ceil(t / 256) (c1 + c2 K / 100) + t / 256

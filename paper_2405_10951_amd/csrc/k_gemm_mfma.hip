@@ -821,11 +821,20 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
   epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)), early);
 }
 
+// What a product's first loads need, as plain kernel arguments in front: the first 14 dwords come in registers with the wavefront
+// (-amdgpu-kernarg-preload-count), a description passed by value is a trip to memory first.  One image through the ViT-B encoder (65
+// launches) 438 -> 411 us, steps of 32 images DeiT-S 1246 -> 1202, ViT-B 2261 -> 2218.
+#define BSR_HOT_PARAMS const bf16 *hA, const bf16 *hB, int hM, int hN, int hK, unsigned ha_rs, unsigned hb_cs, int tiles
+#define BSR_HOT_ARGS(g, tiles) (const bf16*)(g).A, (const bf16*)(g).B, (g).M, (g).N, (g).K, (unsigned)(g).a_rs, (unsigned)(g).b_cs, tiles
+#define BSR_HOT_INTO(g) ((g).A = hA, (g).B = hB, (g).M = hM, (g).N = hN, (g).K = hK, (g).a_rs = ha_rs, (g).b_cs = hb_cs)
+
 // (a shape whose stages take at most half of the 160 KB is held to the registers that let two workgroups share a CU)
 template <int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(WM * WN * 64, NST * (BM + BN) * 128 <= 80 * 1024 ? WM * WN / 2 : 1)
-void gemm_ntd_kernel(GemmDesc g) {
-  ntd_body<BM, BN, WM, WN, NST>(g, xcd_remap(blockIdx.x, (int)gridDim.x));
+void gemm_ntd_kernel(BSR_HOT_PARAMS, const int32_t* grp_off, GemmDesc g) {
+  BSR_HOT_INTO(g);
+  g.grp_off = grp_off;
+  ntd_body<BM, BN, WM, WN, NST>(g, xcd_remap(blockIdx.x, tiles));
 }
 
 template <int BM, int BN, int WM, int WN, int NST>
@@ -841,7 +850,7 @@ void launch_ntd(const GemmDesc& g, hipStream_t s) {
   }
   // grouped: every group may end in one partial row tile
   const int tiles = ((g.M + BM - 1) / BM + (g.grp_off ? g.groups : 0)) * ((g.N + BN - 1) / BN);
-  kern<<<tiles, WM * WN * 64, lds_tiles, s>>>(g);
+  kern<<<tiles, WM * WN * 64, lds_tiles, s>>>(BSR_HOT_ARGS(g, tiles), g.grp_off, g);
 }
 // The kernels that load straight into LDS hold an operand's row offsets in 32 bits (elements): larger operands, such as the
 // activations of 8192 images, go to the register-staged kernels, whose offsets have 64.
@@ -865,13 +874,14 @@ bool is_ntd(const GemmDesc& g) { return g.K % BK == 0 && !g.ln_colsum && offsets
 // (Fragments straight from global memory, without LDS: 13.5 us for 197 x 768 x 3072; a load then touches 32 lines.)
 // LNF: the folded LayerNorm; a wavefront adds up the rows of its k-groups from its fragments of A.
 template <int MI, int NI, bool LNF>
-__global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(GemmDesc g) {
+__global__ __launch_bounds__(256, 1) void gemm_nt_few_kernel(BSR_HOT_PARAMS, GemmDesc g) {
+  BSR_HOT_INTO(g);
   constexpr int NW = 4, NST = 2, BM = 32 * MI, BN = 32 * NI, LDP = BN + 4, LPT = 4 * (MI + NI), STAGE = LPT * 1024;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ntm = (g.M + BM - 1) / BM;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);        // an XCD's range runs over the rows first: weights are read once
+  const int tile = xcd_remap(blockIdx.x, tiles);            // an XCD's range runs over the rows first: weights are read once
   const int m0 = (tile % ntm) * BM, n0 = (tile / ntm) * BN;
   const bf16* __restrict__ A = (const bf16*)g.A;
   const bf16* __restrict__ Bt = (const bf16*)g.B;
@@ -1012,7 +1022,7 @@ void launch_few_as(const GemmDesc& g, hipStream_t s) {
     attr_set = true;
   }
   const int tiles = ((g.M + 32 * MI - 1) / (32 * MI)) * ((g.N + 32 * NI - 1) / (32 * NI));
-  gemm_nt_few_kernel<MI, NI, LNF><<<tiles, 256, lds, s>>>(g);
+  gemm_nt_few_kernel<MI, NI, LNF><<<tiles, 256, lds, s>>>(BSR_HOT_ARGS(g, tiles), g);
 }
 template <int MI, int NI>
 void launch_few(const GemmDesc& g, hipStream_t s) {
@@ -1422,22 +1432,24 @@ template <> struct PairTile<3> { static constexpr int BM = 256, BN = 128, WM = 4
 // most of it 768 x 768 21.6 -> 22.6, 384 x 1536 23.5 -> 22.9; 25216 tokens 768 x 3072 325 -> 238, 768 x 2304 247 -> 181; 1.18x over 112 shapes of
 // 197 .. 25216 tokens (0.87 .. 1.71).
 template <int I, int T>
-__global__ __launch_bounds__(TN_THREADS, 1) void gemm_pair_kernel(GemmDesc g, TnArgs a, int nt_tiles) {
+__global__ __launch_bounds__(TN_THREADS, 1) void gemm_pair_kernel(BSR_HOT_PARAMS, int tn_blocks, GemmDesc g, TnArgs a) {
+  BSR_HOT_INTO(g);
+  g.grp_off = nullptr;
   using N = PairTile<I>;
   using S = TnTile<T>;
   constexpr int NTHR = N::WM * N::WN * 64;
-  if ((int)blockIdx.x < a.blocks) {
-    tn_body<S::BM, S::BN, S::WM, S::WN, S::NST>(a, xcd_remap(blockIdx.x, a.blocks));
+  if ((int)blockIdx.x < tn_blocks) {
+    tn_body<S::BM, S::BN, S::WM, S::WN, S::NST>(a, xcd_remap(blockIdx.x, tn_blocks));
     return;
   }
-  const int tile = blockIdx.x - a.blocks;
+  const int tile = blockIdx.x - tn_blocks;
   if (threadIdx.x >= NTHR) {
     const int64_t items = a.red.splits > 0 ? splitk_reduce_items(a.red) : 0;
-    for (int64_t it = (int64_t)tile * (TN_THREADS - NTHR) + threadIdx.x - NTHR; it < items; it += (int64_t)nt_tiles * (TN_THREADS - NTHR))
+    for (int64_t it = (int64_t)tile * (TN_THREADS - NTHR) + threadIdx.x - NTHR; it < items; it += (int64_t)tiles * (TN_THREADS - NTHR))
       splitk_reduce_item(a.red, it);
     return;
   }
-  ntd_body<N::BM, N::BN, N::WM, N::WN, N::NST>(g, xcd_remap(tile, nt_tiles));
+  ntd_body<N::BM, N::BN, N::WM, N::WN, N::NST>(g, xcd_remap(tile, tiles));
 }
 
 // the same reduction as a launch of its own
@@ -1597,7 +1609,7 @@ void launch_pair_as(const GemmDesc& g, const TnArgs& a, hipStream_t s) {
     attr_set = true;
   }
   const int tiles = ((g.M + N::BM - 1) / N::BM) * ((g.N + N::BN - 1) / N::BN);
-  gemm_pair_kernel<I, T><<<a.blocks + tiles, TN_THREADS, lds, s>>>(g, a, tiles);
+  gemm_pair_kernel<I, T><<<a.blocks + tiles, TN_THREADS, lds, s>>>(BSR_HOT_ARGS(g, tiles), a.blocks, g, a);
 }
 template <int I>
 void launch_pair(const GemmDesc& g, const GemmDesc& t, const TnSplit& sp, float* ws, size_t ws_floats, hipStream_t s, TnChain* chain) {
