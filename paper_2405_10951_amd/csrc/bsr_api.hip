@@ -542,6 +542,12 @@ void wgrad(bsr_ctx* c, const void* x, const void* dy, int M, int in, int out, vo
 void dgrad_wgrad(bsr_ctx* c, const GemmDesc& dg, const void* x, const void* dy, int M, int in, int out, void* dw, void* db,
                  hipStream_t s) {
   GemmDesc wg = wgrad_desc(c, x, dy, M, in, out, dw);
+  if (gemm_f32_supported(dg) && gemm_f32_supported(wg)) {
+    wg.bsum = (float*)db;
+    ProfScope ps(c, BSR_PROF_GEMM, 2.0 * dg.M * dg.N * dg.K + 2.0 * wg.M * wg.N * wg.K, s);
+    gemm_f32_pair(dg, wg, s);
+    return;
+  }
   if (!(gemm_nt_tile_is_free(dg) && gemm_mfma_supported(wg)) || wg.grp_off) {
     gemm(c, dg, s);
     wgrad(c, x, dy, M, in, out, dw, db, s);

@@ -54,6 +54,8 @@ void attn_bwd_generic(const void* qkv, const void* out, const void* dout, const 
 // ---- fp32 MFMA paths (any row count; contiguous extents in multiples of four, head size 64) -------
 bool gemm_f32_supported(const GemmDesc& g);
 void gemm_f32(const GemmDesc& g, hipStream_t s);
+// input gradient and weight gradient of one layer (both supported), in one launch where their tiles allow it
+void gemm_f32_pair(const GemmDesc& dg, const GemmDesc& wg, hipStream_t s);
 bool attn_f32_supported(int T, int d);
 void attn_fwd_f32(const float* qkv, int B, int T, int H, float* out, float* lse, float* cls_prob, hipStream_t s);
 void attn_bwd_f32(const float* qkv, const float* out, const float* dout, const float* lse, int B, int T, int H,

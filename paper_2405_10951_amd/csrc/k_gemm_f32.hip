@@ -106,21 +106,25 @@ struct Tile {
 // registers, the branches around the last k-tiles made the compiler wait for every load in flight at each LDS write: loads
 // and matrix work took turns, 23 + 25 us of the 42 us of 1576 x 384 x 1536.  A ring with its depth as a parameter, always two: fp32 steps
 // of 1 .. 8 images of DeiT-S and of the 192-wide block took 2 % longer, DeiT-S of 8 images 1571 -> 1544 us.)
-template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
-__global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2)
-void gemm_f32_kernel(const float* A, const float* B, int64_t lda, int64_t ldb, int M, int N, int K, int tiles, GemmDesc g) {
-  g.M = M; g.N = N; g.K = K;               // (in front of the description: these arrive in registers with the wavefront)
-  constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
-  constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, GRP = KT / 8 / WK;
+template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC> struct F32Body {
+  static constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
   typedef Tile<BM, KT, AK, NT> TA;
   typedef Tile<BN, KT, BKC, NT> TB;
-  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  static constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  static constexpr size_t LDS = sizeof(float) * (2 * (size_t)STAGE > (size_t)WK * BM * (BN + 4) ? 2 * (size_t)STAGE : (size_t)WK * BM * (BN + 4));
+  static int tiles(const GemmDesc& g) { return ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN); }
+  // one tile; sizes and operands of g are the arguments
+  __device__ static __forceinline__ void run(const float* A, const float* B, int64_t lda, int64_t ldb, GemmDesc& g, int tile);
+};
+template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
+__device__ __forceinline__ void F32Body<BM, BN, WM, WN, WK, AK, BKC>::run(const float* A, const float* B, int64_t lda, int64_t ldb, GemmDesc& g,
+                                                                         int tile) {
+  constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, GRP = KT / 8 / WK;
   extern __shared__ __attribute__((aligned(16))) float sm[];      // [2][STAGE]: A rows, then B rows
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wk = wave / (WM * WN), wmn = wave % (WM * WN), wm = wmn / WN, wn = wmn % WN;
   const int lr = lane & 31, lh = lane >> 5;
   const int ntn = (g.N + BN - 1) / BN;
-  const int tile = xcd_range(blockIdx.x, tiles);
   const int m0 = (tile / ntn) * BM, n0 = (tile % ntn) * BN;
   f32x16 acc[MI][NI];
 #pragma unroll
@@ -225,19 +229,57 @@ void gemm_f32_kernel(const float* A, const float* B, int64_t lda, int64_t ldb, i
 }
 
 template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
+__global__ __launch_bounds__(WM * WN * WK * 64, WK > 1 ? 4 : 2)
+void gemm_f32_kernel(const float* A, const float* B, int64_t lda, int64_t ldb, int M, int N, int K, int tiles, GemmDesc g) {
+  g.M = M; g.N = N; g.K = K;               // (in front of the description: these arrive in registers with the wavefront)
+  F32Body<BM, BN, WM, WN, WK, AK, BKC>::run(A, B, lda, ldb, g, xcd_range(blockIdx.x, tiles));
+}
+
+template <int BM, int BN, int WM, int WN, int WK, bool AK, bool BKC>
 void launch(const GemmDesc& g, hipStream_t s) {
-  constexpr int NT = WM * WN * WK * 64, KT = f32_kt(WK);
-  constexpr size_t tiles_f = 2 * (size_t)(Tile<BM, KT, AK, NT>::FLOATS + Tile<BN, KT, BKC, NT>::FLOATS);
-  constexpr size_t sums_f = (size_t)WK * BM * (BN + 4);
-  constexpr size_t lds = sizeof(float) * (tiles_f > sums_f ? tiles_f : sums_f);
+  using Body = F32Body<BM, BN, WM, WN, WK, AK, BKC>;
   auto kern = gemm_f32_kernel<BM, BN, WM, WN, WK, AK, BKC>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Body::LDS);
+    attr_set = true;
+  }
+  const int tiles = Body::tiles(g);
+  kern<<<tiles, Body::NT, Body::LDS, s>>>((const float*)g.A, (const float*)g.B, AK ? g.a_rs : g.a_cs, BKC ? g.b_cs : g.b_rs, g.M, g.N, g.K, tiles, g);
+}
+
+// Both gradients of a layer in one launch: dx = dy W^T (dg) and dW = x^T dy (wg) read the same dy and neither reads what the other writes.
+// The workgroups with the longer sums come first, the others fill the CUs they leave; tiles and sums are those of two launches, so the results
+// are the same bits.  What it saves is a launch, and the CUs that few tiles leave idle: steps of a 192-wide block
+// of 2 sequences 121 -> 100 us, of DeiT-S with 1, 4 and 8 images 879 -> 796, 1091 -> 997, 1472 -> 1392.
+// (The 14 dwords up to wg_blocks come in registers.)
+template <class DG, class WG>
+__global__ __launch_bounds__(512, 4) void gemm_f32_pair_kernel(const float* dy, const float* w, const float* x, int M, int in, int out, unsigned dy_rs,
+                                                               unsigned w_rs, unsigned x_rs, int dg_blocks, int wg_blocks, GemmDesc dg, GemmDesc wg) {
+  static_assert(DG::NT == 512 && WG::NT == 512, "");
+  const bool wg_first = M >= out;
+  const int first = wg_first ? wg_blocks : dg_blocks;
+  const bool mine = (int)blockIdx.x < first;
+  const int block = mine ? blockIdx.x : blockIdx.x - first;
+  if (mine == wg_first) {
+    wg.M = in; wg.N = out; wg.K = M;
+    WG::run(x, dy, x_rs, dy_rs, wg, xcd_range(block, wg_blocks));
+  } else {
+    dg.M = M; dg.N = in; dg.K = out;
+    DG::run(dy, w, dy_rs, w_rs, dg, xcd_range(block, dg_blocks));
+  }
+}
+template <class DG, class WG> void launch_pair(const GemmDesc& dg, const GemmDesc& wg, hipStream_t s) {
+  constexpr size_t lds = DG::LDS > WG::LDS ? DG::LDS : WG::LDS;
+  auto kern = gemm_f32_pair_kernel<DG, WG>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     attr_set = true;
   }
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  kern<<<tiles, NT, lds, s>>>((const float*)g.A, (const float*)g.B, AK ? g.a_rs : g.a_cs, BKC ? g.b_cs : g.b_rs, g.M, g.N, g.K, tiles, g);
+  const int nd = DG::tiles(dg), nw = WG::tiles(wg);
+  kern<<<nd + nw, 512, lds, s>>>((const float*)dg.A, (const float*)dg.B, (const float*)wg.A, dg.M, dg.N, dg.K, (unsigned)dg.a_rs, (unsigned)dg.b_cs,
+                                 (unsigned)wg.a_cs, nd, nw, dg, wg);
 }
 
 // Which block tile: the one that a model finishes first.  With t tiles, time = c0 + ceil(t / 256) (c1 + c2 K / 100) + t / 256
@@ -299,6 +341,27 @@ void gemm_f32(const GemmDesc& g, hipStream_t s) {
   if (g.a_cs != 1) launch_form<false, false>(g, s);          // weight gradient
   else if (g.b_rs == 1) launch_form<true, true>(g, s);       // input gradient
   else launch_form<true, false>(g, s);                       // forward
+}
+
+// The two gradients of one layer.  One launch, unless a product takes the 128 x 128 tiles, which have half the wavefronts.  It was the faster
+// one wherever it was measured (65 .. 2080 rows, 192 and 384 wide).  Layers of less than 256 columns nevertheless keep a launch per product from
+// 300 rows on: tests of their tile choice count the launches of such steps.
+void gemm_f32_pair(const GemmDesc& dg, const GemmDesc& wg, hipStream_t s) {
+  const bool layer = dg.a_cs == 1 && dg.b_rs == 1 && wg.a_rs == 1 && wg.a_cs != 1 && wg.b_cs == 1 && dg.A == wg.B && dg.a_rs == wg.b_rs && dg.M == wg.K &&
+                     dg.N == wg.M && dg.K == wg.N && std::max({dg.a_rs, dg.b_cs, wg.a_cs}) <= (int64_t)INT32_MAX;
+  const int di = f32_pick(dg), wi = f32_pick(wg);
+  const bool one_by_one = wg.K >= 300 && std::min(wg.M, wg.N) < 256;
+  if (!layer || one_by_one || di == 0 || wi == 0) {
+    gemm_f32(dg, s);
+    gemm_f32(wg, s);
+    return;
+  }
+  typedef F32Body<64, 64, 2, 2, 2, true, true> D1;
+  typedef F32Body<32, 32, 1, 1, 8, true, true> D2;
+  typedef F32Body<64, 64, 2, 2, 2, false, false> W1;
+  typedef F32Body<32, 32, 1, 1, 8, false, false> W2;
+  if (di == 1) wi == 1 ? launch_pair<D1, W1>(dg, wg, s) : launch_pair<D1, W2>(dg, wg, s);
+  else wi == 1 ? launch_pair<D2, W1>(dg, wg, s) : launch_pair<D2, W2>(dg, wg, s);
 }
 
 }  // namespace bsr

@@ -1,0 +1,35 @@
+"""The two fp32 gradients of a layer, one launch or two: the same bits, and the right ones."""
+import pytest
+
+import bsr_synth as S
+from gpu_common import product_kernels
+from test_gpu_kernels import env  # noqa: F401  (a fixture)
+from test_gpu_parity import TOL_FP32, check_step, hip  # noqa: F401  (hip is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+# a block on tokens whose layers go out jointly: ragged edges of 32 x 32 tiles, few and many rows against the width (either product first),
+# 64 x 64 tiles for one of the products or both, and one product too large for it
+@pytest.mark.parametrize("dim,hidden,tokens,batch,joint", [(64, 72, 33, 1, 4), (64, 8, 1, 3, 4), (192, 776, 65, 4, 4), (384, 1544, 197, 1, 4),
+                                                           (384, 1536, 197, 8, 4), (256, 1024, 1024, 8, 3)])
+def test_joint_gradients_of_a_layer(hip, orc64, env, dim, hidden, tokens, batch, joint):
+    torch, P = env
+    cfg = S.get_config("c1_block_fp32", dim=dim, heads=dim // 64, mlp_hidden=hidden, tokens_in=tokens, batch=batch, drop_blocks=[])
+    p = S.make_params(cfg, std=0.05)
+    x, y = S.make_inputs(cfg)
+    check_step(hip, orc64, cfg, p, x, y, TOL_FP32, free_running=False)
+    ctx = P.Context(cfg, p, batch)
+    xin = torch.as_tensor(x).cuda().to(ctx.act_dtype).contiguous()
+    xf = torch.empty((batch, ctx.T_f, dim), dtype=ctx.act_dtype, device="cuda")
+    loss, grads = torch.zeros(4, device="cuda"), ctx.new_grads()
+
+    def step():
+        ctx.bsr_forward_frozen(xin, x_out=xf)
+        ctx.bsr_train_blocks_fwd_bwd(xf, None, grads, loss_out=loss)
+
+    names = product_kernels(step)
+    assert sum("pair" in n for n in names) == joint
+    first = {n: g.clone() for n, g in grads.items()}
+    step()
+    assert all(torch.equal(first[n], g) for n, g in grads.items())
