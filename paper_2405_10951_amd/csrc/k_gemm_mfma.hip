@@ -824,8 +824,8 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
 // What a product's first loads need, as plain kernel arguments in front: the first 14 dwords come in registers with the wavefront
 // (-amdgpu-kernarg-preload-count), a description passed by value is a trip to memory first.  One image through the ViT-B encoder (65
 // launches) 438 -> 411 us, steps of 32 images DeiT-S 1246 -> 1202, ViT-B 2261 -> 2218.
-#define BSR_HOT_PARAMS const bf16 *hA, const bf16 *hB, int hM, int hN, int hK, unsigned ha_rs, unsigned hb_cs, int tiles
-#define BSR_HOT_ARGS(g, tiles) (const bf16*)(g).A, (const bf16*)(g).B, (g).M, (g).N, (g).K, (unsigned)(g).a_rs, (unsigned)(g).b_cs, tiles
+#define BSR_HOT_PARAMS const void *hA, const void *hB, int hM, int hN, int hK, unsigned ha_rs, unsigned hb_cs, int tiles
+#define BSR_HOT_ARGS(g, tiles) (g).A, (g).B, (g).M, (g).N, (g).K, (unsigned)(g).a_rs, (unsigned)(g).b_cs, tiles
 #define BSR_HOT_INTO(g) ((g).A = hA, (g).B = hB, (g).M = hM, (g).N = hN, (g).K = hK, (g).a_rs = ha_rs, (g).b_cs = hb_cs)
 
 // (a shape whose stages take at most half of the 160 KB is held to the registers that let two workgroups share a CU)
@@ -1122,14 +1122,13 @@ struct TnArgs {
   float *partial, *bpartial;     // [1 + parts - run], null where a workgroup takes them all
   int kt_per;                    // k-tiles of a part
   int run;                       // parts of a workgroup
-  int gx;                        // tiles
   int blocks;                    // tiles x runs (or groups)
   TnReduce red;                  // partials of an earlier launch to add up; splits == 0: none
 };
 
 // Workgroup lin of gx tiles x runs (grouped: x groups), tile fastest.
 template <int BM, int BN, int WM, int WN, int NST>
-__device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
+__device__ __forceinline__ void tn_body(TnArgs a, int lin) {
   constexpr int NP = TN_LOADERS, NC = WM * WN;
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, NMF = MI * NI, NFR = MI + NI;
   constexpr int ABYTES = 64 * BM * 2, STAGE = (BM + BN) * 128;       // a stage: 64 token rows of A columns, then of B columns
@@ -1140,8 +1139,8 @@ __device__ __forceinline__ void tn_body(const TnArgs& a, int lin) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   GemmDesc g = a.g;
-  const int ntn = (g.N + BN - 1) / BN, ntm = (g.M + BM - 1) / BM;
-  const int tile = lin % a.gx, by = lin / a.gx;
+  const int ntn = (g.N + BN - 1) / BN, ntm = (g.M + BM - 1) / BM, gx = ntm * ntn;
+  const int tile = lin % gx, by = lin / gx;
   // an XCD's contiguous range of tiles runs along the side with fewer tiles first, so that it spans that side
   // and its L2 fetches the longer operand's token rows once instead of once per XCD
   const bool mfast = ntm < ntn;
@@ -1404,16 +1403,23 @@ template <> struct TnTile<1> { static constexpr int BM = 256, BN = 128, WM = 4, 
 template <class T> constexpr size_t tile_lds() { return (size_t)T::NST * (T::BM + T::BN) * 128; }
 template <class T> constexpr size_t tile_patch_lds() { return (size_t)T::WM * T::WN * 32 * ((T::BN / T::WN) * 4 + 16); }
 
-// A weight gradient on its own.  Workgroups past a.blocks add up the partials of an earlier one.
+// k-tiles of a part and parts of a workgroup as one kernel argument (a workgroup takes at most 16 parts)
+__host__ __device__ inline unsigned tn_pack(const TnArgs& a) { return (unsigned)a.kt_per | (unsigned)a.run << 26; }
+__device__ inline void tn_unpack(TnArgs& a, unsigned parts) { a.kt_per = parts & 0x3ffffff; a.run = parts >> 26; }
+
+// A weight gradient on its own.  Workgroups past the first `blocks` add up the partials of an earlier one.
 template <int T>
-__global__ __launch_bounds__(TN_THREADS, 1) void gemm_tn_kernel(TnArgs a) {
+__global__ __launch_bounds__(TN_THREADS, 1) void gemm_tn_kernel(const void* hA, const void* hB, int hM, int hN, int hK, unsigned ha_cs,
+                                                                unsigned hb_rs, unsigned parts, int blocks, const int32_t* grp_off, TnArgs a) {
   using S = TnTile<T>;
-  if ((int)blockIdx.x >= a.blocks) {
-    const int64_t step = (int64_t)(gridDim.x - a.blocks) * TN_THREADS, items = splitk_reduce_items(a.red);
-    for (int64_t it = (int64_t)(blockIdx.x - a.blocks) * TN_THREADS + threadIdx.x; it < items; it += step) splitk_reduce_item(a.red, it);
+  if ((int)blockIdx.x >= blocks) {
+    const int64_t step = (int64_t)(gridDim.x - blocks) * TN_THREADS, items = splitk_reduce_items(a.red);
+    for (int64_t it = (int64_t)(blockIdx.x - blocks) * TN_THREADS + threadIdx.x; it < items; it += step) splitk_reduce_item(a.red, it);
     return;
   }
-  tn_body<S::BM, S::BN, S::WM, S::WN, S::NST>(a, xcd_remap(blockIdx.x, a.blocks));
+  a.g.A = hA; a.g.B = hB; a.g.M = hM; a.g.N = hN; a.g.K = hK; a.g.a_cs = ha_cs; a.g.b_rs = hb_rs; a.g.grp_off = grp_off;
+  tn_unpack(a, parts);
+  tn_body<S::BM, S::BN, S::WM, S::WN, S::NST>(a, xcd_remap(blockIdx.x, blocks));
 }
 
 // Tiles of the input gradient in a launch that computes a layer's weight gradient as well.
@@ -1431,24 +1437,29 @@ template <> struct PairTile<3> { static constexpr int BM = 256, BN = 128, WM = 4
 // launch of their own: 2144 tokens 768 x 3072 43.6 -> 28.0 us, 3072 x 768 with GELU' 52.6 -> 38.0, 768 x 2304 41.8 -> 24.6; where the partials are
 // most of it 768 x 768 21.6 -> 22.6, 384 x 1536 23.5 -> 22.9; 25216 tokens 768 x 3072 325 -> 238, 768 x 2304 247 -> 181; 1.18x over 112 shapes of
 // 197 .. 25216 tokens (0.87 .. 1.71).
+// dy [M, out], x [M, in] and the weight matrix [in, out]: dx = dy W^T and dW = x^T dy share sizes and dy, and the 14 dwords of arguments that
+// come in registers (below: BSR_HOT_PARAMS) hold what both begin with.
 template <int I, int T>
-__global__ __launch_bounds__(TN_THREADS, 1) void gemm_pair_kernel(BSR_HOT_PARAMS, int tn_blocks, GemmDesc g, TnArgs a) {
-  BSR_HOT_INTO(g);
-  g.grp_off = nullptr;
+__global__ __launch_bounds__(TN_THREADS, 1) void gemm_pair_kernel(const void* dy, const void* w, const void* x, int M, int in, int out,
+                                                                  unsigned dy_rs, unsigned w_rs, unsigned x_rs, unsigned parts, int tn_blocks,
+                                                                  GemmDesc g, TnArgs a) {
   using N = PairTile<I>;
   using S = TnTile<T>;
   constexpr int NTHR = N::WM * N::WN * 64;
   if ((int)blockIdx.x < tn_blocks) {
+    a.g.A = x; a.g.B = dy; a.g.M = in; a.g.N = out; a.g.K = M; a.g.a_cs = x_rs; a.g.b_rs = dy_rs; a.g.grp_off = nullptr;
+    tn_unpack(a, parts);
     tn_body<S::BM, S::BN, S::WM, S::WN, S::NST>(a, xcd_remap(blockIdx.x, tn_blocks));
     return;
   }
-  const int tile = blockIdx.x - tn_blocks;
+  const int tile = blockIdx.x - tn_blocks, tiles = ((M + N::BM - 1) / N::BM) * ((in + N::BN - 1) / N::BN);
   if (threadIdx.x >= NTHR) {
     const int64_t items = a.red.splits > 0 ? splitk_reduce_items(a.red) : 0;
     for (int64_t it = (int64_t)tile * (TN_THREADS - NTHR) + threadIdx.x - NTHR; it < items; it += (int64_t)tiles * (TN_THREADS - NTHR))
       splitk_reduce_item(a.red, it);
     return;
   }
+  g.A = dy; g.B = w; g.M = M; g.N = in; g.K = out; g.a_rs = dy_rs; g.b_cs = w_rs; g.grp_off = nullptr;
   ntd_body<N::BM, N::BN, N::WM, N::WN, N::NST>(g, xcd_remap(tile, tiles));
 }
 
@@ -1464,7 +1475,7 @@ void launch_reduce(const TnReduce& r, hipStream_t s) {
 
 bool is_tn(const GemmDesc& g) {
   return !g.in_f32 && g.out_f32 && g.a_rs == 1 && g.b_cs == 1 && g.M % 8 == 0 && g.N % 8 == 0 && g.M >= 8 &&
-         g.N >= 8 && g.a_cs % 8 == 0 && g.b_rs % 8 == 0 && g.ldc % 8 == 0 && g.K > 0 && !g.res && g.act == ACT_NONE &&
+         g.N >= 8 && g.a_cs % 8 == 0 && g.b_rs % 8 == 0 && g.a_cs <= INT32_MAX && g.b_rs <= INT32_MAX && g.ldc % 8 == 0 && g.K > 0 && !g.res && g.act == ACT_NONE &&
          g.remap_np == 0 && (((uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C) & 15) == 0;
 }
 
@@ -1553,8 +1564,8 @@ TnArgs plan_tn(const GemmDesc& g, const TnSplit& sp, float* ws, size_t ws_floats
   a.partial = a.bpartial = nullptr;
   a.kt_per = sp.kt_per;
   a.run = sp.run;
-  a.gx = ((g.M + kTn[sp.tile].bm - 1) / kTn[sp.tile].bm) * ((g.N + kTn[sp.tile].bn - 1) / kTn[sp.tile].bn);
-  a.blocks = a.gx * (g.grp_off ? g.groups : sp.runs);      // (grouped: tiles x groups already fills the machine)
+  const int tiles = ((g.M + kTn[sp.tile].bm - 1) / kTn[sp.tile].bm) * ((g.N + kTn[sp.tile].bn - 1) / kTn[sp.tile].bn);
+  a.blocks = tiles * (g.grp_off ? g.groups : sp.runs);      // (grouped: tiles x groups already fills the machine)
   *mine = TnReduce();
   if (chain) {       // this launch takes one half of the workspace, the pending reduction reads the other
     if (ws) ws += (size_t)chain->slot * tn_room(ws_floats, true);
@@ -1587,7 +1598,8 @@ void launch_tn_as(const TnArgs& a, hipStream_t s) {
   // sums of an earlier launch: about four items per thread
   const int64_t per = (int64_t)TN_THREADS * 4;
   const int red = a.red.splits > 0 ? (int)std::min<int64_t>(512, (splitk_reduce_items_host(a.red) + per - 1) / per) : 0;
-  gemm_tn_kernel<T><<<a.blocks + red, TN_THREADS, lds, s>>>(a);
+  gemm_tn_kernel<T><<<a.blocks + red, TN_THREADS, lds, s>>>(a.g.A, a.g.B, a.g.M, a.g.N, a.g.K, (unsigned)a.g.a_cs,
+                                                            (unsigned)a.g.b_rs, tn_pack(a), a.blocks, a.g.grp_off, a);
 }
 
 void launch_tn(const GemmDesc& g, const TnSplit& sp, float* ws, size_t ws_floats, hipStream_t s, TnChain* chain) {
@@ -1609,7 +1621,8 @@ void launch_pair_as(const GemmDesc& g, const TnArgs& a, hipStream_t s) {
     attr_set = true;
   }
   const int tiles = ((g.M + N::BM - 1) / N::BM) * ((g.N + N::BN - 1) / N::BN);
-  gemm_pair_kernel<I, T><<<a.blocks + tiles, TN_THREADS, lds, s>>>(BSR_HOT_ARGS(g, tiles), a.blocks, g, a);
+  gemm_pair_kernel<I, T><<<a.blocks + tiles, TN_THREADS, lds, s>>>(g.A, g.B, a.g.A, g.M, g.N, g.K, (unsigned)g.a_rs,
+                                                               (unsigned)g.b_cs, (unsigned)a.g.a_cs, tn_pack(a), a.blocks, g, a);
 }
 template <int I>
 void launch_pair(const GemmDesc& g, const GemmDesc& t, const TnSplit& sp, float* ws, size_t ws_floats, hipStream_t s, TnChain* chain) {
@@ -1742,7 +1755,13 @@ static int few_rows_shape(const GemmDesc& g, bool carries_wgrad) {
   model_pick(kNtStepModel, g, is_ntd(g), &tiled_us);
   return few_us < FEW_LEAD * (tiled_us - EVENTS_US - (carries_wgrad ? TILED_LAUNCH_US : 0.f)) ? few : -1;
 }
-static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) { return is_nt(nt) && is_ntd(nt) && !nt.grp_off && is_tn(tn) && !tn.grp_off; }
+// the two gradients of one layer: one dy, sizes that match
+static bool one_layer(const GemmDesc& nt, const GemmDesc& tn) {
+  return nt.A == tn.B && nt.a_rs == tn.b_rs && nt.M == tn.K && nt.N == tn.M && nt.K == tn.N && (int64_t)tn.K * tn.a_cs <= (int64_t)UINT32_MAX;
+}
+static bool can_pair(const GemmDesc& nt, const GemmDesc& tn) {
+  return is_nt(nt) && is_ntd(nt) && !nt.grp_off && is_tn(tn) && !tn.grp_off && one_layer(nt, tn);
+}
 
 // Tile of the input gradient (index into kPairNt) in a layer's backward launch that is asked to take a shape; -1: the joint kernel
 // has no such tile, two launches.  Several ids name one tile here: loads are straight into LDS whatever the id says, in one depth.
