@@ -700,10 +700,9 @@ void build_shadows(bsr_ctx* c, int first_block, hipStream_t s) {
   if (c->f32) return;
   const bsr_config& cf = c->cfg;
   const int D = cf.dim, F = cf.mlp_hidden;
-  MatTable tab;
+  OptTable tab;
   auto add = [&](const void* w, int rows, int cols, bf16* sp, bf16* tp) {
-    matrix_table_add(tab, (float*)const_cast<void*>(w), nullptr, nullptr, nullptr, rows, cols, sp, tp);
-    if (tab.count == MAT_TABLE_MAX) { matrix_table_run(tab, false, OptArgs(), s); tab = MatTable(); }
+    opt_add_mat(tab, MatEntry{(float*)const_cast<void*>(w), nullptr, nullptr, nullptr, sp, tp, rows, cols}, false, OptArgs(), s);
   };
   if (first_block == 0 && cf.image_size)
     add(c->p.w_patch, cf.in_chans * cf.patch_size * cf.patch_size, D, nullptr, c->b.t_patch);
@@ -731,7 +730,7 @@ void build_shadows(bsr_ctx* c, int first_block, hipStream_t s) {
       add(w.w_fc1, D, F, sh.s_fc1, sh.t_fc1);
     add(w.w_fc2, F, D, sh.s_fc2, sh.t_fc2);
   }
-  matrix_table_run(tab, false, OptArgs(), s);
+  opt_run(tab, false, OptArgs(), s);
   for (int l = first_block; l < cf.depth; ++l)
     if (c->sc.moe[l]) moe_router_copy((const float*)c->p.blocks[l].w_router, D, cf.n_experts, c->b.sh[l].t_router, s);
 }
@@ -1195,27 +1194,22 @@ int32_t bsr_moe_routing_io(bsr_ctx* c, const int32_t* forced_experts, int32_t* e
   return BSR_OK;
 }
 
-// One optimiser step over the trainable tensors: vectors through sgd_table, matrices through the
-// matrix table (which also rewrites their bf16 copies).  m1 / m2: first / second moment tables (null
+// One optimiser step over the trainable tensors, a table at a time (matrices get their bf16 copies rewritten).  m1 / m2: first / second moment tables (null
 // when the rule does not use them).
 static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_params* m1, const bsr_params* m2,
                               const OptArgs& o, hipStream_t s, const char* where) {
   const bsr_config& cf = c->cfg;
   const int D = cf.dim, F = cf.mlp_hidden;
-  SgdTable tab;
-  int ntab = 0;
+  OptTable tab;
   auto vec = [&](void* w, const void* g, void* a, void* b2, int64_t n) {
-    tab.e[ntab++] = SgdEntry{(float*)w, (const float*)g, m1 ? (float*)a : nullptr, m2 ? (float*)b2 : nullptr, n};
-    if (ntab == SGD_TABLE_MAX) { sgd_table(tab, ntab, o, s); ntab = 0; }
+    opt_add_vec(tab, VecEntry{(float*)w, (const float*)g, m1 ? (float*)a : nullptr, m2 ? (float*)b2 : nullptr, n}, true, o, s);
   };
-  MatTable mats;
   auto mat = [&](void* w, const void* g, void* a, void* b2, size_t off, int rows, int cols, bf16* sp, bf16* tp) {
     float* wp = (float*)w + off;
     const float* gp = (const float*)g + off;
     float* ap = m1 ? (float*)a + off : nullptr;
     float* bp = m2 ? (float*)b2 + off : nullptr;
-    matrix_table_add(mats, wp, gp, ap, bp, rows, cols, sp, tp);
-    if (mats.count == MAT_TABLE_MAX) { matrix_table_run(mats, true, o, s); mats = MatTable(); }
+    opt_add_mat(tab, MatEntry{wp, gp, ap, bp, sp, tp, rows, cols}, true, o, s);
   };
   for (int l = cf.first_trainable_block; l < cf.depth; ++l) {
     if (!c->sc.trainable[l]) continue;
@@ -1253,8 +1247,7 @@ static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_par
     vec(W.w_head, G.w_head, A.w_head, V.w_head, (int64_t)D * cf.num_classes);
     vec(W.b_head, G.b_head, A.b_head, V.b_head, cf.num_classes);
   }
-  sgd_table(tab, ntab, o, s);
-  matrix_table_run(mats, true, o, s);
+  opt_run(tab, true, o, s);
   for (int l = cf.first_trainable_block; l < cf.depth; ++l)      // the routers were updated as vectors
     if (c->sc.moe[l] && c->sc.trainable[l])
       moe_router_copy((const float*)c->p.blocks[l].w_router, D, cf.n_experts, c->b.sh[l].t_router, s);

@@ -232,20 +232,22 @@ void moe_unpermute_bwd(const void* dxg, const int32_t* pos, const int32_t* exper
 enum { OPT_SGD = 0, OPT_ADAMW = 1 };
 struct OptArgs { int kind = OPT_SGD; float lr = 0.f, mu = 0.f, wd = 0.f, b1 = 0.f, b2 = 0.f, eps = 0.f, bc1 = 1.f, bc2 = 1.f; };
 
-// A table of weight matrices handled by one launch: bf16 copies (straight and / or transposed) of
-// each, optionally after an optimiser update.  The table travels as a kernel argument (< 4 KB).
-constexpr int MAT_TABLE_MAX = 56;
-struct MatEntry { float* w; const float* g; float* m; float* v2; bf16* s; bf16* t; int rows, cols, tile_start; };
-struct MatTable { MatEntry e[MAT_TABLE_MAX]; int count = 0; int total_tiles = 0; };
-void matrix_table_add(MatTable& t, float* w, const float* g, float* m, float* v2, int rows, int cols, bf16* straight,
-                      bf16* transposed);
-void matrix_table_run(const MatTable& t, bool update, const OptArgs& o, hipStream_t s);
-
-// The same update on up to SGD_TABLE_MAX tensors without bf16 copies in one launch
-constexpr int SGD_TABLE_MAX = 96;
-struct SgdEntry { float* w; const float* g; float* m; float* v2; int64_t n; };
-struct SgdTable { SgdEntry e[SGD_TABLE_MAX]; };
-void sgd_table(const SgdTable& t, int count, const OptArgs& o, hipStream_t s);
+// A table of weight matrices handled by one launch: bf16 copies (straight and / or transposed) of each, optionally after an optimiser
+// update; and of small tensors without copies (biases, LayerNorm parameters, the head), which only get the update.  The table travels as a
+// kernel argument (< 4 KB): six dense blocks, or six and the head, fit.
+constexpr int OPT_MATS = 24, OPT_VECS = 56;
+struct MatEntry { float* w; const float* g; float* m; float* v2; bf16* s; bf16* t; int rows, cols; };
+struct VecEntry { float* w; const float* g; float* m; float* v2; int64_t n; };
+struct OptTable {
+  MatEntry mat[OPT_MATS];
+  VecEntry vec[OPT_VECS];
+  int mat_start[OPT_MATS], vec_start[OPT_VECS];      // first workgroup of each (vectors: behind the matrices')
+  int mats = 0, vecs = 0, mat_blocks = 0, vec_blocks = 0;
+};
+// an entry more; a full table is run first
+void opt_add_mat(OptTable& t, const MatEntry& e, bool update, const OptArgs& o, hipStream_t s);
+void opt_add_vec(OptTable& t, const VecEntry& e, bool update, const OptArgs& o, hipStream_t s);
+void opt_run(OptTable& t, bool update, const OptArgs& o, hipStream_t s);      // leaves it empty
 // fp32 C[M,N] = A.B (+bias) for tiny problems (the classification head)
 void gemm_small_f32(const GemmDesc& g, hipStream_t s);
 

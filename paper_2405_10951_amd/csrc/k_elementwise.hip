@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void mean_sq_kernel(const T* __restrict__ x, i
 }
 
 // ---------------------------------------------------------------- weights: casts and SGD
-// A table of matrices in one launch.  64x64 tiles, 16-byte accesses; the tile goes through LDS so
+// A table of matrices (and small tensors) in one launch.  64x64 tiles, 16-byte accesses; the tile goes through LDS so
 // that both the straight [rows,cols] and the transposed [cols,rows] bf16 copies are written with
 // contiguous rows.  With UPDATE the tile is first updated by SGD (Sec. 5 of the paper):
 //   g' = g + wd*w;  mu > 0: m = mu*m + g', w -= lr*m;  else w -= lr*g'.
@@ -222,13 +222,37 @@ __device__ inline float4 opt_update4(const OptArgs& o, float4 w, float4 g, float
   return w;
 }
 
+constexpr int VEC_PER_BLOCK = 1024;
+// the entry whose workgroups hold block: a lane per entry (walking the table one scalar load after the other, a workgroup began up to 16
+// of them late)
+__device__ inline int table_entry(const int* start, int count, int block) {
+  const int lane = threadIdx.x % WAVE;
+  return __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < count && block >= start[min(lane, count - 1)])) - 1);
+}
+static_assert(OPT_MATS <= WAVE && OPT_VECS <= WAVE, "a lane per entry");
+
 template <bool UPDATE>
-__global__ __launch_bounds__(256) void matrix_table_kernel(MatTable t, OptArgs o) {
+__global__ __launch_bounds__(256) void opt_table_kernel(OptTable t, OptArgs o) {
   __shared__ float tile[64][65];
-  int ei = 0;
-  while (ei + 1 < t.count && (int)blockIdx.x >= t.e[ei + 1].tile_start) ++ei;
-  const MatEntry e = t.e[ei];
-  const int local = blockIdx.x - e.tile_start, tiles_x = (e.cols + 63) / 64;
+  if (UPDATE && (int)blockIdx.x >= t.mat_blocks) {       // a slice of a small tensor
+    const int block = blockIdx.x - t.mat_blocks, ei = table_entry(t.vec_start, t.vecs, block);
+    const VecEntry e = t.vec[ei];
+    const int64_t i0 = (int64_t)(block - t.vec_start[ei]) * VEC_PER_BLOCK + threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < VEC_PER_BLOCK / 256; ++j) {
+      const int64_t i = i0 + 256 * j;
+      if (i >= e.n) break;
+      const bool use_m = o.kind == OPT_ADAMW || o.mu > 0.f, use_v = o.kind == OPT_ADAMW;
+      float mm = use_m ? e.m[i] : 0.f, vv = use_v ? e.v2[i] : 0.f;
+      e.w[i] = opt_update(o, e.w[i], e.g[i], mm, vv);
+      if (use_m) e.m[i] = mm;
+      if (use_v) e.v2[i] = vv;
+    }
+    return;
+  }
+  const int ei = table_entry(t.mat_start, t.mats, blockIdx.x);
+  const MatEntry e = t.mat[ei];
+  const int local = blockIdx.x - t.mat_start[ei], tiles_x = (e.cols + 63) / 64;
   const int c0 = (local % tiles_x) * 64, r0 = (local / tiles_x) * 64;
   const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
 #pragma unroll
@@ -263,23 +287,6 @@ __global__ __launch_bounds__(256) void matrix_table_kernel(MatTable t, OptArgs o
         *(bf16x4_t*)(e.t + (int64_t)c * e.rows + r) = o;
       }
     }
-  }
-}
-
-// SGD on a table of small tensors (biases, LayerNorm parameters, the head) in one launch:
-// blockIdx.y picks the tensor, blockIdx.x a slice of 1024 elements.
-__global__ __launch_bounds__(256) void sgd_table_kernel(SgdTable t, OptArgs o) {
-  const SgdEntry e = t.e[blockIdx.y];
-  const int64_t i0 = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int64_t i = i0 + 256 * j;
-    if (i >= e.n) break;
-    const bool use_m = o.kind == OPT_ADAMW || o.mu > 0.f, use_v = o.kind == OPT_ADAMW;
-    float mm = use_m ? e.m[i] : 0.f, vv = use_v ? e.v2[i] : 0.f;
-    e.w[i] = opt_update(o, e.w[i], e.g[i], mm, vv);
-    if (use_m) e.m[i] = mm;
-    if (use_v) e.v2[i] = vv;
   }
 }
 
@@ -380,26 +387,27 @@ void ln_fold_weights(const float* w, const float* bias, const float* gamma, cons
   ln_fold_kernel<<<(out + 127) / 128, 128, 0, s>>>(w, bias, gamma, beta, in, out, w_t, colsum, bias_out);
 }
 
-void matrix_table_add(MatTable& t, float* w, const float* g, float* m, float* v2, int rows, int cols, bf16* straight,
-                      bf16* transposed) {
-  MatEntry& e = t.e[t.count];
-  e.w = w; e.g = g; e.m = m; e.v2 = v2; e.s = straight; e.t = transposed; e.rows = rows; e.cols = cols;
-  e.tile_start = t.total_tiles;
-  t.total_tiles += ((rows + 63) / 64) * ((cols + 63) / 64);
-  ++t.count;
+void opt_run(OptTable& t, bool update, const OptArgs& o, hipStream_t s) {
+  const int blocks = t.mat_blocks + t.vec_blocks;
+  if (blocks > 0) {
+    if (update) opt_table_kernel<true><<<blocks, 256, 0, s>>>(t, o);
+    else opt_table_kernel<false><<<blocks, 256, 0, s>>>(t, OptArgs());
+  }
+  t.mats = t.vecs = t.mat_blocks = t.vec_blocks = 0;
 }
 
-void matrix_table_run(const MatTable& t, bool update, const OptArgs& o, hipStream_t s) {
-  if (t.count == 0) return;
-  if (update) matrix_table_kernel<true><<<t.total_tiles, 256, 0, s>>>(t, o);
-  else matrix_table_kernel<false><<<t.total_tiles, 256, 0, s>>>(t, OptArgs());
+void opt_add_mat(OptTable& t, const MatEntry& e, bool update, const OptArgs& o, hipStream_t s) {
+  if (t.mats == OPT_MATS) opt_run(t, update, o, s);
+  t.mat[t.mats] = e;
+  t.mat_start[t.mats++] = t.mat_blocks;
+  t.mat_blocks += ((e.rows + 63) / 64) * ((e.cols + 63) / 64);
 }
 
-void sgd_table(const SgdTable& t, int count, const OptArgs& o, hipStream_t s) {
-  if (count <= 0) return;
-  int64_t nmax = 0;
-  for (int i = 0; i < count; ++i) nmax = std::max(nmax, t.e[i].n);
-  sgd_table_kernel<<<dim3((unsigned)((nmax + 1023) / 1024), count), 256, 0, s>>>(t, o);
+void opt_add_vec(OptTable& t, const VecEntry& e, bool update, const OptArgs& o, hipStream_t s) {
+  if (t.vecs == OPT_VECS) opt_run(t, update, o, s);
+  t.vec[t.vecs] = e;
+  t.vec_start[t.vecs++] = t.vec_blocks;
+  t.vec_blocks += (int)((e.n + VEC_PER_BLOCK - 1) / VEC_PER_BLOCK);
 }
 
 }  // namespace bsr
