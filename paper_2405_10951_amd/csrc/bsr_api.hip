@@ -1084,9 +1084,8 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
     const int C = cf.num_classes;
     if (head_takes(B, D, C, (const float*)c->p.w_head)) {
       head_fwd_bwd(x, B, Tl, D, C, f32, (const float*)c->p.lnf_g, (const float*)c->p.lnf_b, c->eps, (const float*)c->p.w_head,
-                   (const float*)c->p.b_head, labels, b.xc, b.z, b.logits, b.dlogits, b.dz, b.loss_rows, dx,
+                   (const float*)c->p.b_head, labels, b.xc, b.z, logits_out ? logits_out : b.logits, b.dlogits, b.dz, b.loss_rows, dx,
                    (float*)grads->w_head, (float*)grads->b_head, (float*)grads->lnf_g, (float*)grads->lnf_b, loss_out, s);
-      if (logits_out) (void)hipMemcpyAsync(logits_out, b.logits, sizeof(float) * (size_t)B * C, hipMemcpyDeviceToDevice, s);
     } else {
     extract_cls(x, B, Tl, D, f32, b.xc, s);
     layernorm_fwd(b.xc, B, D, (const float*)c->p.lnf_g, (const float*)c->p.lnf_b, c->eps, true, b.z, b.meanf, b.rstdf, s);
@@ -1142,17 +1141,19 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
       if (tr) dgrad_wgrad(c, d2, v.h2, b.dgu, M2, D, F, gw.w_fc1, gw.b_fc1, s);
       else gemm(c, d2, s);
     }
+    // adjoint of the token drop: dropped tokens receive nothing from the FFN side.  The LayerNorm's gradient leaves for the places of the
+    // kept ones; where dropped tokens were fused, or for rows it cannot do that with, one more launch does
+    LnScatter kept;
+    if (di >= 0 && !sc.fused[di] && layernorm_bwd_scatters(D, f32)) { kept.idx = idx_used[l]; kept.k = sc.keep_k[di]; kept.T = Ta; }
     if (tr) {
       float* slot = b.ln_partial ? b.ln_partial + (size_t)(ln_slot++) * ln_deferred_partial_floats(D) : nullptr;
       layernorm_bwd(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, b.partial, slot,
-                    (float*)gw.ln2_g, (float*)gw.ln2_b, ln_tab, s);
+                    (float*)gw.ln2_g, (float*)gw.ln2_b, ln_tab, s, 0, kept);
     }
     else
-      layernorm_bwd_dx(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, s);
-    std::swap(dx, dx_other);   // dx: gradient at x_mid (kept tokens)
-
-    // adjoint of the token drop: dropped tokens receive nothing from the FFN side
-    if (di >= 0) {
+      layernorm_bwd_dx(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, s, 0, kept);
+    std::swap(dx, dx_other);   // dx: gradient at x_mid (kept tokens, or all of them)
+    if (di >= 0 && !kept.idx) {
       scatter_tokens(dx, idx_used[l], B, Ta, sc.keep_k[di], D, f32, dx_other, s, sc.fused[di] ? v.fw : nullptr);
       std::swap(dx, dx_other);
     }
@@ -1177,8 +1178,7 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
       layernorm_bwd_dx(b.dh, xin, v.mean1, v.rstd1, (const float*)w.ln1_g, dx, M, D, f32, dx_other, s, period);
     if (l > ft) std::swap(dx, dx_other);
   }
-  ln_deferred_finish(ln_tab, s);
-  gemm_tn_flush(&c->tn_chain, s);
+  ln_deferred_finish(ln_tab, gemm_tn_take(&c->tn_chain), s);
   return check_hip(c, "bsr_train_blocks_fwd_bwd");
 }
 

@@ -82,6 +82,26 @@ struct TnReduce {
   int nb = 0;
   float* bout = nullptr;
 };
+// four elements of a sum of partials (or, past the matrix, up to four of the column sums): added in
+// ascending order
+__device__ inline void splitk_reduce_item(const TnReduce& r, int64_t item) {
+  const int64_t i = item * 4;
+  if (i >= r.n) {
+    for (int64_t j = i - r.n; j < min(i - r.n + 4, (int64_t)r.nb); ++j) {
+      float s = r.bpartial[j];
+      for (int z = 1; z < r.splits; ++z) s += r.bpartial[(int64_t)z * r.nb + j];
+      r.bout[j] = s;
+    }
+    return;
+  }
+  float4 s = *(const float4*)(r.partial + i);
+  for (int z = 1; z < r.splits; ++z) {
+    const float4 v = *(const float4*)(r.partial + (int64_t)z * r.n + i);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  *(float4*)(r.out + i) = s;
+}
+__host__ __device__ inline int64_t splitk_reduce_items(const TnReduce& r) { return r.n / 4 + (r.nb + 3) / 4; }
 struct TnChain {
   TnReduce pending;                 // pending.splits > 0: a reduction is waiting
   int slot = 0;                     // workspace half the next split launch writes
@@ -90,6 +110,7 @@ struct TnChain {
 void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile = 0,
                TnChain* chain = nullptr);
 void gemm_tn_flush(TnChain* chain, hipStream_t s);
+TnReduce gemm_tn_take(TnChain* chain);          // for a caller that adds the waiting partials up itself (splits 0: none wait)
 // input gradient (NT) + weight gradient (TN) of one layer, in one launch when the NT tile shape has that form
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,
                     int tile = 0, TnChain* chain = nullptr);
@@ -122,12 +143,15 @@ void attn_bwd_mfma(const void* qkv, const void* out, const void* dout, const flo
 void layernorm_fwd(const void* x, int64_t M, int D, const float* gamma, const float* beta, float eps,
                    bool f32, void* y, float* mean, float* rstd, hipStream_t s);
 // res may be null, dx null to skip it.  res_period 0: a residual row per row; P > 0: rows 0, P, 2P, ... have one each
-// (the residual then has M / P rows)
-template <typename T> struct LnRows { const T* x; const T* res; T* dx; int res_period; };
+// (the residual then has M / P rows).
+// idx: row m of dx is that of a token behind a drop (k + 1 rows per image, [class; kept], idx [B, k] ascending) and goes to its place among
+// the T tokens before it; the dropped tokens' rows are set to zero
+struct LnScatter { const int32_t* idx = nullptr; int k = 0, T = 0; };
+template <typename T> struct LnRows { const T* x; const T* res; T* dx; int res_period; LnScatter sc; };
 // dx = res + LN'(dy)
 void layernorm_bwd_dx(const void* dy, const void* x, const float* mean, const float* rstd,
                       const float* gamma, const void* res, int64_t M, int D, bool f32, void* dx,
-                      hipStream_t s, int res_period = 0);
+                      hipStream_t s, int res_period = 0, const LnScatter& sc = LnScatter());
 // dgamma[j] = sum_m dy*xhat, dbeta[j] = sum_m dy ; partial is scratch of colsum_partial_floats()
 void layernorm_bwd_params(const void* dy, const void* x, const float* mean, const float* rstd,
                           int64_t M, int D, bool f32, float* partial, float* dgamma, float* dbeta,
@@ -146,8 +170,11 @@ struct LnDeferTable { LnDeferEntry e[LN_DEFER_MAX]; int count = 0; int D = 0; };
 size_t ln_deferred_partial_floats(int D);
 void layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma,
                    const void* res, int64_t M, int D, bool f32, void* dx, float* partial, float* slot, float* dgamma,
-                   float* dbeta, LnDeferTable& t, hipStream_t s, int res_period = 0);
-void ln_deferred_finish(LnDeferTable& t, hipStream_t s);
+                   float* dbeta, LnDeferTable& t, hipStream_t s, int res_period = 0, const LnScatter& sc = LnScatter());
+// whether rows of D can be scattered on the way out
+bool layernorm_bwd_scatters(int D, bool f32);
+// and the partials of the last weight gradient in the same launch (red.splits 0: none)
+void ln_deferred_finish(LnDeferTable& t, const TnReduce& red, hipStream_t s);
 
 // cls given: also writes the class-token rows x[b, 0, :] = cls + pos[0] of the token tensor x [B, T, D] (same launch
 // on the 16-byte path)

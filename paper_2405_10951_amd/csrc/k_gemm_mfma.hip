@@ -1092,28 +1092,6 @@ void launch_few(int pick, const GemmDesc& g, hipStream_t s) {
 // 32 columns; they travel through the same partial / reduce path as dW.
 #define BSR_LDS_PTR(T, p) ((T __attribute__((address_space(3)))*)(p))
 
-// four elements of a sum of partials (or, past the matrix, up to four of the column sums): added in
-// ascending order
-__device__ inline void splitk_reduce_item(const TnReduce& r, int64_t item) {
-  const int64_t i = item * 4;
-  if (i >= r.n) {
-    for (int64_t j = i - r.n; j < min(i - r.n + 4, (int64_t)r.nb); ++j) {
-      float s = r.bpartial[j];
-      for (int z = 1; z < r.splits; ++z) s += r.bpartial[(int64_t)z * r.nb + j];
-      r.bout[j] = s;
-    }
-    return;
-  }
-  float4 s = *(const float4*)(r.partial + i);
-  for (int z = 1; z < r.splits; ++z) {
-    const float4 v = *(const float4*)(r.partial + (int64_t)z * r.n + i);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
-  *(float4*)(r.out + i) = s;
-}
-__device__ inline int64_t splitk_reduce_items(const TnReduce& r) { return r.n / 4 + (r.nb + 3) / 4; }
-inline int64_t splitk_reduce_items_host(const TnReduce& r) { return r.n / 4 + (r.nb + 3) / 4; }
-
 constexpr int TN_LOADERS = 4, TN_THREADS = (8 + TN_LOADERS) * 64;
 
 // What a weight gradient needs in a launch: its product, its parts, and the sums of the previous one.
@@ -1470,7 +1448,7 @@ __global__ void splitk_reduce_kernel(TnReduce r) {
 }
 
 void launch_reduce(const TnReduce& r, hipStream_t s) {
-  splitk_reduce_kernel<<<(unsigned)((splitk_reduce_items_host(r) + 255) / 256), 256, 0, s>>>(r);
+  splitk_reduce_kernel<<<(unsigned)((splitk_reduce_items(r) + 255) / 256), 256, 0, s>>>(r);
 }
 
 bool is_tn(const GemmDesc& g) {
@@ -1597,7 +1575,7 @@ void launch_tn_as(const TnArgs& a, hipStream_t s) {
   }
   // sums of an earlier launch: about four items per thread
   const int64_t per = (int64_t)TN_THREADS * 4;
-  const int red = a.red.splits > 0 ? (int)std::min<int64_t>(512, (splitk_reduce_items_host(a.red) + per - 1) / per) : 0;
+  const int red = a.red.splits > 0 ? (int)std::min<int64_t>(512, (splitk_reduce_items(a.red) + per - 1) / per) : 0;
   gemm_tn_kernel<T><<<a.blocks + red, TN_THREADS, lds, s>>>(a.g.A, a.g.B, a.g.M, a.g.N, a.g.K, (unsigned)a.g.a_cs,
                                                             (unsigned)a.g.b_rs, tn_pack(a), a.blocks, a.g.grp_off, a);
 }
@@ -1786,10 +1764,14 @@ int gemm_nt_runs_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws
   return nt_tile(g, tile);
 }
 
+TnReduce gemm_tn_take(TnChain* chain) {
+  const TnReduce r = chain->pending;
+  chain->pending = TnReduce();
+  return r;
+}
 void gemm_tn_flush(TnChain* chain, hipStream_t s) {
   if (!chain || chain->pending.splits <= 0) return;
-  launch_reduce(chain->pending, s);
-  chain->pending = TnReduce();
+  launch_reduce(gemm_tn_take(chain), s);
 }
 
 // The tiled kernels, in the shape asked for or, for 0 and for a shape that cannot take the product, the model's.

@@ -17,7 +17,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, in
                                                      const float* __restrict__ beta, float eps, T* __restrict__ y,
                                                      float* __restrict__ mean, float* __restrict__ rstd) {
   const int lane = threadIdx.x % WAVE;
-  const int64_t m = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
+  const int64_t m = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   if (m >= M) return;
   typename Chunk<T>::vec raw[MAXC];
   float v[MAXC][Chunk<T>::V];
@@ -58,6 +58,33 @@ template <typename T> __device__ inline const T* res_row(const LnRows<T>& r, int
   if (r.res_period == 0) return r.res + m * D;
   return m % r.res_period == 0 ? r.res + m / r.res_period * D : nullptr;
 }
+
+// Where the gradient of a row goes (LnRows); the rows of the tokens dropped since the row before it, and behind an image's last one, are cleared
+// by the wavefront that has the row: every row of dx is written exactly once, without a search.
+struct RowPlace {
+  unsigned image = 0;
+  int token = 0, before = 0;      // places of this row and of the one before it (-1: none)
+  bool last = false;
+  __device__ __forceinline__ void find(const LnScatter& sc, int64_t m) {       // (row counts fit 31 bits)
+    const unsigned n = (unsigned)sc.k + 1u;
+    image = (unsigned)m / n;
+    const int i = (int)((unsigned)m % n);
+    const int32_t* idx = sc.idx + (int64_t)image * sc.k;
+    token = i == 0 ? 0 : 1 + idx[i - 1];
+    before = i == 0 ? -1 : i == 1 ? 0 : 1 + idx[i - 2];
+    last = i == sc.k;
+  }
+  template <typename T> __device__ __forceinline__ T* row(const LnRows<T>& r, int D, int lane) const {
+    T* img = r.dx + (int64_t)image * r.sc.T * D;
+    auto clear = [&](int t0, int t1) {
+      uint4* z = (uint4*)(img + (int64_t)t0 * D);
+      for (int j = lane; j < (t1 - t0) * (D * (int)sizeof(T) / 16); j += WAVE) z[j] = make_uint4(0u, 0u, 0u, 0u);
+    };
+    clear(before + 1, token);
+    if (last) clear(token + 1, r.sc.T);
+    return img + (int64_t)token * D;
+  }
+};
 
 // dx = res + rstd * (g - mean(g) - xhat * mean(g * xhat)),  g = dy * gamma; any row length
 template <typename T>
@@ -101,7 +128,7 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
   constexpr int V = Chunk<T>::V;
   typedef typename Chunk<T>::vec vec;
   extern __shared__ float red[];            // [wavefronts / 2][2][D]
-  const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE, nw = blockDim.x / WAVE, nch = D / V;
+  const int lane = threadIdx.x % WAVE, w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), nw = blockDim.x / WAVE, nch = D / V;
   const int64_t stride = (int64_t)gridDim.x * nw;
   float gg[MAXC][V], dg[MAXC][V], db[MAXC][V];
 #pragma unroll
@@ -113,8 +140,10 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
   }
   vec na[MAXC], nt[MAXC];                   // the next row, already loading
   float nmu = 0.f, nrs = 0.f;
+  RowPlace nplace;
   auto prefetch = [&](int64_t m) __attribute__((always_inline)) {
     if (m >= M) return;
+    if (r.sc.idx && r.dx) nplace.find(r.sc, m);
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
       const int c = lane + i * WAVE;
@@ -129,6 +158,7 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) { a[i] = na[i]; t[i] = nt[i]; }
     const float mu = nmu, rs = nrs;
+    const RowPlace place = nplace;
     const T* res = r.dx ? res_row(r, m, D) : nullptr;
     if (res)
 #pragma unroll
@@ -147,6 +177,7 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
           s2 += g * xh;
         }
     if (r.dx) {
+      T* out = r.sc.idx ? place.row(r, D, lane) : r.dx + m * D;
       const float m1 = wave_sum(s1) / (float)D, m2 = wave_sum(s2) / (float)D;
 #pragma unroll
       for (int i = 0; i < MAXC; ++i) {
@@ -160,7 +191,7 @@ void ln_bwd_kernel(const T* __restrict__ dy, LnRows<T> r, int64_t M, int D, cons
             if (res) v += (float)rr[i][e];
             o[e] = (T)v;
           }
-          *(vec*)(r.dx + m * D + c * V) = o;
+          *(vec*)(out + c * V) = o;
         }
       }
     }
@@ -239,11 +270,11 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const T* __restrict
 // Pass 2: out[col] = sum over chunks.  Wave w of the block adds chunks w, w+16, ... in ascending order, then the wave
 // sums are added in wave order: a fixed order, bit-reproducible.  The second sum (if out1) starts `second` rows into
 // the partial buffer.
-template <bool TWO> __device__ __forceinline__ void final_columns(const float* __restrict__ partial, int N, int chunks, int second, float* __restrict__ out0,
+template <bool TWO> __device__ __forceinline__ void final_columns(int col_block, const float* __restrict__ partial, int N, int chunks, int second, float* __restrict__ out0,
                                               float* __restrict__ out1) {
   __shared__ float red[2][FINAL_WAVES][WAVE];
   const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
-  const int col = blockIdx.x * WAVE + lane;
+  const int col = col_block * WAVE + lane;
   float s = 0.f, t = 0.f;
   if (col < N) {
 #pragma unroll 8
@@ -266,13 +297,20 @@ template <bool TWO> __device__ __forceinline__ void final_columns(const float* _
 __global__ __launch_bounds__(FINAL_WAVES * WAVE) void colsum_final_kernel(const float* __restrict__ partial, int N, int chunks,
                                                                           int second, float* __restrict__ out0,
                                                                           float* __restrict__ out1) {
-  if (out1) final_columns<true>(partial, N, chunks, second, out0, out1);
-  else final_columns<false>(partial, N, chunks, second, out0, out1);
+  if (out1) final_columns<true>(blockIdx.x, partial, N, chunks, second, out0, out1);
+  else final_columns<false>(blockIdx.x, partial, N, chunks, second, out0, out1);
 }
-// the same reduction for a table of LayerNorm backward passes: blockIdx.y picks the entry
-__global__ __launch_bounds__(FINAL_WAVES * WAVE) void ln_deferred_final_kernel(LnDeferTable t) {
-  const LnDeferEntry e = t.e[blockIdx.y];
-  final_columns<true>(e.partial, t.D, e.blocks, LN_BWD_BLOCKS, e.dgamma, e.dbeta);
+// What the backward pass leaves to be added up at its end, in one launch: the partials of the last weight gradient (the first `red_blocks`
+// workgroups, a thread per four elements) and the same column reduction for a table of LayerNorm backward passes.
+__global__ __launch_bounds__(FINAL_WAVES * WAVE) void splitk_reduce_ln_sums_kernel(int red_blocks, TnReduce red, LnDeferTable t) {
+  if ((int)blockIdx.x < red_blocks) {
+    const int64_t it = (int64_t)blockIdx.x * (FINAL_WAVES * WAVE) + threadIdx.x;
+    if (it < splitk_reduce_items(red)) splitk_reduce_item(red, it);
+    return;
+  }
+  const int block = blockIdx.x - red_blocks, cols = (t.D + WAVE - 1) / WAVE;
+  const LnDeferEntry e = t.e[block / cols];
+  final_columns<true>(block % cols, e.partial, t.D, e.blocks, LN_BWD_BLOCKS, e.dgamma, e.dbeta);
 }
 
 inline int rows_per_chunk(int64_t M) { return (int)((M + COLSUM_R - 1) / COLSUM_R); }
@@ -350,8 +388,8 @@ void bwd_t(const void* dy, const LnRows<T>& r, const float* mean, const float* r
   bwd_dx_t<T>(dy, r, mean, rstd, gamma, M, D, s);
 }
 
-template <typename T> LnRows<T> rows_of(const void* x, const void* res, void* dx, int res_period) {
-  return LnRows<T>{(const T*)x, (const T*)res, (T*)dx, res_period};
+template <typename T> LnRows<T> rows_of(const void* x, const void* res, void* dx, int res_period, const LnScatter& sc) {
+  return LnRows<T>{(const T*)x, (const T*)res, (T*)dx, res_period, sc};
 }
 
 }  // namespace
@@ -364,10 +402,10 @@ void layernorm_fwd(const void* x, int64_t M, int D, const float* gamma, const fl
 }
 
 void layernorm_bwd_dx(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma, const void* res,
-                      int64_t M, int D, bool f32, void* dx, hipStream_t s, int res_period) {
+                      int64_t M, int D, bool f32, void* dx, hipStream_t s, int res_period, const LnScatter& sc) {
   if (M <= 0) return;
-  if (f32) bwd_dx_t<float>(dy, rows_of<float>(x, res, dx, res_period), mean, rstd, gamma, M, D, s);
-  else bwd_dx_t<bf16>(dy, rows_of<bf16>(x, res, dx, res_period), mean, rstd, gamma, M, D, s);
+  if (f32) bwd_dx_t<float>(dy, rows_of<float>(x, res, dx, res_period, sc), mean, rstd, gamma, M, D, s);
+  else bwd_dx_t<bf16>(dy, rows_of<bf16>(x, res, dx, res_period, sc), mean, rstd, gamma, M, D, s);
 }
 
 void layernorm_bwd_params(const void* dy, const void* x, const float* mean, const float* rstd, int64_t M, int D, bool f32,
@@ -377,19 +415,23 @@ void layernorm_bwd_params(const void* dy, const void* x, const float* mean, cons
   else bwd_params_t<bf16>(dy, x, mean, rstd, M, D, partial, dgamma, dbeta, s);
 }
 
+bool layernorm_bwd_scatters(int D, bool f32) { return D % (f32 ? 4 : 8) == 0 && D <= ROW_MAX; }
+
 size_t ln_deferred_partial_floats(int D) { return (size_t)2 * LN_BWD_BLOCKS * (size_t)D; }
 
 void layernorm_bwd(const void* dy, const void* x, const float* mean, const float* rstd, const float* gamma, const void* res, int64_t M,
                    int D, bool f32, void* dx, float* partial, float* slot, float* dgamma, float* dbeta, LnDeferTable& t, hipStream_t s,
-                   int res_period) {
+                   int res_period, const LnScatter& sc) {
   if (M <= 0) return;
-  if (f32) bwd_t<float>(dy, rows_of<float>(x, res, dx, res_period), mean, rstd, gamma, M, D, partial, slot, dgamma, dbeta, t, s);
-  else bwd_t<bf16>(dy, rows_of<bf16>(x, res, dx, res_period), mean, rstd, gamma, M, D, partial, slot, dgamma, dbeta, t, s);
+  if (f32) bwd_t<float>(dy, rows_of<float>(x, res, dx, res_period, sc), mean, rstd, gamma, M, D, partial, slot, dgamma, dbeta, t, s);
+  else bwd_t<bf16>(dy, rows_of<bf16>(x, res, dx, res_period, sc), mean, rstd, gamma, M, D, partial, slot, dgamma, dbeta, t, s);
 }
 
-void ln_deferred_finish(LnDeferTable& t, hipStream_t s) {
-  if (t.count == 0) return;
-  ln_deferred_final_kernel<<<dim3((t.D + WAVE - 1) / WAVE, t.count), FINAL_WAVES * WAVE, 0, s>>>(t);
+void ln_deferred_finish(LnDeferTable& t, const TnReduce& red, hipStream_t s) {
+  constexpr int NT = FINAL_WAVES * WAVE;
+  const int red_blocks = red.splits > 0 ? (int)((splitk_reduce_items(red) + NT - 1) / NT) : 0;
+  const int blocks = red_blocks + t.count * ((t.D + WAVE - 1) / WAVE);
+  if (blocks > 0) splitk_reduce_ln_sums_kernel<<<blocks, NT, 0, s>>>(red_blocks, red, t);
   t.count = 0;
 }
 
