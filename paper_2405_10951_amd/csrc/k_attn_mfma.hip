@@ -233,6 +233,7 @@ void launch_fwd(const bf16* qkv, int B, int T, int H, bf16* out, float* lse, flo
 //   dQ_i = sum_j dS_ij k_j      (kernel "dq":  a wave owns 32 queries, sweeps the key blocks)
 //   dK_j = sum_i dS_ij q_i,  dV_j = sum_i P_ij dO_i   (kernel "dkv": a wave owns 32 keys, sweeps
 //                                                      the query blocks)
+// These two are for 225 .. 256 tokens, whose score gradients do not fit in LDS beside the operands (below: attn_bwd_kernel).
 // Both recompute S with MFMAs; nothing T x T is stored or exchanged between wavefronts, and no
 // atomics are used.  What bounds them is how many wavefronts a CU has to cover the chain read - MFMA - exp - MFMA.  "dq" runs all
 // ceil(T / 32) wavefronts of a head in one workgroup, in 128 registers, so that two heads share a CU, and writes 8-byte pieces:
@@ -413,6 +414,172 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16* __restric
         dst[2 * D] = (bf16)ov[nb][r];
       }
     }
+}
+
+// All three in one launch, up to 224 tokens.  A wavefront owns 32 keys and sweeps the query blocks as in "dkv"; the score gradients, which dQ
+// needs with the keys as contraction index, stay in LDS (ceil(T / 32) blocks of [key][32 queries] in bf16, the factor that "dq" rounds them to), and
+// once every wavefront is done each turns to 32 queries and contracts them with the keys, which by then lie where the queries were.  So scores,
+// probabilities and dP are computed once instead of twice, q, k, v and dO are read once, and delta never leaves LDS but for the caller's copy.
+// Same products in the same order: the same bits as the two kernels.  What bounds it at many images is
+// memory (310 MB at 128 images of 12 heads and 197 tokens, 66 us of the 114), with one head a CU at a time.  Two kernels -> this: 128 images of 12 heads,
+// 197 tokens 148 -> 114 us, 138 tokens 109 -> 79, 67 tokens 44 -> 32; 32 images 48 -> 35, 35 -> 25, 15.5 -> 11.3; one image 19.5 -> 15.0.
+// dS rows are four 16-byte chunks, chunk c of key j at c ^ ((j >> 2) & 3): 8-byte writes of 32 keys and the transpose reads of 4 keys x 32
+// queries touch every bank alike.
+template <int NJ> constexpr size_t attn_bwd_lds() {
+  return (size_t)2 * NJ * 32 * 128 + (size_t)NJ * NJ * 32 * 64 + (size_t)2 * NJ * 32 * sizeof(float);
+}
+template <int NJ>
+__global__ __launch_bounds__(NJ * 64) void attn_bwd_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ out, const bf16* __restrict__ dout,
+                                                           const float* __restrict__ lse, int T, int H, float* __restrict__ delta,
+                                                           bf16* __restrict__ dqkv) {
+  constexpr int Tpad = NJ * 32;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  u32x4* Qs = (u32x4*)smem;
+  u32x4* dOs = Qs + Tpad * 8;
+  unsigned char* dS = (unsigned char*)(dOs + Tpad * 8);      // [NJ query blocks][Tpad keys][64 bytes]
+  float* lse_s = (float*)(dS + NJ * Tpad * 64);              // [Tpad], pre-multiplied by log2(e); +inf beyond T
+  float* del_s = lse_s + Tpad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  const int b = blockIdx.x / H, h = blockIdx.x % H;
+  const int D = H * HD;
+  const int64_t rs = 3 * (int64_t)D;
+  const bf16* base = qkv + (int64_t)b * T * rs + h * HD;
+  const bf16* dobase = dout + (int64_t)b * T * D + h * HD;
+  const int j0 = wave * 32, ji = j0 + lr, jc = min(ji, T - 1);       // this lane's key, and later its query
+  bf16x8 kf[4], vf[4];
+  float dl = 0.f;
+  {
+    const bf16* krow = base + (int64_t)jc * rs + D;
+    const bf16* dorow = dobase + (int64_t)jc * D;
+    const bf16* orow = out + ((int64_t)b * T + jc) * D + h * HD;
+    bf16x8 df[4], of[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      df[ks] = *(const bf16x8*)(dorow + (2 * ks + lh) * 8);
+      of[ks] = *(const bf16x8*)(orow + (2 * ks + lh) * 8);
+      kf[ks] = *(const bf16x8*)(krow + (2 * ks + lh) * 8);
+      vf[ks] = *(const bf16x8*)(krow + D + (2 * ks + lh) * 8);
+    }
+    load_two(base, rs, dobase, D, T, Tpad, Qs, dOs, tid, NJ * 64);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dl += (float)df[ks][e] * (float)of[ks][e];
+  }
+  dl = half_sum(dl);
+  if (lh == 0) {
+    const bool valid = ji < T;
+    lse_s[ji] = valid ? lse[((int64_t)b * H + h) * T + ji] * 1.44269504088896341f : INFINITY;
+    del_s[ji] = valid ? dl : 0.f;
+    if (valid) delta[((int64_t)b * H + h) * T + ji] = dl;
+  }
+  __syncthreads();
+  const float c = 0.125f * 1.44269504088896341f;
+  f32x16 ok[2], ov[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { ok[nb][r] = 0.f; ov[nb][r] = 0.f; }
+  // The scores of query block ib + 1 are under way in the matrix cores while block ib goes through its exponentials: a CU holds one head of
+  // more than 128 tokens, 1 - 2 wavefronts a SIMD, and nobody else covers either
+  // (197 tokens, 128 images: 118 -> 114 us).
+  f32x16 sa, dp;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) { sa[r] = 0.f; dp[r] = 0.f; }
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(Qs, lr, 2 * ks + lh), kf[ks], sa, 0, 0, 0);
+    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag(dOs, lr, 2 * ks + lh), vf[ks], dp, 0, 0, 0);
+  }
+#pragma unroll
+  for (int ib = 0; ib < NJ; ++ib) {
+    f32x16 san, dpn;
+    bf16x8 fq[4], fd[4];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { san[r] = 0.f; dpn[r] = 0.f; }
+    if (ib + 1 < NJ) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        fq[ks] = lds_frag(Qs, (ib + 1) * 32 + lr, 2 * ks + lh);
+        fd[ks] = lds_frag(dOs, (ib + 1) * 32 + lr, 2 * ks + lh);
+      }
+    }
+    bf16x8 pf[2], dsf[2];
+    unsigned char* row = dS + (ib * Tpad + ji) * 64;
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {           // queries 32 ib + 8 g4 + 4 lh + {0..3}
+      if (ib + 1 < NJ) {
+        san = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[g4], kf[g4], san, 0, 0, 0);
+        dpn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fd[g4], vf[g4], dpn, 0, 0, 0);
+      }
+      const float4 l4 = *(const float4*)(lse_s + ib * 32 + 8 * g4 + 4 * lh);
+      const float4 d4 = *(const float4*)(del_s + ib * 32 + 8 * g4 + 4 * lh);
+      const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+      const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
+      bf16x4 q4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = g4 * 4 + e;
+        const float pr = __builtin_amdgcn_exp2f(sa[r] * c - lv[e]);
+        const bf16 ds = (bf16)(pr * (dp[r] - dv[e]) * 0.125f);
+        pf[r >> 3][r & 7] = (bf16)pr;
+        dsf[r >> 3][r & 7] = ds;
+        q4[e] = ji < T ? ds : (bf16)0.f;       // keys past the end repeat the last one: nothing of theirs in dQ
+      }
+      *(bf16x4*)(row + ((g4 ^ ((ji >> 2) & 3)) << 4) + lh * 8) = q4;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        ov[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(dOs, nb, lane, 2 * ib + hf), pf[hf], ov[nb], 0, 0, 0);
+        ok[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(Qs, nb, lane, 2 * ib + hf), dsf[hf], ok[nb], 0, 0, 0);
+      }
+    sa = san;
+    dp = dpn;
+  }
+  if (ji < T) {
+    store_row(dqkv + ((int64_t)b * T + ji) * rs + D + h * HD, ok, lh);
+    store_row(dqkv + ((int64_t)b * T + ji) * rs + 2 * D + h * HD, ov, lh);
+  }
+  __syncthreads();                             // the queries have been read, every score gradient is there
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) *(bf16x8*)(Qs + ji * 8 + ((2 * ks + lh) ^ swz(ji))) = kf[ks];
+  __syncthreads();
+  f32x16 o[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
+  // lane j of 16 (cb: which 16 queries) gets queries' column j of key rows r .. r + 3, as in lds_frag_t
+  const int j = lane & 15, cb = (lane >> 4) & 1, chunk = cb * 2 + ((j & 3) >> 1), half = j & 1;
+  const unsigned char* blk = dS + wave * Tpad * 64;
+#pragma unroll
+  for (int st = 0; st < 2 * NJ; ++st) {
+    const int r0 = 16 * st + 4 * lh + (j >> 2), r1 = r0 + 8;
+    union { bf16x8 v; s16x4 h[2]; } f;
+    f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (s16x4 __attribute__((address_space(3)))*)(blk + r0 * 64 + ((chunk ^ ((r0 >> 2) & 3)) << 4) + half * 8));
+    f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (s16x4 __attribute__((address_space(3)))*)(blk + r1 * 64 + ((chunk ^ ((r1 >> 2) & 3)) << 4) + half * 8));
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(Qs, nb, lane, st), f.v, o[nb], 0, 0, 0);
+  }
+  if (ji < T) store_row(dqkv + ((int64_t)b * T + ji) * rs + h * HD, o, lh);
+}
+
+template <int NJ>
+void launch_bwd_one(const bf16* qkv, const bf16* out, const bf16* dout, const float* lse, int B, int T, int H, float* delta, bf16* dqkv, hipStream_t s) {
+  static bool attr_set = false;
+  constexpr size_t lds = attn_bwd_lds<NJ>();
+  static_assert(lds <= 160 * 1024, "a head's operands and score gradients fit a CU");
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void*)attn_bwd_kernel<NJ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    attr_set = true;
+  }
+  attn_bwd_kernel<NJ><<<B * H, NJ * 64, lds, s>>>(qkv, out, dout, lse, T, H, delta, dqkv);
 }
 
 template <int NJ>
@@ -830,13 +997,13 @@ void attn_bwd_mfma(const void* qkv, const void* out, const void* dout, const flo
   const bf16* d = (const bf16*)dout;
   bf16* g = (bf16*)dqkv;
   switch ((T + 31) / 32) {
-    case 1: launch_bwd<1>(q, o, d, lse, B, T, H, delta, g, s); break;
-    case 2: launch_bwd<2>(q, o, d, lse, B, T, H, delta, g, s); break;
-    case 3: launch_bwd<3>(q, o, d, lse, B, T, H, delta, g, s); break;
-    case 4: launch_bwd<4>(q, o, d, lse, B, T, H, delta, g, s); break;
-    case 5: launch_bwd<5>(q, o, d, lse, B, T, H, delta, g, s); break;
-    case 6: launch_bwd<6>(q, o, d, lse, B, T, H, delta, g, s); break;
-    case 7: launch_bwd<7>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 1: launch_bwd_one<1>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 2: launch_bwd_one<2>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 3: launch_bwd_one<3>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 4: launch_bwd_one<4>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 5: launch_bwd_one<5>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 6: launch_bwd_one<6>(q, o, d, lse, B, T, H, delta, g, s); break;
+    case 7: launch_bwd_one<7>(q, o, d, lse, B, T, H, delta, g, s); break;
     case 8: launch_bwd<8>(q, o, d, lse, B, T, H, delta, g, s); break;
     default: launch_bwd_long(q, d, lse, B, T, H, delta, g, s); break;
   }
