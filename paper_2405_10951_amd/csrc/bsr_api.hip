@@ -912,7 +912,7 @@ int32_t bsr_forward_frozen(bsr_ctx* c, const void* input, int32_t B, void* x_out
     g.pos = (const float*)c->p.pos;
     gemm(c, g, s);
   } else {
-    (void)hipMemcpyAsync(x, input, (size_t)B * sc.T0 * D * E, hipMemcpyDeviceToDevice, s);
+    copy_rows(input, x, (size_t)B * sc.T0 * D * E, s);
   }
 
   size_t idx_off = 0, sc_off = 0;

@@ -180,6 +180,8 @@ void ln_deferred_finish(LnDeferTable& t, const TnReduce& red, hipStream_t s);
 // on the 16-byte path)
 void patchify(const void* img, int B, int C, int S, int P, bool f32, void* out, hipStream_t s,
               const float* cls = nullptr, const float* pos = nullptr, int T = 0, int D = 0, void* x = nullptr);
+// bytes: a multiple of 16, both pointers aligned to 16 (a kernel of its own: the runtime's copy takes the host twice a launch)
+void copy_rows(const void* src, void* dst, size_t bytes, hipStream_t s);
 void write_cls_rows(const float* cls, const float* pos, int B, int T, int D, bool f32, void* x,
                     hipStream_t s);
 // Token selection and what follows it, in one launch (k_select.hip).  Per image: scores = head mean of the class token's

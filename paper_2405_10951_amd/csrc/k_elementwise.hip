@@ -55,6 +55,11 @@ __global__ void patchify_vec_kernel(const T* __restrict__ img, int B, int C, int
   *(uint4*)(out + i * V) = v;                           // out index = ((b*N + p) * C*P*P + (c*P + r)*P + qv*V)
 }
 
+__global__ __launch_bounds__(256) void copy_rows_kernel(const uint4* src, uint4* dst, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) dst[i] = src[i];
+}
+
 template <typename T>
 __global__ void write_cls_rows_kernel(const float* __restrict__ cls, const float* __restrict__ pos,
                                       int B, int T_, int D, T* __restrict__ x) {
@@ -333,6 +338,11 @@ void patchify(const void* img, int B, int C, int S, int P, bool f32, void* out, 
   if (f32) patchify_kernel<float><<<grid, 256, 0, s>>>((const float*)img, B, C, S, P, (float*)out);
   else patchify_kernel<bf16><<<grid, 256, 0, s>>>((const bf16*)img, B, C, S, P, (bf16*)out);
   if (cls) write_cls_rows(cls, pos, B, T, D, f32, x, s);
+}
+
+void copy_rows(const void* src, void* dst, size_t bytes, hipStream_t s) {
+  const int64_t n = (int64_t)(bytes / 16);
+  if (n > 0) copy_rows_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const uint4*)src, (uint4*)dst, n);
 }
 
 void write_cls_rows(const float* cls, const float* pos, int B, int T, int D, bool f32, void* x,
