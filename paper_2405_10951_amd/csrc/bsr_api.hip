@@ -696,13 +696,16 @@ const int32_t* drop_tokens(bsr_ctx* c, int B, int T, int k, const void* x_full, 
   return forced ? forced : idx_own;
 }
 
+// Whether the bf16 copy of a router [D, E] can be written by the kernel of the matrices, which reads rows of four
+bool router_is_matrix(int experts) { return experts % 4 == 0; }
+
 void build_shadows(bsr_ctx* c, int first_block, hipStream_t s) {
   if (c->f32) return;
   const bsr_config& cf = c->cfg;
   const int D = cf.dim, F = cf.mlp_hidden;
   OptTable tab;
-  auto add = [&](const void* w, int rows, int cols, bf16* sp, bf16* tp) {
-    opt_add_mat(tab, MatEntry{(float*)const_cast<void*>(w), nullptr, nullptr, nullptr, sp, tp, rows, cols}, false, OptArgs(), s);
+  auto add = [&](const void* w, int rows, int cols, bf16* sp, bf16* tp, int count = 1) {
+    opt_add_mat(tab, MatEntry{(float*)const_cast<void*>(w), nullptr, nullptr, nullptr, sp, tp, rows, cols, count}, false, OptArgs(), s);
   };
   if (first_block == 0 && cf.image_size)
     add(c->p.w_patch, cf.in_chans * cf.patch_size * cf.patch_size, D, nullptr, c->b.t_patch);
@@ -715,12 +718,10 @@ void build_shadows(bsr_ctx* c, int first_block, hipStream_t s) {
     else
       add(w.w_qkv, D, 3 * D, sh.s_qkv, sh.t_qkv);
     add(w.w_proj, D, D, sh.s_proj, sh.t_proj);
-    if (c->sc.moe[l]) {   // one entry per expert matrix
-      for (int e = 0; e < cf.n_experts; ++e) {
-        const size_t o = (size_t)e * D * F;
-        add((const float*)w.w_fc1 + o, D, F, sh.s_fc1 ? sh.s_fc1 + o : nullptr, sh.t_fc1 + o);
-        add((const float*)w.w_fc2 + o, F, D, sh.s_fc2 ? sh.s_fc2 + o : nullptr, sh.t_fc2 + o);
-      }
+    if (c->sc.moe[l]) {
+      if (router_is_matrix(cf.n_experts)) add(w.w_router, D, cf.n_experts, nullptr, sh.t_router);
+      add(w.w_fc1, D, F, sh.s_fc1, sh.t_fc1, cf.n_experts);
+      add(w.w_fc2, F, D, sh.s_fc2, sh.t_fc2, cf.n_experts);
       continue;
     }
     if (c->sc.fold2[l])
@@ -732,7 +733,7 @@ void build_shadows(bsr_ctx* c, int first_block, hipStream_t s) {
   }
   opt_run(tab, false, OptArgs(), s);
   for (int l = first_block; l < cf.depth; ++l)
-    if (c->sc.moe[l]) moe_router_copy((const float*)c->p.blocks[l].w_router, D, cf.n_experts, c->b.sh[l].t_router, s);
+    if (c->sc.moe[l] && !router_is_matrix(cf.n_experts)) moe_router_copy((const float*)c->p.blocks[l].w_router, D, cf.n_experts, c->b.sh[l].t_router, s);
 }
 
 // only_trainable: a table of gradients or momenta (entries of frozen blocks are not read)
@@ -1194,8 +1195,8 @@ int32_t bsr_moe_routing_io(bsr_ctx* c, const int32_t* forced_experts, int32_t* e
   return BSR_OK;
 }
 
-// One optimiser step over the trainable tensors, a table at a time (matrices get their bf16 copies rewritten).  m1 / m2: first / second moment tables (null
-// when the rule does not use them).
+// One optimiser step over the trainable tensors, a table at a time (matrices get their bf16 copies rewritten).
+// m1 / m2: first / second moment tables (null when the rule does not use them).
 static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_params* m1, const bsr_params* m2,
                               const OptArgs& o, hipStream_t s, const char* where) {
   const bsr_config& cf = c->cfg;
@@ -1204,12 +1205,8 @@ static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_par
   auto vec = [&](void* w, const void* g, void* a, void* b2, int64_t n) {
     opt_add_vec(tab, VecEntry{(float*)w, (const float*)g, m1 ? (float*)a : nullptr, m2 ? (float*)b2 : nullptr, n}, true, o, s);
   };
-  auto mat = [&](void* w, const void* g, void* a, void* b2, size_t off, int rows, int cols, bf16* sp, bf16* tp) {
-    float* wp = (float*)w + off;
-    const float* gp = (const float*)g + off;
-    float* ap = m1 ? (float*)a + off : nullptr;
-    float* bp = m2 ? (float*)b2 + off : nullptr;
-    opt_add_mat(tab, MatEntry{wp, gp, ap, bp, sp, tp, rows, cols}, true, o, s);
+  auto mat = [&](void* w, const void* g, void* a, void* b2, int rows, int cols, bf16* sp, bf16* tp, int count = 1) {
+    opt_add_mat(tab, MatEntry{(float*)w, (const float*)g, m1 ? (float*)a : nullptr, m2 ? (float*)b2 : nullptr, sp, tp, rows, cols, count}, true, o, s);
   };
   for (int l = cf.first_trainable_block; l < cf.depth; ++l) {
     if (!c->sc.trainable[l]) continue;
@@ -1221,22 +1218,20 @@ static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_par
     vec(W.ln1_g, G.ln1_g, A.ln1_g, V.ln1_g, D); vec(W.ln1_b, G.ln1_b, A.ln1_b, V.ln1_b, D);
     vec(W.b_qkv, G.b_qkv, A.b_qkv, V.b_qkv, 3 * D); vec(W.b_proj, G.b_proj, A.b_proj, V.b_proj, D);
     vec(W.ln2_g, G.ln2_g, A.ln2_g, V.ln2_g, D); vec(W.ln2_b, G.ln2_b, A.ln2_b, V.ln2_b, D);
-    mat(W.w_qkv, G.w_qkv, A.w_qkv, V.w_qkv, 0, D, 3 * D, sh.s_qkv, sh.t_qkv);
-    mat(W.w_proj, G.w_proj, A.w_proj, V.w_proj, 0, D, D, sh.s_proj, sh.t_proj);
+    mat(W.w_qkv, G.w_qkv, A.w_qkv, V.w_qkv, D, 3 * D, sh.s_qkv, sh.t_qkv);
+    mat(W.w_proj, G.w_proj, A.w_proj, V.w_proj, D, D, sh.s_proj, sh.t_proj);
     if (c->sc.moe[l]) {   // router, E bias vectors each, E matrices each
       const int E = cf.n_experts;
-      vec(W.w_router, G.w_router, A.w_router, V.w_router, (int64_t)D * E);
+      if (router_is_matrix(E)) mat(W.w_router, G.w_router, A.w_router, V.w_router, D, E, nullptr, sh.t_router);
+      else vec(W.w_router, G.w_router, A.w_router, V.w_router, (int64_t)D * E);
       vec(W.b_fc1, G.b_fc1, A.b_fc1, V.b_fc1, (int64_t)E * F); vec(W.b_fc2, G.b_fc2, A.b_fc2, V.b_fc2, (int64_t)E * D);
-      for (int e = 0; e < E; ++e) {
-        const size_t off = (size_t)e * D * F;
-        mat(W.w_fc1, G.w_fc1, A.w_fc1, V.w_fc1, off, D, F, sh.s_fc1 + off, sh.t_fc1 + off);
-        mat(W.w_fc2, G.w_fc2, A.w_fc2, V.w_fc2, off, F, D, sh.s_fc2 + off, sh.t_fc2 + off);
-      }
+      mat(W.w_fc1, G.w_fc1, A.w_fc1, V.w_fc1, D, F, sh.s_fc1, sh.t_fc1, E);
+      mat(W.w_fc2, G.w_fc2, A.w_fc2, V.w_fc2, F, D, sh.s_fc2, sh.t_fc2, E);
       continue;
     }
     vec(W.b_fc1, G.b_fc1, A.b_fc1, V.b_fc1, F); vec(W.b_fc2, G.b_fc2, A.b_fc2, V.b_fc2, D);
-    mat(W.w_fc1, G.w_fc1, A.w_fc1, V.w_fc1, 0, D, F, sh.s_fc1, sh.t_fc1);
-    mat(W.w_fc2, G.w_fc2, A.w_fc2, V.w_fc2, 0, F, D, sh.s_fc2, sh.t_fc2);
+    mat(W.w_fc1, G.w_fc1, A.w_fc1, V.w_fc1, D, F, sh.s_fc1, sh.t_fc1);
+    mat(W.w_fc2, G.w_fc2, A.w_fc2, V.w_fc2, F, D, sh.s_fc2, sh.t_fc2);
   }
   if (cf.num_classes > 0) {
     const bsr_params& W = c->p;
@@ -1248,8 +1243,8 @@ static int32_t optimizer_step(bsr_ctx* c, const bsr_params* grads, const bsr_par
     vec(W.b_head, G.b_head, A.b_head, V.b_head, cf.num_classes);
   }
   opt_run(tab, true, o, s);
-  for (int l = cf.first_trainable_block; l < cf.depth; ++l)      // the routers were updated as vectors
-    if (c->sc.moe[l] && c->sc.trainable[l])
+  for (int l = cf.first_trainable_block; l < cf.depth; ++l)      // routers that were updated as vectors
+    if (c->sc.moe[l] && c->sc.trainable[l] && !router_is_matrix(cf.n_experts))
       moe_router_copy((const float*)c->p.blocks[l].w_router, D, cf.n_experts, c->b.sh[l].t_router, s);
   return check_hip(c, where);
 }

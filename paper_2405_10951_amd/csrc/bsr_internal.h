@@ -264,8 +264,8 @@ struct OptArgs { int kind = OPT_SGD; float lr = 0.f, mu = 0.f, wd = 0.f, b1 = 0.
 // A table of weight matrices handled by one launch: bf16 copies (straight and / or transposed) of each, optionally after an optimiser
 // update; and of small tensors without copies (biases, LayerNorm parameters, the head), which only get the update.  The table travels as a
 // kernel argument (< 4 KB): six dense blocks, or six and the head, fit.
-constexpr int OPT_MATS = 24, OPT_VECS = 56;
-struct MatEntry { float* w; const float* g; float* m; float* v2; bf16* s; bf16* t; int rows, cols; };
+constexpr int OPT_MATS = 24, OPT_VECS = 52;
+struct MatEntry { float* w; const float* g; float* m; float* v2; bf16* s; bf16* t; int rows, cols, count; };      // count: matrices behind each other
 struct VecEntry { float* w; const float* g; float* m; float* v2; int64_t n; };
 struct OptTable {
   MatEntry mat[OPT_MATS];

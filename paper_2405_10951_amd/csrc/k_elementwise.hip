@@ -256,8 +256,18 @@ __global__ __launch_bounds__(256) void opt_table_kernel(OptTable t, OptArgs o) {
     return;
   }
   const int ei = table_entry(t.mat_start, t.mats, blockIdx.x);
-  const MatEntry e = t.mat[ei];
-  const int local = blockIdx.x - t.mat_start[ei], tiles_x = (e.cols + 63) / 64;
+  MatEntry e = t.mat[ei];
+  const int tiles_x = (e.cols + 63) / 64, tiles = tiles_x * ((e.rows + 63) / 64), which = (blockIdx.x - t.mat_start[ei]) / tiles;
+  const int local = blockIdx.x - t.mat_start[ei] - which * tiles;
+  if (which > 0) {                                        // (uniform)
+    const int64_t at = (int64_t)which * e.rows * e.cols;
+    e.w += at;
+    if (e.g) e.g += at;
+    if (e.m) e.m += at;
+    if (e.v2) e.v2 += at;
+    if (e.s) e.s += at;
+    if (e.t) e.t += at;
+  }
   const int c0 = (local % tiles_x) * 64, r0 = (local / tiles_x) * 64;
   const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
 #pragma unroll
@@ -410,7 +420,7 @@ void opt_add_mat(OptTable& t, const MatEntry& e, bool update, const OptArgs& o, 
   if (t.mats == OPT_MATS) opt_run(t, update, o, s);
   t.mat[t.mats] = e;
   t.mat_start[t.mats++] = t.mat_blocks;
-  t.mat_blocks += ((e.rows + 63) / 64) * ((e.cols + 63) / 64);
+  t.mat_blocks += e.count * ((e.rows + 63) / 64) * ((e.cols + 63) / 64);
 }
 
 void opt_add_vec(OptTable& t, const VecEntry& e, bool update, const OptArgs& o, hipStream_t s) {
