@@ -211,8 +211,11 @@ def bsr_saved_activation_bytes(cfg: bsr_config, batch: int):
 
 
 def _raw_stream(device) -> int:
-    """torch's current stream of a device, without the object around it"""
+    """torch's current stream of a device, without the object around it.  Refuses, as torch's own call does, a device that has no
+    stream: the pointers that go with it would be host memory."""
     import torch
+    if device.type != "cuda":
+        raise ValueError(f"tensors on a GPU are needed, these are on {device}")
     index = device.index
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 

@@ -188,3 +188,26 @@ def test_null_context_is_rejected_before_any_gpu_work():
     assert lib.bsr_pipeline_step(None, None, None, None, None, 1, None, None, None, 0.0, 0.0, 0.0, None, None) == -1
     assert lib.bsr_adamw_step(None, None, None, None, 0.0, 0.9, 0.999, 1e-8, 0.0, 1, None) == -1
     assert lib.bsr_sgd_step(None, None, None, 0.0, 0.0, 0.0, None) == -1
+
+
+@pytest.mark.parametrize("call", [
+    lambda t, w: P.bsr_linear_forward(t, w), lambda t, w: P.bsr_linear_dgrad(t, w), lambda t, w: P.bsr_linear_wgrad(t, t),
+    lambda t, w: P.bsr_linear_wgrad_static(t, t), lambda t, w: P.bsr_linear_backward(t, t, w),
+    lambda t, w: P.bsr_ln_linear_fold(w.float(), w[0].float(), w[0].float(), w[0].float()),
+    lambda t, w: P.bsr_ln_linear_forward(t, w, w[0].float(), w[0].float()),
+    lambda t, w: P.bsr_attention_forward(t[None], 1),
+    lambda t, w: P.bsr_attention_backward(t[None], t[None, :, :64], t[None, :, :64], w.float(), 1),
+    lambda t, w: P.Context(S.get_config("c1_block_fp32"), S.make_params(S.get_config("c1_block_fp32")), 1, device="cpu")])
+def test_host_tensors_are_refused_before_the_library_sees_them(call, monkeypatch):
+    import torch
+    lib = P.load_library()
+
+    class Closed:                     # whatever would launch is not to be reached
+        def __getattr__(self, name):
+            if name in ("bsr_token_schedule", "bsr_workspace_bytes", "bsr_last_error"):
+                return getattr(lib, name)
+            return lambda *a: pytest.fail(f"{name} was called with host memory")
+
+    monkeypatch.setattr(P.binding, "_lib", Closed())
+    with pytest.raises(ValueError):
+        call(torch.zeros(8, 192, dtype=torch.bfloat16), torch.zeros(192, 192, dtype=torch.bfloat16))
