@@ -354,7 +354,7 @@ def bsr_attention_backward(qkv, out, dout, lse, heads):
 
 
 _PointerTable = C.c_uint64 * (C.sizeof(bsr_params) // 8)       # a bsr_params, which holds nothing but pointers, by position
-_position: dict = {}                                            # tensor name -> its position there
+_position: dict = {}                                            # name of one of its tensors -> the position there
 
 
 def _find_position(name: str) -> int:
@@ -365,8 +365,9 @@ def _find_position(name: str) -> int:
         if not 0 <= int(i) < MAX_BLOCKS:
             raise IndexError(f"block {i}: at most {MAX_BLOCKS}")
         field, at = bsr_block_params, bsr_params.blocks.offset + int(i) * C.sizeof(bsr_block_params)
-    names = [f[0] for f in field._fields_]
-    return (at + getattr(field, name).offset) // 8 if name in names and name != "blocks" else -1
+    if field is bsr_params and name == "blocks":
+        raise TypeError("blocks: one tensor does not stand for all blocks")
+    return (at + getattr(field, name).offset) // 8 if name in [f[0] for f in field._fields_] else -1
 
 
 def _params_struct(tensors: dict):
@@ -378,9 +379,11 @@ def _params_struct(tensors: dict):
             continue
         at = _position.get(name)
         if at is None:
-            at = _position[name] = _find_position(name)
-        if at >= 0:
-            p[at] = t.data_ptr()
+            at = _find_position(name)
+            if at < 0:
+                continue
+            _position[name] = at          # (only names of the library's own: a bounded table)
+        p[at] = t.data_ptr()
     return p
 
 

@@ -211,3 +211,20 @@ def test_host_tensors_are_refused_before_the_library_sees_them(call, monkeypatch
     monkeypatch.setattr(P.binding, "_lib", Closed())
     with pytest.raises(ValueError):
         call(torch.zeros(8, 192, dtype=torch.bfloat16), torch.zeros(192, 192, dtype=torch.bfloat16))
+
+
+def test_tensor_names_are_taken_and_refused_as_the_struct_takes_them():
+    import torch
+    from paper_2405_10951_amd import binding
+    t = torch.zeros(1)
+    table = binding._params_struct({"lnf_g": t, "blocks.15.w_router": t, "blocks.0.b_qkv": None, "ema": t, "blocks.0.ema": t})
+    p = binding.bsr_params.from_buffer(table)
+    assert p.lnf_g == p.blocks[15].w_router == t.data_ptr()
+    assert sum(v != 0 for v in table) == 2
+    known = len(binding._position)
+    for i in range(100):                              # names that are none of the library's leave nothing behind
+        binding._params_struct({f"ema.{i}": t})
+    assert len(binding._position) == known
+    for name, error in (("blocks", TypeError), ("blocks.16.w_qkv", IndexError), ("blocks.w_qkv", ValueError)):
+        with pytest.raises(error):
+            binding._params_struct({name: t})
