@@ -201,7 +201,9 @@ int32_t bsr_refresh_weights(bsr_ctx* ctx, void* stream);
  *   scores_out   device fp32, may be NULL: importance scores of the prefix's drops, concatenated,
  *                drop i holding [B,n_i]
  *   forced_idx   device int32, may be NULL: use these indices (layout of kept_idx_out) instead of
- *                ranking — for parity tests against a reference that took the same decisions
+ *                ranking — for parity tests against a reference that took the same decisions.  Every index
+ *                must lie in 0..n_i-1 (device memory: it cannot be checked here), and a list must be ascending
+ *                and distinct, as kept_idx_out is, for the gradients to be those of the step
  * Errors: INVALID_ARG (NULL input/x_out, B < 1 or > max_batch), HIP.
  */
 int32_t bsr_forward_frozen(bsr_ctx* ctx, const void* input, int32_t B, void* x_out,

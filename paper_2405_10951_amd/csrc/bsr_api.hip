@@ -1143,9 +1143,11 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* c, const void* x_in, const int32_t* la
       else gemm(c, d2, s);
     }
     // adjoint of the token drop: dropped tokens receive nothing from the FFN side.  The LayerNorm's gradient leaves for the places of the
-    // kept ones; where dropped tokens were fused, or for rows it cannot do that with, one more launch does
+    // kept ones, with ranked tokens: it takes the list to be ascending, as the selection's is, and a caller's list may be in any order.
+    // For that one, where dropped tokens were fused, and for rows it cannot do that with, one more launch looks every row up
     LnScatter kept;
-    if (di >= 0 && !sc.fused[di] && layernorm_bwd_scatters(D, f32)) { kept.idx = idx_used[l]; kept.k = sc.keep_k[di]; kept.T = Ta; }
+    const bool ranked = di >= 0 && idx_used[l] == v.idx;
+    if (ranked && !sc.fused[di] && layernorm_bwd_scatters(D, f32)) { kept.idx = idx_used[l]; kept.k = sc.keep_k[di]; kept.T = Ta; }
     if (tr) {
       float* slot = b.ln_partial ? b.ln_partial + (size_t)(ln_slot++) * ln_deferred_partial_floats(D) : nullptr;
       layernorm_bwd(b.dh, v.xmid, v.mean2, v.rstd2, (const float*)w.ln2_g, dx, M2, D, f32, dx_other, b.partial, slot,

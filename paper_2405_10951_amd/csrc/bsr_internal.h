@@ -144,8 +144,9 @@ void layernorm_fwd(const void* x, int64_t M, int D, const float* gamma, const fl
                    bool f32, void* y, float* mean, float* rstd, hipStream_t s);
 // res may be null, dx null to skip it.  res_period 0: a residual row per row; P > 0: rows 0, P, 2P, ... have one each
 // (the residual then has M / P rows).
-// idx: row m of dx is that of a token behind a drop (k + 1 rows per image, [class; kept], idx [B, k] ascending) and goes to its place among
-// the T tokens before it; the dropped tokens' rows are set to zero
+// idx: row m of dx is that of a token behind a drop (k + 1 rows per image, [class; kept], idx [B, k] ascending, distinct
+// and below T - 1: nothing checks it, so lists of the selection only) and goes to its place among the T tokens before it; the dropped tokens' rows
+// are set to zero
 struct LnScatter { const int32_t* idx = nullptr; int k = 0, T = 0; };
 template <typename T> struct LnRows { const T* x; const T* res; T* dx; int res_period; LnScatter sc; };
 // dx = res + LN'(dy)

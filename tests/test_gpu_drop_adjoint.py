@@ -58,3 +58,24 @@ def test_gradient_goes_to_the_kept_places(hip, orc64, dtype, tol, dim, depth, ke
     ref = orc64.step(cfg, p, x, y, forced_idx=[np.stack(wanted)])
     for n, g in ref["grads"].items():
         assert hip.rel(got["grads"][n], g) < tol, n
+
+
+@pytest.mark.parametrize("dtype,dim,depth", [("fp32", 64, 3), ("bf16", 768, 1)])
+def test_lists_of_the_caller(hip, dtype, dim, depth):
+    """The ranked list handed back gives the bits of the ranking (its gradient takes another kernel to the same places), and with a list in
+    any order, or with a token twice, every row of the gradient is still this call's: nothing of what the buffers held before."""
+    kept = [1, 3, 5, 7, 9, 11, 13, 15]
+    cfg, wanted = config(dtype, dim, depth, len(kept)), lists_of(kept)
+    p, x, y = ranked_inputs(cfg, wanted)
+    free = hip.run_hip_step(cfg, p, x, y)
+    ctx = free["ctx"]
+    back = hip.run_hip_step(cfg, p, x, y, forced_idx=[np.stack(wanted)], ctx=ctx)
+    assert all(np.array_equal(free["grads"][n], g) for n, g in back["grads"].items())
+    rng = np.random.default_rng(1)
+    for lists in (np.stack([v[::-1] for v in wanted]), np.stack([rng.permutation(v) for v in wanted]), rng.integers(0, N, (3, len(kept)))):
+        seen = []
+        for left in (0.0, 1e4):
+            # other gradients left in the same workspace
+            hip.run_hip_step(cfg, p, x + np.float32(left) * np.roll(x, 1, axis=1), y, ctx=ctx)
+            seen.append(hip.run_hip_step(cfg, p, x, y, forced_idx=[lists], ctx=ctx)["grads"])
+        assert all(np.isfinite(g).all() and np.array_equal(g, seen[1][n]) for n, g in seen[0].items())
