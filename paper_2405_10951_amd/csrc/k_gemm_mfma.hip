@@ -1509,8 +1509,8 @@ struct TnSplit {
 // floats of the split-K workspace that one launch may fill
 size_t tn_room(size_t ws_floats, bool chained) { return chained ? (ws_floats / 2) & ~(size_t)3 : ws_floats; }
 
-// nt: the input gradient of the same launch, or null; us: the time the model gives it
-TnSplit tn_split(const GemmDesc* nt, const GemmDesc& g, size_t room, float* us_out = nullptr) {
+// nt: the input gradient of the same launch, or null
+TnSplit tn_split(const GemmDesc* nt, const GemmDesc& g, size_t room) {
   TnSplit best;
   const int nk = (g.K + BK - 1) / BK, per = tn_kt_per(g, room), parts = (nk + per - 1) / per;
   float least = 0.f;
@@ -1531,7 +1531,6 @@ TnSplit tn_split(const GemmDesc* nt, const GemmDesc& g, size_t room, float* us_o
       }
     }
   }
-  if (us_out) *us_out = least;
   return best;
 }
 
@@ -1726,7 +1725,6 @@ bool gemm_nt_tile_is_free(const GemmDesc& g) { return is_nt(g) && !g.grp_off; }
 // A product goes there when it leads clearly over the tiled kernels as they run in a step, where every launch follows another
 // kernel: near-ties went to the tiled ones there.  (A line without that lead, between the models fitted to chains of equal launches, came
 // to 1.000x over 20 steps, 0.984 .. 1.019, and moved every gradient behind a product that changed sides by up to 1 %.)
-constexpr float APART_LEAD = 1.03f;          // (the joint model leaves out what the GELU' launches lose to each other at many rows)
 constexpr float FEW_LEAD = 0.8f, TILED_LAUNCH_US = 2.6f;      // the latter: the launch that a weight gradient carried along saves
 static int few_rows_shape(const GemmDesc& g, bool carries_wgrad) {
   float few_us = 0.f, tiled_us = 0.f;
@@ -1756,25 +1754,25 @@ static int joint_tile(int tile, const TnSplit& pair) {
 static int nt_tile(const GemmDesc& g, int tile) {
   return !tile || is_retired(tile) || (ntd_stages(tile) && !is_ntd(g)) ? nt_pick(g) : tile;
 }
-// Whether a layer's two gradients, with no shape asked for, go out one after the other: an input gradient with GELU' and many tiles.  A joint
+// Whether a layer's two gradients, with no shape asked for, go out one after the other: an input gradient with GELU' and many rows.  A joint
 // launch has one workgroup a CU, so nothing covers a tile's epilogue, and a GELU' doubles that; on its own such a product takes larger tiles, or two
-// workgroups a CU.  The two models' times put the line at about 16000 rows of 768: steps with all 12 blocks trained, joint -> apart, 128 images (25216
-// rows) 18020 -> 17845 us, 100 images 13446 -> 13305, 64 images (12608 rows) 10237 -> 10268, which stays joint.
-static bool apart(const GemmDesc& nt, const GemmDesc& tn, size_t room) {
-  if (nt.act != ACT_GELU_BWD) return false;
-  float joint_us = 0.f, tn_us = 0.f, nt_us = 0.f;
-  tn_split(&nt, tn, room, &joint_us);
-  tn_split(nullptr, tn, room, &tn_us);
-  model_pick(kNtModel, nt, true, &nt_us);
-  return nt_us + tn_us + TILED_LAUNCH_US < APART_LEAD * joint_us;
-}
+// workgroups a CU, and pays a launch and a second drain of the CUs for it.  Trained part of steps with all 12 blocks trained, joint -> apart, both forced:
+//   3072 x 768:  3940 .. 9456 rows +0.5 .. +2.2 %, 10244 .. 13002 -2.9 .. +0.3 % (-1.2 on average), 13396 .. 25216 -1.9 .. +0.1 % (-1.0)
+//   4096 x 1024: 6304 .. 19700 -0.8 .. +0.3 %
+//   1536 x 384:  6304, 7880 +2.1, +1.0 %, 9456 .. 13002 -1.8 .. +1.2 % (mixed), 13396 .. 25216 -2.9 .. -1.9 %
+//   2048 x 512:  9456 .. 12608 +0.2 .. +1.0 %, 14184 .. 25216 -1.7 .. +0.6 % (-0.8)
+//   768 x 768, 1536 x 768, 3072 x 384: 9456, 12608 -1.5 .. +1.4 %, 14184 .. 25216 -3.0 .. +0.1 % (-1.3)
+//   384 x 384, 768 x 192: 9456 .. 39400 +0.2 .. +3.7 %: too little to multiply for a second launch
+// So the line lies where nothing beyond it loses more than the runs differ by (0.6 %).
+// (The two models' times do not draw this line: both leave out what launches lose to each other, and their rounds of tiles make it jump.)
+constexpr int APART_ROWS = 13312, APART_WEIGHTS = 512 * 1024;
+static bool apart(const GemmDesc& nt) { return nt.act == ACT_GELU_BWD && nt.M >= APART_ROWS && (int64_t)nt.N * nt.K >= APART_WEIGHTS; }
 int gemm_nt_runs_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained, int tile) {
   const int few = few_rows_shape(g, wgrad != nullptr);
   if (few >= 0) return FEW_ROWS_ID + 32000 * kFewShapes[few].mi + 32 * kFewShapes[few].ni;
   if (wgrad && can_pair(g, *wgrad)) {
-    const size_t room = tn_room(splitk_ws_floats, chained);
-    const int i = joint_tile(tile, tn_split(&g, *wgrad, room));
-    if (i >= 0 && (tile || !apart(g, *wgrad, room))) return 7000000 + 1000 * kPairNt[i].bm + kPairNt[i].bn;
+    const int i = joint_tile(tile, tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained)));
+    if (i >= 0 && (tile || !apart(g))) return 7000000 + 1000 * kPairNt[i].bm + kPairNt[i].bn;
   }
   return nt_tile(g, tile);
 }
@@ -1841,7 +1839,7 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
     return;
   }
   const size_t room = tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr);
-  if (can_pair(nt, tn) && (tile || !apart(nt, tn, room))) {
+  if (can_pair(nt, tn) && (tile || !apart(nt))) {
     const TnSplit split = tn_split(&nt, tn, room);
     switch (joint_tile(tile, split)) {
       case 0: launch_pair<0>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
