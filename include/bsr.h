@@ -248,7 +248,8 @@ int32_t bsr_train_blocks_fwd_bwd(bsr_ctx* ctx, const void* x_in, const int32_t* 
  * Measured tile choice (set-up, not part of a step).  The tiled matrix-multiply kernel behind the
  * linear layers comes in several block-tile shapes; which one is fastest for a launch depends on how
  * its tile count divides over the 256 compute units and on what surrounds it in the step.  This call
- * runs bsr_forward_frozen + bsr_train_blocks_fwd_bwd on the given batch once per shape (twice over),
+ * runs bsr_forward_frozen + bsr_train_blocks_fwd_bwd on the given batch once per shape (twice over; and with
+ * the model's choice where that is two launches for the gradients of a layer),
  * times every such launch with HIP events in its place in the step, and from then on gives each
  * launch of a batch of the same size B its fastest shape; other batch sizes keep the built-in cost
  * model.  Every shape adds up an output element in the same order, so results do not change by a
@@ -287,8 +288,10 @@ int32_t bsr_autotune_overlapped(bsr_ctx* ctx, const void* input, const int32_t* 
  * only).  part 0: the launches of bsr_forward_frozen in launch order, part 1: those of bsr_train_blocks_fwd_bwd
  * (a backward launch carries the input gradient named here and, in the same launch, the weight gradient of its layer).
  *   rows, out, in  the product: rows x in times in x out      tile  id of the shape that runs (see bsr_gemm_tile_shapes; ids that
- *                  name the same kernel for a launch are one choice there), or
- *                  9000000 + 1000 rows + columns of a tile of the kernel for products of few rows
+ *                  name the same kernel for a launch are one choice there),
+ *                  9000000 + 1000 rows + columns of a tile of the kernel for products of few rows, or
+ *                  10000000 + the id of a shape: the input gradient in that shape and its layer's weight gradient behind it in a
+ *                  launch of its own, where the id alone names the joint launch
  *   microseconds   what bsr_autotune measured for that shape at that launch (0 after bsr_autotune_overlapped,
  *                  which times whole passes)
  * Returns the number of launches of that part (0 without a choice or with bad arguments); writes at most max.

@@ -1379,8 +1379,11 @@ static int32_t autotune_overlapped(bsr_ctx* c, const void* input, const int32_t*
   return check_hip(c, "bsr_autotune_overlapped");
 }
 
+static bool is_few_rows(int id) { return id >= FEW_ROWS_ID && id < APART_ID; }
+
 // Measured tile choice, launch by launch: the two calls follow each other on `stream`, once per shape (twice
-// over), every NT launch bracketed by events in its place in the step.
+// over), every NT launch bracketed by events in its place in the step; and once more with the model's choice where that is a layer's
+// gradients in two launches, which no shape names.
 static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, int32_t B, void* x_frozen,
                         float* loss_out, const bsr_params* grads, int32_t* launches_out, int32_t* changed_out,
                         void* stream) {
@@ -1389,11 +1392,14 @@ static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, in
   t.batch = 0;
   t.pick[0].clear();
   t.pick[1].clear();
-  const int n = gemm_nt_tile_count();
+  const int shapes = gemm_nt_tile_count();
+  int n = shapes;                                         // candidates: the shapes, and as number `shapes` the model's choice
   constexpr int ROUNDS = 2;
   int rc = BSR_OK;
-  // pass -1 is untimed (first-use set-up of the kernels); then every shape, ROUNDS times
+  // pass -1 is untimed (first-use set-up of the kernels); then every candidate, ROUNDS times
   for (int pass = -1; pass < ROUNDS * n && rc == BSR_OK; ++pass) {
+    if (pass == 1)
+      for (const TuneRec& r : t.recs) n = std::max(n, shapes + (r.model >= APART_ID));
     t.cand = pass < 0 ? -1 : pass % n;
     rc = bsr_forward_frozen(c, input, B, x_frozen, nullptr, nullptr, nullptr, stream);
     if (rc == BSR_OK) rc = bsr_train_blocks_fwd_bwd(c, x_frozen, labels, B, loss_out, nullptr, nullptr, grads, nullptr, nullptr, nullptr, stream);
@@ -1411,7 +1417,8 @@ static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, in
         if (r.kind != k) continue;
         // a shape that stands in for another here (several ids name one joint kernel, some shapes cannot take the product) is timed
         // under that one's own id and not again: more draws would favour it
-        if (r.ran < FEW_ROWS_ID && r.ran != gemm_nt_tile_id(r.cand)) continue;
+        const bool own = r.cand == shapes ? r.ran >= APART_ID : is_few_rows(r.ran) || r.ran == gemm_nt_tile_id(r.cand);
+        if (!own) continue;
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, r.start, r.stop) != hipSuccess) continue;
         float& b = best[r.site * n + r.cand];
@@ -1424,7 +1431,7 @@ static int32_t autotune(bsr_ctx* c, const void* input, const int32_t* labels, in
         for (int j = 0; j < n; ++j)
           if (best[i * n + j] >= 0.f && (arg < 0 || best[i * n + j] < best[i * n + arg])) arg = j;
         const int model = t.pick[k][i].model;           // (a product of few rows has run its own kernel every time)
-        t.pick[k][i].tile = arg < 0 ? 0 : model >= FEW_ROWS_ID ? model : gemm_nt_tile_id(arg);
+        t.pick[k][i].tile = arg < 0 ? 0 : is_few_rows(model) || arg == shapes ? model : gemm_nt_tile_id(arg);
         t.pick[k][i].us = arg < 0 ? 0.f : best[i * n + arg] * 1e3f;
         ++launches;
       }

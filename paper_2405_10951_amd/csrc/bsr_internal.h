@@ -106,7 +106,7 @@ struct TnChain {
   TnReduce pending;                 // pending.splits > 0: a reduction is waiting
   int slot = 0;                     // workspace half the next split launch writes
 };
-// tile: one of gemm_nt_tile_id() for the NT kernel (ignored by the others), 0 = the built-in model chooses
+// tile: one of gemm_nt_tile_id() or what gemm_nt_runs_tile() gave, for the NT kernel (ignored by the others), 0 = the built-in model chooses
 void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile = 0,
                TnChain* chain = nullptr);
 void gemm_tn_flush(TnChain* chain, hipStream_t s);
@@ -117,8 +117,9 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
 // the block-tile shapes the NT kernel is instantiated for, and whether a GEMM is free to take any of them
 int gemm_nt_tile_count();
 constexpr int FEW_ROWS_ID = 9000000;           // + 1000 rows + columns: a tile of the kernel for products of few rows
+constexpr int APART_ID = 10000000;             // + id of a shape that also names a layer's joint launch: its two launches, the input gradient in that shape
 // id of the shape that really runs when `tile` is asked for (0: without a measured choice; wgrad: the weight gradient that goes out
-// with g, or null; the workspace as in the call); from FEW_ROWS_ID on: whatever is asked for
+// with g, or null; the workspace as in the call).  Asked for in turn, it runs the same.  FEW_ROWS_ID + ..: whatever is asked for
 int gemm_nt_runs_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained, int tile);
 int gemm_nt_tile_id(int i);
 // an id that the entry points take: 0, a shape above, or one that was a shape once (the model chooses in its place)

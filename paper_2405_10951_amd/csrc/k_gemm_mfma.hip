@@ -1752,6 +1752,7 @@ static int joint_tile(int tile, const TnSplit& pair) {
 // Shape of a product on its own that is asked to take a shape: the model's for 0, for an id that was a shape once and for a shape that
 // cannot take the product.
 static int nt_tile(const GemmDesc& g, int tile) {
+  if (tile >= APART_ID) tile -= APART_ID;
   return !tile || is_retired(tile) || (ntd_stages(tile) && !is_ntd(g)) ? nt_pick(g) : tile;
 }
 // Whether a layer's two gradients, with no shape asked for, go out one after the other: an input gradient with GELU' and many rows.  A joint
@@ -1767,14 +1768,17 @@ static int nt_tile(const GemmDesc& g, int tile) {
 // (The two models' times do not draw this line: both leave out what launches lose to each other, and their rounds of tiles make it jump.)
 constexpr int APART_ROWS = 13312, APART_WEIGHTS = 512 * 1024;
 static bool apart(const GemmDesc& nt) { return nt.act == ACT_GELU_BWD && nt.M >= APART_ROWS && (int64_t)nt.N * nt.K >= APART_WEIGHTS; }
+// whether they do when `tile` is asked for
+static bool goes_apart(const GemmDesc& nt, int tile) { return tile >= APART_ID || ((!tile || is_retired(tile)) && apart(nt)); }
 int gemm_nt_runs_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained, int tile) {
   const int few = few_rows_shape(g, wgrad != nullptr);
   if (few >= 0) return FEW_ROWS_ID + 32000 * kFewShapes[few].mi + 32 * kFewShapes[few].ni;
-  if (wgrad && can_pair(g, *wgrad)) {
-    const int i = joint_tile(tile, tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained)));
-    if (i >= 0 && (tile || !apart(g))) return 7000000 + 1000 * kPairNt[i].bm + kPairNt[i].bn;
-  }
-  return nt_tile(g, tile);
+  const int alone = nt_tile(g, tile);
+  if (!wgrad || !can_pair(g, *wgrad)) return alone;
+  const TnSplit split = tn_split(&g, *wgrad, tn_room(splitk_ws_floats, chained));
+  if (goes_apart(g, tile)) return joint_tile(alone, split) < 0 ? alone : APART_ID + alone;
+  const int i = joint_tile(tile, split);
+  return i < 0 ? alone : 7000000 + 1000 * kPairNt[i].bm + kPairNt[i].bn;
 }
 
 TnReduce gemm_tn_take(TnChain* chain) {
@@ -1839,7 +1843,7 @@ void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, si
     return;
   }
   const size_t room = tn_room(splitk_ws ? splitk_ws_floats : 0, chain != nullptr);
-  if (can_pair(nt, tn) && (tile || !apart(nt))) {
+  if (can_pair(nt, tn) && !goes_apart(nt, tile)) {
     const TnSplit split = tn_split(&nt, tn, room);
     switch (joint_tile(tile, split)) {
       case 0: launch_pair<0>(nt, tn, split, splitk_ws, splitk_ws_floats, s, chain); return;
