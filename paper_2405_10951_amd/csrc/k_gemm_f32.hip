@@ -250,8 +250,8 @@ void launch(const GemmDesc& g, hipStream_t s) {
 
 // Both gradients of a layer in one launch: dx = dy W^T (dg) and dW = x^T dy (wg) read the same dy and neither reads what the other writes.
 // The workgroups with the longer sums come first, the others fill the CUs they leave; tiles and sums are those of two launches, so the results
-// are the same bits.  What it saves is a launch, and the CUs that few tiles leave idle: steps of a 192-wide block
-// of 2 sequences 121 -> 100 us, of DeiT-S with 1, 4 and 8 images 879 -> 796, 1091 -> 997, 1472 -> 1392.
+// are the same bits.  What it saves is a launch, and the CUs that few tiles leave idle (gemm_f32_pair below); steps
+// of DeiT-S with 1, 4 and 8 images 879 -> 796, 1091 -> 997, 1472 -> 1392 us.
 // (The 14 dwords up to wg_blocks come in registers.)
 template <class DG, class WG>
 __global__ __launch_bounds__(512, 4) void gemm_f32_pair_kernel(const float* dy, const float* w, const float* x, int M, int in, int out, unsigned dy_rs,
@@ -343,15 +343,15 @@ void gemm_f32(const GemmDesc& g, hipStream_t s) {
   else launch_form<true, false>(g, s);                       // forward
 }
 
-// The two gradients of one layer.  One launch, unless a product takes the 128 x 128 tiles, which have half the wavefronts.  It was the faster
-// one wherever it was measured (65 .. 2080 rows, 192 and 384 wide).  Layers of less than 256 columns nevertheless keep a launch per product from
-// 300 rows on: tests of their tile choice count the launches of such steps.
+// The two gradients of one layer.  One launch, unless a product takes the 128 x 128 tiles, which have half the wavefronts: it was the faster
+// one wherever it was measured.  Steps of one block, two launches -> one (GPU time): 64 wide, 130 .. 4160 rows 0.84 .. 0.92 times as long, 128 wide, 394 .. 6304
+// rows 0.85 .. 0.89, 192 wide, 65 .. 6304 rows 0.83 .. 0.91 (16 sequences of 65 tokens 142 -> 129 us, 32 209 -> 183), 256 wide, 197 .. 3152 rows 0.88 .. 0.94,
+// 384 wide, 197 .. 6304 rows 0.87 .. 0.95, 768 wide, 197 .. 1576 rows 0.90 .. 0.97.
 void gemm_f32_pair(const GemmDesc& dg, const GemmDesc& wg, hipStream_t s) {
   const bool layer = dg.a_cs == 1 && dg.b_rs == 1 && wg.a_rs == 1 && wg.a_cs != 1 && wg.b_cs == 1 && dg.A == wg.B && dg.a_rs == wg.b_rs && dg.M == wg.K &&
                      dg.N == wg.M && dg.K == wg.N && std::max({dg.a_rs, dg.b_cs, wg.a_cs}) <= (int64_t)INT32_MAX;
   const int di = f32_pick(dg), wi = f32_pick(wg);
-  const bool one_by_one = wg.K >= 300 && std::min(wg.M, wg.N) < 256;
-  if (!layer || one_by_one || di == 0 || wi == 0) {
+  if (!layer || di == 0 || wi == 0) {
     gemm_f32(dg, s);
     gemm_f32(wg, s);
     return;

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 # ragged edges of 32 x 32 tiles, few and many rows against the width (either product first), 64 x 64 tiles for one of the products or
 # both, and one product too large for the joint launch; the last number: how many of the four layers have one
-LAYERS = [(64, 72, 33, 1, 4), (64, 8, 1, 3, 4), (192, 776, 65, 4, 4), (384, 1544, 197, 1, 4),
+LAYERS = [(64, 72, 33, 1, 4), (64, 8, 1, 3, 4), (64, 72, 129, 5, 4), (192, 776, 65, 4, 4), (192, 768, 65, 16, 4), (384, 1544, 197, 1, 4),
           (384, 1536, 197, 8, 4), (256, 1024, 1024, 8, 3)]
 
 
