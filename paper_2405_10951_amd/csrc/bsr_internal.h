@@ -71,8 +71,8 @@ bool gemm_mfma_supported(const GemmDesc& g);
 // splitk_ws: fp32 scratch for the partial sums of split-K weight gradients (may be null: no split)
 // A weight gradient whose tokens several workgroups share leaves fp32 partials that one more pass has to add up.  With a chain, that
 // pass does not get a launch of its own: it rides on the NEXT weight-gradient launch
-// (which works on the other half of the workspace), and gemm_tn_flush runs the last one.  The sums and
-// their order are the same either way.
+// (which works on the other half of the workspace), and the last one goes out with the sums of the LayerNorms (gemm_tn_take,
+// ln_deferred_finish).  The sums and their order are the same either way.
 struct TnReduce {
   const float* partial = nullptr;   // [splits][n]
   int64_t n = 0;
@@ -109,7 +109,6 @@ struct TnChain {
 // tile: one of gemm_nt_tile_id() or what gemm_nt_runs_tile() gave, for the NT kernel (ignored by the others), 0 = the built-in model chooses
 void gemm_mfma(const GemmDesc& g, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s, int tile = 0,
                TnChain* chain = nullptr);
-void gemm_tn_flush(TnChain* chain, hipStream_t s);
 TnReduce gemm_tn_take(TnChain* chain);          // for a caller that adds the waiting partials up itself (splits 0: none wait)
 // input gradient (NT) + weight gradient (TN) of one layer, in one launch when the NT tile shape has that form
 void gemm_mfma_pair(const GemmDesc& nt, const GemmDesc& tn, float* splitk_ws, size_t splitk_ws_floats, hipStream_t s,

@@ -97,8 +97,9 @@ __global__ void scatter_fused_kernel(const T* __restrict__ dy, const int32_t* __
   }
 }
 
-// Adjoint of the gather: every row of dx is written exactly once (kept rows copied, dropped rows
-// zero), found by a binary search of the ascending kept list — no atomics, no separate memset.
+// Adjoint of the gather where the LayerNorm backward does not place the rows itself (lists of the caller, rows of more than ROW_MAX): every row of
+// dx is written exactly once whatever the list holds (kept rows copied, dropped rows zero), found by a binary search of the kept
+// list — no atomics, no separate memset.
 __global__ void scatter_rows_kernel(const uint4* __restrict__ dy, const int32_t* __restrict__ idx,
                                     int T_, int k, int row_vecs, uint4* __restrict__ dx) {
   const int t = blockIdx.x, b = blockIdx.y;

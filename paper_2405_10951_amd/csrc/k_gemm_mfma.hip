@@ -1786,10 +1786,6 @@ TnReduce gemm_tn_take(TnChain* chain) {
   chain->pending = TnReduce();
   return r;
 }
-void gemm_tn_flush(TnChain* chain, hipStream_t s) {
-  if (!chain || chain->pending.splits <= 0) return;
-  launch_reduce(gemm_tn_take(chain), s);
-}
 
 // The tiled kernels, in the shape asked for or, for 0 and for a shape that cannot take the product, the model's.
 static void nt_tiled(const GemmDesc& g, hipStream_t s, int tile) {
