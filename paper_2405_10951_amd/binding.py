@@ -210,18 +210,22 @@ def bsr_saved_activation_bytes(cfg: bsr_config, batch: int):
     return [as_dict(per[l]) for l in range(cfg.depth)], as_dict(tot)
 
 
-def _raw_stream(device) -> int:
-    """torch's current stream of a device, without the object around it.  Refuses, as torch's own call does, a device that has no
-    stream: the pointers that go with it would be host memory."""
-    import torch
+def _gpu_index(device):
+    """Index of a GPU as torch gives it (None: the current one).  Refuses, as torch's own look-up of a stream does, a device that has
+    none: the pointers that go with it would be host memory."""
     if device.type != "cuda":
         raise ValueError(f"tensors on a GPU are needed, these are on {device}")
-    index = device.index
+    return device.index
+
+
+def _raw_stream(index) -> int:
+    """torch's current stream of a GPU, without the object around it"""
+    import torch
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
 
 def _cur_stream(t):
-    return _raw_stream(t.device)
+    return _raw_stream(_gpu_index(t.device))
 
 
 def bsr_linear_forward(x, w_t, bias=None, act=0, u_out=None, res=None, y=None, tile=0):
@@ -400,6 +404,7 @@ class Context:
         self.torch = torch
         self.lib = load_library()
         self.device = torch.device(device)
+        self._gpu = _gpu_index(self.device)
         self.c = make_config(cfg, max_batch, keep_k)
         self.act_dtype = torch.float32 if self.c.dtype == BSR_FP32 else torch.bfloat16
         self.keep_k, self.tokens_attn, self.tokens_mlp = bsr_token_schedule(self.c)
@@ -424,7 +429,7 @@ class Context:
                                  ((int(n.split(".")[1]) in tb) if tb else int(n.split(".")[1]) >= ft))]
 
     def _stream(self):
-        return _raw_stream(self.device)
+        return _raw_stream(self._gpu)
 
     def _chk(self, rc):
         if rc:
