@@ -251,7 +251,7 @@ void launch(const GemmDesc& g, hipStream_t s) {
 // Both gradients of a layer in one launch: dx = dy W^T (dg) and dW = x^T dy (wg) read the same dy and neither reads what the other writes.
 // The workgroups with the longer sums come first, the others fill the CUs they leave; tiles and sums are those of two launches, so the results
 // are the same bits.  What it saves is a launch, and the CUs that few tiles leave idle (gemm_f32_pair below); steps
-// of DeiT-S with 1, 4 and 8 images 879 -> 796, 1091 -> 997, 1472 -> 1392 us.
+// of DeiT-S with 1, 4 and 8 images 850 -> 790, 1069 -> 996, 1445 -> 1402 us, of a 192-wide block with 2 sequences 110 -> 94.
 // (The 14 dwords up to wg_blocks come in registers.)
 template <class DG, class WG>
 __global__ __launch_bounds__(512, 4) void gemm_f32_pair_kernel(const float* dy, const float* w, const float* x, int M, int in, int out, unsigned dy_rs,

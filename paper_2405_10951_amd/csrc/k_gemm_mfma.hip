@@ -822,8 +822,8 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
 }
 
 // What a product's first loads need, as plain kernel arguments in front: the first 14 dwords come in registers with the wavefront
-// (-amdgpu-kernarg-preload-count), a description passed by value is a trip to memory first.  One image through the ViT-B encoder (65
-// launches) 438 -> 411 us, steps of 32 images DeiT-S 1246 -> 1202, ViT-B 2261 -> 2218.
+// (-amdgpu-kernarg-preload-count), a description passed by value is a trip to memory first.  The present kernels without and
+// with it: one image through the ViT-B encoder (65 launches) 431 -> 410 us, steps of 32 images DeiT-S 1201 -> 1170, ViT-B 2216 -> 2192.
 #define BSR_HOT_PARAMS const void *hA, const void *hB, int hM, int hN, int hK, unsigned ha_rs, unsigned hb_cs, int tiles
 #define BSR_HOT_ARGS(g, tiles) (g).A, (g).B, (g).M, (g).N, (g).K, (unsigned)(g).a_rs, (unsigned)(g).b_cs, tiles
 #define BSR_HOT_INTO(g) ((g).A = hA, (g).B = hB, (g).M = hM, (g).N = hN, (g).K = hK, (g).a_rs = ha_rs, (g).b_cs = hb_cs)

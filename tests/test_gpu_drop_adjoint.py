@@ -63,7 +63,7 @@ def test_gradient_goes_to_the_kept_places(hip, orc64, dtype, tol, dim, depth, ke
 @pytest.mark.parametrize("dtype,dim,depth", [("fp32", 64, 3), ("bf16", 768, 1)])
 def test_lists_of_the_caller(hip, dtype, dim, depth):
     """The ranked list handed back gives the bits of the ranking (its gradient takes another kernel to the same places), and with a list in
-    any order, or with a token twice, every row of the gradient is still this call's: nothing of what the buffers held before."""
+    any order, or with a token twice, every row of the gradient is written once: the same bits every time, whatever the buffers held before."""
     kept = [1, 3, 5, 7, 9, 11, 13, 15]
     cfg, wanted = config(dtype, dim, depth, len(kept)), lists_of(kept)
     p, x, y = ranked_inputs(cfg, wanted)
