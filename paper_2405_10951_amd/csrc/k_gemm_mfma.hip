@@ -1758,16 +1758,18 @@ static int nt_tile(const GemmDesc& g, int tile) {
 // Whether a layer's two gradients, with no shape asked for, go out one after the other: an input gradient with GELU' and many rows.  A joint
 // launch has one workgroup a CU, so nothing covers a tile's epilogue, and a GELU' doubles that; on its own such a product takes larger tiles, or two
 // workgroups a CU, and pays a launch and a second drain of the CUs for it.  Trained part of steps with all 12 blocks trained, joint -> apart, both forced:
-//   3072 x 768:  3940 .. 9456 rows +0.5 .. +2.2 %, 10244 .. 13002 -2.9 .. +0.3 % (-1.2 on average), 13396 .. 25216 -1.9 .. +0.1 % (-1.0)
+//   3072 x 768:  3940 .. 9456 rows +0.5 .. +2.2 %, 10244 .. 13002 -2.9 .. +0.6 % (-1.2 on average), 13396 .. 25216 -1.9 .. +0.1 % (-1.0)
 //   4096 x 1024: 6304 .. 19700 -0.8 .. +0.3 %
 //   1536 x 384:  6304, 7880 +2.1, +1.0 %, 9456 .. 13002 -1.8 .. +1.2 % (mixed), 13396 .. 25216 -2.9 .. -1.9 %
 //   2048 x 512:  9456 .. 12608 +0.2 .. +1.0 %, 14184 .. 25216 -1.7 .. +0.6 % (-0.8)
 //   768 x 768, 1536 x 768, 3072 x 384: 9456, 12608 -1.5 .. +1.4 %, 14184 .. 25216 -3.0 .. +0.1 % (-1.3)
 //   384 x 384, 768 x 192: 9456 .. 39400 +0.2 .. +3.7 %: too little to multiply for a second launch
-// So the line lies where nothing beyond it loses more than the runs differ by (0.6 %).
+// So there is a line for large matrices and one for smaller ones, each where nothing beyond it loses more than the runs differ by (0.6 %).
 // (The two models' times do not draw this line: both leave out what launches lose to each other, and their rounds of tiles make it jump.)
-constexpr int APART_ROWS = 13312, APART_WEIGHTS = 512 * 1024;
-static bool apart(const GemmDesc& nt) { return nt.act == ACT_GELU_BWD && nt.M >= APART_ROWS && (int64_t)nt.N * nt.K >= APART_WEIGHTS; }
+static bool apart(const GemmDesc& nt) {
+  const int64_t weights = (int64_t)nt.N * nt.K;
+  return nt.act == ACT_GELU_BWD && weights >= 512 * 1024 && nt.M >= (weights >= 2048 * 1024 ? 10240 : 13312);
+}
 // whether they do when `tile` is asked for
 static bool goes_apart(const GemmDesc& nt, int tile) { return tile >= APART_ID || ((!tile || is_retired(tile)) && apart(nt)); }
 int gemm_nt_runs_tile(const GemmDesc& g, const GemmDesc* wgrad, size_t splitk_ws_floats, bool chained, int tile) {

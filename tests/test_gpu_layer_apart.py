@@ -12,12 +12,13 @@ pytestmark = pytest.mark.gpu
 APART, JOINT = ["tiled", "wgrad"], ["joint"]
 
 
-# either side of the line, also where the rounds of tiles of one shape or another just end; weight matrices too small for it; without a GELU'
+# either side of the lines of large and of smaller weight matrices, also where the rounds of tiles of one shape or another just end; matrices too
+# small for it; without a GELU'
 @pytest.mark.parametrize("rows,kin,out,gelu,kernels", [
-    (11328, 3072, 768, True, JOINT), (12608, 3072, 768, True, JOINT), (13311, 3072, 768, True, JOINT), (13312, 3072, 768, True, APART),
-    (14200, 3072, 768, True, APART), (16400, 3072, 768, True, APART), (17731, 3072, 768, True, APART), (17731, 3072, 768, False, JOINT),
-    (19700, 3072, 768, True, APART), (13311, 1536, 384, True, JOINT), (13312, 1536, 384, True, APART), (20480, 1536, 384, True, APART),
-    (20480, 384, 384, True, JOINT), (20480, 768, 192, True, JOINT)])
+    (9456, 3072, 768, True, JOINT), (10239, 3072, 768, True, JOINT), (10240, 3072, 768, True, APART), (11328, 3072, 768, True, APART),
+    (12608, 3072, 768, True, APART), (14200, 3072, 768, True, APART), (16400, 3072, 768, True, APART), (17731, 3072, 768, True, APART),
+    (17731, 3072, 768, False, JOINT), (19700, 3072, 768, True, APART), (10240, 1536, 384, True, JOINT), (13311, 1536, 384, True, JOINT),
+    (13312, 1536, 384, True, APART), (20480, 1536, 384, True, APART), (20480, 384, 384, True, JOINT), (20480, 768, 192, True, JOINT)])
 def test_gradients_behind_a_gelu_at_many_rows(env, rows, kin, out, gelu, kernels):
     torch, P = env
     g = torch.Generator(device="cuda").manual_seed(rows)
