@@ -37,24 +37,24 @@ constexpr int NXCD = 8;
 // the rational-exponential form of Abramowitz & Stegun 7.1.26, |error| <= 1.5e-7 (below 1e-6 in
 // fp32 arithmetic): far below the resolution of the bf16 values these epilogues write, at a fraction
 // of the instructions of erff.  Its exp(-x^2) with x = u / sqrt(2) is the Gaussian that phi(u) needs
-// as well.
-__device__ inline float erf_as(float x, float& gauss) {
-  const float ax = fabsf(x);
+// as well.  Its coefficients are halved, so that it is Phi that comes out: exact, and one product of 22 less.
+__device__ inline float phi_as(float u, float& gauss) {
+  const float x = u * 0.70710678118654752f, ax = fabsf(x);
   const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.0f));
-  float p = fmaf(1.061405429f, t, -1.453152027f);
-  p = fmaf(p, t, 1.421413741f);
-  p = fmaf(p, t, -0.284496736f);
-  p = fmaf(p, t, 0.254829592f);
+  float p = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+  p = fmaf(p, t, 0.5f * 1.421413741f);
+  p = fmaf(p, t, 0.5f * -0.284496736f);
+  p = fmaf(p, t, 0.5f * 0.254829592f);
   gauss = __expf(-ax * ax);
-  return copysignf(fmaf(-p * t, gauss, 1.0f), x);
+  return 0.5f + copysignf(fmaf(-p * t, gauss, 0.5f), x);
 }
 __device__ inline float gelu_f(float u) {
   float gauss;
-  return 0.5f * u * (1.0f + erf_as(u * 0.70710678118654752f, gauss));
+  return u * phi_as(u, gauss);
 }
 __device__ inline float gelu_grad_f(float u) {
   float gauss;
-  const float cdf = 0.5f * (1.0f + erf_as(u * 0.70710678118654752f, gauss));
+  const float cdf = phi_as(u, gauss);
   return fmaf(u * 0.39894228040143268f, gauss, cdf);
 }
 
@@ -478,6 +478,10 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // this epilogue with every row block and pass written out (13 700 of the kernel's 14 400 instructions) cost a
 // launch about 3 us.  So the row blocks are a loop (the accumulators of block mi are picked by a switch, which
 // is all that has to be written out per block) and so are the passes: the finishing code exists once.
+// What an epilogue has to do, as a compile-time constant of the kernel: plain products, residuals, the GELU and the GELU' have kernels of their
+// own, in which none of the other forms' branches, registers and code are left (256 x 256 tiles: 6 - 10 KB each, 16 KB with all of them in one);
+// EPI_ANY looks at the description (fp32 results, the positional embedding, a layer's joint backward launch).
+enum Epi { EPI_ANY, EPI_BIAS, EPI_RES, EPI_GELU, EPI_GELU_BWD };
 template <int NI> struct EpiLanes {
   static constexpr int TN = NI * 32;
   static constexpr int CPR = TN / 8, RPP = 64 / CPR;       // 8-column chunks per row, rows per pass of the wave
@@ -488,7 +492,7 @@ template <int NI> struct EpiLanes {
 // (steps of 32 images: DeiT-S 1250 -> 1234 us, ViT-B the same; asked for ahead of the first tiles instead, those land later: ViT-B 0.3 % longer).
 // A slot is 16 bytes: with nothing but a bias to add (`direct`) the bias in the order of the accumulators (wave tiles 32 columns wide), else
 // the bias of the lane's eight columns in two slots and a slot for every pass of a row block.
-template <int MI, int NI> struct EpiAhead {
+template <int MI, int NI, Epi E> struct EpiAhead {
   using L = EpiLanes<NI>;
   static constexpr bool EARLY = MI * NI <= 8;      // (the 320 x 256 shape would spill 27 registers: it asks behind the k-loop)
   static constexpr bool BIAS_EARLY = NI == 1;       // (as many slots either way)
@@ -508,9 +512,15 @@ template <int MI, int NI> struct EpiAhead {
     return g.bias && c < g.N ? *(const f32x4*)(g.bias + c) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
   __device__ __forceinline__ void fetch(const GemmDesc& g, int row0, int col0, int lane) {
-    direct = !g.out_f32 && !g.res && g.remap_np == 0 && g.act == ACT_NONE;
-    bwd = g.act == ACT_GELU_BWD;
-    on = !direct && !g.out_f32 && g.remap_np == 0 && (bwd ? !g.res : g.act == ACT_NONE);
+    direct = E == EPI_ANY ? !g.out_f32 && !g.res && g.remap_np == 0 && g.act == ACT_NONE : E == EPI_BIAS;
+    bwd = E == EPI_ANY ? g.act == ACT_GELU_BWD : E == EPI_GELU_BWD;
+    on = E == EPI_ANY ? !direct && !g.out_f32 && g.remap_np == 0 && (bwd ? !g.res : g.act == ACT_NONE) : E == EPI_RES || E == EPI_GELU_BWD;
+    if constexpr (E == EPI_GELU) {
+      if constexpr (BIAS_EARLY)
+#pragma unroll
+        for (int i = 0; i < 4 * NI; ++i) slot[i] = direct_bias(g, col0, lane, i);
+      return;
+    }
     extra = bwd ? (const bf16*)g.aux : (const bf16*)g.res;
     lde = bwd || !g.ldr ? g.ldc : g.ldr;
     if (direct) {
@@ -522,59 +532,95 @@ template <int MI, int NI> struct EpiAhead {
     const int my_row = lane / L::CPR, col = col0 + lane % L::CPR * 8;
     const bool ok = col < g.N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) slot[i] = g.bias && ok ? *(const f32x4*)(g.bias + col + 4 * i) : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 2; ++i) slot[i] = E != EPI_GELU_BWD && g.bias && ok ? *(const f32x4*)(g.bias + col + 4 * i) : f32x4{0.f, 0.f, 0.f, 0.f};
     if (on) sfor<L::NPASS>([&](auto P) __attribute__((always_inline)) { one(g, row0, col, my_row, ok && my_row < L::RPP, P); });
   }
 };
-template <int MI, int NI>
+template <int MI, int NI, Epi E>
 __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][NI], int row0, int col0, int lane,
-                                           unsigned char* patch, EpiAhead<MI, NI>& early) {
+                                           unsigned char* patch, EpiAhead<MI, NI, E>& early) {
   using L = EpiLanes<NI>;
   constexpr int TN = L::TN, CPR = L::CPR, RPP = L::RPP, NPASS = L::NPASS;
   const int lm = lane & 31, lh = lane >> 5;
   const int my_chunk = lane % CPR, my_row = lane / CPR;
   const int col = col0 + my_chunk * 8;
   const bool col_ok = col < g.N && my_row < RPP;    // N is a multiple of 8 on this path
-  // nothing but the bias to add: round first, move half the bytes
-  if (early.direct) {
+  // nothing but the bias to add, or the GELU behind it: finished where the accumulators are, rounded first, so that half the bytes move.
+  // The GELU is bound by the vector unit, two wavefronts a SIMD: on all values of a row block here it is one run of independent instructions; on eight
+  // values a pass behind an fp32 patch, as it was, every pass waited for the patch and went through the forms' branches.  With a GELU, chains of
+  // launches: 6304 x 3072 x 768 43.3 -> 39.3 us, 25216 rows 159 -> 154, 9232 x 1536 x 384 26.7 -> 22.7 (plain products 32.3 -> 32.0, 122 -> 121, 17.2 -> 17.1).
+  if (E == EPI_GELU || early.direct) {
     constexpr int LDB = TN * 2 + 16;                // bytes per patch row
-    bf16* dst = (bf16*)g.C;
+    using Ahead = EpiAhead<MI, NI, E>;
     f32x4 bq[4 * NI];                               // bias of the columns this lane holds
     auto read_bias = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < 4 * NI; ++i) bq[i] = EpiAhead<MI, NI>::direct_bias(g, col0, lane, i);
+      for (int i = 0; i < 4 * NI; ++i) bq[i] = Ahead::direct_bias(g, col0, lane, i);
     };
-    if constexpr (EpiAhead<MI, NI>::BIAS_EARLY)
+    if constexpr (Ahead::BIAS_EARLY)
 #pragma unroll
       for (int i = 0; i < 4 * NI; ++i) bq[i] = early.slot[i];
-    else if constexpr (EpiAhead<MI, NI>::EARLY) read_bias();
-#pragma nounroll
-    for (int mi = 0; mi < MI; ++mi) {
-      if constexpr (!EpiAhead<MI, NI>::EARLY) read_bias();     // (once per row block: no registers to keep it in)
-      sfor<MI>([&](auto I) __attribute__((always_inline)) {
-        constexpr int i = decltype(I)::value;
-        if (mi != i) return;
+    else if constexpr (Ahead::EARLY) read_bias();
+    // a row block of NI accumulators rounded into the patch, and from there to dst: all rows of the lane on their way at once
+    auto to_patch = [&](auto value) __attribute__((always_inline)) {
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+      for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-          for (int rg = 0; rg < 4; ++rg) {
-            bf16x4 o;
+        for (int rg = 0; rg < 4; ++rg) {
+          bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[i][ni][4 * rg + e] + bq[4 * ni + rg][e]);
-            *(bf16x4*)(patch + lm * LDB + (ni * 32 + 8 * rg + 4 * lh) * 2) = o;
-          }
-      });
+          for (int e = 0; e < 4; ++e) o[e] = (bf16)value(ni, rg, e);
+          *(bf16x4*)(patch + lm * LDB + (ni * 32 + 8 * rg + 4 * lh) * 2) = o;
+        }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
+    };
+    const bool whole_cols = RPP * NPASS == 32 && RPP * CPR == 64 && col0 + TN <= g.N;
+    auto out = [&](bf16* dst, int mi) __attribute__((always_inline)) {
+      const int first = row0 + mi * 32, m = first + my_row;
+      bf16* to = dst + (int64_t)m * g.ldc + col;
+      if (whole_cols && first + 32 <= g.M) {        // (a whole row block: its stores behind each other, without a branch around each)
+        bf16x8 row[NPASS];
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p) row[p] = *(const bf16x8*)(patch + (p * RPP + my_row) * LDB + my_chunk * 16);
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p) *(bf16x8*)(to + (int64_t)(p * RPP) * g.ldc) = row[p];
+      } else {
 #pragma nounroll
-      for (int p = 0; p < NPASS; ++p) {
-        const int lr = p * RPP + my_row;
-        const int m = row0 + mi * 32 + lr;
-        if (lr >= 32 || m >= g.M || !col_ok) continue;
-        *(bf16x8*)(dst + (int64_t)m * g.ldc + col) = *(const bf16x8*)(patch + lr * LDB + my_chunk * 16);
+        for (int p = 0; p < NPASS; ++p)
+          if (p * RPP + my_row < 32 && m + p * RPP < g.M && col_ok)
+            *(bf16x8*)(to + (int64_t)(p * RPP) * g.ldc) = *(const bf16x8*)(patch + (p * RPP + my_row) * LDB + my_chunk * 16);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
+    };
+#pragma nounroll
+    for (int mi = 0; mi < MI; ++mi) {
+      if constexpr (!Ahead::BIAS_EARLY && !Ahead::EARLY) read_bias();     // (once per row block: no registers to keep it in)
+      if constexpr (E == EPI_GELU) {
+        f32x16 blk[NI];                             // (the code of a row block's GELU exists once)
+        sfor<MI>([&](auto I) __attribute__((always_inline)) {
+          constexpr int i = decltype(I)::value;
+          if (mi == i)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) blk[ni] = acc[i][ni];
+        });
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) blk[ni][r] += bq[4 * ni + r / 4][r % 4];
+        if (g.aux) {                                // (its rows leave while the GELU is computed)
+          to_patch([&](int ni, int rg, int e) __attribute__((always_inline)) { return blk[ni][4 * rg + e]; });
+          out((bf16*)g.aux, mi);
+        }
+        to_patch([&](int ni, int rg, int e) __attribute__((always_inline)) { return gelu_f(blk[ni][4 * rg + e]); });
+      } else {
+        sfor<MI>([&](auto I) __attribute__((always_inline)) {
+          constexpr int i = decltype(I)::value;
+          if (mi == i) to_patch([&](int ni, int rg, int e) __attribute__((always_inline)) { return acc[i][ni][4 * rg + e] + bq[4 * ni + rg][e]; });
+        });
+      }
+      out((bf16*)g.C, mi);
     }
     return;
   }
@@ -613,7 +659,10 @@ __device__ __forceinline__ void epilogue_t(const GemmDesc& g, f32x16 (&acc)[MI][
           const f32x4 p1 = *(const f32x4*)(patch + lr * LDF + my_chunk * 32 + 16);
           const float v[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
           bf16x8 o;
-          if (bwd) {
+          if (E == EPI_GELU_BWD) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = (bf16)(v[j] * gelu_grad_f((float)e[j]));
+          } else if (bwd) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) o[j] = (bf16)((v[j] + bias[j]) * gelu_grad_f((float)e[j]));
           } else {
@@ -675,7 +724,7 @@ __device__ __forceinline__ void epilogue_f32(float* c, int64_t ldc, int M, int N
 }
 
 // The work of one tile (a kernel of its own below, and the input-gradient half of a layer's backward launch).
-template <int BM, int BN, int WM, int WN, int NST>
+template <int BM, int BN, int WM, int WN, int NST, Epi E = EPI_ANY>
 __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32, NMF = MI * NI, NFR = MI + NI;
@@ -787,7 +836,7 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
   };
 
   const int nk = g.K / BK;
-  EpiAhead<MI, NI> early;
+  EpiAhead<MI, NI, E> early;
   // prologue: every stage filled (k-tiles 0 .. NST-1), k-tile 0 landed
 #pragma unroll
   for (int j = 0; j < NST; ++j)
@@ -818,7 +867,7 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
   }
   if constexpr (!early.EARLY) early.fetch(g, m0 + wm * TM, n0 + wn * TN, lane);
   // every wavefront is past the last barrier, i.e. has read its last fragments: the stages are free
-  epilogue_t<MI, NI>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)), early);
+  epilogue_t<MI, NI, E>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)), early);
 }
 
 // What a product's first loads need, as plain kernel arguments in front: the first 14 dwords come in registers with the wavefront
@@ -829,21 +878,28 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
 #define BSR_HOT_INTO(g) ((g).A = hA, (g).B = hB, (g).M = hM, (g).N = hN, (g).K = hK, (g).a_rs = ha_rs, (g).b_cs = hb_cs)
 
 // (a shape whose stages take at most half of the 160 KB is held to the registers that let two workgroups share a CU)
-template <int BM, int BN, int WM, int WN, int NST>
+template <int BM, int BN, int WM, int WN, int NST, Epi E>
 __global__ __launch_bounds__(WM * WN * 64, NST * (BM + BN) * 128 <= 80 * 1024 ? WM * WN / 2 : 1)
 void gemm_ntd_kernel(BSR_HOT_PARAMS, const int32_t* grp_off, GemmDesc g) {
   BSR_HOT_INTO(g);
   g.grp_off = grp_off;
-  ntd_body<BM, BN, WM, WN, NST>(g, xcd_remap(blockIdx.x, tiles));
+  ntd_body<BM, BN, WM, WN, NST, E>(g, xcd_remap(blockIdx.x, tiles));
 }
 
-template <int BM, int BN, int WM, int WN, int NST>
-void launch_ntd(const GemmDesc& g, hipStream_t s) {
+Epi epi_of(const GemmDesc& g) {
+  if (g.out_f32 || g.remap_np > 0) return EPI_ANY;
+  if (g.act == ACT_NONE) return g.res ? EPI_RES : EPI_BIAS;
+  if (g.res) return EPI_ANY;
+  return g.act == ACT_GELU ? EPI_GELU : g.act == ACT_GELU_BWD && !g.bias ? EPI_GELU_BWD : EPI_ANY;
+}
+
+template <int BM, int BN, int WM, int WN, int NST, Epi E>
+void launch_ntd_as(const GemmDesc& g, hipStream_t s) {
   static bool attr_set = false;
   constexpr size_t lds_tiles = (size_t)NST * (BM + BN) * 128;
   constexpr size_t lds_patch = (size_t)WM * WN * 32 * ((BN / WN) * 4 + 16);
   static_assert(lds_patch <= lds_tiles, "the epilogue patches live in the stage buffers");
-  auto kern = gemm_ntd_kernel<BM, BN, WM, WN, NST>;
+  auto kern = gemm_ntd_kernel<BM, BN, WM, WN, NST, E>;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_tiles);
     attr_set = true;
@@ -851,6 +907,16 @@ void launch_ntd(const GemmDesc& g, hipStream_t s) {
   // grouped: every group may end in one partial row tile
   const int tiles = ((g.M + BM - 1) / BM + (g.grp_off ? g.groups : 0)) * ((g.N + BN - 1) / BN);
   kern<<<tiles, WM * WN * 64, lds_tiles, s>>>(BSR_HOT_ARGS(g, tiles), g.grp_off, g);
+}
+template <int BM, int BN, int WM, int WN, int NST>
+void launch_ntd(const GemmDesc& g, hipStream_t s) {
+  switch (epi_of(g)) {
+    case EPI_BIAS: launch_ntd_as<BM, BN, WM, WN, NST, EPI_BIAS>(g, s); break;
+    case EPI_RES: launch_ntd_as<BM, BN, WM, WN, NST, EPI_RES>(g, s); break;
+    case EPI_GELU: launch_ntd_as<BM, BN, WM, WN, NST, EPI_GELU>(g, s); break;
+    case EPI_GELU_BWD: launch_ntd_as<BM, BN, WM, WN, NST, EPI_GELU_BWD>(g, s); break;
+    default: launch_ntd_as<BM, BN, WM, WN, NST, EPI_ANY>(g, s); break;
+  }
 }
 // The kernels that load straight into LDS hold an operand's row offsets in 32 bits (elements): larger operands, such as the
 // activations of 8192 images, go to the register-staged kernels, whose offsets have 64.
