@@ -789,9 +789,23 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
     constexpr int ja = mi == 0 ? 0 : NI + mi, jb = 1 + ni;
     acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[set][jb], fr[set][ja], acc[mi][ni], 0, 0, 0);
   };
-  // one k-step: MFMAs on fragment set SET; the fragments of (stage st, k-step ks) go into the other set
-  auto kstep = [&](auto SET, int st, int ks) __attribute__((always_inline)) {
-    constexpr int set = decltype(SET)::value;
+  // The loads of a k-tile are spread evenly over the SPAN MFMAs behind the barrier that frees its stage.  A wavefront that issues loads faster than the CU's
+  // path from L2 takes them (48 bytes per clock) stands still, and its MFMAs with it; issued later they land later.  So large wave tiles spread
+  // them (all of a k-tile with three stages, half with two), small ones, whose k-tiles are short, issue them at once.  Chains of launches, at once -> spread:
+  // 6304 x 768 x 3072 in 256 x 256 tiles 62.4 -> 58.8 us, in 320 x 256 75.2 -> 70.3, in 256 x 128 39.6 -> 36.3; 25216 x 768 x 3072 in 320 x 256 110.4 -> 107.5;
+  // 192 x 256 and 256 x 192 tiles 1.01 .. 1.08 as long, 128 x 128 and 128 x 64 tiles of 132 workgroups (in a step) 1.02 and 1.04.
+  constexpr int PRE = NMF >= 16 ? 4 : (NMF >= 8 ? 2 : 1);         // MFMAs of the last k-step in front of the barrier
+  constexpr int POST = NMF - PRE;
+  constexpr int SPAN = POST + (NST == 2 ? NMF >= 8 : NMF >= 4 ? 3 : NMF == 3 ? 2 : 0) * NMF;    // MFMAs that the loads of a k-tile are spread over
+  auto loads_at = [&](auto P, int kt, int st) __attribute__((always_inline)) {
+    constexpr int p = decltype(P)::value, lo = p >= SPAN ? LPT : (p * LPT + SPAN - 1) / SPAN, hi = p + 1 >= SPAN ? LPT : ((p + 1) * LPT + SPAN - 1) / SPAN;
+    sfor<hi - lo>([&](auto L) __attribute__((always_inline)) { issue1(IC<lo + decltype(L)::value>{}, kt, st); });
+  };
+  constexpr bool LATE = SPAN > POST;                              // some follow in the next k-tile
+  // one k-step: MFMAs on fragment set SET; the fragments of (stage st, k-step ks) go into the other set; LOADS: with its share of the loads of
+  // k-tile ktl into stage stl
+  auto kstep = [&](auto SET, auto LOADS, auto KS, int st, int ktl, int stl) __attribute__((always_inline)) {
+    constexpr int set = decltype(SET)::value, ks = decltype(KS)::value;
     sfor<NMF>([&](auto J) __attribute__((always_inline)) {
       constexpr int j = decltype(J)::value;
       mf1(IC<set>{}, J);
@@ -800,17 +814,16 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
         constexpr int r = j * RPM + decltype(R)::value;
         if constexpr (r < NFR) rd1(IC<set ^ 1>{}, IC<r>{}, st, ks);
       });
+      if constexpr (decltype(LOADS)::value) loads_at(IC<POST + (ks - 1) * NMF + j>{}, ktl, stl);
       BSR_SCHED_FENCE();
     });
   };
   // The last k-step of k-tile kt (fragments in set 1) with the barrier.  VMW >= 0: loads that may stay in flight
-  // at the barrier (steady state, k-tile kt + NST is issued behind it); VMW < 0: tail, nothing is issued and the
+  // at the barrier (steady state, the first loads of k-tile kt + NST follow it); VMW < 0: tail, nothing is issued and the
   // count follows from rem, the number of k-tiles after this one (after the last one barrier and reads are idle).
   auto klast = [&](auto VMW, int kt, int st, int stn, int rem) __attribute__((always_inline)) {
     constexpr int vmw = decltype(VMW)::value;
-    constexpr int PRE = NMF >= 16 ? 4 : (NMF >= 8 ? 2 : 1);       // MFMAs in front of the barrier
-    constexpr int POST = NMF - PRE;
-    constexpr int RPP = (NFR + POST - 1) / POST, LPP = (LPT + POST - 1) / POST;
+    constexpr int RPP = (NFR + POST - 1) / POST;
     sfor<PRE>([&](auto J) __attribute__((always_inline)) { mf1(IC<1>{}, J); BSR_SCHED_FENCE(); });
     wait_lgkmcnt0();
     if constexpr (vmw >= 0) wait_vmcnt<vmw>();
@@ -826,11 +839,7 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
         constexpr int r = p * RPP + decltype(R)::value;
         if constexpr (r < NFR) rd1(IC<0>{}, IC<r>{}, stn, 0);
       });
-      if constexpr (vmw >= 0)
-        sfor<LPP>([&](auto L) __attribute__((always_inline)) {
-          constexpr int l = p * LPP + decltype(L)::value;
-          if constexpr (l < LPT) issue1(IC<l>{}, kt + NST, st);
-        });
+      if constexpr (vmw >= 0) loads_at(P, kt + NST, st);
       BSR_SCHED_FENCE();
     });
   };
@@ -848,23 +857,26 @@ __device__ __forceinline__ void ntd_body(GemmDesc g, int tile) {
   __builtin_amdgcn_s_barrier();
   sfor<NFR>([&](auto J) __attribute__((always_inline)) { rd1(IC<0>{}, J, 0, 0); });
   int st = 0, kt = 0;
-  for (; kt + NST < nk; ++kt) {          // steady state
-    const int stn = (st + 1 == NST) ? 0 : st + 1;
-    kstep(IC<0>{}, st, 1);
-    kstep(IC<1>{}, st, 2);
-    kstep(IC<0>{}, st, 3);
-    klast(IC<(NST - 2) * LPT>{}, kt, st, stn, 0);
+  // a k-tile; LOADS: with the late loads of k-tile kt + NST - 1, whose stage the barrier before this one freed
+  auto ktile = [&](auto LOADS, auto VMW) __attribute__((always_inline)) {
+    const int stn = (st + 1 == NST) ? 0 : st + 1, stl = st == 0 ? NST - 1 : st - 1;
+    kstep(IC<0>{}, LOADS, IC<1>{}, st, kt + NST - 1, stl);
+    kstep(IC<1>{}, LOADS, IC<2>{}, st, kt + NST - 1, stl);
+    kstep(IC<0>{}, LOADS, IC<3>{}, st, kt + NST - 1, stl);
+    klast(VMW, kt, st, stn, nk - 1 - kt);
     st = stn;
+    ++kt;
+  };
+  constexpr IC<(NST - 2) * LPT> steady{};
+  if constexpr (LATE) {
+    if (kt + NST < nk) ktile(IC<0>{}, steady);                    // (the prologue's loads are all out)
+    while (kt + NST < nk) ktile(IC<1>{}, steady);
+    if (kt > 0) ktile(IC<1>{}, IC<-1>{});                         // the last late loads
+  } else {
+    while (kt + NST < nk) ktile(IC<0>{}, steady);
   }
   if constexpr (early.EARLY) early.fetch(g, m0 + wm * TM, n0 + wn * TN, lane);
-  for (; kt < nk; ++kt) {                // the last NST k-tiles: nothing left to issue
-    const int stn = (st + 1 == NST) ? 0 : st + 1;
-    kstep(IC<0>{}, st, 1);
-    kstep(IC<1>{}, st, 2);
-    kstep(IC<0>{}, st, 3);
-    klast(IC<-1>{}, kt, st, stn, nk - 1 - kt);
-    st = stn;
-  }
+  while (kt < nk) ktile(IC<0>{}, IC<-1>{});                       // nothing left to issue
   if constexpr (!early.EARLY) early.fetch(g, m0 + wm * TM, n0 + wn * TN, lane);
   // every wavefront is past the last barrier, i.e. has read its last fragments: the stages are free
   epilogue_t<MI, NI, E>(g, acc, m0 + wm * TM, n0 + wn * TN, lane, smem + wave * (32 * (TN * 4 + 16)), early);
