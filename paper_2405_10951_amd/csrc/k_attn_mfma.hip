@@ -11,6 +11,8 @@
 // operand of the second product O^T = V^T P^T: MFMA contracts over a dummy index, so the key order
 // that the accumulator layout dictates is simply applied to the V^T reads as well.  No T x T tensor
 // ever leaves registers.
+#include <climits>
+
 #include "rowops.h"
 
 namespace bsr {
@@ -89,10 +91,11 @@ __device__ inline void load_two(const bf16* x, int64_t xs, const bf16* y, int64_
 // 16 st + 8 + 4 lh + {0..3}, the order in which a 32x32 accumulator holds its rows.  Two LDS
 // transpose reads (ds_read_b64_tr_b16): within 16 lanes, lane 4e+q passes the address of 4 features of
 // row e and lane j receives feature j of the four rows.
-__device__ inline bf16x8 lds_frag_t(const u32x4* rows, int nb, int lane, int st) {
+// (last: rows past it are read as that row)
+__device__ inline bf16x8 lds_frag_t(const u32x4* rows, int nb, int lane, int st, int last = INT_MAX) {
   const int j = lane & 15, cb = (lane >> 4) & 1, lh = lane >> 5;
   const int chunk = nb * 4 + cb * 2 + ((j & 3) >> 1), half = j & 1;
-  const int r0 = 16 * st + 4 * lh + (j >> 2), r1 = r0 + 8;
+  const int r0 = min(16 * st + 4 * lh + (j >> 2), last), r1 = min(16 * st + 4 * lh + (j >> 2) + 8, last);
   const unsigned char* p = (const unsigned char*)rows;
   union { bf16x8 v; s16x4 h[2]; } f;
   f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -102,14 +105,23 @@ __device__ inline bf16x8 lds_frag_t(const u32x4* rows, int nb, int lane, int st)
   return f.v;
 }
 
+// Rows of K and V in LDS: the tokens and at least one row of zeros where the last block of 32 has room for it, which stands for all rows past it.
+__host__ __device__ inline int fwd_rows(int nj, int T) { return min(nj * 32, (T + 8) & ~7); }
+// From 161 to 224 tokens a head goes to two workgroups of up to four wavefronts, which both stage K and V.  What bounds the kernel is the softmax arithmetic and how
+// many wavefronts a CU has to cover it: at 171 registers a SIMD takes two of them, so one workgroup of seven filled a CU and 384 heads took two rounds.
+// Held to 168 registers, with 200 rows staged for 197 tokens instead of 224, three halves share a CU: 32 images of 12 heads 19.2 -> 13.1 us, 27 18.8 -> 14.6,
+// 128 61.6 -> 51.6 (the class row's way out through LDS is in these: 138 tokens, where it is all, 13.2 -> 10.2).
+constexpr bool fwd_halves(int nj) { return nj == 6 || nj == 7; }
+
 template <int NJ>
-__global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, int T, int H,
+__global__ __launch_bounds__(fwd_halves(NJ) ? 256 : NJ * 64, NJ == 4 || fwd_halves(NJ) ? 3 : 1) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, int T, int H,
                                                                bf16* __restrict__ out, float* __restrict__ lse,
                                                                float* __restrict__ cls_prob) {
-  constexpr int Tpad = NJ * 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  u32x4* Ks = (u32x4*)smem;                         // [Tpad][8 chunks]
-  u32x4* Vs = Ks + Tpad * 8;                        // [Tpad][8 chunks]
+  const int rows = fwd_rows(NJ, T);
+  u32x4* Ks = (u32x4*)smem;                         // [rows][8 chunks]
+  u32x4* Vs = Ks + rows * 8;                        // [rows][8 chunks]
+  float* cls_s = (float*)(Vs + rows * 8);           // [32 NJ]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 31, lh = lane >> 5;
   const int b = blockIdx.x / H, h = blockIdx.x % H;
@@ -125,7 +137,7 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) qf[ks] = *(const bf16x8*)(qrow + (2 * ks + lh) * 8);
   }
-  load_two(base + D, rs, base + 2 * D, rs, T, Tpad, Ks, Vs, tid, blockDim.x);
+  load_two(base + D, rs, base + 2 * D, rs, T, rows, Ks, Vs, tid, blockDim.x);
   __syncthreads();
   if (q0 >= T) return;
 
@@ -138,7 +150,8 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
     for (int r = 0; r < 16; ++r) s[jb][r] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      const bf16x8 kf = *(const bf16x8*)(Ks + (jb * 32 + lr) * 8 + ((2 * ks + lh) ^ sw));
+      const int row = jb == NJ - 1 ? min(jb * 32 + lr, rows - 1) : jb * 32 + lr;
+      const bf16x8 kf = *(const bf16x8*)(Ks + row * 8 + ((2 * ks + lh) ^ (jb == NJ - 1 ? swz(row) : sw)));
       s[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[jb], 0, 0, 0);
     }
   }
@@ -174,15 +187,17 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
   const float inv = 1.0f / sum;
   const int qi = q0 + lr;
   if (lse && lh == 0 && qi < T) lse[((int64_t)b * H + h) * T + qi] = mx * 0.125f + __logf(sum);
-  if (cls_prob && qi == 0) {   // the CLS query: its softmax row in fp32 (Eq. 6)
+  if (cls_prob && q0 == 0) {   // the wavefront of the CLS query: its softmax row in fp32 (Eq. 6), through LDS to leave in whole rows
+    if (lr == 0)
+#pragma unroll
+      for (int jb = 0; jb < NJ; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; r += 4)
+          *(float4*)(cls_s + key_of(jb, r, lh)) = make_float4(s[jb][r] * inv, s[jb][r + 1] * inv, s[jb][r + 2] * inv, s[jb][r + 3] * inv);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     float* dst = cls_prob + ((int64_t)b * H + h) * T;
-#pragma unroll
-    for (int jb = 0; jb < NJ; ++jb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int j = key_of(jb, r, lh);
-        if (j < T) dst[j] = s[jb][r] * inv;
-      }
+    for (int j = lane; j < T; j += 64) dst[j] = cls_s[j];
   }
   // O^T = V^T P^T, contraction over keys in the order the accumulators hold them:
   // step st covers keys 16 st + {4 lh .. 4 lh + 3} and 16 st + 8 + {4 lh .. 4 lh + 3}.
@@ -195,7 +210,7 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
     for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
 #pragma unroll
     for (int st = 0; st < 2 * NJ; ++st)
-      o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(Vs, nb, lane, st), pf[st], o[nb], 0, 0, 0);
+      o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_frag_t(Vs, nb, lane, st, st >= 2 * NJ - 2 ? rows - 1 : INT_MAX), pf[st], o[nb], 0, 0, 0);
   }
   if (qi < T) {
     bf16* orow = out + ((int64_t)b * T + qi) * D + h * HD + 4 * lh;
@@ -214,15 +229,15 @@ __global__ __launch_bounds__(NJ * 64) void attn_fwd_mfma_kernel(const bf16* __re
 template <int NJ>
 void launch_fwd(const bf16* qkv, int B, int T, int H, bf16* out, float* lse, float* cls_prob, hipStream_t s) {
   static bool attr_set = false;
-  constexpr size_t lds = (size_t)2 * NJ * 32 * 128;
+  const auto lds = [](int rows) { return (size_t)2 * rows * 128 + NJ * 32 * sizeof(float); };
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)attn_fwd_mfma_kernel<NJ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)hipFuncSetAttribute((const void*)attn_fwd_mfma_kernel<NJ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds(NJ * 32));
     attr_set = true;
   }
   // Few heads leave CUs idle: their queries go to two workgroups then, which both stage K and V: one image of
   // 12 heads, 197 tokens 8.0 -> 7.4 us.  (From 128 heads on two workgroups a head are more than one a CU.)
-  const int parts = NJ > 1 && B * H <= 128 ? 2 : 1;
-  attn_fwd_mfma_kernel<NJ><<<dim3(B * H, parts), (NJ + parts - 1) / parts * 64, lds, s>>>(qkv, T, H, out, lse, cls_prob);
+  const int parts = fwd_halves(NJ) || (NJ > 1 && B * H <= 128) ? 2 : 1;
+  attn_fwd_mfma_kernel<NJ><<<dim3(B * H, parts), (NJ + parts - 1) / parts * 64, lds(fwd_rows(NJ, T)), s>>>(qkv, T, H, out, lse, cls_prob);
 }
 
 
@@ -605,8 +620,12 @@ void launch_bwd(const bf16* qkv, const bf16* out, const bf16* dout, const float*
 // delta stay in fp32 here (Split below), so results are the exact ones rounded to bf16.  What bounds it is the softmax
 // arithmetic (VALU) beside 12 MFMAs per 32 x 32 scores and the registers of the accumulators: held to 256 (two workgroups per
 // CU) the kernels run 1.4 times as fast as with the 284 the compiler takes by itself.  At 577 tokens, 16 images of 6 heads, calls
-// in a loop: 29 us forward and 87 backward (732 and 2711 with one wavefront per query, of the same precision; 37 and 100 with
-// bf16 factors at 1 workgroup per CU, dq and dk 1.4 to 2.6 times as far from the exact ones).
+// in a loop: 25.7 us forward and 75 backward (732 and 2711 with one wavefront per query, of the same precision; 37 and 100 with
+// bf16 factors at 1 workgroup per CU, dq and dk 1.4 to 2.6 times as far from the exact ones).  Blocks of 32 keys or queries past the last token
+// are left out, and wavefronts without a query or key of their own only stage; that the blocks of a chunk then are separate pieces of code lets
+// exponentials and MFMAs of neighbouring blocks mix, and takes 204 registers instead of 256 (with whole chunks written out without the branch 28.2):
+// forward and backward 28.5 -> 25.7 and 80.7 -> 75 us at 577 tokens, 22.2 -> 19.1 and 58.8 -> 50.3 at 404, 16.3 -> 12.4 and 44.4 -> 36.9 at 283, 4 images of 785
+// 30.5 -> 21.2 and 59.3 -> 55.4.
 // Workgroups are numbered head first: the query blocks of a head then run on one XCD and share its L2.
 constexpr int LC = 128, LCB = LC / 32, LONG_T = 1024;
 
@@ -660,7 +679,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __res
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[nb][r] = 0.f;
-  const bool cls_lane = cls_prob && qi == 0;
+  const bool cls_wave = cls_prob && q0 == 0;
   const int sw = swz(lr);
   ChunkRegs kr, vr;
   chunk_fetch(kr, base + D, rs, 0, T, tid);
@@ -674,10 +693,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __res
       chunk_fetch(kr, base + D, rs, c0 + LC, T, tid);
       chunk_fetch(vr, base + 2 * D, rs, c0 + LC, T, tid);
     }
+    if (q0 >= T) continue;                            // (it only stages)
     f32x16 s[LCB];
     float mx = m;
 #pragma unroll
     for (int jb = 0; jb < LCB; ++jb) {
+      if (c0 + jb * 32 >= T) break;
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[jb][r] = 0.f;
 #pragma unroll
@@ -685,7 +706,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __res
         const bf16x8 kf = *(const bf16x8*)(Ks + (jb * 32 + lr) * 8 + ((2 * ks + lh) ^ sw));
         s[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[jb], 0, 0, 0);
       }
-      if (c0 + jb * 32 + 32 > T) {                  // uniform: this block reaches past the last key
+      if (c0 + jb * 32 + 32 > T) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (c0 + key_of(jb, r, lh) >= T) s[jb][r] = -INFINITY;
@@ -693,25 +714,27 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __res
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[jb][r]);
     }
-    if (cls_lane) {
+    if (cls_wave && lr == 0)
 #pragma unroll
-      for (int jb = 0; jb < LCB; ++jb)
+      for (int jb = 0; jb < LCB; ++jb) {
+        if (c0 + jb * 32 >= T) break;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = c0 + key_of(jb, r, lh);
-          if (j < T) cls_s[j] = s[jb][r];
-        }
-    }
+        for (int r = 0; r < 16; r += 4)
+          *(float4*)(cls_s + c0 + key_of(jb, r, lh)) = make_float4(s[jb][r], s[jb][r + 1], s[jb][r + 2], s[jb][r + 3]);
+      }
     mx = half_max(mx);         // finite: a chunk holds at least one key
     const float alpha = __builtin_amdgcn_exp2f((m - mx) * c), mc = mx * c;
+    if (__any(mx != m)) {      // (else alpha is 1)
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[nb][r] *= alpha;
+    }
     m = mx;
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[nb][r] *= alpha;
     float sum = 0.f;
 #pragma unroll
     for (int jb = 0; jb < LCB; ++jb) {
+      if (c0 + jb * 32 >= T) break;
       Split p[2];
 #pragma unroll
       for (int r = 0; r < 16; r += 2) {
@@ -807,7 +830,7 @@ __global__ __launch_bounds__(256, 2) void attn_delta_long_kernel(const bf16* __r
   __shared__ u32x4 Ks[LC * 8], Vs[LC * 8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
   const LongHead hd(qkv, dout, T, H, heads_total);
-  const int qi = hd.block * 128 + wave * 32 + lr, qc = min(qi, T - 1);
+  const int q0 = hd.block * 128 + wave * 32, qi = q0 + lr, qc = min(qi, T - 1);
   bf16x8 qf[4], dof[4];
   row_frags(qf, hd.base + (int64_t)qc * hd.rs, lh);
   row_frags(dof, hd.dobase + (int64_t)qc * hd.D, lh);
@@ -825,8 +848,10 @@ __global__ __launch_bounds__(256, 2) void attn_delta_long_kernel(const bf16* __r
       chunk_fetch(kr, hd.base + hd.D, hd.rs, c0 + LC, T, tid);
       chunk_fetch(vr, hd.base + 2 * hd.D, hd.rs, c0 + LC, T, tid);
     }
+    if (q0 >= T) continue;                            // (it only stages)
 #pragma unroll
     for (int jb = 0; jb < LCB; ++jb) {
+      if (c0 + jb * 32 >= T) break;
       f32x16 sa, dp;
       score_products(sa, dp, Ks, Vs, jb * 32 + lr, lh, qf, dof);
       block_probs(sa, l2, c0 + jb * 32, lh, T);
@@ -870,8 +895,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_long_kernel(const bf16* __res
         chunk_fetch(ra, hd.base + hd.D, hd.rs, c0 + LC, T, tid);
         chunk_fetch(rb, hd.base + 2 * hd.D, hd.rs, c0 + LC, T, tid);
       }
+      if (q0 >= T) continue;
 #pragma unroll
       for (int jb = 0; jb < LCB; ++jb) {
+        if (c0 + jb * 32 >= T) break;
         f32x16 sa, dp;
         score_products(sa, dp, As, Bs, jb * 32 + lr, lh, qf, dof);
         block_probs(sa, l2, c0 + jb * 32, lh, T);
@@ -921,8 +948,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_long_kernel(const bf16* __res
       chunk_fetch(ra, hd.base, hd.rs, c0 + LC, T, tid);
       chunk_fetch(rb, hd.dobase, hd.D, c0 + LC, T, tid);
     }
+    if (j0 >= T) continue;
 #pragma unroll
     for (int ib = 0; ib < LCB; ++ib) {
+      if (c0 + ib * 32 >= T) break;
       f32x16 sa, dp;
       score_products(sa, dp, As, Bs, ib * 32 + lr, lh, kf, vf);
       Split p[2], ds[2];

@@ -1,0 +1,45 @@
+"""Attention at lengths around the rows it stages and the blocks of 32 it leaves out, with whatever LDS held before (NaN) behind the last token, against the oracle."""
+import numpy as np
+import pytest
+
+from test_gpu_kernels import assert_close, bf16_np, env, to_dev  # noqa: F401  (env is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def fill_lds_with_nan(torch, P, T):
+    """A head of NaN for every CU, twice over: its keys and values stay in LDS behind the kernel."""
+    P.bsr_attention_forward(torch.full((43, T, 3 * 12 * 64), float("nan"), dtype=torch.bfloat16, device="cuda"), 12)
+
+
+# one row of tokens more or less than whole groups of 8 staged rows, blocks of 32 and halves of a head; 1 token: the least
+@pytest.mark.parametrize("T", [1, 7, 8, 9, 32, 33, 96, 127, 128, 129, 159, 160, 161, 167, 168, 192, 193, 199, 200, 201, 223, 224, 225, 255, 256])
+def test_attention_forward_reads_no_row_past_the_tokens(env, orc64, T):
+    torch, P = env
+    rng = np.random.default_rng(T)
+    qkv = bf16_np(rng, (2, T, 3 * 3 * 64), 1.5)
+    fill_lds_with_nan(torch, P, 256)
+    out, lse, cls, used = P.bsr_attention_forward(to_dev(torch, qkv, torch.bfloat16), 3)
+    torch.cuda.synchronize()
+    assert used == 1
+    Pm, o = orc64.attention(qkv, 3)
+    assert_close(out.float().cpu().numpy(), o, "attention output")                   # bounds: those of test_attention_forward
+    assert_close(cls.cpu().numpy(), Pm[:, :, 0, :], "CLS softmax row", tol=2e-3)
+    assert bool(torch.isfinite(lse).all())
+
+
+# 257, 385: one key into a chunk of 128; 288 / 289, 416 / 417: a block of 32 full and one key more; 1023: one short of the limit
+@pytest.mark.parametrize("T", [257, 288, 289, 385, 416, 417, 512, 1023])
+def test_long_attention_leaves_out_blocks_past_the_tokens(env, orc64, T):
+    torch, P = env
+    rng = np.random.default_rng(T)
+    qkv, dout = bf16_np(rng, (1, T, 3 * 2 * 64), 1.0), bf16_np(rng, (1, T, 2 * 64), 1.0)
+    fill_lds_with_nan(torch, P, 512)
+    qt = to_dev(torch, qkv, torch.bfloat16)
+    out, lse, cls, _ = P.bsr_attention_forward(qt, 2)
+    dqkv, _ = P.bsr_attention_backward(qt, out, to_dev(torch, dout, torch.bfloat16), lse, 2)
+    torch.cuda.synchronize()
+    Pm, o = orc64.attention(qkv, 2)
+    assert_close(out.float().cpu().numpy(), o, "attention output")
+    assert_close(cls.cpu().numpy(), Pm[:, :, 0, :], "CLS softmax row", tol=2e-3)
+    assert_close(dqkv.float().cpu().numpy(), orc64.attention_bwd(qkv, Pm, dout, 2), "dq, dk, dv", tol=1.5e-2)
