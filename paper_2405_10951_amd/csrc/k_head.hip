@@ -7,9 +7,14 @@
 //   head_batch_kernel  the sums over the batch: loss, dW_h = z^T dlogits, db_h, dgamma_f, dbeta_f,
 //                      each in a fixed order (bit-reproducible).
 // All arithmetic is fp32 whatever the activation type.
-// Bound by latency: an image's workgroup reads W_h twice (307 KB at 768 x 100, from L2).  Both passes walk W_h as it lies
-// in memory, VEC classes per load, as many rows at once as the 1024 threads cover, every load independent; what is to
-// be added across threads goes through LDS.  (Lanes along the classes with a wave sum per row of W_h: 32 us at 32 images, 768 x 100; now 20.
+// Bound by latency: an image's workgroup reads W_h once (307 KB at 768 x 100, from L2) or, beyond what its registers hold, twice.
+// Both passes walk W_h as it lies in memory, VEC classes per load, as many rows at once as the 1024 threads cover; what is to be
+// added across threads goes through LDS.  A thread's first rows (20 of four classes: all of 768 x 100; 42 of one: all of 384 x 102)
+// are asked for in one go ahead of the LayerNorm and kept for dz, the others seven (of four classes five) at a time with the last batch filled up by
+// repeats, where loops of eight left up to seven rows to be waited for one by one, in every chunk of dz again.  More held, 77 of one
+// class, or the code for it (23 KB, run once) cost 10 classes 0.8 us.  Before -> this, in a step: 768 x 100, 32 images 19.3 -> 16.8 us,
+// 384 x 102, 16 images 24.2 -> 19.0, 768 x 37, 27 images 18.1 -> 17.2, 384 x 100, 32 images 14.1 -> 12.7, 384 x 10 10.5 -> 10.0.
+// (Lanes along the classes with a wave sum per row of W_h: 32 us at 32 images, 768 x 100.
 // The batch kernel with a thread per element walking all images: 13 us at 32 images, 48 at 128; now 6 and 17.)
 #include "rowops.h"
 
@@ -20,6 +25,9 @@ namespace {
 
 constexpr int HT = 1024, HW = HT / WAVE;               // threads and wavefronts per workgroup of the row kernel
 constexpr int SCRATCH = 8192;                          // floats of LDS for partial sums
+// (Registers: 118 of 128 at 20 rows of four classes, 21 in chunks of seven spill; 70 at 42 of one.)
+constexpr int CHUNK4 = 5, CHUNK1 = 7;                  // rows of W_h (of four classes, of one) per thread of the row kernel between two barriers of dz
+constexpr int HELD4 = 4 * CHUNK4, HELD1 = 6 * CHUNK1;  // and those it holds in registers from the logits to dz
 constexpr int WIDE_G = 128, PARTS = 8;                 // groups of VEC classes that make a wide head; its ranges of rows
 constexpr int ZERO_PARTS = 4;                          // workgroups per image that clear the other token rows
 constexpr int BT = 256;                                // threads per workgroup of the batch kernel
@@ -58,6 +66,26 @@ __device__ __forceinline__ void zero_rows(T* dst, int64_t n, int part) {
   }
 }
 
+// v[tid % 8], v[tid % 8 + 8], ... of n values `step` apart, added in that order; four at a time are read together
+__device__ __forceinline__ float every_eighth(const float* v, int step, int n) {
+  float a = 0.f;
+  for (int i = threadIdx.x & 7; i < n; i += 32) {
+    float t[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = v[min(i + 8 * j, n - 1) * step];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (i + 8 * j < n) a += t[j];
+  }
+  return a;
+}
+
+// a value the compiler works out addresses from again, where it would keep those of every row in registers
+__device__ __forceinline__ int anew(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 template <typename T, int VEC, bool WIDE>
 __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, int Tl, int D, int C, int B,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
@@ -80,9 +108,29 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
   float* red = lg + C;            // [HW]
   float* scr = red + HW;          // [SCRATCH] partial sums
   const T* xr = x + (int64_t)b * Tl * D;
+  // G groups of VEC classes, R rows of W_h at a time: thread (r, group) takes rows r, r + R, ... both for the logits and for dz.
+  // Its first HELD rows are asked for ahead of the LayerNorm and stay for dz; a row past the last reads the last and counts nowhere.
+  constexpr int HELD = VEC == 4 ? HELD4 : HELD1, CHUNK = VEC == 4 ? CHUNK4 : CHUNK1;
+  const int G = C / VEC, R = WIDE ? PARTS : max(1, HT / G), first = tid / G, grp = tid % G;
+  vecf held[WIDE ? 1 : HELD];
+  auto rows_of = [&](vecf* w, int k0) {
+    const int row = anew(first);
+#pragma unroll
+    for (int j = 0; j < CHUNK; ++j) w[j] = *(const vecf*)(w_head + (uint32_t)(min(row + (k0 + j) * R, D - 1) * C + grp * VEC));
+  };
   // final LayerNorm of the class token (two passes over the row held in LDS)
   float s = 0.f;
   for (int d = tid; d < D; d += HT) { const float v = (float)xr[d]; xh[d] = v; s += v; }
+  const int y = labels[b];
+  if constexpr (!WIDE) {
+#pragma unroll
+    for (int k = 0; k < HELD; k += CHUNK) {
+      if (k * R < D) rows_of(held + k, k);
+      else
+#pragma unroll
+        for (int j = 0; j < CHUNK; ++j) held[k + j] = (vecf)0.f;
+    }
+  }
   const float mean = block_sum(s, red) / (float)D;
   float q = 0.f;
   for (int d = tid; d < D; d += HT) { const float v = xh[d] - mean; q += v * v; }
@@ -94,9 +142,8 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     z_out[(int64_t)b * D + d] = z;
   }
   __syncthreads();
-  // logits: G groups of VEC classes, R rows of W_h at a time; thread (r, group) adds rows r, r + R, ...  WIDE: a wavefront adds
-  // up one of R ranges of rows, its lanes along the classes, 64 groups at a time.
-  const int G = C / VEC, R = WIDE ? PARTS : max(1, HT / G);
+  // logits: thread (r, group) adds up its rows.  WIDE: a wavefront adds up one of R ranges of rows, its lanes along the classes,
+  // 64 groups at a time.
   if constexpr (WIDE) {
     const int part = tid / WAVE % PARTS, n = D / PARTS;           // (D is a multiple of 8)
     for (int g = tid / WAVE / PARTS * WAVE + tid % WAVE; g < G; g += HT / PARTS) {
@@ -108,21 +155,30 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
       for (int v = 0; v < VEC; ++v) scr[part * C + g * VEC + v] = a[v];
     }
   } else {
-    for (int i = tid; i < R * G; i += HT) {
-      const int r = i / G, g = i % G;
-      const float* wp = w_head + g * VEC;
-      vecf a = (vecf)0.f;
-#pragma unroll 8
-      for (int d = r; d < D; d += R) a += zs[d] * *(const vecf*)(wp + (int64_t)d * C);
+    vecf a = (vecf)0.f;
+    auto add = [&](const vecf* w, int k0) {
+      const int row = anew(first);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) scr[r * C + g * VEC + v] = a[v];
+      for (int j = 0; j < CHUNK; ++j) {
+        const int d = row + (k0 + j) * R;
+        if (d < D) a += zs[d] * w[j];
+      }
+    };
+#pragma unroll
+    for (int k = 0; k < HELD; k += CHUNK)
+      if (k * R < D) add(held + k, k);
+    for (int k = HELD; k * R < D; k += CHUNK) {
+      vecf w[CHUNK];
+      rows_of(w, k);
+      add(w, k);
     }
+    if (first < R)
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) scr[first * C + grp * VEC + v] = a[v];
   }
   __syncthreads();
   for (int i = tid / 8; i < C; i += HT / 8) {          // eight threads per class
-    float a = 0.f;
-    for (int r = tid & 7; r < R; r += 8) a += scr[r * C + i];
-    a = eight_sum(a);
+    float a = eight_sum(every_eighth(scr + i, C, R));
     if ((tid & 7) == 0) {
       if (b_head) a += b_head[i];
       lg[i] = a;
@@ -137,7 +193,6 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
   float se = 0.f;
   for (int c = tid; c < C; c += HT) se += expf(lg[c] - mx);
   const float lse = mx + logf(block_sum(se, red));
-  const int y = labels[b];
   if (tid == 0) loss_rows[b] = lse - ((y >= 0 && y < C) ? lg[y] : 0.f);
   __syncthreads();
   for (int c = tid; c < C; c += HT) {
@@ -146,9 +201,10 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     dlogits_out[(int64_t)b * C + c] = g;
   }
   __syncthreads();
-  // dz = dlogits . W_h^T: the same walk, a chunk of rows at a time; each thread leaves the product of its VEC classes, then
-  // eight threads add up a row.  WIDE (a chunk would be a few rows, and adding them up all there is): a wavefront takes four
-  // rows at a time, its lanes along the classes.
+  // dz = dlogits . W_h^T: the same walk, CHUNK R rows at a time; each thread leaves the product of its VEC classes, then
+  // eight threads add up a row (seven rows a thread are what SCRATCH holds at every G, with the odd pitch from eight groups on).
+  // WIDE (a chunk would be a few rows, and adding them up all there is): a wavefront takes four rows at a time, its lanes along
+  // the classes.
   if constexpr (WIDE) {
     for (int d0 = tid / WAVE * 4; d0 < D; d0 += HW * 4) {
       float a[4] = {0.f, 0.f, 0.f, 0.f};
@@ -171,32 +227,34 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     }
     __syncthreads();
   } else {
-    const int GP = G | 1, DC = max(1, SCRATCH / GP);
-    for (int d0 = 0; d0 < D; d0 += DC) {
-      const int rows = min(DC, D - d0);
-      for (int i = tid; i < R * G; i += HT) {
-        const int g = i % G;
-        float dl[VEC];
+    const int GP = G < 8 ? G : G | 1;
+    float dl[VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) dl[v] = lg[g * VEC + v];
-        const float* wp = w_head + (int64_t)d0 * C + g * VEC;
-#pragma unroll 8
-        for (int r = i / G; r < rows; r += R) {
-          const vecf w = *(const vecf*)(wp + (int64_t)r * C);
-          float a = 0.f;
+    for (int v = 0; v < VEC; ++v) dl[v] = lg[grp * VEC + v];
+    auto chunk = [&](const vecf* w, int k0) {
+      const int d0 = k0 * R, rows = min(CHUNK * R, D - d0), row = anew(first);
 #pragma unroll
-          for (int v = 0; v < VEC; ++v) a = fmaf(dl[v], w[v], a);
-          scr[r * GP + g] = a;
-        }
+      for (int j = 0; j < CHUNK; ++j) {
+        const int r = row + j * R;
+        float a = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) a = fmaf(dl[v], w[j][v], a);
+        if (row < R && r < rows) scr[r * GP + grp] = a;
       }
       __syncthreads();
       for (int r = tid / 8; r < rows; r += HT / 8) {
-        float a = 0.f;
-        for (int g = tid & 7; g < G; g += 8) a += scr[r * GP + g];
-        a = eight_sum(a);
+        const float a = eight_sum(every_eighth(scr + r * GP, 1, G));
         if ((tid & 7) == 0) zs[d0 + r] = a;
       }
       __syncthreads();
+    };
+#pragma unroll
+    for (int k = 0; k < HELD; k += CHUNK)
+      if (k * R < D) chunk(held + k, k);
+    for (int k = HELD; k * R < D; k += CHUNK) {
+      vecf w[CHUNK];
+      rows_of(w, k);
+      chunk(w, k);
     }
   }
   // the LayerNorm backward of the row:
