@@ -662,7 +662,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_long_kernel(const bf16* __res
                                                             bf16* __restrict__ out, float* __restrict__ lse,
                                                             float* __restrict__ cls_prob) {
   __shared__ u32x4 Ks[LC * 8], Vs[LC * 8];
-  __shared__ float cls_s[LONG_T];
+  __shared__ __attribute__((aligned(16))) float cls_s[LONG_T];
+  static_assert(__alignof__(cls_s) >= 16, "written four keys at a time");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
   const int head = blockIdx.x % heads_total, b = head / H, h = head % H, D = H * HD;
   const int q0 = (blockIdx.x / heads_total) * 128 + wave * 32, qi = q0 + lr;
