@@ -3,8 +3,8 @@
 // product, beyond that keys come in chunks and probabilities stay in fp32 (second half of the file).  The CLS row of the
 // softmax map, which Eq. 6 ranks tokens by, leaves the forward kernel in fp32 as a by-product.
 //
-// Forward.  One workgroup = one (image, head), or half the queries of one where there are few: K and V of the head are staged
-// once, and each of its wavefronts owns 32 queries.  K and V sit in LDS row-major (swizzled 16-byte chunks);
+// Forward.  One workgroup = one (image, head), or half the queries of one (fwd_parts): K and V of the head are staged
+// in one go, and each of its wavefronts owns 32 queries.  K and V sit in LDS row-major (swizzled 16-byte chunks);
 // V^T fragments come from the LDS transpose read.  The wave computes S^T = K Q^T with 32x32x16 MFMAs, so that a
 // lane owns one query and the softmax reductions over keys are in-register (plus one exchange between
 // the two halves of the wave).  The normalised P^T accumulators are, as they lie in registers, an
@@ -107,14 +107,29 @@ __device__ inline bf16x8 lds_frag_t(const u32x4* rows, int nb, int lane, int st,
 
 // Rows of K and V in LDS: the tokens and at least one row of zeros where the last block of 32 has room for it, which stands for all rows past it.
 __host__ __device__ inline int fwd_rows(int nj, int T) { return min(nj * 32, (T + 8) & ~7); }
-// From 161 to 224 tokens a head goes to two workgroups of up to four wavefronts, which both stage K and V.  What bounds the kernel is the softmax arithmetic and how
-// many wavefronts a CU has to cover it: at 171 registers a SIMD takes two of them, so one workgroup of seven filled a CU and 384 heads took two rounds.
-// Held to 168 registers, with 200 rows staged for 197 tokens instead of 224, three halves share a CU: 32 images of 12 heads 19.2 -> 13.1 us, 27 18.8 -> 14.6,
-// 128 61.6 -> 51.6 (the class row's way out through LDS is in these: 138 tokens, where it is all, 13.2 -> 10.2).
-constexpr bool fwd_halves(int nj) { return nj == 6 || nj == 7; }
+// Workgroups that a head's queries go to; with two, both stage K and V.  What bounds the kernel is the softmax arithmetic and how many wavefronts a CU has to cover it.
+// Kernel times, whole heads -> halves:
+//   few heads leave CUs idle: one image of 12 heads at 197 tokens 8.0 -> 7.4 us.  (From 128 heads on two workgroups a head are more than one a CU.)
+//   161 .. 199 tokens: of whole heads a CU holds one of seven wavefronts (168 registers: three a SIMD) or two of six, of halves three, with up to 200 rows
+//     staged, 52 KB: finer shares of the work, and beyond 192 tokens half as many wavefronts again.  384 heads at 197 tokens 15.8 -> 12.5, at 161 13.6 -> 10.7;
+//     1536 50.9 -> 49.8 and 41.9 -> 41.4; 192 9.2 -> 9.1 and 8.9 -> 9.3; the least, 132 at 161, 8.2 -> 9.0.
+//   200 .. 224 tokens (208 rows of 256 bytes and the class row are 54 144: the CU's 160 KB are given out in steps that hold two): the same seven wavefronts
+//     at work either way, but two workgroups that do not wait for each other, and K and V twice.  Up to 1.5 rounds of the CUs halves gain: 288 heads 15.9 -> 14.7
+//     at 211 tokens, 384 16.7 -> 15.8.  Beyond, the second K and V cost more: 432 17.5 -> 17.8, 504 19.6 -> 20.4, 768 28.3 -> 31.6, 960 34.6 -> 38.2, 1536 50.8 -> 54.8
+//     (where a last round of CUs is nearly empty the other way: 1284 50.0 -> 48.7), until qkv and output together outgrow the last-level cache and the kernel
+//     waits for memory: 2556 heads at 200 tokens (262 MB) 80.6 -> 83.8, 2688 90.9 -> 89.4, 2880 106.8 -> 98.9; 2304 at 224 (264 MB) 79.9 -> 79.9, 2556 97.4 -> 95.5.
+__host__ __device__ constexpr bool fwd_halves(int nj) { return nj == 6 || nj == 7; }      // forms that are held to three wavefronts a SIMD for it
+inline int fwd_parts(int nj, int T, int64_t heads) {
+  if (nj == 1) return 1;
+  if (heads <= 128) return 2;
+  if (!fwd_halves(nj)) return 1;
+  return fwd_rows(nj, T) <= 200 || heads <= 416 || heads * T * 4 * HD * (int64_t)sizeof(bf16) > (int64_t)256 << 20 ? 2 : 1;
+}
 
+// (97 .. 128 tokens are held to three wavefronts a SIMD as well: left alone that form takes 108 registers and 64 for accumulators beside them, held 117 in all, and
+// four wavefronts fit.  384 heads at 97 tokens 8.5 -> 6.9 us, at 128 9.2 -> 7.8, 1536 heads 21.5 -> 18.1 and 24.4 -> 20.8.)
 template <int NJ>
-__global__ __launch_bounds__(fwd_halves(NJ) ? 256 : NJ * 64, NJ == 4 || fwd_halves(NJ) ? 3 : 1) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, int T, int H,
+__global__ __launch_bounds__(NJ * 64, NJ == 4 || fwd_halves(NJ) ? 3 : 1) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, int T, int H,
                                                                bf16* __restrict__ out, float* __restrict__ lse,
                                                                float* __restrict__ cls_prob) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -234,9 +249,7 @@ void launch_fwd(const bf16* qkv, int B, int T, int H, bf16* out, float* lse, flo
     (void)hipFuncSetAttribute((const void*)attn_fwd_mfma_kernel<NJ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds(NJ * 32));
     attr_set = true;
   }
-  // Few heads leave CUs idle: their queries go to two workgroups then, which both stage K and V: one image of
-  // 12 heads, 197 tokens 8.0 -> 7.4 us.  (From 128 heads on two workgroups a head are more than one a CU.)
-  const int parts = fwd_halves(NJ) || (NJ > 1 && B * H <= 128) ? 2 : 1;
+  const int parts = fwd_parts(NJ, T, (int64_t)B * H);
   attn_fwd_mfma_kernel<NJ><<<dim3(B * H, parts), (NJ + parts - 1) / parts * 64, lds(fwd_rows(NJ, T)), s>>>(qkv, T, H, out, lse, cls_prob);
 }
 

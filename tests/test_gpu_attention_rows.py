@@ -28,6 +28,24 @@ def test_attention_forward_reads_no_row_past_the_tokens(env, orc64, T):
     assert bool(torch.isfinite(lse).all())
 
 
+# A head in one workgroup: 132 heads outside 161 .. 224 tokens, and 516 where no three halves fit a CU (200 and up; 193 and 199: halves on the other side of that line)
+@pytest.mark.parametrize("T,images", [(T, 11) for T in (1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 138, 159, 160, 225, 255, 256)] +
+                         [(T, 43) for T in (193, 199, 200, 207, 208, 215, 216, 223, 224)])
+def test_attention_of_many_heads_reads_no_row_past_the_tokens(env, orc64, T, images):
+    torch, P = env
+    rng = np.random.default_rng(T)
+    qkv = bf16_np(rng, (images, T, 3 * 12 * 64), 1.5)
+    fill_lds_with_nan(torch, P, 256)
+    out, lse, cls, used = P.bsr_attention_forward(to_dev(torch, qkv, torch.bfloat16), 12)
+    torch.cuda.synchronize()
+    assert used == 1
+    some = [0, images - 1]
+    Pm, o = orc64.attention(qkv[some], 12)
+    assert_close(out[some].float().cpu().numpy(), o, "attention output")              # bounds: those of test_attention_forward
+    assert_close(cls[some].cpu().numpy(), Pm[:, :, 0, :], "CLS softmax row", tol=2e-3)
+    assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(lse).all()) and bool(torch.isfinite(cls).all())
+
+
 # 257, 385: one key into a chunk of 128; 288 / 289, 416 / 417: a block of 32 full and one key more; 1023: one short of the limit
 @pytest.mark.parametrize("T", [257, 288, 289, 385, 416, 417, 512, 1023])
 def test_long_attention_leaves_out_blocks_past_the_tokens(env, orc64, T):
