@@ -1736,27 +1736,30 @@ static int ntd_stages(int id) {
 
 // The model: with t tiles, time = c0 + ceil(t / 256) (c1 + c2 K / 64) + t / 256 (c3 + c4 K / 64) + ceil(t / 512) (c5 + c6 K / 64)
 // microseconds, and where a GELU or GELU' is applied ceil(t / 256) c7 + t / 256 c8 more: a fixed part, rounds of one workgroup per CU, what scales with
-// the work, rounds of two per CU.  Where many results leave beside a stored input, or come from one, the time of
-// a tile's two streams counts, which larger tiles overlap better: ceil(t / 256) c9 with a GELU whose input is stored, ceil(t / 256) c10 with a GELU' instead
-// of those (fitted to 318 products with every epilogue).  Steps with all 12 blocks trained: 768 wide 128 images 0.993 .. 0.997 times as long, 96 0.989, 64 0.999,
-// 56 (33.9 M results) 1.006; 384 wide 128 images 0.991; with fewer results those constants pick what is faster in chains of launches, and steps of
-// 16 .. 32 images take 1.000 .. 1.003 times as long.
+// the work, rounds of two per CU.  From MANY_RESULTS on a GELU beside which its input is stored takes ceil(t / 256) c9 instead of those (fitted to 318 products
+// with every epilogue): there the two streams of results count, which larger tiles overlap better.  The line is where nothing beyond it loses; it is measured,
+// not derived.  Steps with all blocks trained at the numbers of images where c9 takes another tile, c7 and c8 -> c9 (runs of one side differ by 0.5 %):
+//   37.7 M results and more: 384 wide 125, 128, 160, 192, 256 images 0.991 .. 0.997, 512 wide 112, 120, 144, 160, 192, 256 images 0.984 .. 0.995,
+//     768 wide 80, 96, 128, 160, 192 0.989 .. 0.994, 1024 wide 56, 72, 96, 112 0.984 .. 0.994
+//   fewer: 384 wide 16 .. 103 images 0.993 .. 1.008, 512 wide 16 .. 77 0.994 .. 1.011, 768 wide 12 .. 51 0.986 .. 1.005, 56 .. 62 1.002 .. 1.012,
+//     1024 wide 22 .. 45 0.991 .. 1.002 (36 steps, 0.999 on average)
+// (A constant of the same kind for the GELU' changed 5 of 805 choices at 3072 x 768 and none at 1536 x 384 and 2048 x 512; steps with and without it 1.000.)
 constexpr int64_t MANY_RESULTS = 36 << 20;
-struct NtModel { int id, bm, bn; float c[11]; };
+struct NtModel { int id, bm, bn; float c[10]; };
 // Direct-to-LDS shapes: constants fitted to chains of equal launches over twelve weight matrices (88 products of 400 .. 25216
 // rows; 384, 768, 1152, 1536, 2304 and 3072 columns).  Of 32 shapes measured there these nine lose 0.8 %, and the model's
 // picks among them 1.2 %, to the fastest of all; the best of the shapes before them (four-wavefront and register-staged
 // ones) took 6.5 % longer, the model's picks of those 14 %.  At other widths the model extrapolates, and tuning is the way to know.
 const NtModel kNtModel[] = {
-    {7128064, 128, 64, {2.231f, 0.226f, 0.225f, 0.244f, 0.063f, 1.485f, 0.040f, 1.032f, 0.000f, 0.514f, 0.380f}},
-    {7192128, 192, 128, {3.692f, 0.495f, 0.423f, 1.425f, 0.145f, 0.000f, 0.241f, 2.731f, 0.000f, 2.115f, 1.595f}},
-    {8128128, 128, 128, {1.293f, 2.977f, 0.363f, 0.000f, 0.181f, 0.000f, 0.000f, 1.970f, 0.623f, 1.448f, 1.221f}},
-    {7128128, 128, 128, {2.632f, 0.784f, 0.200f, 0.475f, 0.149f, 0.273f, 0.363f, 1.768f, 0.000f, 1.302f, 1.014f}},
-    {7320256, 320, 256, {0.696f, 7.695f, 0.752f, 0.000f, 1.252f, 1.771f, 0.190f, 10.720f, 0.381f, 6.316f, 7.325f}},
-    {8192128, 192, 128, {1.428f, 3.720f, 0.438f, 0.000f, 0.294f, 0.000f, 0.000f, 2.450f, 1.429f, 2.910f, 1.846f}},
-    {7192256, 192, 256, {1.340f, 5.269f, 0.721f, 0.000f, 0.597f, 0.321f, 0.000f, 6.615f, 0.367f, 3.911f, 4.765f}},
-    {7256256, 256, 256, {0.390f, 6.475f, 0.912f, 0.000f, 0.791f, 1.970f, 0.000f, 7.088f, 1.735f, 3.884f, 5.438f}},
-    {7256128, 256, 128, {0.000f, 4.160f, 0.564f, 0.268f, 0.342f, 1.936f, 0.000f, 3.777f, 0.839f, 2.225f, 2.389f}},
+    {7128064, 128, 64, {2.231f, 0.226f, 0.225f, 0.244f, 0.063f, 1.485f, 0.040f, 1.032f, 0.000f, 0.514f}},
+    {7192128, 192, 128, {3.692f, 0.495f, 0.423f, 1.425f, 0.145f, 0.000f, 0.241f, 2.731f, 0.000f, 2.115f}},
+    {8128128, 128, 128, {1.293f, 2.977f, 0.363f, 0.000f, 0.181f, 0.000f, 0.000f, 1.970f, 0.623f, 1.448f}},
+    {7128128, 128, 128, {2.632f, 0.784f, 0.200f, 0.475f, 0.149f, 0.273f, 0.363f, 1.768f, 0.000f, 1.302f}},
+    {7320256, 320, 256, {0.696f, 7.695f, 0.752f, 0.000f, 1.252f, 1.771f, 0.190f, 10.720f, 0.381f, 6.316f}},
+    {8192128, 192, 128, {1.428f, 3.720f, 0.438f, 0.000f, 0.294f, 0.000f, 0.000f, 2.450f, 1.429f, 2.910f}},
+    {7192256, 192, 256, {1.340f, 5.269f, 0.721f, 0.000f, 0.597f, 0.321f, 0.000f, 6.615f, 0.367f, 3.911f}},
+    {7256256, 256, 256, {0.390f, 6.475f, 0.912f, 0.000f, 0.791f, 1.970f, 0.000f, 7.088f, 1.735f, 3.884f}},
+    {7256128, 256, 128, {0.000f, 4.160f, 0.564f, 0.268f, 0.342f, 1.936f, 0.000f, 3.777f, 0.839f, 2.225f}},
 };
 // Fitted to every shape forced in turn on the launches of ViT-B and DeiT-S steps (436 launches, event-bracketed, in their place
 // in the step, the event pair included).  The register-staged ones, which come first, are picked from for products that only they
@@ -1776,15 +1779,14 @@ constexpr float EVENTS_US = 4.5f;      // the part of their c0 that a launch ins
 template <int N>
 static int model_pick(const NtModel (&table)[N], const GemmDesc& g, bool direct_ok, float* us_out) {
   int pick = 0;
-  const bool large = (int64_t)g.M * g.N >= MANY_RESULTS;
-  const float k = (float)((g.K + BK - 1) / BK), stored = large && g.act == ACT_GELU && g.aux ? 1.f : 0.f, bwd = large && g.act == ACT_GELU_BWD ? 1.f : 0.f;
-  const float gelu = g.act != ACT_NONE && stored + bwd == 0.f ? 1.f : 0.f;
+  const bool stored = g.act == ACT_GELU && g.aux && (int64_t)g.M * g.N >= MANY_RESULTS;
+  const float k = (float)((g.K + BK - 1) / BK), gelu = g.act != ACT_NONE && !stored ? 1.f : 0.f;
   for (const NtModel& e : table) {
     if ((ntd_stages(e.id) && !direct_ok) || (g.ln_colsum && e.bn < 128)) continue;
     // (a group ends in a partial row tile: half a tile each)
     const int64_t t = (int64_t)((g.M + e.bm - 1) / e.bm + (g.grp_off ? g.groups / 2 : 0)) * ((g.N + e.bn - 1) / e.bn);
     const float r1 = (float)((t + 255) / 256), w = (float)t / 256.f, r2 = (float)((t + 511) / 512);
-    const float us = e.c[0] + r1 * (e.c[1] + e.c[2] * k + e.c[7] * gelu + e.c[9] * stored + e.c[10] * bwd) + w * (e.c[3] + e.c[4] * k + e.c[8] * gelu) +
+    const float us = e.c[0] + r1 * (e.c[1] + e.c[2] * k + e.c[7] * gelu + (stored ? e.c[9] : 0.f)) + w * (e.c[3] + e.c[4] * k + e.c[8] * gelu) +
                      r2 * (e.c[5] + e.c[6] * k);
     if (!pick || us < *us_out) { pick = e.id; *us_out = us; }
   }
