@@ -46,6 +46,20 @@ def test_attention_of_many_heads_reads_no_row_past_the_tokens(env, orc64, T, ima
     assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(lse).all()) and bool(torch.isfinite(cls).all())
 
 
+# 129 .. 160: five blocks of keys, whole heads where there are many; 161 and 199: halves at any number of heads; 43 images: whole heads from 200 tokens on
+@pytest.mark.parametrize("T,images", [(T, 11) for T in (129, 138, 159, 160, 161)] + [(T, 43) for T in (199, 200, 208, 211, 224)])
+def test_attention_of_a_few_heads_is_the_same_bits_as_among_many(env, T, images):
+    """24 heads (two workgroups share a head) against the same heads among 132 or 516 (one workgroup each)."""
+    torch, P = env
+    rng = np.random.default_rng(T)
+    qkv = to_dev(torch, bf16_np(rng, (images, T, 3 * 12 * 64), 1.5), torch.bfloat16)
+    many = P.bsr_attention_forward(qkv, 12)
+    few = P.bsr_attention_forward(qkv[:2].contiguous(), 12)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("out", "lse", "CLS row"), many, few):
+        assert torch.equal(a[:2], b), name
+
+
 # 257, 385: one key into a chunk of 128; 288 / 289, 416 / 417: a block of 32 full and one key more; 1023: one short of the limit
 @pytest.mark.parametrize("T", [257, 288, 289, 385, 416, 417, 512, 1023])
 def test_long_attention_leaves_out_blocks_past_the_tokens(env, orc64, T):

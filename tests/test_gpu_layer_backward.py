@@ -114,13 +114,12 @@ def test_ids_that_are_no_longer_shapes_run_what_no_id_runs(env, tile):
     assert product_kernels(lambda: P.bsr_linear_forward(x, w, None, tile=tile)) == default
 
 
-# (11 images, 161 .. 199 tokens: halves either way, as any number of heads beyond 24 is there; 43 images: whole heads from 200 tokens on)
-@pytest.mark.parametrize("T,images", [(T, 11) for T in (1, 33, 64, 65, 128, 129, 138, 159, 160, 197, 256)] + [(T, 43) for T in (199, 200, 208, 211, 224)])
-def test_attention_of_few_heads_is_the_same_bits(env, T, images):
-    """24 heads (two workgroups share a head) against the same heads among 132 or 516 (one workgroup each)."""
+@pytest.mark.parametrize("T", [1, 33, 64, 65, 128, 197, 256])
+def test_attention_of_few_heads_is_the_same_bits(env, T):
+    """24 heads (two workgroups share a head) against the same heads among 132 (one workgroup each)."""
     torch, P = env
     rng = np.random.default_rng(T)
-    qkv = K.to_dev(torch, K.bf16_np(rng, (images, T, 3 * 12 * 64), 1.5), torch.bfloat16)
+    qkv = K.to_dev(torch, K.bf16_np(rng, (11, T, 3 * 12 * 64), 1.5), torch.bfloat16)
     many = P.bsr_attention_forward(qkv, 12)
     few = P.bsr_attention_forward(qkv[:2].contiguous(), 12)
     torch.cuda.synchronize()
