@@ -9,25 +9,31 @@
 // All arithmetic is fp32 whatever the activation type.
 // Bound by latency: an image's workgroup reads W_h once (307 KB at 768 x 100, from L2) or, beyond what its registers hold, twice.
 // Both passes walk W_h as it lies in memory, VEC classes per load, as many rows at once as the 1024 threads cover; what is to be
-// added across threads goes through LDS.  A thread's first rows (20 of four classes: all of 768 x 100; 42 of one: all of 384 x 102)
-// are asked for in one go ahead of the LayerNorm and kept for dz, the others seven (of four classes five) at a time with the last batch filled up by
-// repeats, where loops of eight left up to seven rows to be waited for one by one, in every chunk of dz again.  More held, 77 of one
-// class, or the code for it (23 KB, run once) cost 10 classes 0.8 us.  Before -> this, in a step: 768 x 100, 32 images 19.3 -> 16.8 us,
-// 384 x 102, 16 images 24.2 -> 19.0, 768 x 37, 27 images 18.1 -> 17.2, 384 x 100, 32 images 14.1 -> 12.7, 384 x 10 10.5 -> 10.0.
+// added across threads goes through LDS.  A thread's first rows (20 of four classes: all of 768 x 100; 40 of one: 384 x 102 takes 39, 768 x 101 77)
+// are asked for in one go ahead of the LayerNorm and kept for dz, the others eight (of four classes five) at a time with the last batch filled up by
+// repeats, where loops of eight left up to seven rows to be waited for one by one, in every chunk of dz again.  A thread's 48 rows of one class held: as long within
+// 1 %, 10 classes 1.02 times; 14 of the others asked for together 1.02 .. 1.05.  Head launches in a graph, loops of eight -> this, 32 images: 768 x 100 21.1 -> 18.6 us,
+// 768 x 102 39.7 -> 31.4, 768 x 37 20.6 -> 18.8, 768 x 10 16.1 -> 14.4, 384 x 102 25.7 -> 20.5, 384 x 100 16.7 -> 15.5, 384 x 10 13.6 -> 13.4, 1024 x 101 40.0 -> 38.3.
+// dz takes eight rows a thread between two barriers, as those loops did: with the five or seven asked for together between two barriers, and four
+// values for every sum of at most eight, 192 x 120 had become 1.03, 768 x 28 1.06, 1024 x 20 1.06, 384 x 56 1.03 and 1024 x 101 1.02 times as long as those loops.
 // (Lanes along the classes with a wave sum per row of W_h: 32 us at 32 images, 768 x 100.
 // The batch kernel with a thread per element walking all images: 13 us at 32 images, 48 at 128; now 6 and 17.)
 #include "rowops.h"
 
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace bsr {
 namespace {
 
 constexpr int HT = 1024, HW = HT / WAVE;               // threads and wavefronts per workgroup of the row kernel
-constexpr int SCRATCH = 8192;                          // floats of LDS for partial sums
-// (Registers: 118 of 128 at 20 rows of four classes, 21 in chunks of seven spill; 70 at 42 of one.)
-constexpr int CHUNK4 = 5, CHUNK1 = 7;                  // rows of W_h (of four classes, of one) per thread of the row kernel between two barriers of dz
-constexpr int HELD4 = 4 * CHUNK4, HELD1 = 6 * CHUNK1;  // and those it holds in registers from the logits to dz
+constexpr int SCRATCH = 9216, TAKES_SCRATCH = 8192;    // floats of LDS for partial sums; those that decide which heads come here
+// (Registers: 118 of 128 at 20 rows of four classes, 21 in chunks of seven spill; 65 at 40 of one.)
+constexpr int CHUNK4 = 5, CHUNK1 = 8;                  // rows of W_h (of four classes, of one) that a thread of the row kernel asks for together
+constexpr int HELD4 = 4 * CHUNK4, HELD1 = 5 * CHUNK1;  // and those it holds in registers from the logits to dz
+constexpr int SUM = 8;                                 // held rows between two barriers of dz
+static_assert(SUM * 1152 <= SCRATCH && CHUNK4 <= SUM && CHUNK1 <= SUM, "R rows at the pitch of dz are at most 128 x 9 numbers");
 constexpr int WIDE_G = 128, PARTS = 8;                 // groups of VEC classes that make a wide head; its ranges of rows
 constexpr int ZERO_PARTS = 4;                          // workgroups per image that clear the other token rows
 constexpr int BT = 256;                                // threads per workgroup of the batch kernel
@@ -66,10 +72,11 @@ __device__ __forceinline__ void zero_rows(T* dst, int64_t n, int part) {
   }
 }
 
-// v[tid % 8], v[tid % 8 + 8], ... of n values `step` apart, added in that order; four at a time are read together
+// v[tid % 8], v[tid % 8 + 8], ... of n values `step` apart, added in that order; behind the first, four at a time are read together
 __device__ __forceinline__ float every_eighth(const float* v, int step, int n) {
-  float a = 0.f;
-  for (int i = threadIdx.x & 7; i < n; i += 32) {
+  const int first = threadIdx.x & 7;
+  float a = first < n ? 0.f + v[first * step] : 0.f;
+  for (int i = first + 8; i < n; i += 32) {
     float t[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) t[j] = v[min(i + 8 * j, n - 1) * step];
@@ -121,7 +128,7 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
   // final LayerNorm of the class token (two passes over the row held in LDS)
   float s = 0.f;
   for (int d = tid; d < D; d += HT) { const float v = (float)xr[d]; xh[d] = v; s += v; }
-  const int y = labels[b];
+  const int early_y = WIDE ? 0 : labels[b];      // (WIDE: no other loads ahead that its wait could hide behind)
   if constexpr (!WIDE) {
 #pragma unroll
     for (int k = 0; k < HELD; k += CHUNK) {
@@ -193,6 +200,7 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
   float se = 0.f;
   for (int c = tid; c < C; c += HT) se += expf(lg[c] - mx);
   const float lse = mx + logf(block_sum(se, red));
+  const int y = WIDE ? labels[b] : early_y;
   if (tid == 0) loss_rows[b] = lse - ((y >= 0 && y < C) ? lg[y] : 0.f);
   __syncthreads();
   for (int c = tid; c < C; c += HT) {
@@ -201,8 +209,8 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     dlogits_out[(int64_t)b * C + c] = g;
   }
   __syncthreads();
-  // dz = dlogits . W_h^T: the same walk, CHUNK R rows at a time; each thread leaves the product of its VEC classes, then
-  // eight threads add up a row (seven rows a thread are what SCRATCH holds at every G, with the odd pitch from eight groups on).
+  // dz = dlogits . W_h^T: the same walk, SUM R rows at a time of those held, CHUNK R of the others; each thread leaves the product of its
+  // VEC classes, then eight threads add up a row (odd pitch from eight groups on).
   // WIDE (a chunk would be a few rows, and adding them up all there is): a wavefront takes four rows at a time, its lanes along
   // the classes.
   if constexpr (WIDE) {
@@ -231,10 +239,11 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
     float dl[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) dl[v] = lg[grp * VEC + v];
-    auto chunk = [&](const vecf* w, int k0) {
-      const int d0 = k0 * R, rows = min(CHUNK * R, D - d0), row = anew(first);
+    auto chunk = [&](const vecf* w, int k0, auto n) {
+      constexpr int N = decltype(n)::value;
+      const int d0 = k0 * R, rows = min(N * R, D - d0), row = anew(first);
 #pragma unroll
-      for (int j = 0; j < CHUNK; ++j) {
+      for (int j = 0; j < N; ++j) {
         const int r = row + j * R;
         float a = 0.f;
 #pragma unroll
@@ -248,13 +257,16 @@ __global__ __launch_bounds__(HT) void head_rows_kernel(const T* __restrict__ x, 
       }
       __syncthreads();
     };
+    constexpr std::integral_constant<int, SUM> some{};
 #pragma unroll
-    for (int k = 0; k < HELD; k += CHUNK)
-      if (k * R < D) chunk(held + k, k);
+    for (int k = 0; k + SUM <= HELD; k += SUM)
+      if (k * R < D) chunk(held + k, k, some);
+    if constexpr (HELD % SUM)
+      if (HELD / SUM * SUM * R < D) chunk(held + HELD / SUM * SUM, HELD / SUM * SUM, std::integral_constant<int, HELD % SUM>{});
     for (int k = HELD; k * R < D; k += CHUNK) {
       vecf w[CHUNK];
       rows_of(w, k);
-      chunk(w, k);
+      chunk(w, k, std::integral_constant<int, CHUNK>{});
     }
   }
   // the LayerNorm backward of the row:
@@ -349,8 +361,8 @@ __global__ __launch_bounds__(BT) void head_batch_kernel(const float* __restrict_
 
 static bool four_classes(int C, const float* w_head) { return C % 4 == 0 && ((uintptr_t)w_head & 15) == 0; }   // (as rows of W_h start)
 static bool wide_head(int C, const float* w_head) { return C / (four_classes(C, w_head) ? 4 : 1) >= WIDE_G; }
-static size_t head_lds_bytes(int D, int C, const float* w_head) {
-  return sizeof(float) * ((size_t)2 * D + (size_t)C + HW + (wide_head(C, w_head) ? (size_t)PARTS * C : (size_t)SCRATCH));
+static size_t head_lds_bytes(int D, int C, const float* w_head, int scratch) {
+  return sizeof(float) * ((size_t)2 * D + (size_t)C + HW + (wide_head(C, w_head) ? (size_t)PARTS * C : (size_t)scratch));
 }
 
 // Whether these kernels take a head, or the general ones do (products of their own, which share W_h among all CUs where here
@@ -359,7 +371,7 @@ static size_t head_lds_bytes(int D, int C, const float* w_head) {
 // 114 .. 147, 192 x 1640 101 .. 151 / 120 .. 152.  Where the classes are no multiple of four the general products go without
 // the matrix cores and take longer by the image: 768 x 1301 256 .. 317 / 132 .. 602, equal at 40.
 bool head_takes(int B, int D, int C, const float* w_head) {
-  if (head_lds_bytes(D, C, w_head) > 64 * 1024) return false;
+  if (head_lds_bytes(D, C, w_head, TAKES_SCRATCH) > 64 * 1024) return false;
   return (int64_t)D * C < 300000 || (!four_classes(C, w_head) && B > 40);
 }
 
@@ -367,11 +379,13 @@ void head_fwd_bwd(const void* x, int B, int Tl, int D, int C, bool f32, const fl
                   const float* w_head, const float* b_head, const int32_t* labels, float* xhat, float* z, float* logits,
                   float* dlogits, float* dz, float* loss_rows, void* dx, float* dw, float* db, float* dgamma, float* dbeta,
                   float* loss, hipStream_t s) {
-  const size_t lds = head_lds_bytes(D, C, w_head);
+  const size_t lds = head_lds_bytes(D, C, w_head, SCRATCH);          // (at most 68 KB)
   const dim3 grid(B, Tl > 1 ? 1 + ZERO_PARTS : 1);
   auto rows = [&](auto zero, auto vec, auto wide) {
     typedef decltype(zero) T;
-    head_rows_kernel<T, decltype(vec)::value, decltype(wide)::value != 0><<<grid, HT, lds, s>>>(
+    auto kern = head_rows_kernel<T, decltype(vec)::value, decltype(wide)::value != 0>;
+    if (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    kern<<<grid, HT, lds, s>>>(
         (const T*)x, Tl, D, C, B, gamma, beta, eps, w_head, b_head, labels, xhat, z, logits, dlogits, dz, loss_rows, (T*)dx);
   };
   auto forms = [&](auto zero) {

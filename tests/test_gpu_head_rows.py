@@ -31,3 +31,16 @@ def test_head_at_the_edges_of_held_rows(hip, orc64, dtype, tol, dim, classes):  
             assert hip.rel(out["grads"][n], ref["grads"][n]) < tol, n
         else:
             assert abs(out["grads"][n]).max() == 0.0, n
+
+
+# rows per thread around the eight that are added up together: four classes (400) 8, 9, 16, 17; one class (102) 8, 9, 40 (all held), 41, 48, 49; sums of as many
+# values as threads share, fewer and one more (7, 8, 9 groups; 8 and 9 rows at a time); the largest scratch with an odd pitch (8 groups, two chunks)
+@pytest.mark.parametrize("dtype,tol", [("fp32", TOL_FP32), ("bf16", TOL_BF16)])
+@pytest.mark.parametrize("dim,classes", [(80, 400), (88, 400), (160, 400), (168, 400), (80, 102), (88, 102), (400, 102), (408, 102), (480, 102),
+                                         (488, 102), (768, 28), (256, 36), (80, 127), (80, 508), (128, 113), (1032, 32)])
+def test_head_at_the_edges_of_a_sum(hip, orc64, dtype, tol, dim, classes):  # noqa: F811
+    test_head_at_the_edges_of_held_rows(hip, orc64, dtype, tol, dim, classes)
+
+
+def test_the_widest_rows_take_more_than_64_kb_of_lds(hip, orc64):  # noqa: F811
+    test_head_at_the_edges_of_held_rows(hip, orc64, "bf16", TOL_BF16, 3904, 10)
