@@ -109,20 +109,22 @@ __device__ inline bf16x8 lds_frag_t(const u32x4* rows, int nb, int lane, int st,
 __host__ __device__ inline int fwd_rows(int nj, int T) { return min(nj * 32, (T + 8) & ~7); }
 // Workgroups that a head's queries go to; with two, both stage K and V.  What bounds the kernel is the softmax arithmetic and how many wavefronts a CU has to cover it.
 // Kernel times, whole heads -> halves:
-//   few heads leave CUs idle: one image of 12 heads at 197 tokens 8.0 -> 7.4 us.  (From 128 heads on two workgroups a head are more than one a CU.)
-//   161 .. 199 tokens: of whole heads a CU holds one of seven wavefronts (168 registers: three a SIMD) or two of six, of halves three, with up to 200 rows
-//     staged, 52 KB: finer shares of the work, and beyond 192 tokens half as many wavefronts again.  384 heads at 197 tokens 15.8 -> 12.5, at 161 13.6 -> 10.7;
-//     1536 50.9 -> 49.8 and 41.9 -> 41.4; 192 9.2 -> 9.1 and 8.9 -> 9.3; the least, 132 at 161, 8.2 -> 9.0.
+//   up to 128 heads leave CUs idle: one image of 12 heads at 197 tokens 8.0 -> 7.4 us.
+//   129 .. 256 heads are one round of whole heads over the CUs, and halves would be more than one a CU: 132 heads 7.4 -> 7.9 us at 161 tokens, 8.2 -> 8.4 at 197, 8.3 -> 8.5 at 211;
+//     252 8.2 -> 9.1, 9.2 -> 9.9 and 9.3 -> 10.3; 256 9.2 -> 9.5 at 211 (all of 161 .. 224 tokens and 132 .. 256 heads tried 1.02 .. 1.16).  Up to 160 tokens whole heads at any more heads.
+//   161 .. 199 tokens, more heads: of whole heads a CU holds one of seven wavefronts (168 registers: three a SIMD) or two of six, of halves three, with up to 200 rows
+//     staged, 52 KB: finer shares of the work, and beyond 192 tokens half as many wavefronts again.  258 heads 13.0 -> 10.2 at 161 tokens, 15.0 -> 11.6 at 197; 288 13.1 -> 10.1
+//     and 15.2 -> 11.3; 384 13.4 -> 10.4 and 15.8 -> 12.3; 1536 41.9 -> 41.4 and 50.9 -> 49.8.
 //   200 .. 224 tokens (208 rows of 256 bytes and the class row are 54 144: the CU's 160 KB are given out in steps that hold two): the same seven wavefronts
-//     at work either way, but two workgroups that do not wait for each other, and K and V twice.  Up to 1.5 rounds of the CUs halves gain: 288 heads 15.9 -> 14.7
-//     at 211 tokens, 384 16.7 -> 15.8.  Beyond, the second K and V cost more: 432 17.5 -> 17.8, 504 19.6 -> 20.4, 768 28.3 -> 31.6, 960 34.6 -> 38.2, 1536 50.8 -> 54.8
+//     at work either way, but two workgroups that do not wait for each other, and K and V twice.  Up to 1.5 rounds of the CUs halves gain: 288 heads 15.5 -> 14.2
+//     at 211 tokens, 384 16.7 -> 15.8 (258, the first of them, 15.1 -> 15.4).  Beyond, the second K and V cost more: 432 17.5 -> 17.8, 504 19.6 -> 20.4, 768 28.3 -> 31.6, 960 34.6 -> 38.2, 1536 50.8 -> 54.8
 //     (where a last round of CUs is nearly empty the other way: 1284 50.0 -> 48.7), until qkv and output together outgrow the last-level cache and the kernel
 //     waits for memory: 2556 heads at 200 tokens (262 MB) 80.6 -> 83.8, 2688 90.9 -> 89.4, 2880 106.8 -> 98.9; 2304 at 224 (264 MB) 79.9 -> 79.9, 2556 97.4 -> 95.5.
 __host__ __device__ constexpr bool fwd_halves(int nj) { return nj == 6 || nj == 7; }      // forms that are held to three wavefronts a SIMD for it
 inline int fwd_parts(int nj, int T, int64_t heads) {
   if (nj == 1) return 1;
   if (heads <= 128) return 2;
-  if (!fwd_halves(nj)) return 1;
+  if (!fwd_halves(nj) || heads <= 256) return 1;
   return fwd_rows(nj, T) <= 200 || heads <= 416 || heads * T * 4 * HD * (int64_t)sizeof(bf16) > (int64_t)256 << 20 ? 2 : 1;
 }
 

@@ -28,8 +28,8 @@ def test_attention_forward_reads_no_row_past_the_tokens(env, orc64, T):
     assert bool(torch.isfinite(lse).all())
 
 
-# A head in one workgroup: 132 heads outside 161 .. 224 tokens, and 516 where no three halves fit a CU (200 and up; 193 and 199: halves on the other side of that line)
-@pytest.mark.parametrize("T,images", [(T, 11) for T in (1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 138, 159, 160, 225, 255, 256)] +
+# A head in one workgroup: 132 heads, and 516 where no three halves fit a CU (200 and up; 193 and 199: halves on the other side of that line)
+@pytest.mark.parametrize("T,images", [(T, 11) for T in (1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 138, 159, 160, 161, 192, 193, 199, 223, 224, 225, 255, 256)] +
                          [(T, 43) for T in (193, 199, 200, 207, 208, 215, 216, 223, 224)])
 def test_attention_of_many_heads_reads_no_row_past_the_tokens(env, orc64, T, images):
     torch, P = env
@@ -46,10 +46,10 @@ def test_attention_of_many_heads_reads_no_row_past_the_tokens(env, orc64, T, ima
     assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(lse).all()) and bool(torch.isfinite(cls).all())
 
 
-# 129 .. 160: five blocks of keys, whole heads where there are many; 161 and 199: halves at any number of heads; 43 images: whole heads from 200 tokens on
-@pytest.mark.parametrize("T,images", [(T, 11) for T in (129, 138, 159, 160, 161)] + [(T, 43) for T in (199, 200, 208, 211, 224)])
+# 11 images: whole heads; 22 (264 heads): halves of 161 .. 224 tokens; 43: whole heads again from 200 tokens on
+@pytest.mark.parametrize("T,images", [(T, 11) for T in (129, 138, 159, 160, 161, 192, 193, 224)] + [(T, 22) for T in (160, 161, 224)] + [(T, 43) for T in (199, 200, 208, 211, 224)])
 def test_attention_of_a_few_heads_is_the_same_bits_as_among_many(env, T, images):
-    """24 heads (two workgroups share a head) against the same heads among 132 or 516 (one workgroup each)."""
+    """24 heads (two workgroups share a head) against the same heads among 132, 264 or 516."""
     torch, P = env
     rng = np.random.default_rng(T)
     qkv = to_dev(torch, bf16_np(rng, (images, T, 3 * 12 * 64), 1.5), torch.bfloat16)
