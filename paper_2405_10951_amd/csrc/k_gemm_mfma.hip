@@ -479,7 +479,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 // launch about 3 us.  So the row blocks are a loop (the accumulators of block mi are picked by a switch, which
 // is all that has to be written out per block) and so are the passes: the finishing code exists once.
 // What an epilogue has to do, as a compile-time constant of the kernel: plain products, residuals, the GELU and the GELU' have kernels of their
-// own, in which none of the other forms' branches, registers and code are left (256 x 256 tiles: 6 - 10 KB each, 16 KB with all of them in one);
+// own, in which none of the other forms' branches, registers and code are left (256 x 256 tiles: 7 - 11 KB each, 17 KB with all of them in one);
 // EPI_ANY looks at the description (fp32 results, the positional embedding, a layer's joint backward launch).
 enum Epi { EPI_ANY, EPI_BIAS, EPI_RES, EPI_GELU, EPI_GELU_BWD };
 template <int NI> struct EpiLanes {
